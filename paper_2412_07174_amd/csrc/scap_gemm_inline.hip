@@ -174,7 +174,7 @@ __device__ __forceinline__ float word_half_to_f32(uint32_t wd, int half) {
 // of 8 channels): it loads tokens tg and tg+8 of its octet and tests its 16 elements; the compare masks are
 // scalar registers, so a channel's keep bits over all tokens are one byte of a mask and "kept by any token" is
 // a nonzero-byte test.  Everything in the test is straight-line: the instruction count per element is what the
-// prologue costs, repeated by every column tile.  Per-token lists and counts (column tile 0, on request) are
+// prologue costs, repeated by every column tile.  Per-token lists and counts (on request, the tile's own tokens) are
 // read back from the staged tile with one channel per lane.  Returns the list length; ends with a barrier.
 template <int WAVES, int MAXC, bool SUPERSET>
 __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile, int split, const Lds& L, char* xs,
@@ -185,8 +185,8 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     const int lane = tid & 63;
     const int k0 = split * a.Kc;
     const int kend = min(k0 + a.Kc, a.K);
-    const bool per_token = tile == 0 && (a.nnz_out != nullptr || a.idx_out != nullptr);
-    const bool want_idx = tile == 0 && a.idx_out != nullptr;
+    const uint32_t own = owned_tokens(a, tile);  // tokens whose lists and counts this tile's workgroups leave
+    const bool want_idx = a.idx_out != nullptr;
     // dense mode as data, not as control flow: x - 0 is x, and every valid element is kept
     const bool dense = a.mode == kModeDense;
     const float m_eff = dense ? 0.f : a.m;
@@ -315,7 +315,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     }
     __syncthreads();  // counts published, tile staged
 
-    // ---- per-token counts (column tile 0 on request): one channel per lane from the staged tile
+    // ---- per-token counts (on request, the tile's own tokens): one channel per lane from the staged tile
     auto kept_by = [&](int j, int b) {
         const int c = min(c_begin + j, nchunk - 1);
         const int k = k0 + (c_begin + j) * kWave + lane;
@@ -324,8 +324,9 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
         const float dv = act_code_to_f32(code, bf16_sel) - m_eff;
         return valid & (dense | (fabsf(dv) > a.tau));
     };
-    if (per_token) {
+    if (own) {
         for (int b = 0; b < BT; ++b) {
+            if (!((own >> b) & 1u)) continue;
             int tc = 0;
 #pragma unroll
             for (int j = 0; j < MAXC; ++j) tc += __popcll(__ballot(kept_by(j, b)));
@@ -348,8 +349,9 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
         if ((um[j] >> lane) & 1ull) L.idx[ubase + lanes_below(um[j])] = k0 + (c_begin + j) * kWave + lane;
         ubase += __popcll(um[j]);
     }
-    if (per_token) {
+    if (own) {
         for (int b = 0; b < BT; ++b) {
+            if (!((own >> b) & 1u)) continue;
             int tbase = 0, ttotal = 0;
             for (int i = 0; i < WAVES; ++i) {
                 const int v = L.hdr[(1 + b) * WAVES + i];
@@ -364,7 +366,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
                     store_dev(&a.idx_out[(int64_t)b * a.K + k0 + tbase + lanes_below(tb)], k0 + (c_begin + j) * kWave + lane);
                 tbase += __popcll(tb);
             }
-            if (tid == 0 && b < a.B) store_dev(&a.seg_cnt[b * a.Sl + split], ttotal);
+            if (tid == 0) store_dev(&a.seg_cnt[b * a.Sl + split], ttotal);
         }
     }
     if (tile == 0 && tid == 0) {  // size of the union: the list's length, or the exact count where the list is a superset
