@@ -37,6 +37,24 @@ __device__ __forceinline__ uint4 load_weights16(const void* p) {
     return load_weights16((global_u32x4_t*)(uint64_t)p);
 }
 
+// 8 consecutive 16-bit inputs from an address that is 2-byte aligned only: with several tokens and an input length that
+// is not a multiple of 8, the later tokens' rows start anywhere.  (The hardware takes any alignment; one 16-byte
+// load that crosses a line instead of eight 2-byte loads.)  The caller makes sure that all 8 exist.
+struct __attribute__((packed, aligned(2))) InputOctet {
+    uint32_t w[4];
+};
+__device__ __forceinline__ uint4 load_octet(const uint16_t* p) {
+    const InputOctet t = *reinterpret_cast<const InputOctet*>(p);
+    return make_uint4(t.w[0], t.w[1], t.w[2], t.w[3]);
+}
+// the same where only the first `n` exist (the others read as 0)
+__device__ __forceinline__ uint4 load_octet_cut(const uint16_t* p, int n) {
+    uint32_t h[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) h[j] = j < n ? (uint32_t)p[j] : 0u;
+    return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+}
+
 // number of weight elements in one 16-byte load
 template <int WDT> struct Vec { static constexpr int kElems = (WDT == kI8) ? 16 : 8; static constexpr int kBytes = (WDT == kI8) ? 1 : 2; };
 

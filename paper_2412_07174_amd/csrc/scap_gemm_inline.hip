@@ -1,7 +1,7 @@
 // Batched sparse FC on the matrix cores in ONE launch (gfx950 MFMA): bf16 or int8 weights from 2 tokens, fp16
-// weights from 5, up to 16 tokens.  Two kernels: gemm_inline_kernel (below) keeps per-token value lists in LDS;
-// gemm_inline_raw_kernel (further down, the default whenever K is a multiple of 8 and 16 token slots are used)
-// stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
+// weights from 5, up to 16 tokens.  Two kernels: gemm_inline_kernel (below) keeps per-token value lists in LDS (four
+// token slots, and the launch that reads the lists of the gated product); gemm_inline_raw_kernel (further down, 16
+// token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
 //
 // Workgroup (K split, column tile of 16 lanes x 16 bytes) centres, thresholds and compacts its Kc input
 // channels of every token into LDS exactly as the one-token kernel does (SCAP Alg. 3 steps 1-2; per-token
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 }
 
 // ---------------------------------------------------------------------------------------------- staged-tile form
-// 16 token slots, K a multiple of 8.  The prologue above costs ~10 us at 16 tokens: 80 two-byte loads per lane,
+// 16 token slots.  The prologue above costs ~10 us at 16 tokens: 80 two-byte loads per lane,
 // ~10 ALU operations per input element and 16 four-byte LDS writes per kept channel, repeated by every column
 // tile.  Here the workgroup's input tile is staged as it is (16-byte loads, 16-byte LDS writes), only the union
 // list of channels is compacted, and the centred, thresholded value of (token, channel) is formed from the
@@ -176,7 +176,9 @@ __device__ __forceinline__ float word_half_to_f32(uint32_t wd, int half) {
 // a nonzero-byte test.  Everything in the test is straight-line: the instruction count per element is what the
 // prologue costs, repeated by every column tile.  Per-token lists and counts (on request, the tile's own tokens) are
 // read back from the staged tile with one channel per lane.  Returns the list length; ends with a barrier.
-template <int WAVES, int MAXC, bool SUPERSET>
+// RAGGED (16-bit weights): K is not a multiple of 8 -- token rows start at any 2-byte boundary and the last octet is cut.  A template
+// argument: the tests for it cost a kernel that does not need them 1 us (14336 x 4096 int8, 12 tokens: 23.3 -> 24.2 us).
+template <int WAVES, int MAXC, bool SUPERSET, bool RAGGED>
 __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile, int split, const Lds& L, char* xs,
                                                      uint32_t xrow) {
     constexpr int BT = kMfmaTokens;
@@ -198,14 +200,39 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     const int c_end = min(c_begin + cpw, nchunk);
     const int tg = lane & 7, o = lane >> 3;
 
-    // ---- all loads, branch-free (slots past the end re-read a valid octet)
+    // ---- all loads (slots past the end re-read the last octet)
     uint4 xv[MAXC][2];
+    if constexpr (!RAGGED) {
 #pragma unroll
-    for (int j = 0; j < MAXC; ++j) {
-        const int kb = min(k0 + (c_begin + j) * kWave + 8 * o, a.K - 8);
+        for (int j = 0; j < MAXC; ++j) {
+            const int kb = min(k0 + (c_begin + j) * kWave + 8 * o, a.K - 8);
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
-            xv[j][r] = *reinterpret_cast<const uint4*>(a.x + (int64_t)min(tg + 8 * r, a.B - 1) * a.K + kb);
+            for (int r = 0; r < 2; ++r)
+                xv[j][r] = *reinterpret_cast<const uint4*>(a.x + (int64_t)min(tg + 8 * r, a.B - 1) * a.K + kb);
+        }
+    } else {
+        // Rows that start anywhere; a token's last octet runs into the next token's row (masked below).  Only the very
+        // last octet of x can be cut: it is read from 8 elements before the end like any other load, then once more
+        // element by element.
+        const int last_octet = (a.K - 1) & ~7, total = a.B * a.K;
+#pragma unroll
+        for (int j = 0; j < MAXC; ++j) {
+            const int kb = min(k0 + (c_begin + j) * kWave + 8 * o, last_octet);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int p = min(tg + 8 * r, a.B - 1) * a.K + kb;
+                xv[j][r] = total >= 8 ? load_octet(a.x + min(p, total - 8)) : make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < MAXC; ++j) {
+            const int kb = min(k0 + (c_begin + j) * kWave + 8 * o, last_octet);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int p = min(tg + 8 * r, a.B - 1) * a.K + kb;
+                if (p > total - 8) xv[j][r] = load_octet_cut(a.x + p, total - p);
+            }
+        }
     }
     // ---- stage, test, union mask per chunk
     uint64_t um[MAXC];
@@ -244,7 +271,10 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
             const int c = c_begin + j;
             um[j] = 0;
             if (c < c_end) {  // wave-uniform
-                const bool oct_ok = (k0 + c * kWave + 8 * o) < kend;  // K and Kc are multiples of 8: whole octets
+                const int nvo = kend - (k0 + c * kWave + 8 * o);  // elements of this lane's octet that exist
+                const bool oct_ok = nvo > 0;
+                const int nvc = kend - (k0 + c * kWave);  // the same for the chunk
+                const bool cut_chunk = RAGGED && nvc < (int)kWave;  // wave-uniform
                 uint64_t kp[8];  // lane masks (bit tg + 8*o): channel 8*o+e kept by token tg or tg+8
                 uint64_t any_ok = 0;
 #pragma unroll
@@ -255,6 +285,14 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
                     // an element that does not exist becomes a NaN: the strict compare drops it
                     uint4 v = xv[j][r];
                     v = make_uint4(ok ? v.x : nan_pair, ok ? v.y : nan_pair, ok ? v.z : nan_pair, ok ? v.w : nan_pair);
+                    if (cut_chunk) {
+                        uint32_t* vw = reinterpret_cast<uint32_t*>(&v);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            if (nvo <= 2 * q) vw[q] = nan_pair;
+                            else if (nvo == 2 * q + 1) vw[q] = (vw[q] & 0xffffu) | (nan_pair & 0xffff0000u);
+                        }
+                    }
                     const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -273,6 +311,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
                     const uint64_t nz = (((v & 0x7f7f7f7f7f7f7f7full) + 0x7f7f7f7f7f7f7f7full) | v) & 0x8080808080808080ull;
                     u |= nz >> (7 - e);
                 }
+                if (cut_chunk) u &= (1ull << nvc) - 1ull;  // (dense mode keeps whole octets above)
                 um[j] = u;  // bit i: channel i of the chunk is kept by some token
                 ucount += __popcll(u);
                 ecount += __popcll(u);
@@ -380,7 +419,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
 
 // X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 151 registers per lane against 109, i.e. one
 // workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
-template <int WDT, int FUSE, bool X32>
+template <int WDT, int FUSE, bool X32, bool RAGGED>
 __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
@@ -407,7 +446,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
     // ------------------------------------------------------------------ 1. stage the inputs, list the union
     // int8 weights: 256-column tiles, so half as many workgroups repeat a split's prologue and a wavefront has
     // two chunks; listing supersets measured no gain there (and 0.14 us lost to the extra code)
-    const int cnt = stage_inputs_and_list<WAVES, kRawChunks, WDT != kI8>(a, tile, split, L, xs, xrow);
+    const int cnt = stage_inputs_and_list<WAVES, kRawChunks, WDT != kI8, RAGGED>(a, tile, split, L, xs, xrow);
     const int n_blocks = (cnt + kMfmaBlock - 1) / kMfmaBlock;
 
     // ------------------------------------------------------------------ 2. stream the kept rows
@@ -588,7 +627,7 @@ static int launch_inline(const GemvArgs& a, size_t lds, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool X32>
+template <int WDT, int FUSE, bool X32, bool RAGGED>
 static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
     if (lds > 64 * 1024) {
@@ -597,45 +636,57 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave),
+    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave),
                        lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
+// 16 token slots: the staged-tile kernel, or the value-list kernel where the inputs are the gated product's lists;
+// 4 slots: the value-list kernel (not fp16 weights: 2-4 tokens stay on the vector kernels).
+// An input length that is not a multiple of 8: the staged-tile kernel too (5461 x 2744 bf16, 8 tokens 19.7 -> 17.7 us
+// per call, block 4095 -> 6144 -> 4096 56.0 -> 51.9), but not with int8 weights, where a wavefront has only two chunks
+// to test and the value lists stay 3 % faster (5461 x 2752, 16 tokens 23.3 against 24.0; the block 41.7 against 43.0).
+__host__ constexpr bool staged_tile(int wdt, int K) { return wdt != kI8 || K % 8 == 0; }
+
 template <int WDT, int FUSE>
-static int launch_inline_wdt(const GemvArgs& a, int bt, bool raw, size_t lds, hipStream_t stream) {
-    if constexpr (FUSE != kFuseList) {
-        if (raw) {
-            if constexpr (WDT != kI8) {
-                if ((long)a.S * a.T <= 256) return launch_inline_raw<WDT, FUSE, true>(a, lds, stream);
+static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t stream) {
+    if (bt == kMfmaTokens) {
+        if constexpr (FUSE == kFuseList) {
+            return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
+        } else {
+            if constexpr (WDT == kI8) {
+                if (!staged_tile(WDT, a.K)) return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
+            } else {
+                if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
+                if ((long)a.S * a.T <= 256) return launch_inline_raw<WDT, FUSE, true, false>(a, lds, stream);
             }
-            return launch_inline_raw<WDT, FUSE, false>(a, lds, stream);
+            return launch_inline_raw<WDT, FUSE, false, false>(a, lds, stream);
         }
     }
-    if constexpr (WDT == kF16)  // fp16 weights: 16 token slots only (2-4 tokens stay on the vector kernel)
-        return launch_inline<WDT, 16, FUSE>(a, lds, stream);
+    if constexpr (WDT == kF16)
+        return SCAP_ERR_CONFIG;
     else
-        return bt == 4 ? launch_inline<WDT, 4, FUSE>(a, lds, stream) : launch_inline<WDT, 16, FUSE>(a, lds, stream);
+        return launch_inline<WDT, 4, FUSE>(a, lds, stream);
 }
 
 template <int FUSE>
-static int launch_inline_any(const GemvArgs& a, int wdt, int bt, bool raw, size_t lds, hipStream_t stream) {
-    if (wdt == kBF16) return launch_inline_wdt<kBF16, FUSE>(a, bt, raw, lds, stream);
-    if (wdt == kF16) return bt == kMfmaTokens ? launch_inline_wdt<kF16, FUSE>(a, bt, raw, lds, stream) : SCAP_ERR_CONFIG;
-    if (wdt == kI8) return launch_inline_wdt<kI8, FUSE>(a, bt, raw, lds, stream);
+static int launch_inline_any(const GemvArgs& a, int wdt, int bt, size_t lds, hipStream_t stream) {
+    if (wdt == kBF16) return launch_inline_wdt<kBF16, FUSE>(a, bt, lds, stream);
+    if (wdt == kF16) return launch_inline_wdt<kF16, FUSE>(a, bt, lds, stream);
+    if (wdt == kI8) return launch_inline_wdt<kI8, FUSE>(a, bt, lds, stream);
     return SCAP_ERR_CONFIG;
 }
 
 // Plan one launch: token slots, rows per workgroup (bounded by LDS and, for the input prologue, by the
 // registers that hold a wavefront's chunks), LDS bytes.
 static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, int* bt_out, size_t* lds_out,
-                       bool* raw_out = nullptr, bool slots16 = false) {
+                       bool slots16 = false) {
     if (wdt != kBF16 && wdt != kI8 && wdt != kF16) return SCAP_ERR_CONFIG;
     if (a.B < 1 || a.B > kMfmaTokens) return SCAP_ERR_CONFIG;
     const int bt = (a.B <= 4 && !slots16) ? 4 : 16;
@@ -657,18 +708,14 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
     *lds_out = lds_bytes(a.Kc, bt, red);
-    // staged-tile form: 16 token slots, whole octets of channels, 16-byte aligned token rows
-    const bool raw = raw_out != nullptr && bt == kMfmaTokens && fuse != kFuseList && a.K >= 8 && (a.K % 8) == 0 &&
-                     (reinterpret_cast<uintptr_t>(a.x) & 15u) == 0 && a.Kc <= kInlineWaves * kWave * kRawChunks;
-    if (raw) {
+    if (bt == kMfmaTokens && fuse != kFuseList && staged_tile(wdt, a.K)) {  // staged-tile form: the inputs as they are in place of the value lists
         const size_t body = (size_t)a.Kc * 4 + raw_tile_bytes(a.Kc);
         *lds_out = kHdrBytes + (body > red ? body : red);
     }
-    if (raw_out) *raw_out = raw;
     return SCAP_OK;
 }
 
-// slots16: run 2-4 tokens in the 16-slot kernels (the staged-tile form when the shape allows it)
+// slots16: run 2-4 tokens in the 16-slot staged-tile kernel
 int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipStream_t stream, bool slots16) {
     GemvArgs a = a_in;
     if (a.B < kMfmaMinTokens) return SCAP_ERR_CONFIG;
@@ -680,12 +727,11 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     }
     int bt = 0;
     size_t lds = 0;
-    bool raw = false;
-    const int rc = plan_inline(a, wdt, kc, kc != 0, kFusePlain, &bt, &lds, &raw, slots16);
+    const int rc = plan_inline(a, wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
     a.Kl = a.Kc;
     a.Sl = a.S;
-    return launch_inline_any<kFusePlain>(a, wdt, bt, raw, lds, stream);
+    return launch_inline_any<kFusePlain>(a, wdt, bt, lds, stream);
 }
 
 // The two launches of the fused SwiGLU block on the matrix cores (see scap_swiglu.hip for the vector form).
@@ -693,8 +739,7 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     GemvArgs up = up_in, dn = dn_in;
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
-    bool raw_up = false;
-    int rc = plan_inline(up, wdt, 0, false, kFuseSwiglu, &bt_up, &lds_up, &raw_up);
+    int rc = plan_inline(up, wdt, 0, false, kFuseSwiglu, &bt_up, &lds_up);
     if (rc != SCAP_OK) return rc;
     up.Kl = up.Kc;
     up.Sl = up.S;
@@ -704,9 +749,9 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     dn.Sl = (dn.K + kWave - 1) / kWave;
     const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (tile 0's last arrival)
     if (lds_dn < tables) lds_dn = tables;
-    rc = launch_inline_any<kFuseSwiglu>(up, wdt, bt_up, raw_up, lds_up, stream);
+    rc = launch_inline_any<kFuseSwiglu>(up, wdt, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;
-    return launch_inline_any<kFuseList>(dn, wdt, bt_dn, false, lds_dn, stream);
+    return launch_inline_any<kFuseList>(dn, wdt, bt_dn, lds_dn, stream);
 }
 
 }  // namespace scap

@@ -126,11 +126,10 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
 }
 
 // Two tokens, or three to four (16-bit weights; int8 where N <= 4096, i.e. 8-byte lanes), through the two- /
-// four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, an input length
-// that is not a multiple of 8 (the later tokens' rows would not be 16-byte aligned), more than 2048 channels per
-// workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
+// four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, more than 2048
+// channels per workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
 int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
-    if (g.B < 2 || g.B > 4 || g.mode == kModeFold || (g.K % 8) != 0) return kG1NotApplicable;
+    if (g.B < 2 || g.B > 4 || g.mode == kModeFold || (wdt == kF16 && g.K % 8 != 0)) return kG1NotApplicable;
 
     Gemv1bArgs b;
     b.B = g.B;
@@ -197,7 +196,7 @@ int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& dn, int wdt, int up
 // Fused SwiGLU block of two tokens (down launch: up to four): each of its launches can run on the multi-slot kernel, in the list format of the
 // batched block kernels (64-channel segments, 2 token slots), so either can be paired with the general kernel's.
 //   part 0, the gate|up launch with the gating epilogue: int8 weights in 16-byte lanes (2F > 4096; a wavefront's
-//           slice is then 128 columns = one segment), input length a multiple of 8;
+//           slice is then 128 columns = one segment);
 //   part 1, the down launch reading the lists: any weights, unless 16-bit and too wide for the fixed-point hand-over
 //           (with partial sums handed over the general kernel's down launch measured 0.5 us faster).
 // Measured on 4096 -> 14336 -> 4096, two tokens, both launches general / these (us): int8 45.8 / 41.9 with nothing
@@ -208,7 +207,7 @@ static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int
     const bool four = (up.B == 3 || up.B == 4) && part == 1 && wdt != kI8;
     if (up.B != 2 && !four) return kG1NotApplicable;
     const GemvArgs& src = part == 0 ? up : dn;
-    if (part == 0 && (wdt != kI8 || (src.K % 8) != 0)) return kG1NotApplicable;
+    if (part == 0 && wdt != kI8) return kG1NotApplicable;
     if (part == 1 && wdt != kI8 && (int64_t)up.B * (int64_t)src.N > (int64_t)kFxCols) return kG1NotApplicable;
     Plan1 pl;
     const int rc = plan_gemv1(src, wdt, 0, false, kG1bWaves, kWave, four ? 4 : 2, &pl);  // whole 64-channel pieces: whole segments

@@ -103,17 +103,25 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     const int kend = min(k0 + Kc, K);
 
     // ------------------------------------------------------------------ 1. inputs: every wavefront, all Kc, all tokens
-    // (K is a multiple of 8 -- checked on the host --, so every token's row is 16-byte aligned and no octet is ragged)
     uint4 xv[BT][NCH];
     if constexpr (FUSE != kFuseList) {
+        auto load_inputs = [&](auto octet) {
 #pragma unroll
-        for (int b = 0; b < BT; ++b) {
+            for (int b = 0; b < BT; ++b) {
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                xv[b][c] = make_uint4(0u, 0u, 0u, 0u);
-                const int kb = k0 + c * kG1Chunk + 8 * lane;
-                if (b < B && kb < kend) xv[b][c] = *reinterpret_cast<const uint4*>(x + (size_t)b * K + kb);
+                for (int c = 0; c < NCH; ++c) {
+                    xv[b][c] = make_uint4(0u, 0u, 0u, 0u);
+                    const int kb = k0 + c * kG1Chunk + 8 * lane;
+                    if (b < B && kb < kend) xv[b][c] = octet(x + (size_t)b * K + kb, (B - b) * K - kb);
+                }
             }
+        };
+        if ((K & 7) == 0) {  // every token's row is 16-byte aligned and no octet is ragged
+            load_inputs([](const uint16_t* p, int) { return *reinterpret_cast<const uint4*>(p); });
+        } else {
+            // rows start at any 2-byte boundary; a token's last octet runs into the next token's row -- those elements
+            // are masked below --, and only the very last octet of x (`left` elements) is read element by element
+            load_inputs([](const uint16_t* p, int left) { return left >= 8 ? load_octet(p) : load_octet_cut(p, left); });
         }
     }
     // Column c of this lane is fcol + c * CSTR: lanes side by side (every store and atomic of the hand-over then covers

@@ -95,8 +95,8 @@ int launch_gemv(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStrea
 // workgroup would own more channels than that kernel tests per wavefront: the caller takes launch_gemv's kernel.
 constexpr int kG1NotApplicable = 1;
 int launch_gemv1(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStream_t stream);
-// Two to four tokens through that kernel's two- / four-slot form; kG1NotApplicable likewise (also for another token count, bias
-// folding and an input length that is not a multiple of 8).
+// Two to four tokens through that kernel's two- / four-slot form; kG1NotApplicable likewise (also for another token count and
+// bias folding).
 int launch_gemv1b(const GemvArgs& a, int wdt, int flags, hipStream_t stream);
 // The fused block of one token on the same kernel (two launches); kG1NotApplicable likewise.
 // Two-token block: whether launch `part` (0: gate|up with the gating epilogue, 1: down reading the lists) can run on the

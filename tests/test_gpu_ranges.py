@@ -4,13 +4,16 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+import paper_2412_07174_amd as scap
 import workloads as wl
 from workloads import BF16, F16, I8
 
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import Layer, check_against_oracle
+    from gpu_util import Layer, assert_y_close, check_against_oracle, to_dev
+    from test_gpu_swiglu import Block
 
 
 def _layer(K, N, wdt, seed, B=16):
@@ -30,3 +33,35 @@ def test_lists_of_a_batch_whatever_the_number_of_tiles(K, N, lanes):
         for tau in (0.3, 1.2):
             print(f"lists K={K} N={N} B={B} lanes={lanes} tau={tau}", flush=True)
             check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, 0, 0, lanes) if lanes else None, what=f"{K} {N} {B} {lanes}")
+
+
+# an input length that is not a multiple of 8: the later tokens' rows start at any 2-byte boundary and the last octet is
+# cut; shorter than an octet, just past chunk boundaries (64, 512), several splits
+@pytest.mark.parametrize("wdt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,N", [(1, 144), (7, 144), (9, 4112), (65, 1040), (513, 144), (1001, 4112), (2047, 1040), (5461, 2752)])
+def test_batches_over_an_odd_input_length(K, N, wdt):
+    layer, xdt = _layer(K, N, wdt, 910 + K)
+    for B in (2, 3, 4, 5, 9, 16):
+        X = wl.laplace(B, K, 911 + K, xdt, loc=0.1, scale=0.5)
+        for tau in (0.0, 0.9):
+            print(f"odd K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
+            check_against_oracle(layer, X, xdt, 0.1, tau, None, what=f"K={K} N={N} wdt={wdt} B={B} tau={tau}")
+        y = scap.dense_fc(layer.W, to_dev(X, xdt), None, col_scale=layer.scale, workspace=layer.ws)
+        torch.cuda.synchronize()
+        want = oracle.dense_fc(layer.W_host, X, None, wdt, xdt, col_scale=layer.scale_host)
+        assert_y_close(y.cpu().numpy(), want, f"dense K={K} N={N} wdt={wdt} B={B}")
+
+
+# the block over an odd hidden size; gated products that end inside a 32- or 64-channel segment
+@pytest.mark.parametrize("dt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,F,N", [(129, 72, 144), (1001, 2088, 528), (519, 4104, 4112)])
+def test_blocks_over_an_odd_hidden_size(K, F, N, dt):
+    blk = Block(K, F, N, dt, 930 + K, B=16)
+    xdt = F16 if dt == F16 else BF16
+    rng = np.random.default_rng(931 + K)
+    bg, bu, bd = (rng.standard_normal(n).astype(np.float32) * 0.1 for n in (F, F, N))
+    for B in (2, 3, 4, 5, 16):
+        X = wl.laplace(B, K, 932 + B, xdt, loc=0.05, scale=0.5)
+        for tau_x, tau_z in ((0.0, 0.0), (0.3, 0.02), (0.8, 1e6)):
+            print(f"odd block {K}->{F}->{N} dt={dt} B={B} tau_x={tau_x} tau_z={tau_z}", flush=True)
+            blk.check_batch(X, xdt, 0.05, tau_x, bg, bu, 0.01, tau_z, bd, what=f"{K} {F} {N} B={B} {tau_x} {tau_z}")
