@@ -129,7 +129,7 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
 // four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, more than 2048
 // channels per workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
 int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
-    if (g.B < 2 || g.B > 4 || g.mode == kModeFold || (wdt == kF16 && g.K % 8 != 0)) return kG1NotApplicable;
+    if (g.B < 2 || g.B > 4 || g.mode == kModeFold) return kG1NotApplicable;
 
     Gemv1bArgs b;
     b.B = g.B;

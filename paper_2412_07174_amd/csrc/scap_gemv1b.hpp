@@ -310,8 +310,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             return load_row<WDT>(wbase, (uint32_t)__builtin_amdgcn_readlane(vidx, i), row_bytes, lane_off);
         };
         auto fma_rows = [&](const uint4& r, int i) {
-#pragma unroll
-            for (int b = 0; b < BT; ++b) fma_row<WDT>(acc[b], r, read_lane_f(vd[b], i));
+            fma_row<WDT, BT>(acc, r, [&](int b) { return read_lane_f(vd[b], i); });
         };
         uint4 r[UNROLL];
         if (nb < UNROLL) {
