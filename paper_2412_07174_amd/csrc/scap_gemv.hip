@@ -18,7 +18,8 @@
 namespace scap {
 
 // ---------------------------------------------------------------------------------------------- launch
-int plan_splits(GemvArgs& a, int tile, int floats_per_entry, int kc, bool kc_forced, size_t lds_budget, int granule) {
+int plan_splits(GemvArgs& a, int tile, int floats_per_entry, int kc, bool kc_forced, size_t lds_budget, int granule,
+                SplitCost split_cost) {
     a.T = (int)((a.N + tile - 1) / tile);
     if (a.T > kMaxTiles) return SCAP_ERR_SHAPE;
     // bounds from the workspace (at most kMaxSplits splits and partial_capacity floats per token) and from
@@ -33,8 +34,8 @@ int plan_splits(GemvArgs& a, int tile, int floats_per_entry, int kc, bool kc_for
         // launch takes about as long as the busiest unit: ceil(workgroups / 256) workgroups, each costing
         // its kc rows plus a fixed part (prologue, reduction, hand-over) worth about kFixedRows rows.
         // Slightly more than 256 workgroups is the worst case (on 4096 x 28672, 280 workgroups of 832 rows
-        // took 50.8 us, 224 of 1024 rows 38.2 us); more splits than needed only lengthen the final
-        // reduction, so ties go to the larger kc.
+        // took 50.8 us, 224 of 1024 rows 38.2 us).  Every split adds its hand-over (split_cost, from sweeps of kc over
+        // the kernel that plans); ties go to the larger kc.
         // Candidates: for every split count the smallest kc (a multiple of `granule`) that gives it; any other
         // kc with the same split count only costs more.
         constexpr int kFixedRows = 128;
@@ -44,7 +45,8 @@ int plan_splits(GemvArgs& a, int tile, int floats_per_entry, int kc, bool kc_for
             const int c = (int)align_up((size_t)((a.K + sp - 1) / sp), (size_t)granule);
             if (c > kc_lds) continue;
             const long splits = (a.K + c - 1) / c;
-            const long cost = ((splits * a.T + 255) / 256) * (c + kFixedRows);
+            long cost = ((splits * a.T + 255) / 256) * (c + kFixedRows) + splits * split_cost.rows;
+            if (split_cost.soft_max > 0 && splits > split_cost.soft_max) cost += split_cost.beyond_rows;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 kc = c;
@@ -122,7 +124,9 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // dense call with a long input into a narrow layer stays on the staged-tile kernel.  int8 weights in 8-byte lanes
     // (N <= 4096; wider int8 layers do not fit and fall through to the matrix cores): 14336 x 4096, 4 tokens,
     // 19.7 / 17.7 / 12.9 at 50 / 70 / 90 % against 19.9 / 18.3 / 14.0, 3 tokens 18.1 / 15.8 / 11.9 against 19.1 / 17.0 / 12.9.
-    const bool four_slots = (a.B == 3 || a.B == 4) &&
+    // bf16 layers of at most 1024 columns keep the vector kernel (4096 x 1024, 4 tokens: 9.4 against 10.0 us; int8 and fp16
+    // are faster here: 12.3 -> 10.4, 12.9 -> 10.5).
+    const bool four_slots = (a.B == 3 || a.B == 4) && !(wdt == kBF16 && a.N <= 1024) &&
                             !(a.mode == kModeDense && (int64_t)a.K >= 2 * (int64_t)a.N);
     if ((a.B == 2 || four_slots) && lanes == 0 &&
         (wdt == kI8 || a.N <= 8192 || 2 * (int64_t)a.N <= (int64_t)kFxCols) &&

@@ -52,11 +52,19 @@ int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, in
     if (fixed_lds + (int64_t)kWave * (4 + entry) > lds_max) return kG1NotApplicable;
     const size_t lds_budget = (size_t)(lds_max - fixed_lds) + kHdrBytes;
     // Rows per workgroup in multiples of 64, unless the input is so short that 64-row pieces would leave compute
-    // units without a workgroup (1024 x 4096: 16 splits x 8 tiles; with 32-row pieces 8.5 -> 6.5 us dense)
+    // units without a workgroup (finer pieces elsewhere gained and lost 2 % by turns)
     p.T = (p.N + out->tile - 1) / out->tile;
     int granule = ((int64_t)((p.K + kWave - 1) / kWave) * p.T < 256) ? 8 : kWave;
     if (granule < granule_min) granule = granule_min;
-    const int rc = plan_splits(p, out->tile, entry / 4 - 1, kc, kc_forced, lds_budget, granule);
+    // A split costs 2 rows' time and one more per 4096 columns: its atomics queue up on the columns' words.  Fitted to
+    // sweeps of kc over 100 (shape, type, token count) points with kc from 16 to 1408; without it narrow layers
+    // were cut into pieces of 8-32 rows (us, before / now: 1024 x 1024 bf16 8.8 / 4.6, 4096 x 1024 9.4 / 5.7, 2 tokens
+    // 12.3 / 5.9 and 13.4 / 7.0).  Beyond 64 splits partial sums are handed over instead, about 4 us more.
+    SplitCost sc;
+    sc.rows = 2 + (p.N + 2048) / 4096;
+    sc.soft_max = kFxMaxSplits;
+    sc.beyond_rows = 512;
+    const int rc = plan_splits(p, out->tile, entry / 4 - 1, kc, kc_forced, lds_budget, granule, sc);
     if (rc != SCAP_OK) return rc == SCAP_ERR_SHAPE ? kG1NotApplicable : rc;
     if (p.Kc > kG1MaxChunks * kG1Chunk) return kG1NotApplicable;
     out->Kc = p.Kc;

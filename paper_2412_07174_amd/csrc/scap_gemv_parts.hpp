@@ -827,10 +827,18 @@ inline size_t lds_bytes(int Kc, int floats_per_entry, size_t red_bytes) {
     return kHdrBytes + body;
 }
 
+// What a K split costs beyond its rows, in rows of one workgroup (see plan_splits): the hand-over of one more partial sum
+// per column and token.
+struct SplitCost {
+    int rows = 0;         // per split
+    int soft_max = 0;     // more splits than this (0: no such limit) cost ...
+    int beyond_rows = 0;  // ... this much once
+};
+
 // Choose the K split of a launch: fills a.T, a.Kc, a.S.  `tile` = columns per workgroup, `kc` = requested
 // rows per workgroup (0 = about one workgroup per compute unit).  Returns a scap_status.
 // `lds_budget` = LDS bytes one workgroup may use for its list.
 int plan_splits(GemvArgs& a, int tile, int floats_per_entry, int kc, bool kc_forced, size_t lds_budget = 64 * 1024,
-                int granule = kWave);
+                int granule = kWave, SplitCost split_cost = SplitCost{});
 
 }  // namespace scap

@@ -65,3 +65,14 @@ def test_blocks_over_an_odd_hidden_size(K, F, N, dt):
         for tau_x, tau_z in ((0.0, 0.0), (0.3, 0.02), (0.8, 1e6)):
             print(f"odd block {K}->{F}->{N} dt={dt} B={B} tau_x={tau_x} tau_z={tau_z}", flush=True)
             blk.check_batch(X, xdt, 0.05, tau_x, bg, bu, 0.01, tau_z, bd, what=f"{K} {F} {N} B={B} {tau_x} {tau_z}")
+
+
+# narrow layers: K splits that used to be pieces of 8-32 rows, up to the 64 splits of the fixed-point hand-over and past it
+@pytest.mark.parametrize("wdt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,N", [(512, 512), (1024, 1024), (4096, 1024), (4099, 1040), (8200, 512), (33000, 128)])
+def test_narrow_layers_of_one_to_four_tokens(K, N, wdt):
+    layer, xdt = _layer(K, N, wdt, 940 + K, B=4)
+    for B in (1, 2, 3, 4):
+        X = wl.swiglu(B, K, 941 + K, xdt)
+        print(f"narrow K={K} N={N} wdt={wdt} B={B}", flush=True)
+        check_against_oracle(layer, X, xdt, 0.0, 0.4, None, what=f"K={K} N={N} wdt={wdt} B={B}")
