@@ -34,12 +34,24 @@ struct Plan1 {
     int elems, tile, Kc, S, T;
 };
 
+// int8 weights: 8 bytes per lane (512-column tiles) up to kI8HalfCols columns -- twice the tiles, so half the K splits
+// and half the sums per wavefront to add at the end --, 16 beyond, where there are tiles enough.  16-byte / 8-byte
+// lanes at 50 %, us: 4096 x 11008 one token 9.9 / 8.9, two 14.0 / 11.9; 1024 x 8192 7.0 / 5.8 and 10.0 / 7.8;
+// 4096 x 16384 11.5 / 10.4 and 16.5 / 14.4; 4096 x 28672 14.7 / 15.2 and 21.4 / 22.3.
+constexpr int kI8HalfCols = 16384;
+constexpr int kI8WideCols = 4096;
+// Four slots over int8 weights issue four FMAs per weight and token: as the stream gets longer the matrix cores win (3 / 4
+// tokens at 50 %, matrix cores / here: 4096 x 11008 18.3 / 16.7 and 19.2 / 17.9, 8192 x 8192 21.0 / 20.1 and 21.9 / 21.4,
+// 4096 x 16384 dense 22.8 / 22.2 and 23.2 / 23.4, 14336 x 8192 29.4 / 30.7 and 30.5 / 32.8); up to kI8WideCols columns
+// they never do.
+constexpr int64_t kI8FourSlotWeights = (int64_t)1 << 26;
+
 // K split and lane width of one launch.  SCAP_OK, kG1NotApplicable or a scap_status.
 // bt = token slots: 1 (one-token kernel), 2 or 4 (its multi-token forms, 8 wavefronts).
-int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out) {
-    // int8 weights: 16 bytes per lane (1024-column tiles) unless that leaves at most 4 tiles -- then 8 bytes per
-    // lane, twice the tiles and half the K splits (14336 x 4096 int8: 15.9 -> 14.2 us dense)
-    out->i8_half = wdt == kI8 && g.N <= 4 * 1024;
+// wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
+int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out,
+               bool wide_lanes = false) {
+    out->i8_half = wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols);
     out->elems = wdt == kI8 && !out->i8_half ? 16 : 8;
     out->tile = kWave * out->elems;
     GemvArgs p = g;
@@ -133,11 +145,13 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
     return SCAP_ERR_DTYPE;
 }
 
-// Two tokens, or three to four (16-bit weights; int8 where N <= 4096, i.e. 8-byte lanes), through the two- /
+// Two tokens, or three to four (int8 weights: in 8-byte lanes only), through the two- /
 // four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, more than 2048
 // channels per workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
 int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
     if (g.B < 2 || g.B > 4 || g.mode == kModeFold) return kG1NotApplicable;
+
+    if (wdt == kI8 && g.B > 2 && g.N > kI8WideCols && (int64_t)g.K * g.N > kI8FourSlotWeights) return kG1NotApplicable;
 
     Gemv1bArgs b;
     b.B = g.B;
@@ -218,7 +232,8 @@ static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int
     if (part == 0 && wdt != kI8) return kG1NotApplicable;
     if (part == 1 && wdt != kI8 && (int64_t)up.B * (int64_t)src.N > (int64_t)kFxCols) return kG1NotApplicable;
     Plan1 pl;
-    const int rc = plan_gemv1(src, wdt, 0, false, kG1bWaves, kWave, four ? 4 : 2, &pl);  // whole 64-channel pieces: whole segments
+    // whole 64-channel pieces: whole segments
+    const int rc = plan_gemv1(src, wdt, 0, false, kG1bWaves, kWave, four ? 4 : 2, &pl, part == 0);
     if (rc != SCAP_OK) return kG1NotApplicable;
     if (four && pl.Kc > 2 * kG1Chunk) return kG1NotApplicable;  // (its prologue holds every entry slot in registers)
     if (part == 0 && pl.i8_half) return kG1NotApplicable;

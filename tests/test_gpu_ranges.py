@@ -76,3 +76,15 @@ def test_narrow_layers_of_one_to_four_tokens(K, N, wdt):
         X = wl.swiglu(B, K, 941 + K, xdt)
         print(f"narrow K={K} N={N} wdt={wdt} B={B}", flush=True)
         check_against_oracle(layer, X, xdt, 0.0, 0.4, None, what=f"K={K} N={N} wdt={wdt} B={B}")
+
+
+# int8 weights in 8- or 16-byte lanes: either side of the column count where the lanes change, and of the layer size
+# from which 3-4 tokens go to the matrix cores
+@pytest.mark.parametrize("K,N", [(300, 4096), (300, 4112), (1100, 16384), (1100, 16400), (5000, 16384)])
+def test_int8_lane_widths(K, N):
+    layer, xdt = _layer(K, N, I8, 950 + K, B=4)
+    bf = np.random.default_rng(951 + K).standard_normal(N).astype(np.float32)
+    for B in (1, 2, 3, 4):
+        X = wl.laplace(B, K, 952 + K, xdt, loc=0.1, scale=0.5)
+        print(f"int8 lanes K={K} N={N} B={B}", flush=True)
+        check_against_oracle(layer, X, xdt, 0.1, 0.5, bf, what=f"K={K} N={N} B={B}")
