@@ -3,10 +3,10 @@
 //
 // The calibration activations are 16-bit codes, so a pooled sample of any size has at most 65 536 distinct
 // values.  ONE streaming pass over the sample counts how often each code occurs; every statistic the
-// estimators need is then a function of those 65 536 counts and is evaluated on the host with the same
-// IEEE operations the pruner uses on the device (widening is exact, d = fp32(x) - m is one fp32
-// subtraction): order statistics by walking the counts in value order -- exact, no float error -- the mean
-// as an fp64 sum of count x value, the histogram mode from fp64 bin arithmetic.
+// estimators need is then a function of those 65 536 counts, evaluated with the same IEEE operations the pruner
+// uses (widening is exact, d = fp32(x) - m is one fp32 subtraction).  With the median or m = 0 that is two order
+// statistics, which one workgroup selects from the counts on the GPU (select_kernel); the mean (an fp64 sum of count x
+// value), the histogram mode (fp64 bin arithmetic) and samples of 2^32 values or more are evaluated on the host.
 #include <math.h>
 #include <cmath>
 #include <string.h>
@@ -76,6 +76,175 @@ __global__ __launch_bounds__(kHistThreads) void code_hist_kernel(const uint16_t*
     for (int i = tid; i < kHalf; i += kHistThreads) {
         const uint32_t v = sh[i];
         if (v) atomicAdd(&hist[half * kHalf + i], (unsigned long long)v);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- order statistics
+// m = median of the sample (or 0) and tau = k-th smallest |value - m| from the counts, by one workgroup (M < 2^32): each
+// selection is a radix select over LDS bins.  A first pass lists the groups of 64 codes that have counts at all (most
+// samples touch a tenth of the bf16 codes, and neighbouring ones); the others read those groups again, from L2.  The
+// loops are rolled: with the counts in registers and every loop unrolled the kernel took 56 us, waiting for its own
+// 100 KB of instructions; with 16 groups in flight 43, with 8 36.  A call with the median, us, before (the counts copied
+// to the host and walked there) / now: bf16 256 x 1024 140 / 66, 16384 x 4096 171 / 94; fp16 186 / 105 and 268 / 157.
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / kWave;
+constexpr int kGroups = kCodes / kWave;
+constexpr int kSelBins = 2048;
+constexpr int kSelFly = 8;  // groups in flight per wavefront
+constexpr uint32_t kNoRank = 0xFFFFFFFFu;
+
+// sum over the wavefront, in every lane: within rows of 16 by DPP, the four rows by scalar adds
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lanes 1,0,3,2 of a quad
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lanes 2,3,0,1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // mirrored in each half row
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // mirrored in each row
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16) +
+           (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+}
+
+struct SelLds {
+    uint32_t bins[kSelBins];
+    uint32_t wave[kSelWaves];
+    uint16_t live[kGroups];  // groups with counts, in no particular order
+    int nlive;
+    uint32_t bin, rank;  // where a rank fell: its bin and the rank inside it
+};
+
+__device__ __forceinline__ void sel_clear(SelLds& s) {
+    for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) s.bins[i] = 0;
+    __syncthreads();
+}
+
+// bins[bin] += c.  Consecutive codes often fall into one bin: then one add per wavefront instead of 64 on one word.
+__device__ __forceinline__ void sel_add(SelLds& s, uint32_t bin, uint32_t c) {
+    const uint64_t live = __ballot(c != 0);
+    if (live == 0) return;  // wave-uniform
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, __builtin_ctzll(live));
+    if (__ballot(c != 0 && bin != first) == 0) {
+        const uint32_t sum = wave_total(c);
+        if (lane_id() == 0) atomicAdd(&s.bins[first], sum);
+    } else if (c != 0) {
+        atomicAdd(&s.bins[bin], c);
+    }
+}
+
+// The bin that holds rank r (1-based; s.bin = kNoRank past the total) and the rank inside it.  Ends with a barrier.
+__device__ __forceinline__ void sel_find(SelLds& s, uint32_t r) {
+    const int tid = threadIdx.x, w = tid >> 6;
+    __syncthreads();
+    if (tid == 0) s.bin = kNoRank;
+    const uint32_t a = s.bins[2 * tid], b = s.bins[2 * tid + 1];
+    const uint32_t inc = (uint32_t)wave_inclusive_scan((int)(a + b));
+    if (lane_id() == kWave - 1) s.wave[w] = inc;
+    __syncthreads();
+    uint32_t before = inc - (a + b);
+    for (int i = 0; i < w; ++i) before += s.wave[i];
+    if (r > before && r - before <= a) {
+        s.bin = 2 * tid;
+        s.rank = r - before;
+    } else if (r > before + a && r - before - a <= b) {
+        s.bin = 2 * tid + 1;
+        s.rank = r - before - a;
+    }
+    __syncthreads();
+}
+static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
+
+// position of a code in ascending value order (sign-magnitude; -0 before +0) and back
+__device__ __forceinline__ uint32_t code_rank(uint32_t c) { return (c & 0x8000u) ? 0xFFFFu - c : 0x8000u + c; }
+__device__ __forceinline__ uint32_t rank_code(uint32_t p) { return p < 0x8000u ? 0xFFFFu - p : p - 0x8000u; }
+
+__global__ __launch_bounds__(kSelThreads) void select_kernel(const unsigned long long* __restrict__ hist, uint32_t M, int xdt,
+                                                            int median, uint32_t k, float* __restrict__ out) {
+    __shared__ SelLds s;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int w = uniform(tid >> 6);
+    const float nan = __uint_as_float(0x7FFFFFFFu);
+    auto value = [&](uint32_t c) { return xdt == kBF16 ? bf16_bits_to_f32(c) : f16_bits_to_f32(c); };
+    // f(code, count) for this lane's code of each group of `n` listed ones (of all groups: n < 0); NaN codes rank behind
+    // every number and are not counted
+    auto for_groups = [&](int n, auto f) {
+        const int total = n < 0 ? kGroups : n;
+        for (int g0 = w * kSelFly; g0 < total; g0 += kSelWaves * kSelFly) {
+            uint32_t code[kSelFly], c[kSelFly];
+#pragma unroll
+            for (int u = 0; u < kSelFly; ++u) {
+                const int g = min(g0 + u, total - 1);
+                code[u] = (uint32_t)(n < 0 ? g : (int)s.live[g]) * kWave + lane;
+                c[u] = (uint32_t)hist[code[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kSelFly; ++u) {
+                const float v = value(code[u]);
+                f(code[u], (g0 + u < total && v == v) ? c[u] : 0u);
+            }
+        }
+    };
+    if (tid == 0) s.nlive = 0;
+    __syncthreads();
+    for_groups(-1, [&](uint32_t code, uint32_t c) {
+        if (__ballot(c != 0) != 0 && lane == 0) s.live[atomicAdd(&s.nlive, 1)] = (uint16_t)(code / kWave);
+    });
+    __syncthreads();
+    const int n = s.nlive;
+    float m = 0.f;
+    if (median) {  // the middle value, or the mean of the two middle ones; 2048 bins of 32 codes, then the 32 codes
+        float mid[2];
+        sel_clear(s);
+        for_groups(n, [&](uint32_t code, uint32_t c) { sel_add(s, code_rank(code) >> 5, c); });
+        uint32_t bin[2], rank[2];
+        for (int j = 0; j < 2; ++j) {
+            sel_find(s, (M % 2 == 1) ? M / 2 + 1 : M / 2 + (uint32_t)j);
+            bin[j] = s.bin;
+            rank[j] = s.rank;
+        }
+        sel_clear(s);  // the codes of the first rank's bin in bins 0-31, of the second's, if another, in 32-63
+        for_groups(n, [&](uint32_t code, uint32_t c) {
+            const uint32_t p = code_rank(code), pb = p >> 5;
+            sel_add(s, (p & 31u) + (pb == bin[0] ? 0u : 32u), pb == bin[0] || pb == bin[1] ? c : 0u);
+        });
+        __syncthreads();
+        if (bin[1] != bin[0] && bin[0] != kNoRank) {  // uniform: bins 32-63 follow what bins 0-31 hold
+            uint32_t first = 0;
+            for (int i = 0; i < 32; ++i) first += s.bins[i];
+            rank[1] += first;
+        }
+        for (int j = 0; j < 2; ++j) {
+            mid[j] = nan;
+            if (bin[j] == kNoRank) continue;  // uniform
+            sel_find(s, rank[j]);
+            mid[j] = value(rank_code((bin[j] << 5) | (s.bin & 31u)));
+        }
+        m = (M % 2 == 1) ? mid[0] : (float)(((double)mid[0] + (double)mid[1]) / 2.0);
+    }
+    float tau = 0.f;
+    if (k > 0) {
+        tau = nan;
+        if (m == m) {
+            // |value - m| as a 31-bit key: bits 30-20, 19-10, 9-0 (infinite values of the sign of an infinite m: NaN, last)
+            uint32_t prefix = 0, rank = k;
+            bool found = true;
+            for (int pass = 0; pass < 3 && found; ++pass) {
+                const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
+                sel_clear(s);
+                for_groups(n, [&](uint32_t code, uint32_t c) {
+                    const float d = fabsf(value(code) - m);
+                    const uint32_t key = __float_as_uint(d);
+                    const bool in = d == d && (pass == 0 || (key >> (shift + 10)) == prefix);
+                    sel_add(s, pass == 0 ? key >> 20 : (key >> shift) & 1023u, in ? c : 0u);
+                });
+                sel_find(s, rank);
+                found = s.bin != kNoRank;
+                prefix = pass == 0 ? s.bin : (prefix << 10) | s.bin;
+                rank = s.rank;
+            }
+            if (found) tau = __uint_as_float(prefix);
+        }
+    }
+    if (tid == 0) {
+        out[0] = m;
+        out[1] = tau;
     }
 }
 
@@ -264,6 +433,19 @@ int run_calibrate(const uint16_t* X, int64_t M, int xdt, float s, int est, float
     }
     hipLaunchKernelGGL(code_hist_kernel, dim3(2 * kHistChunks), dim3(kHistThreads), kHalf * 4, stream, X, M, d_hist);
     if (!ok(hipGetLastError())) return SCAP_ERR_HIP;
+    const int64_t k = quantile_rank((double)s, M);
+    if ((est == SCAP_MODE_ZERO || est == SCAP_MODE_MEDIAN) && M < ((int64_t)1 << 32)) {
+        float* d_out = reinterpret_cast<float*>(static_cast<char*>(workspace) + kOffSelected);
+        hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kSelThreads), 0, stream, d_hist, (uint32_t)M, xdt,
+                           est == SCAP_MODE_MEDIAN ? 1 : 0, (uint32_t)k, d_out);
+        float got[2];
+        if (!ok(hipGetLastError()) || !ok(hipMemcpyAsync(got, d_out, sizeof(got), hipMemcpyDeviceToHost, stream)) ||
+            !ok(hipStreamSynchronize(stream)))
+            return SCAP_ERR_HIP;
+        *m_out = got[0];
+        *tau_out = got[1];
+        return SCAP_OK;
+    }
     std::vector<unsigned long long> hist(kCodes);
     if (!ok(hipMemcpyAsync(hist.data(), d_hist, sizeof(unsigned long long) * kCodes, hipMemcpyDeviceToHost, stream)))
         return SCAP_ERR_HIP;
@@ -275,7 +457,7 @@ int run_calibrate(const uint16_t* X, int64_t M, int xdt, float s, int est, float
         double sum = t.nans ? (double)quiet_nan() : 0.0;
         for (size_t i = 0; i < t.val.size(); ++i) sum += (double)t.cnt[i] * (double)t.val[i];
         m = (float)(sum / (double)M);
-    } else if (est == SCAP_MODE_MEDIAN) {
+    } else if (est == SCAP_MODE_MEDIAN) {  // 2^32 values or more
         if (M % 2 == 1) {
             m = select_raw(t, (unsigned long long)(M / 2 + 1));
         } else {
@@ -288,7 +470,6 @@ int run_calibrate(const uint16_t* X, int64_t M, int xdt, float s, int est, float
     }
 
     float tau = 0.f;
-    const int64_t k = quantile_rank((double)s, M);
     if (k > 0) tau = select_centred(t, m, (unsigned long long)k);
     *m_out = m;
     *tau_out = tau;

@@ -21,6 +21,7 @@ constexpr int kModeFold = 2;    // d = m for every channel            (Eq. 6, et
 
 // ---------------------------------------------------------------------------------------------
 // Workspace layout (byte offsets into the caller's buffer)
+//   [0, +8)              calibration: the two statistics selected on the GPU
 //   [65536, +32768)      int32 seg_cnt[17][256]  kept-channel counts per (token | union, K split)
 //   [131072, +1 MiB)     int32 counter per column tile, one every 1 KiB so that the arrival tickets of
 //                        different tiles go to different memory channels; zero at rest
@@ -32,6 +33,7 @@ constexpr int kModeFold = 2;    // d = m for every channel            (Eq. 6, et
 //   [.., +68*(K+16384))  batched path (B >= 2): union list of every list segment (64 bytes of A operands and
 //                        the channel index per entry)
 // ---------------------------------------------------------------------------------------------
+constexpr size_t kOffSelected = 0;
 constexpr size_t kOffSegCnt = 65536;
 constexpr size_t kOffCounters = 131072;
 constexpr int kCounterStride = 256;  // int32 words between the counters of neighbouring tiles

@@ -88,3 +88,22 @@ def test_int8_lane_widths(K, N):
         X = wl.laplace(B, K, 952 + K, xdt, loc=0.1, scale=0.5)
         print(f"int8 lanes K={K} N={N} B={B}", flush=True)
         check_against_oracle(layer, X, xdt, 0.1, 0.5, bf, what=f"K={K} N={N} B={B}")
+
+
+# order statistics selected on the GPU: tiny samples, one value, even and odd counts, a median between two codes, between
+# the signs and next to the NaNs, infinities on one side and on both, every target rank of a small sample
+@pytest.mark.parametrize("dt", [F16, BF16])
+def test_calibration_of_small_and_awkward_samples(dt):
+    inf, nan = float("inf"), float("nan")
+    samples = [[1.5], [1.5, -2.0], [0.0, -0.0], [-0.25, 0.5, 0.75], [2.0] * 100, [-1.0, -1.0, 1.0, 1.0], [1.0, inf, inf],
+               [-inf, 0.25, inf], [inf, inf, inf, 1.0], [-inf, -inf, inf, inf], [nan, 1.0, 2.0], [nan, nan, 1.0],
+               [nan] * 5, list(np.linspace(-3, 3, 77)), [6e-8, -6e-8, 3e-5, 0.0, 1e-7]]
+    for v in samples:
+        bits = wl.encode(np.array([v], dtype=np.float32), dt)
+        ws = scap.Workspace(bits.shape[1], 0, 1)
+        for est in (scap.MODE_ZERO, scap.MODE_MEDIAN):
+            for s in (0.0, 0.01, 0.34, 0.5, 0.67, 0.99):
+                print(f"calibrate dt={dt} {v[:5]} est={est} s={s}", flush=True)
+                got = scap.calibrate(to_dev(bits, dt), s, est, workspace=ws)
+                want = oracle.calibrate(bits, dt, s, est)
+                assert np.array_equal(np.float32(got), np.float32(want), equal_nan=True), (v[:5], est, s, got, want)
