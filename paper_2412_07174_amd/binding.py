@@ -116,13 +116,13 @@ def _check(rc: int, where: str) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # ctypes makes a pointer of it (argtypes)
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _code(t: torch.Tensor, what: str) -> int:
@@ -199,6 +199,42 @@ class _Args:
         return 1 if x.dim() == 1 else x.shape[0]
 
 
+# What a decoding loop passes on every call -- plain tensors of exactly the expected type, shape and device -- is
+# recognised with a few attribute reads; whatever is not goes through _Args, which accepts the rest or names the fault.
+# (A 1024 x 4096 call in a Python loop: 13.7 -> 11.6 us, most of the rest ctypes and the launch.)
+def _is(t, dtype, shape, dev: int) -> bool:
+    return (type(t) is torch.Tensor and t.dtype is dtype and t.shape == shape and t.get_device() == dev
+            and t.is_contiguous())
+
+
+def _is_or_none(t, dtype, shape, dev: int) -> bool:
+    return t is None or _is(t, dtype, shape, dev)
+
+
+def _plain_weights(W, col_scale) -> int:
+    """The device of a plain [K, N] weight matrix with its column scales, or -1."""
+    if type(W) is not torch.Tensor or W.dim() != 2 or not W.is_contiguous():
+        return -1
+    dev = W.get_device()
+    if W.dtype is torch.int8:
+        return dev if _is(col_scale, torch.float16, (W.shape[1],), dev) else -1
+    return dev if col_scale is None and W.dtype in _ACT else -1
+
+
+def _plain_tokens(x, K: int, dev: int) -> int:
+    """The number of tokens of a plain input, or 0."""
+    if type(x) is not torch.Tensor or x.dtype not in _ACT or x.get_device() != dev or not x.is_contiguous():
+        return 0
+    shape = x.shape
+    if shape[-1:] != (K,):
+        return 0
+    return shape[0] if len(shape) == 2 else (1 if len(shape) == 1 else 0)
+
+
+def _on_gpu(workspace, dev: int) -> bool:
+    return type(workspace) is Workspace and workspace.buf.get_device() == dev
+
+
 def _cfg(cfg):
     if cfg is None:
         return None
@@ -265,20 +301,28 @@ def sparse_fc(W: torch.Tensor, x: torch.Tensor, m: float, tau: float, b_fused: O
               workspace: Workspace, cfg=None, stream=None) -> torch.Tensor:
     """y[B,N] = ((x - m) masked by |x - m| > tau) @ W + b_fused.  x is [K] or [B, K]."""
     lib = load_library()
-    a = _Args()
-    a.weights(W, col_scale)
-    K, N = W.shape
-    B = a.tokens(x, K, W.device)
-    a.want(b_fused, "b_fused", shape=(N,), dtype=torch.float32, optional=True)
-    a.rows(y, "y", B, N, torch.float32)
-    a.rows(idx_out, "idx_out", B, K, torch.int32)
-    for t, what in ((nnz_out, "nnz_out"), (union_nnz_out, "union_nnz_out")):
-        a.want(t, what, dtype=torch.int32, optional=True)
-    if nnz_out is not None and nnz_out.numel() < B:
-        raise ValueError(f"nnz_out: {nnz_out.numel()} entries for {B} tokens")
-    if union_nnz_out is not None and union_nnz_out.numel() < 1:
-        raise ValueError("union_nnz_out: needs one entry")
-    a.on_one_gpu(workspace)
+    dev = _plain_weights(W, col_scale)
+    B = 0
+    if dev >= 0:
+        K, N = W.shape
+        B = _plain_tokens(x, K, dev)
+    if not (B and _is_or_none(b_fused, torch.float32, (N,), dev) and _is_or_none(y, torch.float32, (B, N), dev)
+            and _is_or_none(idx_out, torch.int32, (B, K), dev) and _is_or_none(nnz_out, torch.int32, (B,), dev)
+            and _is_or_none(union_nnz_out, torch.int32, (1,), dev) and _on_gpu(workspace, dev)):
+        a = _Args()
+        a.weights(W, col_scale)
+        K, N = W.shape
+        B = a.tokens(x, K, W.device)
+        a.want(b_fused, "b_fused", shape=(N,), dtype=torch.float32, optional=True)
+        a.rows(y, "y", B, N, torch.float32)
+        a.rows(idx_out, "idx_out", B, K, torch.int32)
+        for t, what in ((nnz_out, "nnz_out"), (union_nnz_out, "union_nnz_out")):
+            a.want(t, what, dtype=torch.int32, optional=True)
+        if nnz_out is not None and nnz_out.numel() < B:
+            raise ValueError(f"nnz_out: {nnz_out.numel()} entries for {B} tokens")
+        if union_nnz_out is not None and union_nnz_out.numel() < 1:
+            raise ValueError("union_nnz_out: needs one entry")
+        a.on_one_gpu(workspace)
     if y is None:
         y = torch.empty((B, N), dtype=torch.float32, device=x.device)
     args = [_ptr(W), _ptr(col_scale), K, N, _code(W, "W"), _ptr(x), _code(x, "x"), B, float(m), float(tau),
@@ -325,13 +369,20 @@ def sparse_fc_static(W: torch.Tensor, x: torch.Tensor, m: float, tau: float, b_f
 def dense_fc(W: torch.Tensor, x: torch.Tensor, bias: Optional[torch.Tensor] = None, *, col_scale=None,
              y: Optional[torch.Tensor] = None, workspace: Workspace, cfg=None, stream=None) -> torch.Tensor:
     lib = load_library()
-    a = _Args()
-    a.weights(W, col_scale)
-    K, N = W.shape
-    B = a.tokens(x, K, W.device)
-    a.want(bias, "bias", shape=(N,), dtype=torch.float32, optional=True)
-    a.rows(y, "y", B, N, torch.float32)
-    a.on_one_gpu(workspace)
+    dev = _plain_weights(W, col_scale)
+    B = 0
+    if dev >= 0:
+        K, N = W.shape
+        B = _plain_tokens(x, K, dev)
+    if not (B and _is_or_none(bias, torch.float32, (N,), dev) and _is_or_none(y, torch.float32, (B, N), dev)
+            and _on_gpu(workspace, dev)):
+        a = _Args()
+        a.weights(W, col_scale)
+        K, N = W.shape
+        B = a.tokens(x, K, W.device)
+        a.want(bias, "bias", shape=(N,), dtype=torch.float32, optional=True)
+        a.rows(y, "y", B, N, torch.float32)
+        a.on_one_gpu(workspace)
     if y is None:
         y = torch.empty((B, N), dtype=torch.float32, device=x.device)
     rc = lib.scap_dense_fc(_ptr(W), _ptr(col_scale), K, N, _code(W, "W"), _ptr(x), _code(x, "x"), B, _ptr(bias),
@@ -364,24 +415,34 @@ def swiglu_block(W_gu: torch.Tensor, W_down: torch.Tensor, x: torch.Tensor, m_x:
     residual=True (one token): scap_swiglu_block_residual, the block's output is added to the given y.
     cfg: launch flags of the one-token form (scap_swiglu_block_ex), not together with residual."""
     lib = load_library()
-    a = _Args()
-    a.weights(W_gu, gu_scale, "W_gu")
-    a.weights(W_down, down_scale, "W_down")
-    K, F2 = W_gu.shape
-    F, N = W_down.shape
-    if F2 != 2 * F:
-        raise ValueError(f"W_gu has {F2} columns, W_down has {F} rows")
-    B = a.tokens(x, K, W_gu.device)
-    dev = W_gu.device
-    a.want(b_gu_fused, "b_gu_fused", shape=(2 * F,), dtype=torch.float32, optional=True)
-    a.want(b_down_fused, "b_down_fused", shape=(N,), dtype=torch.float32, optional=True)
-    a.rows(y, "y", B, N, torch.float32)
-    a.rows(z_out, "z_out", B, F, torch.float32)
-    a.rows(idx_z_out, "idx_z_out", B, F, torch.int32)
-    a.want(nnz_z_out, "nnz_z_out", dtype=torch.int32, optional=True)
-    if nnz_z_out is not None and nnz_z_out.numel() < B:
-        raise ValueError(f"nnz_z_out: {nnz_z_out.numel()} entries for {B} tokens")
-    a.on_one_gpu(workspace)
+    dev = _plain_weights(W_gu, gu_scale)
+    B = 0
+    if dev >= 0 and _plain_weights(W_down, down_scale) == dev and W_gu.shape[1] == 2 * W_down.shape[0]:
+        K = W_gu.shape[0]
+        F, N = W_down.shape
+        B = _plain_tokens(x, K, dev)
+    if not (B and _is_or_none(b_gu_fused, torch.float32, (2 * F,), dev) and _is_or_none(b_down_fused, torch.float32, (N,), dev)
+            and _is_or_none(y, torch.float32, (B, N), dev) and _is_or_none(z_out, torch.float32, (B, F), dev)
+            and _is_or_none(idx_z_out, torch.int32, (B, F), dev) and _is_or_none(nnz_z_out, torch.int32, (B,), dev)
+            and _on_gpu(workspace, dev)):
+        a = _Args()
+        a.weights(W_gu, gu_scale, "W_gu")
+        a.weights(W_down, down_scale, "W_down")
+        K, F2 = W_gu.shape
+        F, N = W_down.shape
+        if F2 != 2 * F:
+            raise ValueError(f"W_gu has {F2} columns, W_down has {F} rows")
+        B = a.tokens(x, K, W_gu.device)
+        dev = W_gu.device
+        a.want(b_gu_fused, "b_gu_fused", shape=(2 * F,), dtype=torch.float32, optional=True)
+        a.want(b_down_fused, "b_down_fused", shape=(N,), dtype=torch.float32, optional=True)
+        a.rows(y, "y", B, N, torch.float32)
+        a.rows(z_out, "z_out", B, F, torch.float32)
+        a.rows(idx_z_out, "idx_z_out", B, F, torch.int32)
+        a.want(nnz_z_out, "nnz_z_out", dtype=torch.int32, optional=True)
+        if nnz_z_out is not None and nnz_z_out.numel() < B:
+            raise ValueError(f"nnz_z_out: {nnz_z_out.numel()} entries for {B} tokens")
+        a.on_one_gpu(workspace)
     if y is None:
         if residual:
             raise ValueError("residual=True adds to y: pass the tensor that holds the addend")
