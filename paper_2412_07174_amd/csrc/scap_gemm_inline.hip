@@ -142,7 +142,10 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 // list of channels is compacted, and the centred, thresholded value of (token, channel) is formed from the
 // staged tile when the matrix-core operand is assembled, in the shadow of the weight stream.  Same arithmetic
 // per element (one fp32 subtraction, strict compare), so masks and values are those of the other forms.
-constexpr int kRawChunks = 5;  // chunks of 64 channels per wavefront (loads of all of them are in flight at once)
+// Chunks of 64 channels per wavefront (loads of all of them are in flight at once): 5, or 1 for workgroups of up to 512
+// channels, where four of five would re-read what is there (4096 x 4096 bf16, 16 tokens: 15.8 -> 14.3 us, 1024 x 1024,
+// 8 tokens: 9.2 -> 8.0).  Two instantiations: with the choice made inside, the first test waited for all loads.
+constexpr int kRawChunks = 5;
 constexpr int kRawPad = 16;    // bytes between token rows of the staged tile: rows start 4 LDS banks apart
 
 __host__ __device__ constexpr size_t raw_tile_bytes(int Kc) { return (size_t)kMfmaTokens * ((size_t)Kc * 2 + kRawPad); }
@@ -200,7 +203,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     const int c_end = min(c_begin + cpw, nchunk);
     const int tg = lane & 7, o = lane >> 3;
 
-    // ---- all loads (slots past the end re-read the last octet)
+    // ---- all loads, branch-free (slots past the end re-read the last octet)
     uint4 xv[MAXC][2];
     if constexpr (!RAGGED) {
 #pragma unroll
@@ -419,7 +422,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
 
 // X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 151 registers per lane against 109, i.e. one
 // workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
-template <int WDT, int FUSE, bool X32, bool RAGGED>
+template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC>
 __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
@@ -446,7 +449,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
     // ------------------------------------------------------------------ 1. stage the inputs, list the union
     // int8 weights: 256-column tiles, so half as many workgroups repeat a split's prologue and a wavefront has
     // two chunks; listing supersets measured no gain there (and 0.14 us lost to the extra code)
-    const int cnt = stage_inputs_and_list<WAVES, kRawChunks, WDT != kI8, RAGGED>(a, tile, split, L, xs, xrow);
+    const int cnt = stage_inputs_and_list<WAVES, MAXC, WDT != kI8, RAGGED>(a, tile, split, L, xs, xrow);
     const int n_blocks = (cnt + kMfmaBlock - 1) / kMfmaBlock;
 
     // ------------------------------------------------------------------ 2. stream the kept rows
@@ -627,8 +630,8 @@ static int launch_inline(const GemvArgs& a, size_t lds, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool X32, bool RAGGED>
-static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
+template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC>
+static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
     if (lds > 64 * 1024) {
         constexpr int kMaxDevices = 64;
@@ -636,15 +639,23 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave),
+    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave),
                        lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
+}
+
+template <int WDT, int FUSE, bool X32, bool RAGGED>
+static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
+    if constexpr (!RAGGED) {
+        if (a.Kc <= kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
+    }
+    return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, kRawChunks>(a, lds, stream);
 }
 
 // 16 token slots: the staged-tile kernel, or the value-list kernel where the inputs are the gated product's lists;
@@ -701,7 +712,11 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     }
     const size_t by_cap = kHdrBytes + (size_t)kc_cap * 4 * (1 + bt);
     if (by_cap < budget) budget = by_cap;
-    const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget);
+    // 16 slots: a split's partial sums cost the tile's last arrival as much time as 12 rows (sweeps of kc; 4096 x 1024,
+    // 16 tokens, pieces of 128 / 256 rows: 13.2 / 11.6 us bf16, 8 tokens int8 13.1 / 12.8 against 15.9 with 64)
+    SplitCost sc;
+    sc.rows = bt == kMfmaTokens ? 12 : 0;
+    const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget, kWave, sc);
     if (rc != SCAP_OK) return rc;
     if (a.Kc > kc_cap) return SCAP_ERR_SHAPE;
     size_t red = (size_t)kTreeFloats * 4;

@@ -107,3 +107,15 @@ def test_calibration_of_small_and_awkward_samples(dt):
                 got = scap.calibrate(to_dev(bits, dt), s, est, workspace=ws)
                 want = oracle.calibrate(bits, dt, s, est)
                 assert np.array_equal(np.float32(got), np.float32(want), equal_nan=True), (v[:5], est, s, got, want)
+
+
+# the staged-tile kernel's two prologues (workgroups of up to 512 channels, and longer ones) and its narrow-layer plan
+@pytest.mark.parametrize("wdt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,N", [(64, 128), (512, 512), (4096, 1024), (4104, 1040), (8192, 2048), (5000, 8208)])
+def test_staged_tile_short_and_long_workgroups(K, N, wdt):
+    layer, xdt = _layer(K, N, wdt, 960 + K)
+    for B in (5, 9, 16):
+        X = wl.laplace(B, K, 961 + K, xdt, loc=0.1, scale=0.5)
+        for tau in (0.0, 1.1):
+            print(f"staged K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
+            check_against_oracle(layer, X, xdt, 0.1, tau, None, what=f"K={K} N={N} wdt={wdt} B={B} tau={tau}")
