@@ -653,7 +653,9 @@ static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t s
 template <int WDT, int FUSE, bool X32, bool RAGGED>
 static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if constexpr (!RAGGED) {
-        if (a.Kc <= kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
+        if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
+        if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
+        if (a.Kc <= 4 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);
     }
     return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, kRawChunks>(a, lds, stream);
 }
