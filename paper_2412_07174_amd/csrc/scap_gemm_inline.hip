@@ -27,7 +27,13 @@ constexpr int kInlineWaves = 8;
 // chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
 constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
 
-constexpr int kTreeFloats = 32 * 1024 / 4;  // LDS floats of the reduction tree (and of the final reduction)
+// LDS floats of the reduction of the wavefronts' sums (and of the final one).  Kernels that run one workgroup per compute
+// unit anyway take all eight wavefronts' sums at once, 64 KB: two barriers and one turn fewer (reduce_waves_and_emit).
+constexpr int tree_floats(bool whole) { return (whole ? 64 : 32) * 1024 / 4; }
+// ... which are the 16-slot launch that reads lists (158 registers) and the 32-deep staged-tile form, 16-bit weights
+__host__ __device__ constexpr bool whole_reduction(int wdt, int bt, int fuse, bool x32) {
+    return wdt != kI8 && bt == 16 && (fuse == kFuseList || x32);
+}
 
 // FUSE (kFusePlain / kFuseSwiglu / kFuseList) as in the vector kernel: where the inputs come from and what the
 // tile's last arrival does with the finished columns (the two launches of the fused SwiGLU block, Alg. 2).
@@ -39,7 +45,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + kTreeFloats;  // behind both uses of the reduction buffer
+    constexpr bool WHOLE = whole_reduction(WDT, BT, FUSE, false);
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);  // behind both uses of the reduction buffer
     const int tid = threadIdx.x;
     const int w = uniform(tid >> 6);
     const int lane = tid & 63;
@@ -129,7 +136,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 
     // ------------------------------------------------------------------ 3. add the wavefronts' sums
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the list is done with
+    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the list is done with
 
     // ------------------------------------------------------------------ 4. last arrival finishes the tile
     finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
@@ -142,9 +149,10 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 // list of channels is compacted, and the centred, thresholded value of (token, channel) is formed from the
 // staged tile when the matrix-core operand is assembled, in the shadow of the weight stream.  Same arithmetic
 // per element (one fp32 subtraction, strict compare), so masks and values are those of the other forms.
-// Chunks of 64 channels per wavefront (loads of all of them are in flight at once): 5, or 1 for workgroups of up to 512
-// channels, where four of five would re-read what is there (4096 x 4096 bf16, 16 tokens: 15.8 -> 14.3 us, 1024 x 1024,
-// 8 tokens: 9.2 -> 8.0).  Two instantiations: with the choice made inside, the first test waited for all loads.
+// Chunks of 64 channels per wavefront (loads of all of them are in flight at once): 1, 2, 4 or 5 by the workgroup's
+// channels; with 5 for all of them the others re-read what was there (4096 x 4096 bf16, 16 tokens: 15.8 -> 14.0 us with 1;
+// 4096 x 11008 fp16, 8 tokens: 23.8 -> 22.9 with 2; 4096 x 28672 bf16, 16 tokens: 48.6 -> 46.8 with 4).  Instantiations,
+// not a choice made inside: behind such a branch the first test waits for all loads.
 constexpr int kRawChunks = 5;
 constexpr int kRawPad = 16;    // bytes between token rows of the staged tile: rows start 4 LDS banks apart
 
@@ -431,7 +439,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + kTreeFloats;
+    constexpr bool WHOLE = whole_reduction(WDT, BT, FUSE, X32);
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);
     char* xs = reinterpret_cast<char*>(L.idx + a.Kc);  // staged inputs [16][Kc * 2 + pad] in place of the value lists
     const uint32_t xrow = (uint32_t)a.Kc * 2 + kRawPad;
     const int tid = threadIdx.x;
@@ -603,7 +612,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
 
     // ------------------------------------------------------------------ 3. add the wavefronts' sums
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the tile is done with
+    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the tile is done with
 
     // ------------------------------------------------------------------ 4. last arrival finishes the tile
     finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
@@ -721,7 +730,8 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget, kWave, sc);
     if (rc != SCAP_OK) return rc;
     if (a.Kc > kc_cap) return SCAP_ERR_SHAPE;
-    size_t red = (size_t)kTreeFloats * 4;
+    const bool x32 = staged_tile(wdt, a.K) && a.K % 8 == 0 && (int64_t)a.S * a.T <= 256;  // (as launch_inline_wdt chooses)
+    size_t red = (size_t)tree_floats(whole_reduction(wdt, bt, fuse, x32)) * 4;
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
     *lds_out = lds_bytes(a.Kc, bt, red);

@@ -722,8 +722,12 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, __amdgpu_buffer_r
                         s.w += v[j].w;
                     }
                 }
-                *reinterpret_cast<float4*>(s_red + (q * per_pass + li) * 4) = s;
+                if (Q == 1)  // the thread holds the whole sum
+                    finish_columns<WDT, TILE, FUSE>(a, tile, b, g, s, L.fin, mine);  // g == tid % GROUPS
+                else
+                    *reinterpret_cast<float4*>(s_red + (q * per_pass + li) * 4) = s;
             }
+            if (Q == 1) continue;  // workgroup-uniform
             __syncthreads();
             if (q == 0 && item < nitems) {
                 float4 s = *reinterpret_cast<const float4*>(s_red + li * 4);

@@ -186,7 +186,8 @@ __device__ __forceinline__ void mfma_block32(f32x4_t* __restrict__ acc, const s1
 // (FUSE / s_fin: see finish_columns -- with one split the sums are final and may go to the gating step)
 // ONE_LEVEL (8 wavefronts): the form described inside; otherwise a binary tree over the wavefronts.  The
 // two-launch kernel keeps the tree: the one-level form costs it registers it needs for two workgroups per CU.
-template <int WDT, int WAVES, int FUSE = kFusePlain, bool ONE_LEVEL = false>
+// WHOLE: with 64 KB the one-level form takes all wavefronts at once instead of four and four; the same order of sums.
+template <int WDT, int WAVES, int FUSE = kFusePlain, bool ONE_LEVEL = false, bool WHOLE = false>
 __device__ __forceinline__ void reduce_waves_and_emit(const GemvArgs& a, __amdgpu_buffer_rsrc_t pbuf, int tile, int split,
                                                       f32x4_t* __restrict__ acc, float* s_red, float* s_fin = nullptr) {
     constexpr int ELEMS = Vec<WDT>::kElems;
@@ -205,14 +206,14 @@ __device__ __forceinline__ void reduce_waves_and_emit(const GemvArgs& a, __amdgp
         // KB (write-through stores of half-filled 32-byte sectors cost visibly more).  Four barriers per 8
         // columns instead of seven with a tree plus a hand-over to the storing threads (1.3 -> 0.6 us at 16 tokens).
         constexpr int ITEMS = kMfmaTokens * 32;
-        constexpr int H = WAVES / 2;
-        static_assert(H * ITEMS * 16 <= 32 * 1024 && ITEMS == WAVES * kWave, "reduction buffer, one item per thread");
+        constexpr int H = WHOLE ? WAVES : WAVES / 2;
+        static_assert(H * ITEMS * 16 <= (WHOLE ? 64 : 32) * 1024 && ITEMS == WAVES * kWave, "reduction buffer, one item per thread");
         static_assert(ELEMS % 8 == 0, "accumulators are handed over eight columns at a time");
 #pragma unroll
         for (int c0 = 0; c0 < ELEMS; c0 += 8) {
             f32x4_t t = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int hw = 0; hw < 2; ++hw) {
+            for (int hw = 0; hw < WAVES / H; ++hw) {
                 __syncthreads();  // the buffer is free (the list, or the previous values, have been read)
                 if (w / H == hw) {
 #pragma unroll
