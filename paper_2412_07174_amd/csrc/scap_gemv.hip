@@ -137,6 +137,8 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot forms for int8 weights unless the layer
     // is very wide (its narrow tiles repeat the prologue), and than the vector kernel for a long input into a
     // narrow bf16 layer (14336 x 4096, 4 tokens: 28.7 -> 27.3 us dense, 22.2 -> 20.0 at 90 %).
+    // int8 weights over an input length that is not a multiple of 8 keep the 4-slot lists (4097 x 8192, 4 tokens, 60 %:
+    // 17.2 against 19.4 us; 14337 x 4096, 3 tokens dense 21.0 against 22.6).
     if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 &&
         ((wdt == kI8 && a.K % 8 == 0 && (int64_t)a.N <= 4 * (int64_t)a.K) || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
         const int rc = launch_gemm_inline(a, wdt, cfg, stream, true);
