@@ -124,9 +124,13 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // dense call with a long input into a narrow layer stays on the staged-tile kernel.  int8 weights in 8-byte lanes
     // (wider int8 layers do not fit and fall through to the matrix cores): 14336 x 4096, 4 tokens,
     // 19.7 / 17.7 / 12.9 at 50 / 70 / 90 % against 19.9 / 18.3 / 14.0, 3 tokens 18.1 / 15.8 / 11.9 against 19.1 / 17.0 / 12.9.
-    // bf16 layers of at most 1024 columns keep the vector kernel (4096 x 1024, 4 tokens: 9.4 against 10.0 us; int8 and fp16
-    // are faster here: 12.3 -> 10.4, 12.9 -> 10.5).
-    const bool four_slots = (a.B == 3 || a.B == 4) && !(wdt == kBF16 && a.N <= 1024) &&
+    // bf16 layers of at most 1024 columns with K >= 2 N go to the staged-tile kernel below: 4 tokens at 50 / 90 %, there
+    // against here, 4096 x 1024 8.5 / 7.9 us against 10.3 / 8.7, 768 x 256 7.1 / 6.6 against 8.0 / 7.1.  That kernel
+    // carries x - m as two bf16 halves (error with m != 0 about 1.8e-6 instead of 1.3e-7), so only from 512 channels on and
+    // over whole octets of channels, where it always ran: shorter inputs (512 x 256, 4 tokens at 50 % 7.6 us against 6.7
+    // there) and odd lengths (5461 x 1024 10.9 against 13.3) keep their 32 bits.
+    const bool narrow_staged = wdt == kBF16 && a.N <= 1024 && a.K % 8 == 0 && a.K > 512 && (int64_t)a.K >= 2 * (int64_t)a.N;
+    const bool four_slots = (a.B == 3 || a.B == 4) && !narrow_staged &&
                             !(a.mode == kModeDense && (int64_t)a.K >= 2 * (int64_t)a.N);
     if ((a.B == 2 || four_slots) && lanes == 0 &&
         (wdt == kI8 || a.N <= 8192 || 2 * (int64_t)a.N <= (int64_t)kFxCols) &&

@@ -52,6 +52,38 @@ def test_batches_over_an_odd_input_length(K, N, wdt):
         assert_y_close(y.cpu().numpy(), want, f"dense K={K} N={N} wdt={wdt} B={B}")
 
 
+def _exact(layer, X, xdt, m, tau):
+    """float64 result of a layer without a fused bias (tau < 0: dense); x - m is one fp32 subtraction, as everywhere."""
+    d = wl.decode(X, xdt).astype(np.float32)
+    if tau >= 0:
+        d = d - np.float32(m)
+        d = np.where(np.abs(d) > np.float32(tau), d, np.float32(0))
+    if layer.wdt == I8:
+        W = layer.W_host.astype(np.float64) * wl.decode(layer.scale_host, F16).astype(np.float64)
+    else:
+        W = wl.decode(layer.W_host, layer.wdt).astype(np.float64)
+    return d.astype(np.float64) @ W
+
+
+def _rel(got, want):
+    return np.linalg.norm(np.asarray(got, np.float64) - want) / np.linalg.norm(want)
+
+
+# 3-4 tokens whose centred inputs need more bits than bf16 has.  Sums of K fp32 products in several chains stay within
+# about 2^-23 of the result (1.3e-7 here); an operand split into two bf16 halves leaves up to 2^-17 per term, 1.8e-6 over
+# random signs.  5e-7 lies between the two; 1e-5 would show a lost half (2^-9).
+@pytest.mark.parametrize("K,N,bar", [(512, 256, 5e-7), (512, 512, 5e-7), (1024, 1024, 5e-7), (1000, 800, 5e-7),
+                                     (513, 256, 5e-7), (2047, 1024, 5e-7), (5461, 1024, 5e-7), (520, 256, 1e-5), (4096, 1024, 1e-5)])
+def test_centred_inputs_over_narrow_bf16_layers(K, N, bar):
+    layer, xdt = _layer(K, N, BF16, 970 + K, B=4)
+    for B in (3, 4):
+        X = wl.laplace(B, K, 971 + K, xdt, loc=0.1, scale=0.5)
+        print(f"centred narrow K={K} N={N} B={B}", flush=True)
+        got, _ = check_against_oracle(layer, X, xdt, 0.1, 0.35, None, what=f"K={K} N={N} B={B}")
+        err = _rel(got["y"], _exact(layer, X, xdt, 0.1, 0.35))
+        assert err <= bar, (K, N, B, err)
+
+
 # the block over an odd hidden size; gated products that end inside a 32- or 64-channel segment
 @pytest.mark.parametrize("dt", [BF16, F16, I8])
 @pytest.mark.parametrize("K,F,N", [(129, 72, 144), (1001, 2088, 528), (519, 4104, 4112)])
