@@ -129,9 +129,12 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // carries x - m as two bf16 halves (error with m != 0 about 1.8e-6 instead of 1.3e-7), so only from 512 channels on and
     // over whole octets of channels, where it always ran: shorter inputs (512 x 256, 4 tokens at 50 % 7.6 us against 6.7
     // there) and odd lengths (5461 x 1024 10.9 against 13.3) keep their 32 bits.
+    // Dense bf16 calls of an odd length stay here too: the staged-tile kernel's form for them is the slower one in most
+    // layers (3 / 4 tokens, here against there: 513 x 256 7.4 / 8.0 us against 10.8 / 10.1, 8193 x 2048 13.5 / 14.3 against
+    // 14.9 / 16.1, 9001 x 3000 17.3 / 18.0 against 20.7 / 22.1, 14337 x 4096 30.3 / 31.4 against 28.2 / 29.9).
     const bool narrow_staged = wdt == kBF16 && a.N <= 1024 && a.K % 8 == 0 && a.K > 512 && (int64_t)a.K >= 2 * (int64_t)a.N;
     const bool four_slots = (a.B == 3 || a.B == 4) && !narrow_staged &&
-                            !(a.mode == kModeDense && (int64_t)a.K >= 2 * (int64_t)a.N);
+                            !(a.mode == kModeDense && (int64_t)a.K >= 2 * (int64_t)a.N && !(wdt == kBF16 && a.K % 8 != 0));
     if ((a.B == 2 || four_slots) && lanes == 0 &&
         (wdt == kI8 || a.N <= 8192 || 2 * (int64_t)a.N <= (int64_t)kFxCols) &&
         !(cfg && ((cfg->flags & SCAP_CFG_GENERAL_KERNEL) || cfg->waves_per_group || cfg->rows_per_group || cfg->unroll))) {
@@ -141,10 +144,11 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot forms for int8 weights unless the layer
     // is very wide (its narrow tiles repeat the prologue), and than the vector kernel for a long input into a
     // narrow bf16 layer (14336 x 4096, 4 tokens: 28.7 -> 27.3 us dense, 22.2 -> 20.0 at 90 %).
-    // int8 weights over an input length that is not a multiple of 8 keep the 4-slot lists (4097 x 8192, 4 tokens, 60 %:
-    // 17.2 against 19.4 us; 14337 x 4096, 3 tokens dense 21.0 against 22.6).
-    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 &&
-        ((wdt == kI8 && a.K % 8 == 0 && (int64_t)a.N <= 4 * (int64_t)a.K) || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
+    // Not over an input length that is not a multiple of 8: int8 weights keep the 4-slot lists (4097 x 8192, 4 tokens, 60 %:
+    // 17.2 against 19.4 us; 14337 x 4096, 3 tokens dense 21.0 against 22.6), and bf16 calls that the four-slot kernel does
+    // not take the general vector kernel with its fp32 operands.
+    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 && a.K % 8 == 0 &&
+        ((wdt == kI8 && (int64_t)a.N <= 4 * (int64_t)a.K) || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
         const int rc = launch_gemm_inline(a, wdt, cfg, stream, true);
         if (rc != SCAP_ERR_SHAPE) return rc;
     }

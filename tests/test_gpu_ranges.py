@@ -84,6 +84,24 @@ def test_centred_inputs_over_narrow_bf16_layers(K, N, bar):
         assert err <= bar, (K, N, B, err)
 
 
+# odd input lengths that the four-slot kernel does not take (more than 64 K splits; partial sums asked for), and dense
+# ones: 3-4 tokens over bf16 weights stay with fp32 operands.  Bar as above.
+@pytest.mark.parametrize("K,N,flags", [(100001, 128, 0), (5461, 1024, scap.CFG_PARTIAL_SUMS), (2047, 264, scap.CFG_GENERAL_KERNEL)])
+def test_centred_inputs_of_odd_length_on_the_general_kernel(K, N, flags):
+    layer, xdt = _layer(K, N, BF16, 980 + K, B=4)
+    for B in (3, 4):
+        X = wl.laplace(B, K, 981 + K, xdt, loc=0.1, scale=0.5)
+        print(f"odd general K={K} N={N} B={B} flags={flags}", flush=True)
+        cfg = (0, 0, 0, 0, flags) if flags else None
+        got, _ = check_against_oracle(layer, X, xdt, 0.1, 0.35, None, cfg=cfg, what=f"K={K} N={N} B={B}")
+        err = _rel(got["y"], _exact(layer, X, xdt, 0.1, 0.35))
+        assert err <= 5e-7, (K, N, B, err)
+        y = scap.dense_fc(layer.W, to_dev(X, xdt), None, workspace=layer.ws, cfg=cfg)
+        torch.cuda.synchronize()
+        err = _rel(y.cpu().numpy(), _exact(layer, X, xdt, 0.0, -1.0))
+        assert err <= 5e-7, (K, N, B, err)
+
+
 # the block over an odd hidden size; gated products that end inside a 32- or 64-channel segment
 @pytest.mark.parametrize("dt", [BF16, F16, I8])
 @pytest.mark.parametrize("K,F,N", [(129, 72, 144), (1001, 2088, 528), (519, 4104, 4112)])
