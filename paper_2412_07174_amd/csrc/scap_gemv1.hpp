@@ -47,12 +47,18 @@ constexpr int kG1FlagParkSlices = 16;  // gating epilogue: always take the way t
 // Fixed-point hand-over: one 64-bit word per output column, updated by ONE atomic add per arrival:
 //   bits 63-57 arrivals so far, bits 56-50 how many of them escaped, bits 49-0 the sum of (partial * 2^frac + BIAS).
 constexpr int kFxMaxSplits = 64;
-constexpr int kFxRangeBits = 20;  // partial sums below 2^20 in magnitude travel as fixed point; others escape
+// Partial sums below 2^range in magnitude travel as fixed point, others escape.  Of the 49 bits a sum has, the range is
+// set so that ordinary sums lie in the middle of what the word carries: over 16-bit weights 2^10, i.e. steps of 2^-33 to
+// 2^-35 at 64 to 16 splits; over int8 weights, whose sums are handed over before the column scale is applied, 2^18.
+__host__ __device__ constexpr int fx_range_bits(bool int8_weights) { return int8_weights ? 18 : 10; }
 __host__ __device__ inline int fx_limit_bits(int S) {  // bits of one arrival's magnitude: S biased values fit 50 bits
-    int hs = 0;
-    while ((1 << hs) < S) ++hs;
-    return 49 - hs;
+    return 49 - (S > 1 ? 32 - __builtin_clz((unsigned)(S - 1)) : 0);
 }
+// From 2^(23 - frac) on, an fp32 value is a multiple of the step 2^-frac.  A slice whose partials are all below that
+// escapes as well, or its sums would keep fewer bits than fp32 has: results of about 1e-3 and less (16-bit weights).  Those
+// calls pay for the second way: 14336 x 4096 bf16, one token, 13.6 -> 15.8 us, 4096 x 4096, four tokens, 14.2 -> 22.6; with
+// 2^20 of range and no such rule 1024 x 1024 bf16 had an error of 1e-5 at results of 1e-2 and 4e-3 at 2e-5, now 1e-7.
+__device__ __forceinline__ float fx_whole_from(int frac) { return __int_as_float((127 + 23 - frac) << 23); }
 
 // int8 weights read 8 bytes per lane instead of 16 (internal to this kernel): the column tile is 512 columns
 // instead of 1024, so a layer with few columns gets twice the tiles and half the K splits.  With 4096 columns
@@ -220,6 +226,55 @@ template <> struct SliceVec<4> {
         store_coherent16(r, off, make_float4(v[0], v[1], v[2], v[3]));
     }
 };
+
+// The columns of this lane whose partials cannot travel as fixed point.  `in(c)`: whether column c exists; the same call
+// in every lane of the wavefront that holds the slice.
+template <int CPL, typename In>
+__device__ __forceinline__ bool fx_escapes(const SliceVec<CPL>& sum, int range_bits, int frac, bool (&esc)[CPL], In in) {
+    const float range = __int_as_float((127 + range_bits) << 23), whole = fx_whole_from(frac);
+    bool any_whole = false, any_esc = false;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) any_whole |= in(c) && !(fabsf(sum.v[c]) < whole);
+    const bool small = __ballot(any_whole) == 0ull;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        esc[c] = in(c) && (!(fabsf(sum.v[c]) < range) || (small && sum.v[c] != 0.f));  // also NaN and Inf
+        any_esc |= esc[c];
+    }
+    return any_esc;
+}
+
+// Adds the escaped partials of this lane's columns of a slice, in split order: n_esc of a column are 0 where none escaped
+// or this lane did not finish it, word(c) holds its marks (cleared here), the slots of a split start at `pmine`, `pstride`
+// bytes apart.  FLY splits' slots are fetched together; those that did not escape are read and dropped.  Where everything
+// escaped the marks are not needed.
+template <int CPL, typename Word>
+__device__ __forceinline__ void fx_add_escaped(float (&yv)[CPL], const int (&n_esc)[CPL], Word word, __amdgpu_buffer_rsrc_t pbuf,
+                                               uint32_t pmine, uint32_t pstride, int S) {
+    constexpr int FLY = 16 / CPL;
+    static_assert(kFxMaxSplits % FLY == 0, "no shift past the last split's mark");
+    unsigned long long mask[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        mask[c] = n_esc[c] == 0 ? 0ull : ~0ull >> (64 - S);
+        if (n_esc[c] != 0 && n_esc[c] != S) mask[c] = load_dev(word(c));
+    }
+    for (int sp0 = 0; sp0 < S; sp0 += FLY) {
+        SliceVec<CPL> v[FLY];
+#pragma unroll
+        for (int j = 0; j < FLY; ++j) v[j] = SliceVec<CPL>::load_coherent(pbuf, (uint32_t)min(sp0 + j, S - 1) * pstride + pmine);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+            for (int j = 0; j < FLY; ++j) {
+                const uint32_t in = 0u - ((uint32_t)(mask[c] >> (sp0 + j)) & 1u);
+                yv[c] += __uint_as_float(__float_as_uint(v[j].v[c]) & in);
+            }
+    }
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+        if (n_esc[c] != 0) store_dev(word(c), 0ull);
+}
 
 // exclusive prefix sum across the 64 lanes of a wave
 __device__ __forceinline__ int wave_exclusive_scan(int v) { return wave_inclusive_scan(v) - v; }
@@ -649,49 +704,40 @@ __global__ __launch_bounds__(WAVES * kWave) void gemv1_kernel(const uint16_t* x,
 
     // ------------------------------------------------------------------ 4a. split-K hand-over in fixed point
     // The S partial sums of a column are added as INTEGERS: each arrival rounds its partial to a multiple of
-    // 2^-frac (frac chosen so that S of them fit 50 bits with 2^20 of range; 2^-24 for 32 splits) and adds it,
+    // 2^-frac (frac chosen so that S of them fit 50 bits with fx_range_bits of range; 2^-34 for 32 splits) and adds it,
     // biased to be non-negative, to the column's 64-bit word together with a 1 in the arrival count -- ONE
     // atomic with return per column.  Integer addition is associative, so the sum does not depend on the order of
     // the arrivals (y is bit-reproducible) and nobody has to collect anything: whoever sees the count reach S holds
     // the complete sum in the value its own atomic returned, converts it once (fp64, one rounding to fp32), applies
     // scale and bias, stores y and clears the word.  One memory round trip after the last row instead of three.
-    // A partial that is not finite or not below 2^20 in magnitude ESCAPES: it is handed over the old way -- stored
-    // as fp32 into its partial-sum slot, its split marked in the column's escape mask, both acknowledged before the
+    // A partial that is not finite or not below 2^fx_range_bits in magnitude ESCAPES, and so do those of a slice in which
+    // none is large enough to travel whole (fx_whole_from): they are handed over the old way -- stored
+    // as fp32 into their partial-sum slots, the split marked in the column's escape mask, both acknowledged before the
     // atomic, which then carries a zero and a 1 in the escape count -- and the finisher adds the escaped values, in
     // split order, to the converted sum.  So every input gives the IEEE result the partial-sum hand-over gives, up
-    // to the rounding of the non-escaped partials to 2^-frac.
+    // to the rounding of the non-escaped partials to 2^-frac, at most an ulp of the largest partial of their slice.
     {
         if (a.fx_acc != nullptr) {
             const int limit_bits = fx_limit_bits(a.S);
-            const int frac = limit_bits - kFxRangeBits;
+            const int frac = limit_bits - fx_range_bits(IS_I8);
             const double to_fixed = __hiloint2double((1023 + frac) << 20, 0);     // 2^frac
             const double from_fixed = __hiloint2double((1023 - frac) << 20, 0);   // 2^-frac
             const unsigned long long bias = 1ull << limit_bits;
             unsigned long long* escw = a.fx_acc + kFxCols;
+            const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(a.partial, (uint32_t)a.S * a.T * TILE * 4u);
+            const uint32_t pstride = (uint32_t)a.T * TILE * 4u;
+            const uint32_t pmine = (uint32_t)((tile * TILE + w * SLICE + lane * CPL) * 4);
             bool esc[CPL];
-            bool any_esc = false;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                esc[c] = fcol + c * CSTR < a.N && !(fabsf(sum.v[c]) < 1048576.f);  // also NaN and Inf
-                any_esc |= esc[c];
-            }
+            const bool any_esc = fx_escapes<CPL>(sum, fx_range_bits(IS_I8), frac, esc, [&](int c) { return fcol + c * CSTR < a.N; });
             if (__ballot(any_esc) != 0ull) {  // rare: some partial of this slice escapes
-                const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(a.partial, (uint32_t)a.S * a.T * TILE * 4u);
-                const uint32_t pstride = (uint32_t)a.T * TILE * 4u;
-                const uint32_t pmine = (uint32_t)((tile * TILE + w * SLICE + lane * CPL) * 4);
                 sum.store_coherent(pbuf, split * pstride + pmine);
 #pragma unroll
                 for (int c = 0; c < CPL; ++c)
                     if (esc[c]) __hip_atomic_fetch_or(&escw[fcol + c * CSTR], 1ull << split, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 wait_memory_ops();  // value and mask bit are in place before the arrival is counted
             }
-            float fin_p[CPL];  // the gating epilogue: finished columns stay in registers
+            float fin_p[CPL];
             bool fin_done[CPL];
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                fin_p[c] = 0.f;
-                fin_done[c] = false;
-            }
             // all of the lane's atomics first (one round trip for the lot), then what they returned
             unsigned long long now_c[CPL];
 #pragma unroll
@@ -702,26 +748,26 @@ __global__ __launch_bounds__(WAVES * kWave) void gemv1_kernel(const uint16_t* x,
                 const unsigned long long inc = (1ull << 57) | (esc[c] ? 1ull << 50 : 0ull) | (unsigned long long)(vfix + (long long)bias);
                 now_c[c] = __hip_atomic_fetch_add(&a.fx_acc[fcol + c * CSTR], inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + inc;
             }
+            float sums[CPL];
+            int n_esc[CPL];
+            bool some_esc = false;
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
                 const unsigned long long now = now_c[c];
-                if ((int)(now >> 57) != a.S) continue;  // not the column's last arrival (or no column: count 0, S > 1)
                 const long long total = (long long)(now & ((1ull << 50) - 1)) - (long long)a.S * (long long)bias;
-                float yv = (float)((double)total * from_fixed);
-                if ((now >> 50) & 127ull) {  // escaped partials: add them in split order
-                    unsigned long long mask = load_dev(&escw[fcol + c * CSTR]);
-                    const float* pcol = a.partial + (size_t)tile * TILE + (w * SLICE + lane * CPL + c);
-                    while (mask) {
-                        const int sp = __builtin_ctzll(mask);
-                        mask &= mask - 1;
-                        yv += load_dev(pcol + (size_t)sp * a.T * TILE);
-                    }
-                    store_dev(&escw[fcol + c * CSTR], 0ull);
-                }
-                yv = (IS_I8 ? yv * cscale[c] : yv) + cbias[c];
-                if constexpr (FUSE != kFuseSwiglu) store_dev(&a.y[fcol + c * CSTR], yv);
-                fin_p[c] = yv;
-                fin_done[c] = true;
+                fin_done[c] = (int)(now >> 57) == a.S;  // the column's last arrival (no column: count 0, S > 1)
+                sums[c] = (float)((double)total * from_fixed);
+                n_esc[c] = fin_done[c] ? (int)(now >> 50) & 127 : 0;
+                some_esc |= n_esc[c] != 0;
+            }
+            if (some_esc)
+                fx_add_escaped<CPL>(sums, n_esc, [&](int c) { return &escw[fcol + c * CSTR]; }, pbuf, pmine, pstride, a.S);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                fin_p[c] = 0.f;
+                if (!fin_done[c]) continue;
+                fin_p[c] = (IS_I8 ? sums[c] * cscale[c] : sums[c]) + cbias[c];
+                if constexpr (FUSE != kFuseSwiglu) store_dev(&a.y[fcol + c * CSTR], fin_p[c]);
                 store_dev(&a.fx_acc[fcol + c * CSTR], 0ull);  // zero at rest
             }
             if constexpr (FUSE == kFuseSwiglu) {

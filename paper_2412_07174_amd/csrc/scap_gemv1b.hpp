@@ -447,16 +447,17 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     // ------------------------------------------------------------------ 4a. split-K hand-over in fixed point
     // As in the one-token kernel (scap_gemv1.hpp, 4a), one 64-bit word per (token, column): every arrival adds its
     // partial, rounded to 2^-frac and biased, and a 1 in the arrival count with ONE atomic; whoever completes a
-    // column's count holds its sum, converts it once, applies scale and bias and stores y.  A partial that is not
-    // finite or not below 2^20 travels as fp32 through its partial-sum slot and the column's escape mask.
+    // column's count holds its sum, converts it once, applies scale and bias and stores y.  What cannot
+    // travel so (fx_escapes; each token's slice by itself) goes as fp32 through its partial-sum slot and the column's escape mask.
     if constexpr (FUSE != kFuseSwiglu) {
         if (fx_acc != nullptr) {
             const int limit_bits = fx_limit_bits(S);
-            const int frac = limit_bits - kFxRangeBits;
+            const int frac = limit_bits - fx_range_bits(IS_I8);
             const double to_fixed = __hiloint2double((1023 + frac) << 20, 0);    // 2^frac
             const double from_fixed = __hiloint2double((1023 - frac) << 20, 0);  // 2^-frac
             const unsigned long long fbias = 1ull << limit_bits;
             unsigned long long* escw = fx_acc + kFxCols;
+            const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(partial, (uint32_t)S * T * B * TILE * 4u);
             const uint32_t pstride = (uint32_t)T * B * TILE * 4u;
             const uint32_t pmine = (uint32_t)((tile * B * TILE + w * SLICE + lane * CPL) * 4);
             const uint32_t ptok = (uint32_t)TILE * 4u;
@@ -464,13 +465,8 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             bool any_esc = false;
 #pragma unroll
             for (int b = 0; b < BT; ++b)
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    esc[b][c] = b < B && fcol + c * CSTR < N && !(fabsf(sum[b].v[c]) < 1048576.f);  // also NaN and Inf
-                    any_esc |= esc[b][c];
-                }
+                any_esc |= fx_escapes<CPL>(sum[b], fx_range_bits(IS_I8), frac, esc[b], [&](int c) { return b < B && fcol + c * CSTR < N; });
             if (__ballot(any_esc) != 0ull) {  // rare
-                const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(partial, (uint32_t)S * T * B * TILE * 4u);
 #pragma unroll
                 for (int b = 0; b < BT; ++b) {
                     if (b < B) sum[b].store_coherent(pbuf, split * pstride + pmine + b * ptok);
@@ -492,28 +488,49 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
                     const unsigned long long inc = (1ull << 57) | (esc[b][c] ? 1ull << 50 : 0ull) | (unsigned long long)(vfix + (long long)fbias);
                     now_c[b][c] = __hip_atomic_fetch_add(&fx_acc[(size_t)b * N + fcol + c * CSTR], inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + inc;
                 }
+            float yv[BT][CPL];
+            int n_esc[BT][CPL];
+            bool done[BT][CPL], some_esc = false;
 #pragma unroll
             for (int b = 0; b < BT; ++b)
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
                     const unsigned long long now = now_c[b][c];
-                    if ((int)(now >> 57) != S) continue;  // not the column's last arrival (or no column: count 0, S > 1)
                     const long long total = (long long)(now & ((1ull << 50) - 1)) - (long long)S * (long long)fbias;
-                    float yv = (float)((double)total * from_fixed);
-                    const size_t word = (size_t)b * N + fcol + c * CSTR;
-                    if ((now >> 50) & 127ull) {  // escaped partials: add them in split order
-                        unsigned long long mask = load_dev(&escw[word]);
-                        const float* pcol = partial + (size_t)(tile * B + b) * TILE + w * SLICE + lane * CPL + c;
-                        while (mask) {
-                            const int sp = __builtin_ctzll(mask);
-                            mask &= mask - 1;
-                            yv += load_dev(pcol + (size_t)sp * T * B * TILE);
+                    done[b][c] = (int)(now >> 57) == S;  // the column's last arrival (no column: count 0, S > 1)
+                    yv[b][c] = (float)((double)total * from_fixed);
+                    n_esc[b][c] = done[b][c] ? (int)(now >> 50) & 127 : 0;
+                    some_esc |= n_esc[b][c] != 0;
+                }
+            auto word = [&](int b, int c) { return (size_t)b * N + fcol + c * CSTR; };
+            if (some_esc) {
+                // One copy of the code for all tokens, and one token after the other: with four copies (or the registers of
+                // all tokens) every call that jumps over them was 0.5 us slower at four slots.
+#pragma unroll 1
+                for (int b = 0; b < B; ++b) {
+                    float t[CPL];
+                    int n[CPL];
+#pragma unroll
+                    for (int i = 0; i < BT; ++i)
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) {
+                            t[c] = i == 0 || i == b ? yv[i][c] : t[c];
+                            n[c] = i == 0 || i == b ? n_esc[i][c] : n[c];
                         }
-                        store_dev(&escw[word], 0ull);
-                    }
-                    yv = (IS_I8 ? yv * cscale[c] : yv) + cbias[c];
-                    store_dev(&y[word], yv);
-                    store_dev(&fx_acc[word], 0ull);  // zero at rest
+                    fx_add_escaped<CPL>(t, n, [&](int c) { return &escw[word(b, c)]; }, pbuf, pmine + b * ptok, pstride, S);
+#pragma unroll
+                    for (int i = 0; i < BT; ++i)
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) yv[i][c] = i == b ? t[c] : yv[i][c];
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    if (!done[b][c]) continue;
+                    store_dev(&y[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
+                    store_dev(&fx_acc[word(b, c)], 0ull);  // zero at rest
                 }
             if (!want_lists || S == 1) return;
             // token w's list (tile 0, wavefront w < B) still needs the last of its writers to close the gaps: they

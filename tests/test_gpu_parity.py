@@ -319,7 +319,7 @@ def test_two_tokens_ties_nonfinite_and_one_empty_mask():
 
 @pytest.mark.parametrize("B", [1, 2, 3, 4])
 def test_fixed_point_hand_over_escapes(B):
-    """Partial sums the fixed-point hand-over cannot carry -- 2^20 or more in magnitude, infinite, NaN -- travel as
+    """Partial sums the fixed-point hand-over cannot carry -- 2^10 or more in magnitude, infinite, NaN -- travel as
     fp32 beside it: columns whose partial sums are all huge, columns where only some splits escape, and
     non-finite inputs, against the oracle at fp32 relative accuracy (one token: the one-token kernel; two to four: its
     two- and four-slot forms, the second token with sums that stay small); the words are back at zero afterwards (an

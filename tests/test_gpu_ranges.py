@@ -12,8 +12,8 @@ from workloads import BF16, F16, I8
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import Layer, assert_y_close, check_against_oracle, to_dev
-    from test_gpu_swiglu import Block
+    from gpu_util import Layer, assert_y_close, check_against_oracle, gpu_sparse_fc, to_dev
+    from test_gpu_swiglu import B_MATRIX, Block
 
 
 def _layer(K, N, wdt, seed, B=16):
@@ -138,6 +138,71 @@ def test_int8_lane_widths(K, N):
         X = wl.laplace(B, K, 952 + K, xdt, loc=0.1, scale=0.5)
         print(f"int8 lanes K={K} N={N} B={B}", flush=True)
         check_against_oracle(layer, X, xdt, 0.1, 0.5, bf, what=f"K={K} N={N} B={B}")
+
+
+# Small results keep their bits: a split's partial sums are handed over in fixed point only where that loses nothing
+# against fp32.  Columns 512 and up (other slices than the first ones') are scaled by `scale`, in columns 64-127 only the
+# later splits, columns 128-159 are huge; with several tokens the last one's inputs are scaled by 2^-8.  Each part by itself
+# within the 5e-7 of above, as with ordinary magnitudes.
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -6, 2.0 ** -15, 2.0 ** -40])
+@pytest.mark.parametrize("K,N,wdt", [(1024, 1024, BF16), (1024, 1024, F16), (1024, 1024, I8), (4096, 1032, BF16),
+                                     (5461, 2744, BF16), (8193, 2048, BF16), (5461, 2752, I8), (4096, 11008, I8)])
+def test_small_results_keep_their_bits(K, N, wdt, scale):
+    if wdt == F16:
+        scale = max(scale, 2.0 ** -6)  # smaller fp16 weights would underflow
+    xdt = F16 if wdt == F16 else BF16
+    if wdt == I8:
+        q, sc = wl.quantize_i8(K, N, 990 + K)
+        layer = Layer(q, I8, col_scale_bits=sc, B=4)
+    else:
+        w = wl.decode(wl.weights(K, N, 990 + K, wdt), wdt).astype(np.float32)
+        w[:, 512:] *= np.float32(scale)
+        w[K // 2:, 64:128] *= np.float32(scale)
+        w[:, 128:160] *= np.float32(2.0 ** 14)
+        layer = Layer(wl.encode(w, wdt), wdt, B=4)
+    for B in (1, 2, 3, 4):
+        x = wl.decode(wl.laplace(B, K, 991 + K, xdt, loc=0.1, scale=0.5), xdt).astype(np.float32)
+        m, tau = 0.1, 0.35
+        if wdt == I8:  # int8 weights have no small columns before their scale: all inputs small instead
+            x, m, tau = x * np.float32(scale), 0.1 * scale, 0.35 * scale
+        elif B > 1:
+            x[-1] = 0.1 + (x[-1] - 0.1) * 2.0 ** -8
+            tau = 0.35 * 2.0 ** -8
+        X = wl.encode(x.astype(np.float32), xdt)
+        print(f"small K={K} N={N} wdt={wdt} B={B} scale={scale}", flush=True)
+        want = _exact(layer, X, xdt, m, tau)
+        for cfg in (None, (0, 0, 0, 0, scap.CFG_PARTIAL_SUMS))[:2 if B <= 2 else 1]:
+            got = gpu_sparse_fc(layer, X, xdt, m, tau, None, cfg=cfg)["y"]
+            for b in range(B):
+                for lo, hi in ((0, 64), (64, 128), (128, 160), (160, 512), (512, N)):
+                    err = _rel(got[b, lo:hi], want[b, lo:hi])
+                    assert err <= 5e-7, (K, N, wdt, B, b, lo, scale, cfg, err)
+
+
+# the block of one to four tokens with gate and up so small that every hand-over escapes, after one with ordinary weights on
+# the same workspace and before another.  z and y are products of two and three sums: three times the bar, and expf.
+@pytest.mark.parametrize("dt", [BF16, I8])
+def test_small_blocks_keep_their_bits(dt):
+    K, F, N = 1032, 2056, 1032
+    if dt == I8:
+        K, F, N = 1040, 2064, 1040
+    big, small = Block(K, F, N, dt, 1000, B=4), Block(K, F, N, dt, 1003, std=0.05 * (1.0 if dt == I8 else 2.0 ** -9), B=4)
+    small.ws = big.ws
+    m, spread = (0.05, 0.5) if dt == BF16 else (2.0 ** -14, 2.0 ** -13)
+    X = wl.laplace(4, K, 1004, BF16, loc=m, scale=spread)
+    for blk in (big, small, big):
+        f = (lambda w, s: w.astype(np.float64) * wl.decode(s, F16).astype(np.float64) if dt == I8 else wl.decode(w, dt).astype(np.float64))
+        Wg, Wu, Wd = f(blk.Wg, blk.sg), f(blk.Wu, blk.su), f(blk.Wd, blk.sd)
+        for B in (1, 2, 3, 4):
+            print(f"small block dt={dt} B={B} {'small' if blk is small else 'big'}", flush=True)
+            d = (wl.decode(X[:B], BF16).astype(np.float32) - np.float32(m)).astype(np.float64)
+            g, u = d @ Wg, d @ Wu
+            z = g / (1 + np.exp(-g)) * u
+            got = blk.run_batch(X[:B], BF16, m, 0.0, None, None, 0.0, 0.0, None)
+            bar = 1e-5 if B_MATRIX(dt, B) else 2e-6
+            for b in range(B):
+                assert _rel(got[b]["z"], z[b]) <= bar, (dt, B, b, _rel(got[b]["z"], z[b]))
+                assert _rel(got[b]["y"], z[b] @ Wd) <= bar, (dt, B, b, _rel(got[b]["y"], z[b] @ Wd))
 
 
 # order statistics selected on the GPU: tiny samples, one value, even and odd counts, a median between two codes, between
