@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
 #pragma unroll
             for (int b = 0; b < BT; ++b)
                 any_esc |= fx_escapes<CPL>(sum[b], fx_range_bits(IS_I8), frac, esc[b], [&](int c) { return b < B && fcol + c * CSTR < N; });
-            if (__ballot(any_esc) != 0ull) {  // rare
+            if (__builtin_expect(__ballot(any_esc) != 0ull, 0)) {  // rare
 #pragma unroll
                 for (int b = 0; b < BT; ++b) {
                     if (b < B) sum[b].store_coherent(pbuf, split * pstride + pmine + b * ptok);
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
                     some_esc |= n_esc[b][c] != 0;
                 }
             auto word = [&](int b, int c) { return (size_t)b * N + fcol + c * CSTR; };
-            if (some_esc) {
+            if (__builtin_expect(some_esc, 0)) {
                 // One copy of the code for all tokens, and one token after the other: with four copies (or the registers of
                 // all tokens) every call that jumps over them was 0.5 us slower at four slots.
 #pragma unroll 1
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             for (int b = 0; b < BT; ++b)
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    if (!done[b][c]) continue;
+                    if (__builtin_expect(!done[b][c], 0)) continue;
                     store_dev(&y[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
                     store_dev(&fx_acc[word(b, c)], 0ull);  // zero at rest
                 }
