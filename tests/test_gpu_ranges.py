@@ -224,7 +224,7 @@ def test_calibration_of_small_and_awkward_samples(dt):
                 assert np.array_equal(np.float32(got), np.float32(want), equal_nan=True), (v[:5], est, s, got, want)
 
 
-# the staged-tile kernel's two prologues (workgroups of up to 512 channels, and longer ones) and its narrow-layer plan
+# the staged-tile kernel as it is planned: workgroups of up to 512 channels and longer ones, narrow layers
 @pytest.mark.parametrize("wdt", [BF16, F16, I8])
 @pytest.mark.parametrize("K,N", [(64, 128), (512, 512), (4096, 1024), (4104, 1040), (8192, 2048), (5000, 8208)])
 def test_staged_tile_short_and_long_workgroups(K, N, wdt):
@@ -234,3 +234,17 @@ def test_staged_tile_short_and_long_workgroups(K, N, wdt):
         for tau in (0.0, 1.1):
             print(f"staged K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
             check_against_oracle(layer, X, xdt, 0.1, tau, None, what=f"K={K} N={N} wdt={wdt} B={B} tau={tau}")
+
+
+# each form of its prologue (1, 2, 4 or 5 chunks of 64 channels per wavefront) at the longest and shortest workgroup that
+# takes it, the last workgroup cut inside a chunk; 130 column tiles make more than 256 workgroups, i.e. the 16-deep matrix
+# instruction over 16-bit weights, few tiles the 32-deep one and its larger reduction
+@pytest.mark.parametrize("wdt,N", [(BF16, 144), (F16, 144), (I8, 272), (BF16, 130 * 128)])
+@pytest.mark.parametrize("rows,K", [(2368, 2408), (2368, 4720), (2112, 2120), (2048, 4088), (1088, 2160), (1024, 1032), (576, 1144), (512, 1016)])
+def test_staged_tile_prologues(rows, K, wdt, N):
+    layer, xdt = _layer(K, N, wdt, 1010 + K)
+    for B in (5, 16):
+        X = wl.laplace(B, K, 1011 + K, xdt, loc=0.1, scale=0.5)
+        for tau in (0.0, 1.4) if N < 1000 else (1.4,):
+            print(f"prologue rows={rows} K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
+            check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
