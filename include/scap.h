@@ -76,8 +76,9 @@ typedef enum {
  * single-launch kernel also 5..16 tokens over fp16 weights; there waves_per_group must be 0 or 8 -- the
  * two-launch form also takes 16 with bf16 -- and rows_per_group is a multiple of 64, rounded up to whole
  * 512-channel list segments by the two-launch form, whose unroll (1, 2, 4; int8: 1, 2) counts 16-row blocks
- * in flight per wavefront).  By default batches of 5 or more tokens (3 or more over wide int8 layers) run on
- * the matrix cores. */
+ * in flight per wavefront).  By default batches of 5 or more tokens run on
+ * the matrix cores, and of 3-4 tokens those over wide int8 layers and those over bf16 layers with K >= 2 N whose input is
+ * dense or that have at most 1024 columns. */
 typedef struct {
     int32_t waves_per_group; /* 4, 8 or 16 wavefronts per workgroup */
     int32_t rows_per_group;  /* input channels owned by one workgroup; multiple of 64 */

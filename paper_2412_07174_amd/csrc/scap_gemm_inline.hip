@@ -189,6 +189,7 @@ __device__ __forceinline__ float word_half_to_f32(uint32_t wd, int half) {
 // read back from the staged tile with one channel per lane.  Returns the list length; ends with a barrier.
 // RAGGED (16-bit weights): K is not a multiple of 8 -- token rows start at any 2-byte boundary and the last octet is cut.  A template
 // argument: the tests for it cost a kernel that does not need them 1 us (14336 x 4096 int8, 12 tokens: 23.3 -> 24.2 us).
+// It exists in one form, with five chunks and the 16-deep matrix instruction; the others were not tried.
 template <int WAVES, int MAXC, bool SUPERSET, bool RAGGED>
 __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile, int split, const Lds& L, char* xs,
                                                      uint32_t xrow) {
@@ -774,7 +775,7 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     if (rc != SCAP_OK) return rc;
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
-    const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (tile 0's last arrival)
+    const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
     rc = launch_inline_any<kFuseSwiglu>(up, wdt, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;

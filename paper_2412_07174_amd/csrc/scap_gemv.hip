@@ -11,8 +11,8 @@
 //   3. the wavefronts' sums are added through LDS and stored as one split-K partial;
 //   4. the last workgroup to arrive at a tile (device-scope counter) adds the S partials in split order
 //      -- a fixed order, so y is bit-reproducible -- plus the fused bias, and resets the counter.
-// The last arrival of tile 0 also closes the gaps between the per-split index lists that the splits
-// left in idx_out, and writes nnz_out.
+// The last arrival of a tile also closes the gaps between the per-split index lists that the splits left in idx_out,
+// and writes nnz_out, for the tile's own tokens (owned_tokens; one token: tile 0).
 #include "scap_gemv_body.hpp"
 
 namespace scap {
@@ -122,7 +122,7 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // (dense / 50 / 90 %, us): 4 tokens 4096 x 14336 bf16 24.4 / 23.0 / 13.4 against 26.1 / 24.9 / 14.8, 4096 x 6144
     // 15.2 / 14.5 / 10.5 against 18.1 / 17.2 / 12.4, 14336 x 4096 25.5 / 24.6 / 14.9 against 24.7 / 25.5 / 15.6 -- so a
     // dense call with a long input into a narrow layer stays on the staged-tile kernel.  int8 weights in 8-byte lanes
-    // (wider int8 layers do not fit and fall through to the matrix cores): 14336 x 4096, 4 tokens,
+    // (up to 16384 columns, beyond 4096 up to 2^26 weights; others fall through to the matrix cores): 14336 x 4096, 4 tokens,
     // 19.7 / 17.7 / 12.9 at 50 / 70 / 90 % against 19.9 / 18.3 / 14.0, 3 tokens 18.1 / 15.8 / 11.9 against 19.1 / 17.0 / 12.9.
     // bf16 layers of at most 1024 columns with K >= 2 N go to the staged-tile kernel below: 4 tokens at 50 / 90 %, there
     // against here, 4096 x 1024 8.5 / 7.9 us against 10.3 / 8.7, 768 x 256 7.1 / 6.6 against 8.0 / 7.1.  That kernel

@@ -122,9 +122,12 @@ int launch_pack_gate_up(const void* gate, const void* up, int64_t rows, int64_t 
 
 // Batched tokens over bf16 or int8 weights on the matrix cores: possible from kMfmaMinTokens tokens on (the
 // workspace then carries the union lists of the two-launch form), chosen by default from kMfmaAutoTokens
-// (bf16) / kMfmaAutoTokensI8 (int8) tokens on.  Below that the vector kernel is as fast or faster (bf16, 4
-// tokens on 14336 x 4096: 28.9 us against 28.3 us; 2 tokens: 25.1 against 27.5); with int8 weights the vector
-// kernel is bound by its per-element converts from 3 tokens on (34.6 us against 20.7 us).
+// (bf16) / kMfmaAutoTokensI8 (int8) tokens on, where launch_gemv's rules for 2-4 tokens have not chosen a kernel before.
+// From 5 tokens on the vector kernel takes two launches' worth of FMAs (vector / matrix cores at 50 %, us: bf16 14336 x
+// 4096, 5 tokens 44.3 / 28.0, 4096 x 14336, 8 tokens 46.3 / 29.2; fp16 4096 x 11008, 5 tokens 34.5 / 22.3); at 4 tokens
+// over 16-bit weights it does not (14336 x 4096 29.8 / 27.4, 4096 x 14336 27.3 / 28.0, the four-slot kernel 25.8 and
+// 25.7).  With int8 weights it is bound by its per-element converts from 3 tokens on (4096 x 28672 35.6 / 30.1; two 23.5 /
+// 28.2).
 constexpr int kMfmaMinTokens = 2;
 constexpr int kMfmaAutoTokens = 5;
 constexpr int kMfmaAutoTokensI8 = 3;

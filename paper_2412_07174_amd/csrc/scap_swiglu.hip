@@ -55,7 +55,7 @@ static int launch_block(GemvArgs up, GemvArgs dn, int wdt, int flags, hipStream_
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
     size_t lds_dn = lds_bytes(dn.Kc, BT, RED * 4);
-    const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (tile 0's last arrival)
+    const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
     if (lds_up > 64 * 1024 || lds_dn > 64 * 1024) return SCAP_ERR_SHAPE;
 
