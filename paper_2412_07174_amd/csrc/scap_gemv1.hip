@@ -46,12 +46,11 @@ constexpr int kI8WideCols = 4096;
 // they never do.
 constexpr int64_t kI8FourSlotWeights = (int64_t)1 << 26;
 
-// K split and lane width of one launch.  SCAP_OK, kG1NotApplicable or a scap_status.
-// bt = token slots: 1 (one-token kernel), 2 or 4 (its multi-token forms, 8 wavefronts).
-// wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
-int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out,
-               bool wide_lanes = false) {
-    out->i8_half = wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols);
+// K split of one launch with the given lane width and split cost; SCAP_OK, kG1NotApplicable (also for more channels per
+// workgroup than the kernel tests) or a scap_status.
+int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, bool i8_half,
+                     bool split_cost, Plan1* out) {
+    out->i8_half = i8_half;
     out->elems = wdt == kI8 && !out->i8_half ? 16 : 8;
     out->tile = kWave * out->elems;
     GemvArgs p = g;
@@ -73,9 +72,11 @@ int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, in
     // were cut into pieces of 8-32 rows (us, before / now: 1024 x 1024 bf16 8.8 / 4.6, 4096 x 1024 9.4 / 5.7, 2 tokens
     // 12.3 / 5.9 and 13.4 / 7.0).  Beyond 64 splits partial sums are handed over instead, about 4 us more.
     SplitCost sc;
-    sc.rows = 2 + (p.N + 2048) / 4096;
-    sc.soft_max = kFxMaxSplits;
-    sc.beyond_rows = 512;
+    if (split_cost) {
+        sc.rows = 2 + (p.N + 2048) / 4096;
+        sc.soft_max = kFxMaxSplits;
+        sc.beyond_rows = 512;
+    }
     const int rc = plan_splits(p, out->tile, entry / 4 - 1, kc, kc_forced, lds_budget, granule, sc);
     if (rc != SCAP_OK) return rc == SCAP_ERR_SHAPE ? kG1NotApplicable : rc;
     if (p.Kc > kG1MaxChunks * kG1Chunk) return kG1NotApplicable;
@@ -83,6 +84,25 @@ int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, in
     out->S = p.S;
     out->T = p.T;
     return SCAP_OK;
+}
+
+// K split and lane width of one launch.  SCAP_OK, kG1NotApplicable or a scap_status.
+// bt = token slots: 1 (one-token kernel), 2 or 4 (its multi-token forms, 8 wavefronts).
+// wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
+// must: no other kernel does what the call asks for (y += result)
+int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out,
+               bool wide_lanes = false, bool must = false) {
+    const bool half = wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols);
+    const int rc = plan_gemv1_lanes(g, wdt, kc, kc_forced, waves, granule_min, bt, half, true, out);
+    if (rc != kG1NotApplicable) return rc;
+    // Long inputs and very wide layers for which fewer, longer pieces than the kernel tests look best: the split that fills
+    // the compute units alone, in wide lanes, if there is one.  It is worth taking with one workgroup per unit and the
+    // fixed-point hand-over (us, general kernel / here, one and two tokens at 50 %: 62238 x 4592 int8 39.9 / 37.3 and 54.2 /
+    // 51.6, 22968 x 11200 int8 33.8 / 32.4 and 45.9 / 44.2), not otherwise (132456 x 1040 int8, 83 splits, 29.2 / 30.9 and 39.2 /
+    // 42.6; 98580 x 9328 int8, 500 workgroups, 94.2 / 96.1 and 135.5 / 138.9).
+    const int rc2 = plan_gemv1_lanes(g, wdt, kc, kc_forced, waves, granule_min, bt, wdt == kI8 && g.N <= kI8WideCols, false, out);
+    if (rc2 != SCAP_OK || must) return rc2;
+    return out->S <= kFxMaxSplits && (int64_t)out->S * out->T <= 256 ? SCAP_OK : kG1NotApplicable;
 }
 
 Gemv1Args args_of(const GemvArgs& g, const Plan1& pl, int flags) {
@@ -132,7 +152,7 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
         if (kc > kG1MaxChunks * kG1Chunk) return kG1NotApplicable;
     }
     Plan1 pl;
-    const int rc = plan_gemv1(g, wdt, kc, cfg && cfg->rows_per_group, waves, 8, 1, &pl);
+    const int rc = plan_gemv1(g, wdt, kc, cfg && cfg->rows_per_group, waves, 8, 1, &pl, false, (flags & kG1FlagAccumulate) != 0);
     if (rc != SCAP_OK) return rc;
     // rows in flight per wavefront: 4 x 1 KB (16-byte lanes), 8 x 512 bytes (8-byte lanes)
     if (unroll == 0) unroll = pl.i8_half ? 8 : 4;
@@ -188,9 +208,10 @@ static int launch_block_half(const Gemv1Args& a, int wdt, bool i8_half, hipStrea
 int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& dn, int wdt, int up_flags, int down_flags, hipStream_t stream) {
     if (up.B != 1) return kG1NotApplicable;
     Plan1 pu, pd;
-    int rc = plan_gemv1(up, wdt, 0, false, 8, kWave, 1, &pu);
+    const bool must = (down_flags & kG1FlagAccumulate) != 0;
+    int rc = plan_gemv1(up, wdt, 0, false, 8, kWave, 1, &pu, false, must);
     if (rc != SCAP_OK) return rc;
-    rc = plan_gemv1(dn, wdt, 0, false, 8, kWave, 1, &pd);  // whole 64-channel pieces: whole list segments
+    rc = plan_gemv1(dn, wdt, 0, false, 8, kWave, 1, &pd, false, must);  // whole 64-channel pieces: whole list segments
     if (rc != SCAP_OK) return rc;
     const int segz = pu.tile / 8 / 2;  // gated channels a wavefront slice of the gate|up launch finishes: 32 or 64
     if (pd.Kc % segz != 0 || pd.Kc / segz > kWave) return kG1NotApplicable;

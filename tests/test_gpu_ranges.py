@@ -128,6 +128,51 @@ def test_narrow_layers_of_one_to_four_tokens(K, N, wdt):
         check_against_oracle(layer, X, xdt, 0.0, 0.4, None, what=f"K={K} N={N} wdt={wdt} B={B}")
 
 
+# Long inputs and very wide layers whose best K split would give a workgroup more channels than the one-token kernel tests
+# (2048): the split is taken among those it can run, so y += result, which no other kernel does, is not refused.
+@pytest.mark.parametrize("K,N,wdt", [(132456, 1040, BF16), (133214, 1040, I8), (5169, 55600, BF16)])
+def test_splits_stay_within_what_the_one_token_kernel_tests(K, N, wdt):
+    g = torch.Generator(device="cuda").manual_seed(1020)
+    if wdt == I8:
+        W = torch.randint(-127, 128, (K, N), generator=g, device="cuda", dtype=torch.int8)
+        scale = torch.full((N,), 2.0 ** -12, device="cuda").half()
+        Wd = W.double() * scale.double()
+    else:
+        W, scale = (torch.randn(K, N, generator=g, device="cuda") * 0.02).bfloat16(), None
+        Wd = W.double()
+    x = (torch.randn(2, K, generator=g, device="cuda") + 0.1).bfloat16()
+    d = x.float() - 0.1
+    want = torch.where(d.abs() > 0.7, d, 0.0).double() @ Wd
+    del Wd
+    ws = scap.Workspace(K, N, 2)
+    for B in (1, 2):
+        print(f"long pieces K={K} N={N} wdt={wdt} B={B}", flush=True)
+        y = scap.sparse_fc(W, x[:B].contiguous(), 0.1, 0.7, None, col_scale=scale, workspace=ws)
+        torch.cuda.synchronize()
+        assert float((y.double() - want[:B]).norm() / want[:B].norm()) <= 5e-7
+    print(f"long pieces K={K} N={N} wdt={wdt} accumulate", flush=True)
+    addend = torch.randn(1, N, generator=g, device="cuda")
+    y = addend.clone()
+    scap.sparse_fc(W, x[:1].contiguous(), 0.1, 0.7, None, col_scale=scale, y=y, workspace=ws, cfg=(0, 0, 0, 0, scap.CFG_ACCUMULATE))
+    torch.cuda.synchronize()
+    assert float((y.double() - want[:1] - addend).norm() / want[:1].norm()) <= 2e-6  # up to 256 additions in any order
+
+
+def test_residual_block_with_a_very_wide_gate_up_layer():
+    K, F, N = 5176, 27800, 64
+    g = torch.Generator(device="cuda").manual_seed(1021)
+    W_gu = (torch.randn(K, 2 * F, generator=g, device="cuda") * 0.02).bfloat16()
+    W_down = (torch.randn(F, N, generator=g, device="cuda") * 0.02).bfloat16()
+    x, addend = torch.randn(1, K, generator=g, device="cuda").bfloat16(), torch.randn(1, N, generator=g, device="cuda")
+    ws = scap.Workspace(K, N, 1, F=F)
+    print("residual block", flush=True)
+    y = addend.clone()
+    scap.swiglu_block(W_gu, W_down, x, 0.0, 0.5, None, 0.0, 0.0, None, y=y, workspace=ws, residual=True)
+    want = scap.swiglu_block(W_gu, W_down, x, 0.0, 0.5, None, 0.0, 0.0, None, workspace=ws, cfg=(0, 0, 0, 0, scap.CFG_GENERAL_KERNEL))
+    torch.cuda.synchronize()
+    assert float((y - addend - want).norm() / want.norm()) <= 1e-5  # both sums of fp32 products, gated: no threshold on z
+
+
 # int8 weights in 8- or 16-byte lanes: either side of the column count where the lanes change, and of the layer size
 # from which 3-4 tokens go to the matrix cores
 @pytest.mark.parametrize("K,N", [(300, 4096), (300, 4112), (1100, 16384), (1100, 16400), (5000, 16384)])
