@@ -35,6 +35,21 @@ __host__ __device__ constexpr bool whole_reduction(int wdt, int bt, int fuse, bo
     return wdt != kI8 && bt == 16 && (fuse == kFuseList || x32);
 }
 
+// A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
+// offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
+// were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay
+// below kNoRow: at most 4096 rows of 1024 tiles x 256 bytes.
+constexpr uint32_t kNoRow = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const GemvArgs& a, int k0, uint32_t row_bytes) {
+    return make_raw_buffer(const_cast<char*>(reinterpret_cast<const char*>(a.W)) + (uint64_t)k0 * row_bytes,
+                           (uint32_t)min(a.Kc, a.K - k0) * row_bytes);
+}
+constexpr int kAuxNonTemporal = 1 << 1;  // "nt" bit of the buffer cache policy: see load_weights16
+__device__ __forceinline__ uint4 load_row_part(__amdgpu_buffer_rsrc_t rows, uint32_t off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, kAuxNonTemporal);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // FUSE (kFusePlain / kFuseSwiglu / kFuseList) as in the vector kernel: where the inputs come from and what the
 // tile's last arrival does with the finished columns (the two launches of the fused SwiGLU block, Alg. 2).
 template <int WDT, int BT, int FUSE>
@@ -53,9 +68,6 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
     const int tile = blockIdx.x % a.T;
     const int split = blockIdx.x / a.T;
 
-    // constants of the column group this thread finishes if its workgroup is the tile's last arrival
-    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
-
     // ------------------------------------------------------------------ 1. centre, threshold, compact
     int cnt;
     if constexpr (FUSE == kFuseList)
@@ -68,9 +80,10 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
     const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
     const int kg = lane >> 4;  // row group: list rows 4*kg .. 4*kg+3 of a block
     const int col0 = tile * TILE + cg * ELEMS;
-    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : 0u;
+    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : kNoRow;
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
-    const char* wbase = reinterpret_cast<const char*>(a.W);
+    const int k0 = split * a.Kc;
+    const __amdgpu_buffer_rsrc_t wbuf = weight_rows(a, k0, row_bytes);
     const int tok = cg < BT ? cg : BT - 1;  // token slots past BT carry zeros (read slot BT-1, discard)
     const float* d_tok = L.d + tok * a.Kc;
 
@@ -79,8 +92,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
     for (int e = 0; e < ELEMS; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // Three stages per wavefront: list entries of block n+2 come out of LDS while the weight rows of block
-    // n+1 are in flight and the MFMAs of block n run.  No branch anywhere: a slot past the end of the list
-    // reads LDS at a clamped position and weight row 0, and is zeroed by a select.
+    // n+1 are in flight and the MFMAs of block n run.  A slot past the end of the list reads LDS at a clamped position
+    // and no weights.  The loop stops issuing with the last block (see the staged-tile kernel: TAIL).
     struct Entries {
         int4 rows;
         float4 d;
@@ -104,9 +117,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool ok = j < en.left;
-            const uint32_t row = ok ? (uint32_t)rj[j] : 0u;
-            const uint4 v = load_weights16(wbase + (uint64_t)row * row_bytes + lane_off);
-            st.r[j] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+            st.r[j] = load_row_part(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
             dm[j] = (ok && cg < BT) ? dj[j] : 0.f;
         }
         st.d = make_float4(dm[0], dm[1], dm[2], dm[3]);
@@ -117,24 +128,35 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
         mfma_block<WDT>(acc, a_hi, a_lo, st.r);
     };
 
-    Entries E0, E1;
-    Stage A, Bs;
-    entries(w, E0);
-    entries(w + WAVES, E1);
-    issue(E0, A);
-    for (int blk = w; blk < n_blocks;) {
-        entries(blk + 2 * WAVES, E0);
-        issue(E1, Bs);
+    if (w < n_blocks) {
+        Entries E;
+        Stage A, Bs;
+        entries(w, E);
+        issue(E, A);
+        entries(w + WAVES, E);
+        int blk = w;
+        for (;;) {
+            if (blk + WAVES >= n_blocks) break;
+            issue(E, Bs);
+            entries(blk + 2 * WAVES, E);
+            compute(A);
+            blk += WAVES;
+            if (blk + WAVES >= n_blocks) {
+                A = Bs;
+                break;
+            }
+            issue(E, A);
+            entries(blk + 2 * WAVES, E);
+            compute(Bs);
+            blk += WAVES;
+        }
         compute(A);
-        blk += WAVES;
-        if (blk >= n_blocks) break;
-        entries(blk + 2 * WAVES, E1);
-        issue(E0, A);
-        compute(Bs);
-        blk += WAVES;
     }
 
     // ------------------------------------------------------------------ 3. add the wavefronts' sums
+    // constants of the column group this thread finishes if its workgroup is the tile's last arrival: fetched behind the
+    // reduction (not at the start: no registers for them while the rows stream)
+    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
     reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the list is done with
 
@@ -429,10 +451,10 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     return cnt;
 }
 
-// X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 151 registers per lane against 109, i.e. one
+// X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 180 registers per lane against 123, i.e. one
 // workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
 template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC>
-__global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(const GemvArgs a) {
+__global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
     constexpr int ELEMS = Vec<WDT>::kElems;
@@ -454,8 +476,6 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
     const float m_eff = dense ? 0.f : a.m;  // dense mode: x - 0 is x
     const uint32_t bf16_sel = a.xdt == kBF16 ? 0xffffffffu : 0u;
 
-    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
-
     // ------------------------------------------------------------------ 1. stage the inputs, list the union
     // int8 weights: 256-column tiles, so half as many workgroups repeat a split's prologue and a wavefront has
     // two chunks; listing supersets measured no gain there (and 0.14 us lost to the extra code)
@@ -466,9 +486,16 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
     const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
     const int kg = lane >> 4;  // row group: list rows 4*kg .. 4*kg+3 of a block
     const int col0 = tile * TILE + cg * ELEMS;
-    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : 0u;
+    // Two forms of the row loads.  LONG -- 16-bit weights, two workgroups per compute unit, pieces of more than 1024 rows
+    // -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in registers:
+    // with the other form's loads and order 4096 x 28672 bf16, 16 tokens, took 50.4 instead of 49.8 us and fp16 50.4
+    // instead of 48.2, 8192 x 16384 53.0 instead of 52.2; with shorter pieces it is the slower one (4096 x 22016 44.3
+    // against 40.0, fp16 47.4 against 40.1).
+    constexpr bool LONG = !X32 && WDT != kI8 && MAXC >= 4;
+    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const char* wbase = reinterpret_cast<const char*>(a.W);
+    const __amdgpu_buffer_rsrc_t wbuf = weight_rows(a, k0, row_bytes);
     const bool tok_ok = cg < a.B;  // token slots past B carry zeros
     const char* xs_tok = xs + (size_t)min(cg, a.B - 1) * xrow;
 
@@ -476,9 +503,14 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
 #pragma unroll
     for (int e = 0; e < ELEMS; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // Four stages per wavefront, no branch anywhere: list rows of block n+3 and staged inputs of block n+2 come
-    // out of LDS while the weight rows of block n+1 are in flight and the MFMAs of block n run.  A slot past the
-    // end of the list reads LDS at a clamped position and weight row 0, and is zeroed by a select.
+    // Four stages per wavefront: list rows of block n+3 and staged inputs of block n+2 come out of LDS while the weight
+    // rows of block n+1 are in flight and the MFMAs of block n run.  A slot past the end of the list reads LDS at a
+    // clamped position and no weights (zeros).  The loop runs as long as there is a next block to fetch and the last one
+    // is multiplied behind it (TAIL): a stage of loads past the end, even of lanes that fetch nothing, costs a wavefront
+    // as much time in the load pipe as a stage of rows (removing the one stage that the loop issued in vain: 1024 x 4096
+    // bf16, 16 tokens, 9.7 -> 9.1 us, 4096 x 4096 13.8 -> 13.1; a second one added 1.2 us).  In the 16-deep form over 16-bit
+    // weights the copy of the stage behind the loop does not fit the 128 registers of two workgroups per unit.
+    constexpr bool TAIL = X32 || WDT == kI8;
     struct Rows {
         int4 rows;
         int left;  // valid entries from this lane's first one on (<= 0: none)
@@ -513,9 +545,13 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool ok = j < en.left;
-            const uint32_t row = ok ? (uint32_t)rj[j] : 0u;
-            const uint4 v = load_weights16(wbase + (uint64_t)row * row_bytes + lane_off);
-            st.r[j] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+            if constexpr (LONG) {
+                const uint32_t row = ok ? (uint32_t)rj[j] : 0u;
+                const uint4 v = load_weights16(wbase + (uint64_t)row * row_bytes + lane_off);
+                st.r[j] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+            } else {
+                st.r[j] = load_row_part(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
+            }
             const float dv = act_code_to_f32(en.code[j], bf16_sel) - m_eff;  // one fp32 subtraction
             const bool keep = ok & tok_ok & (dense | (fabsf(dv) > a.tau));    // strict; NaN is pruned
             dm[j] = keep ? dv : 0.f;
@@ -530,27 +566,74 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
             split_operand<WDT>(st.d, a_hi, a_lo);
             mfma_block<WDT>(acc, a_hi, a_lo, st.r);
         };
-        Rows R;
-        Entries E0, E1;
-        Stage A, Bs;
-        rows_of(w, R);
-        codes_of(R, E0);
-        rows_of(w + WAVES, R);
-        codes_of(R, E1);
-        rows_of(w + 2 * WAVES, R);
-        issue(E0, A);
-        for (int blk = w; blk < n_blocks;) {
+        if constexpr (LONG) {
+            Rows R;
+            Entries E0, E1;
+            Stage A, Bs;
+            rows_of(w, R);
             codes_of(R, E0);
-            rows_of(blk + 3 * WAVES, R);
-            issue(E1, Bs);
-            compute(A);
-            blk += WAVES;
-            if (blk >= n_blocks) break;
+            rows_of(w + WAVES, R);
             codes_of(R, E1);
-            rows_of(blk + 3 * WAVES, R);
+            rows_of(w + 2 * WAVES, R);
             issue(E0, A);
-            compute(Bs);
-            blk += WAVES;
+            for (int blk = w; blk < n_blocks;) {
+                codes_of(R, E0);
+                rows_of(blk + 3 * WAVES, R);
+                issue(E1, Bs);
+                compute(A);
+                blk += WAVES;
+                if (blk >= n_blocks) break;
+                codes_of(R, E1);
+                rows_of(blk + 3 * WAVES, R);
+                issue(E0, A);
+                compute(Bs);
+                blk += WAVES;
+            }
+        } else if (w < n_blocks) {
+            Rows R;
+            Entries E;
+            Stage A, Bs;
+            rows_of(w, R);
+            codes_of(R, E);
+            rows_of(w + WAVES, R);
+            issue(E, A);
+            codes_of(R, E);
+            rows_of(w + 2 * WAVES, R);
+            if constexpr (TAIL) {
+                int blk = w;
+                for (;;) {
+                    if (blk + WAVES >= n_blocks) break;
+                    issue(E, Bs);
+                    codes_of(R, E);
+                    rows_of(blk + 3 * WAVES, R);
+                    compute(A);
+                    blk += WAVES;
+                    if (blk + WAVES >= n_blocks) {
+                        A = Bs;
+                        break;
+                    }
+                    issue(E, A);
+                    codes_of(R, E);
+                    rows_of(blk + 3 * WAVES, R);
+                    compute(Bs);
+                    blk += WAVES;
+                }
+                compute(A);
+            } else {
+                for (int blk = w; blk < n_blocks;) {
+                    issue(E, Bs);
+                    codes_of(R, E);
+                    rows_of(blk + 3 * WAVES, R);
+                    compute(A);
+                    blk += WAVES;
+                    if (blk >= n_blocks) break;
+                    issue(E, A);
+                    codes_of(R, E);
+                    rows_of(blk + 3 * WAVES, R);
+                    compute(Bs);
+                    blk += WAVES;
+                }
+            }
         }
     } else {
         // The matrix instruction is 32 rows deep (gfx950's 16x16x32): a wavefront's blocks are taken two at a time,
@@ -587,31 +670,41 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_raw_kernel(co
         const int n_mine = n_blocks > w ? (n_blocks - w + WAVES - 1) / WAVES : 0;  // blocks w, w + WAVES, ...
         const int n_pairs = (n_mine + 1) / 2;
 
-        Rows2 R;
-        Entries2 E0, E1;
-        Stage2 A, Bs;
-        rows2_of(0, R);
-        codes2_of(R, E0);
-        rows2_of(1, R);
-        codes2_of(R, E1);
-        rows2_of(2, R);
-        issue2(E0, A);
-        for (int pr = 0; pr < n_pairs;) {
-            codes2_of(R, E0);
-            rows2_of(pr + 3, R);
-            issue2(E1, Bs);
+        if (n_pairs > 0) {
+            Rows2 R;
+            Entries2 E;
+            Stage2 A, Bs;
+            rows2_of(0, R);
+            codes2_of(R, E);
+            rows2_of(1, R);
+            issue2(E, A);
+            codes2_of(R, E);
+            rows2_of(2, R);
+            int pr = 0;
+            for (;;) {
+                if (pr + 1 >= n_pairs) break;
+                issue2(E, Bs);
+                codes2_of(R, E);
+                rows2_of(pr + 3, R);
+                compute2(A);
+                if (++pr + 1 >= n_pairs) {
+                    A = Bs;
+                    break;
+                }
+                issue2(E, A);
+                codes2_of(R, E);
+                rows2_of(pr + 3, R);
+                compute2(Bs);
+                ++pr;
+            }
             compute2(A);
-            if (++pr >= n_pairs) break;
-            codes2_of(R, E1);
-            rows2_of(pr + 3, R);
-            issue2(E0, A);
-            compute2(Bs);
-            ++pr;
         }
-
     }
 
     // ------------------------------------------------------------------ 3. add the wavefronts' sums
+    // constants of the column group this thread finishes if its workgroup is the tile's last arrival: fetched behind the
+    // reduction (not at the start: no registers for them while the rows stream)
+    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
     reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the tile is done with
 
