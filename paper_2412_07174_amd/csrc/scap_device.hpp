@@ -55,8 +55,13 @@ __device__ __forceinline__ uint4 load_octet_cut(const uint16_t* p, int n) {
     return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
-// number of weight elements in one 16-byte load
-template <int WDT> struct Vec { static constexpr int kElems = (WDT == kI8) ? 16 : 8; static constexpr int kBytes = (WDT == kI8) ? 1 : 2; };
+// int8 weights read 8 bytes per lane instead of 16 (internal to the kernels): column tiles are half as wide, so a layer
+// has twice the tiles and half the K splits.
+constexpr int kI8Half = 3;
+__host__ __device__ constexpr bool is_int8(int wdt) { return wdt == kI8 || wdt == kI8Half; }
+
+// number of weight elements in one lane's load: 16 bytes, or 8
+template <int WDT> struct Vec { static constexpr int kElems = (WDT == kI8) ? 16 : 8; static constexpr int kBytes = is_int8(WDT) ? 1 : 2; };
 
 // acc[j] += d * w[j] for the elements packed in one 16-byte vector
 template <int WDT>

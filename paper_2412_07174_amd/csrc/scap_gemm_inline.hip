@@ -24,6 +24,7 @@ namespace scap {
 
 constexpr size_t kInlineLdsBudget = 160 * 1024;
 constexpr int kInlineWaves = 8;
+constexpr int kInlineSplitRows = 12;  // rows' time that a K split's hand-over costs (16 token slots)
 // chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
 constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
 
@@ -45,9 +46,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const GemvArgs& a,
                            (uint32_t)min(a.Kc, a.K - k0) * row_bytes);
 }
 constexpr int kAuxNonTemporal = 1 << 1;  // "nt" bit of the buffer cache policy: see load_weights16
+template <int WDT>
 __device__ __forceinline__ uint4 load_row_part(__amdgpu_buffer_rsrc_t rows, uint32_t off) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, kAuxNonTemporal);
-    return make_uint4(v[0], v[1], v[2], v[3]);
+    if constexpr (WDT == kI8Half) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rows, (int)off, 0, kAuxNonTemporal);
+        return make_uint4(v[0], v[1], 0u, 0u);
+    } else {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, kAuxNonTemporal);
+        return make_uint4(v[0], v[1], v[2], v[3]);
+    }
 }
 
 // FUSE (kFusePlain / kFuseSwiglu / kFuseList) as in the vector kernel: where the inputs come from and what the
@@ -117,7 +124,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool ok = j < en.left;
-            st.r[j] = load_row_part(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
+            st.r[j] = load_row_part<WDT>(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
             dm[j] = (ok && cg < BT) ? dj[j] : 0.f;
         }
         st.d = make_float4(dm[0], dm[1], dm[2], dm[3]);
@@ -173,7 +180,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 // per element (one fp32 subtraction, strict compare), so masks and values are those of the other forms.
 // Chunks of 64 channels per wavefront (loads of all of them are in flight at once): 1, 2, 4 or 5 by the workgroup's
 // channels; with 5 for all of them the others re-read what was there (4096 x 4096 bf16, 16 tokens: 15.8 -> 14.0 us with 1;
-// 4096 x 11008 fp16, 8 tokens: 23.8 -> 22.9 with 2; 4096 x 28672 bf16, 16 tokens: 48.6 -> 46.8 with 4).  Instantiations,
+// 4096 x 11008 fp16, 8 tokens: 23.8 -> 22.9 with 2; 4096 x 28672 bf16, 16 tokens: 48.6 -> 46.8 with 4; odd input lengths,
+// where an octet is two loads: 5461 x 2744 bf16, 16 tokens, 19.2 -> 13.5 with 1, 4097 x 11008 36.0 -> 26.8 with 2).  Instantiations,
 // not a choice made inside: behind such a branch the first test waits for all loads.
 constexpr int kRawChunks = 5;
 constexpr int kRawPad = 16;    // bytes between token rows of the staged tile: rows start 4 LDS banks apart
@@ -209,9 +217,9 @@ __device__ __forceinline__ float word_half_to_f32(uint32_t wd, int half) {
 // a nonzero-byte test.  Everything in the test is straight-line: the instruction count per element is what the
 // prologue costs, repeated by every column tile.  Per-token lists and counts (on request, the tile's own tokens) are
 // read back from the staged tile with one channel per lane.  Returns the list length; ends with a barrier.
-// RAGGED (16-bit weights): K is not a multiple of 8 -- token rows start at any 2-byte boundary and the last octet is cut.  A template
+// RAGGED (16-bit weights, int8 in 8-byte lanes): K is not a multiple of 8 -- token rows start at any 2-byte boundary and the last octet is cut.  A template
 // argument: the tests for it cost a kernel that does not need them 1 us (14336 x 4096 int8, 12 tokens: 23.3 -> 24.2 us).
-// It exists in one form, with five chunks and the 16-deep matrix instruction; the others were not tried.
+// It exists with the 16-deep matrix instruction, and not for 16-byte int8 lanes.
 template <int WAVES, int MAXC, bool SUPERSET, bool RAGGED>
 __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile, int split, const Lds& L, char* xs,
                                                      uint32_t xrow) {
@@ -477,8 +485,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     const uint32_t bf16_sel = a.xdt == kBF16 ? 0xffffffffu : 0u;
 
     // ------------------------------------------------------------------ 1. stage the inputs, list the union
-    // int8 weights: 256-column tiles, so half as many workgroups repeat a split's prologue and a wavefront has
-    // two chunks; listing supersets measured no gain there (and 0.14 us lost to the extra code)
+    // int8 weights in 16-byte lanes: 256-column tiles, so half as many workgroups repeat a split's prologue and a wavefront
+    // has two chunks; listing supersets measured no gain there (and 0.14 us lost to the extra code)
     const int cnt = stage_inputs_and_list<WAVES, MAXC, WDT != kI8, RAGGED>(a, tile, split, L, xs, xrow);
     const int n_blocks = (cnt + kMfmaBlock - 1) / kMfmaBlock;
 
@@ -490,8 +498,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     // -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in registers:
     // with the other form's loads and order 4096 x 28672 bf16, 16 tokens, took 50.4 instead of 49.8 us and fp16 50.4
     // instead of 48.2, 8192 x 16384 53.0 instead of 52.2; with shorter pieces it is the slower one (4096 x 22016 44.3
-    // against 40.0, fp16 47.4 against 40.1).
-    constexpr bool LONG = !X32 && WDT != kI8 && MAXC >= 4;
+    // against 40.0, fp16 47.4 against 40.1), and over odd input lengths (14337 x 4096 fp16, 10 tokens, 34.6 against 31.1).
+        constexpr bool LONG = !X32 && !is_int8(WDT) && MAXC >= 4 && !RAGGED;
     const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const char* wbase = reinterpret_cast<const char*>(a.W);
@@ -510,7 +518,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     // as much time in the load pipe as a stage of rows (removing the one stage that the loop issued in vain: 1024 x 4096
     // bf16, 16 tokens, 9.7 -> 9.1 us, 4096 x 4096 13.8 -> 13.1; a second one added 1.2 us).  In the 16-deep form over 16-bit
     // weights the copy of the stage behind the loop does not fit the 128 registers of two workgroups per unit.
-    constexpr bool TAIL = X32 || WDT == kI8;
+    constexpr bool TAIL = X32 || is_int8(WDT);
     struct Rows {
         int4 rows;
         int left;  // valid entries from this lane's first one on (<= 0: none)
@@ -550,7 +558,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
                 const uint4 v = load_weights16(wbase + (uint64_t)row * row_bytes + lane_off);
                 st.r[j] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
             } else {
-                st.r[j] = load_row_part(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
+                st.r[j] = load_row_part<WDT>(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
             }
             const float dv = act_code_to_f32(en.code[j], bf16_sel) - m_eff;  // one fp32 subtraction
             const bool keep = ok & tok_ok & (dense | (fabsf(dv) > a.tau));    // strict; NaN is pruned
@@ -560,7 +568,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     };
     if constexpr (!X32) {
         // (int8 weights always: with 16 columns per lane the 32-deep form needs 180 registers and measured slower,
-        // 14336 x 4096, 16 tokens: 23.3 against 24.8 us)
+        // 14336 x 4096, 16 tokens: 23.3 against 24.8 us; with 8 columns 14336 x 4096, 5 tokens, 18.3 against 19.4)
         auto compute = [&](const Stage& st) {
             s16x4_t a_hi, a_lo;
             split_operand<WDT>(st.d, a_hi, a_lo);
@@ -755,9 +763,9 @@ static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t s
 
 template <int WDT, int FUSE, bool X32, bool RAGGED>
 static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
-    if constexpr (!RAGGED) {
-        if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
-        if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
+    if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
+    if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
+    if constexpr (!RAGGED || is_int8(WDT)) {
         if (a.Kc <= 4 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);
     }
     return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, kRawChunks>(a, lds, stream);
@@ -766,8 +774,8 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
 // 16 token slots: the staged-tile kernel, or the value-list kernel where the inputs are the gated product's lists;
 // 4 slots: the value-list kernel (not fp16 weights: 2-4 tokens stay on the vector kernels).
 // An input length that is not a multiple of 8: the staged-tile kernel too (5461 x 2744 bf16, 8 tokens 19.7 -> 17.7 us
-// per call, block 4095 -> 6144 -> 4096 56.0 -> 51.9), but not with int8 weights, where a wavefront has only two chunks
-// to test and the value lists stay 3 % faster (5461 x 2752, 16 tokens 23.3 against 24.0; the block 41.7 against 43.0).
+// per call, block 4095 -> 6144 -> 4096 56.0 -> 51.9), but not with int8 weights in 16-byte lanes, where a wavefront has
+// only two chunks to test and the value lists stay 3 % faster (5461 x 2752, 16 tokens 23.3 against 24.0).
 __host__ constexpr bool staged_tile(int wdt, int K) { return wdt != kI8 || K % 8 == 0; }
 
 template <int WDT, int FUSE>
@@ -778,6 +786,8 @@ static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t 
         } else {
             if constexpr (WDT == kI8) {
                 if (!staged_tile(WDT, a.K)) return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
+            } else if constexpr (WDT == kI8Half) {
+                if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
             } else {
                 if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
                 if ((long)a.S * a.T <= 256) return launch_inline_raw<WDT, FUSE, true, false>(a, lds, stream);
@@ -785,7 +795,7 @@ static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t 
             return launch_inline_raw<WDT, FUSE, false, false>(a, lds, stream);
         }
     }
-    if constexpr (WDT == kF16)
+    if constexpr (WDT == kF16 || WDT == kI8Half)
         return SCAP_ERR_CONFIG;
     else
         return launch_inline<WDT, 4, FUSE>(a, lds, stream);
@@ -796,6 +806,7 @@ static int launch_inline_any(const GemvArgs& a, int wdt, int bt, size_t lds, hip
     if (wdt == kBF16) return launch_inline_wdt<kBF16, FUSE>(a, bt, lds, stream);
     if (wdt == kF16) return launch_inline_wdt<kF16, FUSE>(a, bt, lds, stream);
     if (wdt == kI8) return launch_inline_wdt<kI8, FUSE>(a, bt, lds, stream);
+    if (wdt == kI8Half) return launch_inline_wdt<kI8Half, FUSE>(a, bt, lds, stream);
     return SCAP_ERR_CONFIG;
 }
 
@@ -803,7 +814,7 @@ static int launch_inline_any(const GemvArgs& a, int wdt, int bt, size_t lds, hip
 // registers that hold a wavefront's chunks), LDS bytes.
 static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, int* bt_out, size_t* lds_out,
                        bool slots16 = false) {
-    if (wdt != kBF16 && wdt != kI8 && wdt != kF16) return SCAP_ERR_CONFIG;
+    if (wdt != kBF16 && !is_int8(wdt) && wdt != kF16) return SCAP_ERR_CONFIG;
     if (a.B < 1 || a.B > kMfmaTokens) return SCAP_ERR_CONFIG;
     const int bt = (a.B <= 4 && !slots16) ? 4 : 16;
     if (wdt == kF16 && bt != kMfmaTokens) return SCAP_ERR_CONFIG;  // fp16: the 16-slot kernels only
@@ -817,14 +828,14 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     }
     const size_t by_cap = kHdrBytes + (size_t)kc_cap * 4 * (1 + bt);
     if (by_cap < budget) budget = by_cap;
-    // 16 slots: a split's partial sums cost the tile's last arrival as much time as 12 rows (sweeps of kc; 4096 x 1024,
+    // 16 slots: a split's partial sums cost the tile's last arrival as much time as kInlineSplitRows rows (sweeps of kc; 4096 x 1024,
     // 16 tokens, pieces of 128 / 256 rows: 13.2 / 11.6 us bf16, 8 tokens int8 13.1 / 12.8 against 15.9 with 64)
     SplitCost sc;
-    sc.rows = bt == kMfmaTokens ? 12 : 0;
+    sc.rows = bt == kMfmaTokens ? kInlineSplitRows : 0;
     const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget, kWave, sc);
     if (rc != SCAP_OK) return rc;
     if (a.Kc > kc_cap) return SCAP_ERR_SHAPE;
-    const bool x32 = staged_tile(wdt, a.K) && a.K % 8 == 0 && (int64_t)a.S * a.T <= 256;  // (as launch_inline_wdt chooses)
+    const bool x32 = wdt != kI8Half && staged_tile(wdt, a.K) && a.K % 8 == 0 && (int64_t)a.S * a.T <= 256;  // (as launch_inline_wdt chooses)
     size_t red = (size_t)tree_floats(whole_reduction(wdt, bt, fuse, x32)) * 4;
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
@@ -834,6 +845,40 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
         *lds_out = kHdrBytes + (body > red ? body : red);
     }
     return SCAP_OK;
+}
+
+// What a planned launch takes, in rows of one workgroup (as plan_splits weighs them), times the columns of its tile.
+static int64_t inline_cost(const GemvArgs& a, int tile_cols) {
+    return (((int64_t)a.S * a.T + 255) / 256 * (a.Kc + 128) + (int64_t)a.S * kInlineSplitRows) * tile_cols;
+}
+
+// The same with the lane width of int8 weights chosen on the way (*wdt becomes kI8Half: 8-byte lanes, 128-column tiles).
+// Narrow tiles halve the K splits, the wavefronts' sums and what a tile's last arrival collects, wide ones halve the
+// prologues and read rows in pieces of 256 instead of 128 bytes.  Which is faster follows what the two plans cost (16
+// tokens, wide / narrow, us: 1024 x 4096 12.0 / 8.5, 4096 x 4096 14.0 / 10.9, 14336 x 4096 21.5 / 19.6, 4096 x 24576 35.3 /
+// 30.3, 16384 x 16384 69.7 / 66.4; 5 tokens 18.9 / 18.2 on 14336 x 4096, but 29.3 / 30.9 on 4096 x 28672, where both plans
+// cost the same).  The launch that reads lists gains less from the narrow tiles (block 2048 -> 8192 -> 2048, 16 tokens,
+// 34.1 / 28.9, 4096 -> 8192 -> 4096 40.5 / 39.3, but 4096 -> 11008 -> 4096 48.9 / 49.4 and 8192 -> 16384 -> 8192 99.5 / 109.7).
+// An input length that is not a multiple of 8: the staged tile exists for narrow tiles only, and beats the value lists
+// (16 tokens, lists / tile: 513 x 1024 17.0 / 8.8, 5461 x 2752 23.3 / 12.5, 14337 x 4096 27.3 / 24.2; 5 tokens 4097 x 28672
+// 36.7 / 33.0) but for more than 8 tokens and a long stream (16 tokens 4097 x 28672 40.0 / 43.2, 10 tokens 36.4 / 37.4).
+static int plan_inline_lanes(GemvArgs& a, int* wdt, int kc, bool kc_forced, int fuse, int* bt_out, size_t* lds_out,
+                             bool slots16 = false) {
+    const GemvArgs in = a;
+    const int rc = plan_inline(a, *wdt, kc, kc_forced, fuse, bt_out, lds_out, slots16);
+    if (rc != SCAP_OK || *wdt != kI8 || *bt_out != kMfmaTokens) return rc;
+    const bool ragged = fuse != kFuseList && in.K % 8 != 0;
+    if (ragged && in.B > 8 && (int64_t)in.K * in.N > ((int64_t)1 << 26)) return rc;
+    GemvArgs h = in;
+    int bt = 0;
+    size_t lds = 0;
+    if (plan_inline(h, kI8Half, kc, kc_forced, fuse, &bt, &lds, slots16) != SCAP_OK) return rc;
+    const int percent = fuse == kFuseList ? 77 : 99;
+    if (!ragged && inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * percent) return rc;
+    a = h;
+    *lds_out = lds;
+    *wdt = kI8Half;
+    return rc;
 }
 
 // slots16: run 2-4 tokens in the 16-slot staged-tile kernel
@@ -848,7 +893,7 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     }
     int bt = 0;
     size_t lds = 0;
-    const int rc = plan_inline(a, wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
+    const int rc = plan_inline_lanes(a, &wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
     a.Kl = a.Kc;
     a.Sl = a.S;
@@ -860,19 +905,20 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     GemvArgs up = up_in, dn = dn_in;
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
-    int rc = plan_inline(up, wdt, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+    int wup = wdt, wdn = wdt;
+    int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
     if (rc != SCAP_OK) return rc;
     up.Kl = up.Kc;
     up.Sl = up.S;
-    rc = plan_inline(dn, wdt, 0, false, kFuseList, &bt_dn, &lds_dn);
+    rc = plan_inline_lanes(dn, &wdn, 0, false, kFuseList, &bt_dn, &lds_dn);
     if (rc != SCAP_OK) return rc;
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
     const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
-    rc = launch_inline_any<kFuseSwiglu>(up, wdt, bt_up, lds_up, stream);
+    rc = launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;
-    return launch_inline_any<kFuseList>(dn, wdt, bt_dn, lds_dn, stream);
+    return launch_inline_any<kFuseList>(dn, wdn, bt_dn, lds_dn, stream);
 }
 
 }  // namespace scap

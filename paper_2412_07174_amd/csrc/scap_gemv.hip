@@ -141,14 +141,15 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
         const int rc = launch_gemv1b(a, wdt, cfg ? cfg->flags : 0, stream);
         if (rc != kG1NotApplicable) return rc;
     }
-    // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot forms for int8 weights unless the layer
-    // is very wide (its narrow tiles repeat the prologue), and than the vector kernel for a long input into a
-    // narrow bf16 layer (14336 x 4096, 4 tokens: 28.7 -> 27.3 us dense, 22.2 -> 20.0 at 90 %).
-    // Not over an input length that is not a multiple of 8: int8 weights keep the 4-slot lists (4097 x 8192, 4 tokens, 60 %:
-    // 17.2 against 19.4 us; 14337 x 4096, 3 tokens dense 21.0 against 22.6), and bf16 calls that the four-slot kernel does
-    // not take the general vector kernel with its fp32 operands.
-    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 && a.K % 8 == 0 &&
-        ((wdt == kI8 && (int64_t)a.N <= 4 * (int64_t)a.K) || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
+    // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot lists for int8 weights (3 tokens at 50 %, lists /
+    // here, us: 512 x 24576 13.4 / 7.2, 1024 x 28672 15.9 / 10.3, 4096 x 24576 34.2 / 25.8, 4096 x 28672 29.2 / 27.5, 8192 x
+    // 28672 53.3 / 53.0), and than the vector kernel for a long input into a narrow bf16 layer (14336 x 4096, 4 tokens:
+    // 28.7 -> 27.3 us dense, 22.2 -> 20.0 at 90 %).
+    // Not over an input length that is not a multiple of 8: int8 weights keep the 4-slot lists beyond 2048 channels (4
+    // tokens at 70 %, lists / here: 1023 x 28672 14.9 / 11.0, 2047 x 28672 18.5 / 17.4, 4097 x 20480 21.7 / 23.9, 8193 x 16384
+    // 27.9 / 30.0), and bf16 calls that the four-slot kernel does not take the general vector kernel with its fp32 operands.
+    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 && (a.K % 8 == 0 || (wdt == kI8 && a.K <= 2048)) &&
+        (wdt == kI8 || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
         const int rc = launch_gemm_inline(a, wdt, cfg, stream, true);
         if (rc != SCAP_ERR_SHAPE) return rc;
     }

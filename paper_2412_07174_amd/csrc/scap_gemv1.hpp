@@ -60,12 +60,8 @@ __host__ __device__ inline int fx_limit_bits(int S) {  // bits of one arrival's 
 // 2^20 of range and no such rule 1024 x 1024 bf16 had an error of 1e-5 at results of 1e-2 and 4e-3 at 2e-5, now 1e-7.
 __device__ __forceinline__ float fx_whole_from(int frac) { return __int_as_float((127 + 23 - frac) << 23); }
 
-// int8 weights read 8 bytes per lane instead of 16 (internal to this kernel): the column tile is 512 columns
-// instead of 1024, so a layer with few columns gets twice the tiles and half the K splits.  With 4096 columns
+// int8 weights in 8-byte lanes (kI8Half): the column tile is 512 columns instead of 1024.  With 4096 columns
 // that is 8 tiles of 32 splits instead of 4 of 64: half as many partial sums per finished slice.
-constexpr int kI8Half = 3;
-template <> struct Vec<kI8Half> { static constexpr int kElems = 8; static constexpr int kBytes = 1; };
-
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) const u32x2_t global_u32x2_t;
 

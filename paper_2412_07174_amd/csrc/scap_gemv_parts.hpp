@@ -598,7 +598,7 @@ __device__ __forceinline__ ColConst load_col_const(const GemvArgs& a, int tile, 
     const int col = tile * TILE + 4 * g;
     if (col < a.N) {  // N is a multiple of 8: a group is inside or outside as a whole
         if (a.bias) c.bias = *reinterpret_cast<const float4*>(a.bias + col);
-        if (WDT == kI8) {
+        if (is_int8(WDT)) {
             const uint2 h = *reinterpret_cast<const uint2*>(a.col_scale + col);
             c.scale = make_float4(f16_bits_to_f32(h.x & 0xFFFFu), f16_bits_to_f32(h.x >> 16), f16_bits_to_f32(h.y & 0xFFFFu),
                                   f16_bits_to_f32(h.y >> 16));
@@ -613,7 +613,7 @@ __device__ __forceinline__ void finish_columns(const GemvArgs& a, int tile, int 
                                                const ColConst& c) {
     const int col = tile * TILE + 4 * g;
     if (col >= a.N) return;
-    if (WDT == kI8) {
+    if (is_int8(WDT)) {
         s.x *= c.scale.x;
         s.y *= c.scale.y;
         s.z *= c.scale.z;

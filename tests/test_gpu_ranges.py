@@ -293,3 +293,37 @@ def test_staged_tile_prologues(rows, K, wdt, N):
         for tau in (0.0, 1.4) if N < 1000 else (1.4,):
             print(f"prologue rows={rows} K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
             check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
+
+
+# the same over input lengths that are not a multiple of 8 (the staged tile in 8-byte lanes for int8 weights), more than
+# 256 workgroups among them
+@pytest.mark.parametrize("wdt,N", [(BF16, 144), (F16, 144), (I8, 144), (I8, 130 * 128)])
+@pytest.mark.parametrize("rows,K", [(2368, 2403), (2112, 2113), (1088, 2157), (1024, 1031), (576, 1141), (512, 1017), (64, 7)])
+def test_staged_tile_prologues_of_odd_lengths(rows, K, wdt, N):
+    layer, xdt = _layer(K, N, wdt, 1110 + K)
+    for B in (5, 8, 16):
+        X = wl.laplace(B, K, 1111 + K, xdt, loc=0.1, scale=0.5)
+        for tau in (0.0, 1.4) if N < 1000 else (1.4,):
+            print(f"odd prologue rows={rows} K={K} N={N} wdt={wdt} B={B} tau={tau}", flush=True)
+            check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
+
+
+# int8 layers around the choice between 16- and 8-byte lanes: both plans cost the same at 28672 columns (16-byte lanes), a
+# tile less or more and 8-byte lanes are cheaper; 3-4 tokens take the same kernel
+@pytest.mark.parametrize("K,N", [(1048, 28672), (2056, 28672), (1048, 24576), (2040, 28416), (1023, 28672), (2049, 20496)])
+def test_int8_batches_of_both_lane_widths(K, N):
+    layer, xdt = _layer(K, N, I8, 1210 + K)
+    for B in (3, 4, 5, 16):
+        X = wl.laplace(B, K, 1211 + K, xdt, loc=0.1, scale=0.5)
+        print(f"int8 lanes K={K} N={N} B={B}", flush=True)
+        check_against_oracle(layer, X, xdt, 0.1, 0.8, None, what=f"K={K} N={N} B={B}")
+
+
+# ... and of the block's launch that reads lists: 16-byte lanes for the longer of the two
+@pytest.mark.parametrize("K,F,N", [(64, 6144, 8192), (64, 2048, 8208), (136, 4104, 1040)])
+def test_int8_blocks_of_both_lane_widths(K, F, N):
+    blk = Block(K, F, N, I8, 1310 + K, B=16)
+    for B in (5, 16):
+        X = wl.laplace(B, K, 1311 + B, BF16, loc=0.0, scale=0.5)
+        print(f"int8 block lanes {K}->{F}->{N} B={B}", flush=True)
+        blk.check_batch(X, BF16, 0.0, 0.3, None, None, 0.0, 0.004, None, what=f"{K} {F} {N} B={B}")
