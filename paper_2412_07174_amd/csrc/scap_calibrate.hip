@@ -30,9 +30,16 @@ constexpr int kHistChunks = 128;    // workgroups per half of the code space
 // equals `half` (the sign) in LDS, then adds its non-zero counters to the global histogram.  The kernel is bound
 // by instruction issue (shift, compare, masked LDS add per code), so every code is looked at by as few
 // workgroups as LDS allows: two.
+// (16-bit counters, two to a word, hold the whole code space, so that every code is looked at once; with sweeps between
+// rounds of 32768 codes against overflow that took 49 instead of 34 us on bf16 16384 x 4096 and 87 instead of 41 on fp16:
+// neighbouring codes are the frequent ones, and their adds meet on one word.)
+// COUNT: 32-bit counts and, behind them, one bit per group of 64 codes that has any (samples of less than 2^32 values whose
+// statistics are selected on the GPU), or 64-bit counts.
+template <typename COUNT>
 __global__ __launch_bounds__(kHistThreads) void code_hist_kernel(const uint16_t* __restrict__ X, int64_t M,
-                                                                unsigned long long* __restrict__ hist) {
+                                                                COUNT* __restrict__ hist) {
     extern __shared__ uint32_t sh[];  // [kHalf]
+    __shared__ uint32_t s_live[kHalf / kWave / 32];
     const int tid = threadIdx.x;
     // The two workgroups that read the same share sit on one XCD (blockIdx % 8) and start together, so the share
     // comes from HBM once and from that XCD's L2 the second time.
@@ -41,6 +48,7 @@ __global__ __launch_bounds__(kHistThreads) void code_hist_kernel(const uint16_t*
     const int chunk = xcd + 8 * (j >> 1);
     const int nchunk = gridDim.x >> 1;
     for (int i = tid; i < kHalf; i += kHistThreads) sh[i] = 0;
+    if (tid < kHalf / kWave / 32) s_live[tid] = 0;
     __syncthreads();
     auto count = [&](uint32_t code) {
         if ((code >> 15) == half) atomicAdd(&sh[code & (kHalf - 1)], 1u);
@@ -75,58 +83,50 @@ __global__ __launch_bounds__(kHistThreads) void code_hist_kernel(const uint16_t*
     __syncthreads();
     for (int i = tid; i < kHalf; i += kHistThreads) {
         const uint32_t v = sh[i];
-        if (v) atomicAdd(&hist[half * kHalf + i], (unsigned long long)v);
+        if (v) atomicAdd(&hist[half * kHalf + i], (COUNT)v);
+        if constexpr (sizeof(COUNT) == 4) {
+            const int g = i / kWave;  // wave-uniform
+            if (__ballot(v != 0) != 0 && lane_id() == 0) atomicOr(&s_live[g >> 5], 1u << (g & 31));
+        }
+    }
+    if constexpr (sizeof(COUNT) == 4) {
+        __syncthreads();
+        constexpr int WORDS = kHalf / kWave / 32;
+        if (tid < WORDS && s_live[tid] != 0) atomicOr(&hist[kCodes + half * WORDS + tid], s_live[tid]);
     }
 }
 
 // ---------------------------------------------------------------------------------------------- order statistics
 // m = median of the sample (or 0) and tau = k-th smallest |value - m| from the counts, by one workgroup (M < 2^32): each
-// selection is a radix select over LDS bins.  A first pass lists the groups of 64 codes that have counts at all (most
-// samples touch a tenth of the bf16 codes, and neighbouring ones); the others read those groups again, from L2.  The
-// loops are rolled: with the counts in registers and every loop unrolled the kernel took 56 us, waiting for its own
-// 100 KB of instructions; with 16 groups in flight 43, with 8 36.  A call with the median, us, before (the counts copied
-// to the host and walked there) / now: bf16 256 x 1024 140 / 66, 16384 x 4096 171 / 94; fp16 186 / 105 and 268 / 157.
+// selection is a radix select over LDS bins.  The groups of 64 codes that have counts at all (most samples touch a tenth
+// of the bf16 codes, and neighbouring ones) are known from the counting kernel's bits; their counts are fetched once, into
+// LDS, and every pass reads them there (groups past its room from memory).  A pass's work is shared out by runs of codes,
+// one per thread, not by groups, one per wavefront: a few instructions per code and wavefront are what one compute unit
+// spends its time on where many codes occur (fp16).  The loops are rolled: with the counts in registers and every loop
+// unrolled the kernel waited for its own 100 KB of instructions.  16384 x 4096 sample, before (every pass read 64-bit counts
+// from L2, behind one that looked for the groups) / now: bf16 35.6 / 21.7 us, fp16 98 / 61; the whole call with the median
+// 94 / 81 and 157 / 119.
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kGroups = kCodes / kWave;
 constexpr int kSelBins = 2048;
 constexpr int kSelFly = 8;  // groups in flight per wavefront
+constexpr int kSelGroups = 560;  // groups whose counts are kept in LDS (140 of gfx950's 160 KB)
 constexpr uint32_t kNoRank = 0xFFFFFFFFu;
-
-// sum over the wavefront, in every lane: within rows of 16 by DPP, the four rows by scalar adds
-__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lanes 1,0,3,2 of a quad
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lanes 2,3,0,1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // mirrored in each half row
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // mirrored in each row
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16) +
-           (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-}
 
 struct SelLds {
     uint32_t bins[kSelBins];
     uint32_t wave[kSelWaves];
     uint16_t live[kGroups];  // groups with counts, in no particular order
+    uint32_t held;           // entries of the bin where the last rank fell
     int nlive;
     uint32_t bin, rank;  // where a rank fell: its bin and the rank inside it
+    uint32_t counts[kSelGroups * kWave];  // counts of the first kSelGroups listed groups
 };
 
 __device__ __forceinline__ void sel_clear(SelLds& s) {
     for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) s.bins[i] = 0;
     __syncthreads();
-}
-
-// bins[bin] += c.  Consecutive codes often fall into one bin: then one add per wavefront instead of 64 on one word.
-__device__ __forceinline__ void sel_add(SelLds& s, uint32_t bin, uint32_t c) {
-    const uint64_t live = __ballot(c != 0);
-    if (live == 0) return;  // wave-uniform
-    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, __builtin_ctzll(live));
-    if (__ballot(c != 0 && bin != first) == 0) {
-        const uint32_t sum = wave_total(c);
-        if (lane_id() == 0) atomicAdd(&s.bins[first], sum);
-    } else if (c != 0) {
-        atomicAdd(&s.bins[bin], c);
-    }
 }
 
 // The bin that holds rank r (1-based; s.bin = kNoRank past the total) and the rank inside it.  Ends with a barrier.
@@ -143,9 +143,11 @@ __device__ __forceinline__ void sel_find(SelLds& s, uint32_t r) {
     if (r > before && r - before <= a) {
         s.bin = 2 * tid;
         s.rank = r - before;
+        s.held = a;
     } else if (r > before + a && r - before - a <= b) {
         s.bin = 2 * tid + 1;
         s.rank = r - before - a;
+        s.held = b;
     }
     __syncthreads();
 }
@@ -155,66 +157,97 @@ static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
 __device__ __forceinline__ uint32_t code_rank(uint32_t c) { return (c & 0x8000u) ? 0xFFFFu - c : 0x8000u + c; }
 __device__ __forceinline__ uint32_t rank_code(uint32_t p) { return p < 0x8000u ? 0xFFFFu - p : p - 0x8000u; }
 
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const unsigned long long* __restrict__ hist, uint32_t M, int xdt,
+__global__ __launch_bounds__(kSelThreads) void select_kernel(const uint32_t* __restrict__ hist, uint32_t M, int xdt,
                                                             int median, uint32_t k, float* __restrict__ out) {
-    __shared__ SelLds s;
+    extern __shared__ uint32_t sel_raw[];
+    SelLds& s = *reinterpret_cast<SelLds*>(sel_raw);
     const int tid = threadIdx.x, lane = lane_id();
     const int w = uniform(tid >> 6);
     const float nan = __uint_as_float(0x7FFFFFFFu);
     auto value = [&](uint32_t c) { return xdt == kBF16 ? bf16_bits_to_f32(c) : f16_bits_to_f32(c); };
-    // f(code, count) for this lane's code of each group of `n` listed ones (of all groups: n < 0); NaN codes rank behind
-    // every number and are not counted
-    auto for_groups = [&](int n, auto f) {
-        const int total = n < 0 ? kGroups : n;
-        for (int g0 = w * kSelFly; g0 < total; g0 += kSelWaves * kSelFly) {
-            uint32_t code[kSelFly], c[kSelFly];
-#pragma unroll
-            for (int u = 0; u < kSelFly; ++u) {
-                const int g = min(g0 + u, total - 1);
-                code[u] = (uint32_t)(n < 0 ? g : (int)s.live[g]) * kWave + lane;
-                c[u] = (uint32_t)hist[code[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < kSelFly; ++u) {
-                const float v = value(code[u]);
-                f(code[u], (g0 + u < total && v == v) ? c[u] : 0u);
-            }
-        }
-    };
     if (tid == 0) s.nlive = 0;
     __syncthreads();
-    for_groups(-1, [&](uint32_t code, uint32_t c) {
-        if (__ballot(c != 0) != 0 && lane == 0) s.live[atomicAdd(&s.nlive, 1)] = (uint16_t)(code / kWave);
-    });
+    {  // one bit per thread: the groups that have counts
+        const bool live = (hist[kCodes + tid / 32] >> (tid & 31)) & 1u;
+        const uint64_t bal = __ballot(live);
+        int base = 0;
+        if (lane == 0 && bal != 0) base = atomicAdd(&s.nlive, __popcll(bal));
+        base = uniform(base);
+        if (live) s.live[base + lanes_below(bal)] = (uint16_t)tid;
+    }
+    static_assert(kGroups == kSelThreads, "one group per thread");
     __syncthreads();
     const int n = s.nlive;
+    // NaN codes rank behind every number and are not counted
+    auto counted = [&](uint32_t code) {
+        const uint32_t c = hist[code];
+        const float v = value(code);
+        return v == v ? c : 0u;
+    };
+    for (int g0 = w * kSelFly; g0 < min(n, kSelGroups); g0 += kSelWaves * kSelFly) {
+        uint32_t c[kSelFly];
+#pragma unroll
+        for (int u = 0; u < kSelFly; ++u) c[u] = counted((uint32_t)s.live[min(g0 + u, n - 1)] * kWave + lane);
+#pragma unroll
+        for (int u = 0; u < kSelFly; ++u)
+            if (g0 + u < min(n, kSelGroups)) s.counts[(g0 + u) * kWave + lane] = c[u];
+    }
+    // Adds the counts of the listed groups to the bins: bin(code) of a code, kNoRank where it is not counted.  Every thread
+    // takes runs of 16 or 32 neighbouring codes, whose bins are mostly the same, and adds a run of equal bins at once.
+    // (Every pass begins with sel_clear, whose barrier also stands between the counts' fetch and their first reader.)
+    const int run = n <= kSelThreads / 4 ? 16 : 32;
+    auto add_to_bins = [&](auto bin) {
+        const int per_group = kWave / run;
+        for (int r = tid; r < n * per_group; r += kSelThreads) {
+            const int g = r / per_group, e0 = (r % per_group) * run;
+            const uint32_t c0 = (uint32_t)s.live[g] * kWave;
+            uint32_t cur = kNoRank, sum = 0;
+#pragma unroll 4
+            for (int j = 0; j < run; ++j) {
+                const int e = e0 + ((j + lane) & (run - 1));  // lanes start at different places: fewer meet on one LDS bank
+                const uint32_t c = g < kSelGroups ? s.counts[g * kWave + e] : counted(c0 + e);
+                const uint32_t b = c != 0 ? bin(c0 + e) : kNoRank;
+                if (b != cur) {
+                    if (sum != 0) atomicAdd(&s.bins[cur], sum);
+                    cur = b;
+                    sum = 0;
+                }
+                sum += b != kNoRank ? c : 0u;
+            }
+            if (sum != 0) atomicAdd(&s.bins[cur], sum);
+        }
+    };
     float m = 0.f;
     if (median) {  // the middle value, or the mean of the two middle ones; 2048 bins of 32 codes, then the 32 codes
         float mid[2];
         sel_clear(s);
-        for_groups(n, [&](uint32_t code, uint32_t c) { sel_add(s, code_rank(code) >> 5, c); });
+        add_to_bins([&](uint32_t code) { return code_rank(code) >> 5; });
         uint32_t bin[2], rank[2];
         for (int j = 0; j < 2; ++j) {
+            if (j == 1 && (M % 2 == 1 || (bin[0] != kNoRank && rank[0] < s.held))) {  // the same value, or the next in the same bin
+                bin[1] = bin[0];
+                rank[1] = rank[0] + (M % 2 == 1 ? 0u : 1u);
+                break;
+            }
             sel_find(s, (M % 2 == 1) ? M / 2 + 1 : M / 2 + (uint32_t)j);
             bin[j] = s.bin;
             rank[j] = s.rank;
         }
-        sel_clear(s);  // the codes of the first rank's bin in bins 0-31, of the second's, if another, in 32-63
-        for_groups(n, [&](uint32_t code, uint32_t c) {
-            const uint32_t p = code_rank(code), pb = p >> 5;
-            sel_add(s, (p & 31u) + (pb == bin[0] ? 0u : 32u), pb == bin[0] || pb == bin[1] ? c : 0u);
-        });
-        __syncthreads();
-        if (bin[1] != bin[0] && bin[0] != kNoRank) {  // uniform: bins 32-63 follow what bins 0-31 hold
-            uint32_t first = 0;
-            for (int i = 0; i < 32; ++i) first += s.bins[i];
-            rank[1] += first;
+        // the 32 codes of a bin: lanes 0-31 the first rank's, 32-63 the second's, in every wavefront alike
+        const uint32_t b = lane < 32 ? bin[0] : bin[1];
+        const uint32_t code = b == kNoRank ? 0u : rank_code((b << 5) | (lane & 31u));
+        uint32_t c = b == kNoRank ? 0u : hist[code];
+        if (value(code) != value(code)) c = 0u;
+        uint32_t inc = c;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const uint32_t t = (uint32_t)__shfl_up((int)inc, off, 32);
+            if ((lane & 31) >= off) inc += t;
         }
+        const uint64_t at = __ballot(inc >= (lane < 32 ? rank[0] : rank[1]) && b != kNoRank);
         for (int j = 0; j < 2; ++j) {
-            mid[j] = nan;
-            if (bin[j] == kNoRank) continue;  // uniform
-            sel_find(s, rank[j]);
-            mid[j] = value(rank_code((bin[j] << 5) | (s.bin & 31u)));
+            const uint32_t half = (uint32_t)(at >> (32 * j));
+            mid[j] = half == 0u ? nan : value(rank_code((bin[j] << 5) | (uint32_t)__builtin_ctz(half)));
         }
         m = (M % 2 == 1) ? mid[0] : (float)(((double)mid[0] + (double)mid[1]) / 2.0);
     }
@@ -228,11 +261,11 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const unsigned long
             for (int pass = 0; pass < 3 && found; ++pass) {
                 const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
                 sel_clear(s);
-                for_groups(n, [&](uint32_t code, uint32_t c) {
+                add_to_bins([&](uint32_t code) {
                     const float d = fabsf(value(code) - m);
                     const uint32_t key = __float_as_uint(d);
-                    const bool in = d == d && (pass == 0 || (key >> (shift + 10)) == prefix);
-                    sel_add(s, pass == 0 ? key >> 20 : (key >> shift) & 1023u, in ? c : 0u);
+                    if (!(d == d && (pass == 0 || (key >> (shift + 10)) == prefix))) return kNoRank;
+                    return pass == 0 ? key >> 20 : (key >> shift) & 1023u;
                 });
                 sel_find(s, rank);
                 found = s.bin != kNoRank;
@@ -410,33 +443,46 @@ float histogram_mode(const Table& t, int64_t M) {
     return (float)centre;
 }
 
+// More dynamic LDS than the default limit for `kernel`: asked for once per device.
+constexpr int kMaxDevices = 64;
+int allow_lds(std::atomic<bool> (&asked)[kMaxDevices], const void* kernel, int bytes) {
+    int dev = 0;
+    if (!ok(hipGetDevice(&dev)) || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
+    if (!asked[dev].load(std::memory_order_acquire)) {
+        if (!ok(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes))) return SCAP_ERR_HIP;
+        asked[dev].store(true, std::memory_order_release);
+    }
+    return SCAP_OK;
+}
+
+// Counts of every code of the sample into `hist`, `words` 32-bit words of which are cleared first.
+template <typename COUNT>
+int count_codes(const uint16_t* X, int64_t M, COUNT* hist, size_t words, hipStream_t stream) {
+    int rc = launch_zero_words(reinterpret_cast<int32_t*>(hist), words, stream);
+    if (rc != SCAP_OK) return rc;
+    static std::atomic<bool> asked[kMaxDevices];
+    rc = allow_lds(asked, reinterpret_cast<const void*>(&code_hist_kernel<COUNT>), kHalf * 4);
+    if (rc != SCAP_OK) return rc;
+    hipLaunchKernelGGL(code_hist_kernel<COUNT>, dim3(2 * kHistChunks), dim3(kHistThreads), kHalf * 4, stream, X, M, hist);
+    return ok(hipGetLastError()) ? SCAP_OK : SCAP_ERR_HIP;
+}
+
 }  // namespace
 
 int run_calibrate(const uint16_t* X, int64_t M, int xdt, float s, int est, float* m_out, float* tau_out, void* workspace,
                   hipStream_t stream) {
     if (est < SCAP_MODE_ZERO || est > SCAP_MODE_HIST) return SCAP_ERR_DTYPE;
-    unsigned long long* d_hist = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + kOffCodeHist);
-    int rc = launch_zero_words(reinterpret_cast<int32_t*>(d_hist), 2 * (size_t)kCodes, stream);
-    if (rc != SCAP_OK) return rc;
-    {
-        // 128 KB of dynamic LDS: above the default limit, asked for once per device
-        constexpr int kMaxDevices = 64;
-        static std::atomic<bool> asked[kMaxDevices];
-        int dev = 0;
-        if (!ok(hipGetDevice(&dev)) || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
-        if (!asked[dev].load(std::memory_order_acquire)) {
-            if (!ok(hipFuncSetAttribute(reinterpret_cast<const void*>(&code_hist_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, kHalf * 4)))
-                return SCAP_ERR_HIP;
-            asked[dev].store(true, std::memory_order_release);
-        }
-    }
-    hipLaunchKernelGGL(code_hist_kernel, dim3(2 * kHistChunks), dim3(kHistThreads), kHalf * 4, stream, X, M, d_hist);
-    if (!ok(hipGetLastError())) return SCAP_ERR_HIP;
     const int64_t k = quantile_rank((double)s, M);
+    void* counts = static_cast<char*>(workspace) + kOffCodeHist;
     if ((est == SCAP_MODE_ZERO || est == SCAP_MODE_MEDIAN) && M < ((int64_t)1 << 32)) {
+        uint32_t* d_hist = static_cast<uint32_t*>(counts);
+        int rc = count_codes<uint32_t>(X, M, d_hist, kCodes + kGroups / 32, stream);
+        if (rc != SCAP_OK) return rc;
+        static std::atomic<bool> asked[kMaxDevices];
+        rc = allow_lds(asked, reinterpret_cast<const void*>(&select_kernel), (int)sizeof(SelLds));
+        if (rc != SCAP_OK) return rc;
         float* d_out = reinterpret_cast<float*>(static_cast<char*>(workspace) + kOffSelected);
-        hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kSelThreads), 0, stream, d_hist, (uint32_t)M, xdt,
+        hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kSelThreads), sizeof(SelLds), stream, d_hist, (uint32_t)M, xdt,
                            est == SCAP_MODE_MEDIAN ? 1 : 0, (uint32_t)k, d_out);
         float got[2];
         if (!ok(hipGetLastError()) || !ok(hipMemcpyAsync(got, d_out, sizeof(got), hipMemcpyDeviceToHost, stream)) ||
@@ -446,6 +492,9 @@ int run_calibrate(const uint16_t* X, int64_t M, int xdt, float s, int est, float
         *tau_out = got[1];
         return SCAP_OK;
     }
+    unsigned long long* d_hist = static_cast<unsigned long long*>(counts);
+    const int rc = count_codes<unsigned long long>(X, M, d_hist, 2 * (size_t)kCodes, stream);
+    if (rc != SCAP_OK) return rc;
     std::vector<unsigned long long> hist(kCodes);
     if (!ok(hipMemcpyAsync(hist.data(), d_hist, sizeof(unsigned long long) * kCodes, hipMemcpyDeviceToHost, stream)))
         return SCAP_ERR_HIP;
