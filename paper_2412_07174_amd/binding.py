@@ -119,8 +119,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()   # ctypes makes a pointer of it (argtypes)
 
 
+# The handle of the current stream without a stream object: 2.7 -> 0.4 us of every call (1024 x 4096 fp16 in a Python loop
+# 12.2 -> 10.4)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
