@@ -101,8 +101,9 @@ typedef struct {
                                 of adding them as fixed-point integers with one atomic per column (both are
                                 bit-reproducible; they differ in the last bits of y).  Bit 0 implies it;
                                 bit 4 (SCAP_CFG_PARK_SLICES, scap_swiglu_block_ex only, for tests): the first launch
-                                of a one-token block gates every slice by the way a slice takes when its columns were
-                                finished by more than one wavefront (through memory) */
+                                of a one-token block, or of a two-token block over int8 weights, gates every slice by
+                                the way a slice takes when its columns were finished by more than one wavefront
+                                (through memory) */
 } scap_launch_cfg;
 #define SCAP_CFG_DEVICE_SCOPE_LOADS 1
 #define SCAP_CFG_GENERAL_KERNEL 2
@@ -265,7 +266,7 @@ int scap_swiglu_block(const void* W_gu, const void* gu_scale, const void* W_down
                       void* stream);
 
 /* Same as scap_swiglu_block with launch flags for its one-token form (cfg may be NULL): of cfg only the flags
- * SCAP_CFG_PARTIAL_SUMS and SCAP_CFG_PARK_SLICES (B == 1) and SCAP_CFG_GENERAL_KERNEL (B <= 4: both launches on the
+ * SCAP_CFG_PARTIAL_SUMS (B == 1), SCAP_CFG_PARK_SLICES (B <= 2) and SCAP_CFG_GENERAL_KERNEL (B <= 4: both launches on the
  * general kernels instead of the one-token kernel and its two- and four-slot forms) are read.  For tests and measurements. */
 int scap_swiglu_block_ex(const void* W_gu, const void* gu_scale, const void* W_down, const void* down_scale, int64_t K,
                          int64_t F, int64_t N, int wdt, const void* x, int xdt, int64_t B, float m_x, float tau_x,

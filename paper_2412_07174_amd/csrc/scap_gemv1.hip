@@ -90,9 +90,10 @@ int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int wav
 // bt = token slots: 1 (one-token kernel), 2 or 4 (its multi-token forms, 8 wavefronts).
 // wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
 // must: no other kernel does what the call asks for (y += result)
+// lanes8: int8 weights in 8-byte lanes whatever the columns
 int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out,
-               bool wide_lanes = false, bool must = false) {
-    const bool half = wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols);
+               bool wide_lanes = false, bool must = false, bool lanes8 = false) {
+    const bool half = lanes8 || (wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols));
     const int rc = plan_gemv1_lanes(g, wdt, kc, kc_forced, waves, granule_min, bt, half, true, out);
     if (rc != kG1NotApplicable) return rc;
     // Long inputs and very wide layers for which fewer, longer pieces than the kernel tests look best: the split that fills
@@ -236,34 +237,38 @@ int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& dn, int wdt, int up
     return launch_block_half<kFuseList>(b, wdt, pd.i8_half, stream);
 }
 
-// Fused SwiGLU block of two tokens (down launch: up to four): each of its launches can run on the multi-slot kernel, in the list format of the
-// batched block kernels (64-channel segments, 2 token slots), so either can be paired with the general kernel's.
-//   part 0, the gate|up launch with the gating epilogue: int8 weights in 16-byte lanes (2F > 4096; a wavefront's
-//           slice is then 128 columns = one segment);
+// Fused SwiGLU block of two tokens (down launch: up to four) on the multi-slot kernel.
+//   part 0, the gate|up launch with the gating epilogue: int8 weights.  It leaves one list segment per wavefront slice:
+//           64 channels in 16-byte lanes -- the format of the batched block kernels, so each launch can be paired with the
+//           general kernel's other half --, 32 channels with packed counts in 8-byte lanes (lanes8), which only this
+//           kernel's down launch reads (launch_swiglu_block2_pair);
 //   part 1, the down launch reading the lists: any weights, unless 16-bit and too wide for the fixed-point hand-over
 //           (with partial sums handed over the general kernel's down launch measured 0.5 us faster).
 // Measured on 4096 -> 14336 -> 4096, two tokens, both launches general / these (us): int8 45.8 / 41.9 with nothing
 // pruned, 38.0 / 34.5 at 50 %, 21.8 / 19.6 at 90 %; bf16 (down launch only) 65.3 / 64.3, 55.9 / 54.7, 25.9 / 24.8.
-// Returns SCAP_OK and fills *g, or kG1NotApplicable.
-static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, Gemv1bArgs* g, bool* i8_half) {
+// Fills *g and returns SCAP_OK, or kG1NotApplicable.
+static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, bool lanes8, int flags, Gemv1bArgs* g,
+                            bool* i8_half) {
     // 3-4 tokens: the down launch only, 16-bit weights, on the four-slot form (the lists then carry 4 token slots)
     const bool four = (up.B == 3 || up.B == 4) && part == 1 && wdt != kI8;
     if (up.B != 2 && !four) return kG1NotApplicable;
     const GemvArgs& src = part == 0 ? up : dn;
     if (part == 0 && wdt != kI8) return kG1NotApplicable;
-    if (part == 1 && wdt != kI8 && (int64_t)up.B * (int64_t)src.N > (int64_t)kFxCols) return kG1NotApplicable;
+    const bool fits_fx = (int64_t)up.B * (int64_t)src.N <= (int64_t)kFxCols;
+    if (part == 1 && wdt != kI8 && !fits_fx) return kG1NotApplicable;
     Plan1 pl;
-    // whole 64-channel pieces: whole segments
-    const int rc = plan_gemv1(src, wdt, 0, false, kG1bWaves, kWave, four ? 4 : 2, &pl, part == 0);
+    // the down launch: whole 64-channel pieces, i.e. whole segments
+    const int rc = plan_gemv1(src, wdt, 0, false, kG1bWaves, part == 0 && lanes8 ? 8 : kWave, four ? 4 : 2, &pl, part == 0, false, part == 0 && lanes8);
     if (rc != SCAP_OK) return kG1NotApplicable;
-    if (four && pl.Kc > 2 * kG1Chunk) return kG1NotApplicable;  // (its prologue holds every entry slot in registers)
-    if (part == 0 && pl.i8_half) return kG1NotApplicable;
+    if (part == 1 && four && pl.Kc > 2 * kG1Chunk) return kG1NotApplicable;  // (its prologue holds every entry slot in registers)
     if (part == 1 && (pl.Kc % kWave) != 0) return kG1NotApplicable;
     g->B = (int)up.B;
     g->bt = four ? 4 : 2;
-    g->a = args_of(src, pl, 0);
-    if (part == 0 || (size_t)up.B * (size_t)src.N > (size_t)kFxCols) g->a.fx_acc = nullptr;
-    if (four && g->a.fx_acc == nullptr) return kG1NotApplicable;  // four slots: fixed-point hand-over only
+    g->a = args_of(src, pl, flags);
+    if (!fits_fx || (part == 0 && !pl.i8_half)) g->a.fx_acc = nullptr;
+    // the gating epilogue parks finished columns behind the partial-sum slots when a slice is finished piecemeal
+    if (part == 0 && (size_t)(pl.S + 1) * pl.T * pl.tile > partial_capacity(src.N)) g->a.fx_acc = nullptr;
+    if (four && g->a.fx_acc == nullptr) return kG1NotApplicable;
     g->a.m2 = up.m2;
     g->a.tau2 = up.tau2;
     g->a.zl_idx = up.zl_idx;
@@ -281,24 +286,50 @@ static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int
     return SCAP_OK;
 }
 
-bool swiglu_block2_part_applies(const GemvArgs& up, const GemvArgs& dn, int wdt, int part) {
-    Gemv1bArgs g;
-    bool half = false;
-    return plan_block2_part(up, dn, wdt, part, &g, &half) == SCAP_OK;
-}
-
-int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, hipStream_t stream) {
-    Gemv1bArgs g;
-    bool half = false;
-    const int rc = plan_block2_part(up, dn, wdt, part, &g, &half);
-    if (rc != SCAP_OK) return rc;
-    const int fuse = part == 0 ? kFuseSwiglu : kFuseList;
+static int launch_block2(const Gemv1bArgs& g, int wdt, bool half, int fuse, hipStream_t stream) {
     switch (wdt) {
         case kF16: return launch_gemv1b_block_wdt<kF16>(g, fuse, stream);
         case kBF16: return launch_gemv1b_block_wdt<kBF16>(g, fuse, stream);
         case kI8: return half ? launch_gemv1b_block_wdt<kI8Half>(g, fuse, stream) : launch_gemv1b_block_wdt<kI8>(g, fuse, stream);
     }
     return SCAP_ERR_DTYPE;
+}
+
+// One of the launches in the batched block kernels' list format.
+static int plan_block2_64(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, int flags, Gemv1bArgs* g, bool* half) {
+    const int rc = plan_block2_part(up, dn, wdt, part, false, flags, g, half);
+    if (rc != SCAP_OK) return rc;
+    return part == 0 && *half ? kG1NotApplicable : SCAP_OK;
+}
+
+bool swiglu_block2_part_applies(const GemvArgs& up, const GemvArgs& dn, int wdt, int part) {
+    Gemv1bArgs g;
+    bool half = false;
+    return plan_block2_64(up, dn, wdt, part, 0, &g, &half) == SCAP_OK;
+}
+
+int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, int flags, hipStream_t stream) {
+    Gemv1bArgs g;
+    bool half = false;
+    const int rc = plan_block2_64(up, dn, wdt, part, part == 0 ? flags & kG1FlagParkSlices : 0, &g, &half);
+    if (rc != SCAP_OK) return rc;
+    return launch_block2(g, wdt, half, part == 0 ? kFuseSwiglu : kFuseList, stream);
+}
+
+// Both launches, lists of 32-channel segments between them; kG1NotApplicable where either does not run here so.  8-byte
+// lanes have one column per lane and slice, so the gate|up launch hands over in fixed point, and small blocks have tiles
+// enough (2F <= 4096 ran on the general kernel).  us, two tokens, before / now (40 / 70 % and 80 / 80 %): 4096 -> 2048 ->
+// 4096 23.7 / 18.2 and 22.1 / 16.4, 2048 -> 8192 -> 2048 22.3 / 20.7 and 20.0 / 18.5, 8192 -> 16384 -> 8192 72.7 / 69.2 and
+// 45.3 / 43.6, 4096 -> 14336 -> 4096 37.0 / 37.1 and 27.6 / 26.8, 4096 -> 11008 -> 4096 32.4 / 32.9 and 25.0 / 24.6.
+int launch_swiglu_block2_pair(const GemvArgs& up, const GemvArgs& dn, int wdt, int flags, hipStream_t stream) {
+    Gemv1bArgs gu, gd;
+    bool hu = false, hd = false;
+    if (plan_block2_part(up, dn, wdt, 0, true, flags & kG1FlagParkSlices, &gu, &hu) != SCAP_OK || !hu || gu.a.fx_acc == nullptr ||
+        plan_block2_part(up, dn, wdt, 1, true, 0, &gd, &hd) != SCAP_OK)
+        return kG1NotApplicable;
+    const int rc = launch_block2(gu, wdt, hu, kFuseSwiglu, stream);
+    if (rc != SCAP_OK) return rc;
+    return launch_block2(gd, wdt, hd, kFuseList32, stream);
 }
 
 }  // namespace scap

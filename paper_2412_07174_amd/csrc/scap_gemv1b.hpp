@@ -4,10 +4,11 @@
 // workgroup's inputs and keeps every 8th union position, the ring of row loads, one barrier and the slice-wise
 // reduction, the split-K hand-over (fixed point by default, else ticketed partial sums per (tile, slice)) -- with BT
 // token slots.  Wavefront b of a tile-0 workgroup writes token b's ascending list; the last of its writers closes it.
-// FUSE gives it the two halves of the fused SwiGLU block (Alg. 2) in the list format of the batched block kernels
-// (scap_gemv_parts.hpp, "list input"): kFuseSwiglu (2 slots) -- the wavefront that finishes a (tile, slice) of the
-// gate|up launch gates it (16-byte int8 lanes only: its slice is 128 columns = one 64-channel list segment) --, and
-// kFuseList (2 or 4 slots) -- the down launch takes its channels and centred values from those segments instead of x.
+// FUSE gives it the two halves of the fused SwiGLU block (Alg. 2): kFuseSwiglu (2 slots, int8) -- the wavefront that
+// finishes a (tile, slice) of the gate|up launch gates it and leaves one list segment: 64 channels from 16-byte lanes, in
+// the list format of the batched block kernels (scap_gemv_parts.hpp, "list input"), 32 channels with the counts packed
+// into one word from 8-byte lanes --; kFuseList (2 or 4 slots) and kFuseList32 (2) -- the down launch takes its channels
+// and centred values from those segments instead of x.
 // BT = 2 token slots, and 4 (3-4 tokens) for 16-bit weights and for plain calls with int8 weights in 8-byte lanes.
 // With the partial-sum hand-over the kernel's fixed part grows with the token slots -- the last arrival of a tile
 // pulls S x BT partial slices through one compute unit's L1 (14336 x 4096 bf16: 0.9 us for one token, 2.1 for two,
@@ -80,8 +81,10 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     constexpr int CPL = ELEMS / WAVES;  // columns per lane of a wavefront's slice
     constexpr int SLICE = kWave * CPL;
     static_assert(CPL == 1 || CPL == 2, "a slice is 4 or 8 bytes per lane");
-    static_assert(BT == 2 || (BT == 4 && FUSE != kFuseSwiglu), "two token slots; four without the gating epilogue");
-    static_assert(FUSE != kFuseSwiglu || CPL == 2, "the gating epilogue needs a slice of 128 columns: one 64-channel list segment");
+    static_assert(BT == 2 || (BT == 4 && FUSE != kFuseSwiglu && FUSE != kFuseList32), "two token slots; four without the gating epilogue");
+    constexpr bool LIST = FUSE == kFuseList || FUSE == kFuseList32;
+    // channels of a list segment: what a wavefront's slice of the gate|up launch holds, 32 or 64
+    constexpr int SEGZ = FUSE == kFuseSwiglu ? SLICE / 2 : (FUSE == kFuseList32 ? 32 : 64);
     typedef SliceVec<CPL> slice_t;
 
     extern __shared__ uint4 smem_raw[];
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
 
     // ------------------------------------------------------------------ 1. inputs: every wavefront, all Kc, all tokens
     uint4 xv[BT][NCH];
-    if constexpr (FUSE != kFuseList) {
+    if constexpr (!LIST) {
         auto load_inputs = [&](auto octet) {
 #pragma unroll
             for (int b = 0; b < BT; ++b) {
@@ -129,6 +132,10 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     // lanes and keeps a lane's columns adjacent.
     constexpr int CSTR = FUSE == kFuseSwiglu ? 1 : kWave;
     constexpr int LSTR = FUSE == kFuseSwiglu ? CPL : 1;
+    // The gating epilogue behind two columns per lane (16-byte int8 lanes) hands partial sums over: in fixed point a lane's
+    // second atomic per token waits behind its first (block 4096 -> 14336 -> 4096, 80 %: 27.5 us with partial sums, 28.3 with
+    // lanes side by side and fixed point; 4096 -> 11008 -> 4096 25.0 and 26.3).
+    constexpr bool FIXED = FUSE != kFuseSwiglu || CPL == 1;
     const int fcol = tile * TILE + w * SLICE + lane * LSTR;
     float cbias[CPL], cscale[CPL];
 #pragma unroll
@@ -146,15 +153,26 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     const uint32_t keep_all = mode == kModeSparse ? 0u : 1u;
     int cnt = 0;   // union positions so far -- wave-uniform
     int lcnt = 0;  // kept channels of token w so far (tile 0, w < B)
-    if constexpr (FUSE == kFuseList) {
-        // The workgroup's channels are Kc / 64 list segments of the gated product (K = F here; Kc is a multiple of
+    if constexpr (LIST) {
+        // The workgroup's channels are Kc / SEGZ list segments of the gated product (K = F here; Kc is a multiple of
         // 64).  Every entry slot of those segments and their counts are fetched together, whatever the counts will
         // say (one memory round trip; slots past a segment's count hold stale entries and are dropped below); lane l
         // takes the count of segment l, a prefix sum gives every entry its position in the workgroup's list.
-        constexpr int ITS = 8 * NCH;  // Kc / 64 segments at most
-        const int seg0 = k0 >> 6;
-        const int nsegw = (kend - k0 + kWave - 1) >> 6;
-        const int nsegs = (K + kWave - 1) >> 6;
+        constexpr int ITS = 8 * NCH;  // Kc / 64 fetches of 64 entries at most
+        constexpr int PER = kWave / SEGZ;  // segments per fetch
+        const int sub = lane / SEGZ, r = lane % SEGZ;
+        const int seg0 = k0 / SEGZ;
+        const int nsegw = (kend - k0 + SEGZ - 1) / SEGZ;  // at most 64
+        const int nsegs = (K + SEGZ - 1) / SEGZ;
+        // entries of a segment, and those of token b; 32-channel segments: the bytes of one word
+        auto entries = [&](int sg) {
+            const int c = SEGZ == 64 ? zl_cnt[sg] : zl_cnt[sg] & 255;
+            return min(max(c, 0), SEGZ);  // keeps LDS writes in range whatever the memory holds
+        };
+        auto entries_of = [&](int b, int sg) {
+            const int c = SEGZ == 64 ? zl_cnt[(1 + b) * nsegs + sg] : (zl_cnt[sg] >> (8 * (1 + b))) & 255;
+            return min(max(c, 0), SEGZ);
+        };
         int eidx[ITS];
         float ed[ITS][BT];
 #pragma unroll
@@ -162,8 +180,8 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             eidx[it] = 0;
 #pragma unroll
             for (int b = 0; b < BT; ++b) ed[it][b] = 0.f;
-            if (it < nsegw) {
-                const int64_t e = (int64_t)(seg0 + it) * kWave + lane;
+            if (it * PER + sub < nsegw) {
+                const int64_t e = (int64_t)(seg0 + it * PER + sub) * SEGZ + r;
                 eidx[it] = zl_idx[e];
                 typedef float dvec_t __attribute__((ext_vector_type(BT)));
                 const dvec_t dv = *reinterpret_cast<const dvec_t*>(zl_d + e * BT);
@@ -171,16 +189,16 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
                 for (int b = 0; b < BT; ++b) ed[it][b] = dv[b];
             }
         }
-        int c_l = lane < nsegw ? zl_cnt[seg0 + lane] : 0;
-        c_l = min(max(c_l, 0), (int)kWave);  // keeps LDS writes in range whatever the memory holds
+        const int c_l = lane < nsegw ? entries(seg0 + lane) : 0;
         const int inc = wave_inclusive_scan(c_l);
         const int off_l = inc - c_l;
         cnt = __shfl(inc, kWave - 1, kWave);
         int pos[ITS];
 #pragma unroll
         for (int it = 0; it < ITS; ++it) {
-            const int c_s = __shfl(c_l, it, kWave), o_s = __shfl(off_l, it, kWave);
-            pos[it] = (it < nsegw && lane < c_s) ? o_s + lane : -1;
+            const int sg = it * PER + sub;
+            const int c_s = __shfl(c_l, sg & 63, kWave), o_s = __shfl(off_l, sg & 63, kWave);
+            pos[it] = (sg < nsegw && r < c_s) ? o_s + r : -1;
         }
 #pragma unroll
         for (int it = 0; it < ITS; ++it)
@@ -192,7 +210,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             int before = 0;
             for (int s0 = 0; s0 < seg0; s0 += kWave) {
                 const int sg = s0 + lane;
-                before += sg < seg0 ? min(max(zl_cnt[(1 + w) * nsegs + sg], 0), (int)kWave) : 0;
+                before += sg < seg0 ? entries_of(w, sg) : 0;
             }
             before = wave_sum(before);
             int run = 0;
@@ -366,7 +384,71 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
         }
     }
 
-    // the finished slice of both tokens: scaled (int8), fused bias added (Eq. 6); y written through to memory, or gated
+    // Gating epilogue: `p` = the finished columns of the slice (scaled, bias added).
+    // Columns come in groups of 8: 4 gate pre-activations, then the 4 matching up pre-activations; a lane holds CPL adjacent
+    // ones, so the lanes that hold a group's gate columns fetch their up partners from LPG / 2 lanes further on.
+    // z = silu(gate) * up (Alg. 2), centred and thresholded like any layer input (Alg. 3 steps 1-2, strict compare of
+    // Eq. 2; each token its own mask); the slice's channels kept by any token become one list segment, ascending, the tokens'
+    // centred values side by side (0 where a token pruned the channel), with the union's and the tokens' counts.
+    auto gate = [&](const float (&p)[BT][CPL]) {
+        constexpr int LPG = 8 / CPL;  // lanes per group of 8 columns
+        const bool gate_lane = (lane % LPG) < LPG / 2;
+        float dz[BT][CPL];
+        bool keep[BT][CPL], any[CPL];
+        int chan[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const int col = fcol + c;
+            chan[c] = (col >> 3) * 4 + (col & 3);
+            const bool live = gate_lane && col < N && chan[c] < F;
+            any[c] = false;
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const float up = __shfl_down(p[b][c], LPG / 2, kWave);
+                const float z = p[b][c] / (1.f + expf(-p[b][c])) * up;
+                if (live && b < B && z_out) store_dev(&z_out[(int64_t)b * F + chan[c]], z);
+                const float d = z - m2;  // one fp32 subtraction
+                keep[b][c] = live && b < B && fabsf(d) > tau2;  // strict; NaN is pruned
+                dz[b][c] = keep[b][c] ? d : 0.f;
+                any[c] |= keep[b][c];
+            }
+        }
+        const int seg = tile * WAVES + w;  // this slice's segment: channels seg * SEGZ ...
+        const int nsegs = (F + SEGZ - 1) / SEGZ;
+        if ((int64_t)seg * SEGZ < F) {  // wave-uniform
+            int rank = 0, total_kept = 0;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                const uint64_t bal = __ballot(any[c]);
+                rank += lanes_below(bal);
+                total_kept += __popcll(bal);
+            }
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                if (any[c]) {
+                    const int64_t e = (int64_t)seg * SEGZ + rank;
+                    store_dev(&zl_idx[e], chan[c]);
+                    store_dev(reinterpret_cast<unsigned long long*>(zl_d + e * BT),
+                              (unsigned long long)__float_as_uint(dz[0][c]) | ((unsigned long long)__float_as_uint(dz[1][c]) << 32));
+                    ++rank;  // the lane's own earlier column comes first
+                }
+            }
+            int packed = total_kept;  // 32-channel segments: the counts as bytes of one word
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                int kept_b = 0;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) kept_b += __popcll(__ballot(keep[b][c]));
+                if (SEGZ == 64) {
+                    if (lane == 0 && b < B) store_dev(&zl_cnt[(1 + b) * nsegs + seg], kept_b);
+                } else {
+                    packed |= kept_b << (8 * (1 + b));
+                }
+            }
+            if (lane == 0) store_dev(&zl_cnt[seg], SEGZ == 64 ? total_kept : packed);
+        }
+    };
+    // the finished slice of all tokens: scaled (int8), fused bias added (Eq. 6); y written through to memory, or gated
     auto finish = [&](const slice_t* s) {
         float p[BT][CPL];
 #pragma unroll
@@ -380,63 +462,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
                 for (int c = 0; c < CPL; ++c)
                     if (b < B && fcol + c * CSTR < N) store_dev(&y[(size_t)b * N + fcol + c * CSTR], p[b][c]);
         } else {
-            // Columns come in groups of 8: 4 gate pre-activations, then the 4 matching up pre-activations; a lane holds
-            // 2 adjacent columns, so lanes 0-1 of every 4 hold a group's gate columns and fetch their up partners from
-            // 2 lanes further on.  z = silu(gate) * up (Alg. 2), centred and thresholded like any layer input (Alg. 3
-            // steps 1-2, strict compare of Eq. 2; each token its own mask); the slice's channels kept by either token
-            // become one 64-channel list segment, ascending, the tokens' centred values side by side (0 where a token
-            // pruned the channel), with the union's and the tokens' counts.
-            constexpr int LPG = 8 / CPL;
-            const bool gate_lane = (lane % LPG) < LPG / 2;
-            float dz[BT][CPL];
-            bool keep[BT][CPL], any[CPL];
-            int chan[CPL];
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const int col = fcol + c;
-                chan[c] = (col >> 3) * 4 + (col & 3);
-                const bool live = gate_lane && col < N && chan[c] < F;
-                any[c] = false;
-#pragma unroll
-                for (int b = 0; b < BT; ++b) {
-                    const float up = __shfl_down(p[b][c], LPG / 2, kWave);
-                    const float z = p[b][c] / (1.f + expf(-p[b][c])) * up;
-                    if (live && b < B && z_out) store_dev(&z_out[(int64_t)b * F + chan[c]], z);
-                    const float d = z - m2;  // one fp32 subtraction
-                    keep[b][c] = live && b < B && fabsf(d) > tau2;  // strict; NaN is pruned
-                    dz[b][c] = keep[b][c] ? d : 0.f;
-                    any[c] |= keep[b][c];
-                }
-            }
-            const int seg = tile * WAVES + w;  // this slice's segment: channels seg * 64 ...
-            const int nsegs = (F + kWave - 1) >> 6;
-            if ((int64_t)seg * kWave < F) {  // wave-uniform
-                int rank = 0, total_kept = 0;
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    const uint64_t bal = __ballot(any[c]);
-                    rank += lanes_below(bal);
-                    total_kept += __popcll(bal);
-                }
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    if (any[c]) {
-                        const int64_t e = (int64_t)seg * kWave + rank;
-                        store_dev(&zl_idx[e], chan[c]);
-                        store_dev(reinterpret_cast<unsigned long long*>(zl_d + e * BT),
-                                  (unsigned long long)__float_as_uint(dz[0][c]) | ((unsigned long long)__float_as_uint(dz[1][c]) << 32));
-                        ++rank;  // the lane's own earlier column comes first
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < BT; ++b) {
-                    int kept_b = 0;
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) kept_b += __popcll(__ballot(keep[b][c]));
-                    if (lane == 0 && b < B) store_dev(&zl_cnt[(1 + b) * nsegs + seg], kept_b);
-                }
-                if (lane == 0) store_dev(&zl_cnt[seg], total_kept);
-            }
+            gate(p);
         }
     };
     if (S == 1) {
@@ -449,7 +475,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     // partial, rounded to 2^-frac and biased, and a 1 in the arrival count with ONE atomic; whoever completes a
     // column's count holds its sum, converts it once, applies scale and bias and stores y.  What cannot
     // travel so (fx_escapes; each token's slice by itself) goes as fp32 through its partial-sum slot and the column's escape mask.
-    if constexpr (FUSE != kFuseSwiglu) {
+    if constexpr (FIXED) {
         if (fx_acc != nullptr) {
             const int limit_bits = fx_limit_bits(S);
             const int frac = limit_bits - fx_range_bits(IS_I8);
@@ -528,10 +554,53 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
             for (int b = 0; b < BT; ++b)
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
+                    if (FUSE == kFuseSwiglu) yv[b][c] = done[b][c] ? (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c] : 0.f;
                     if (__builtin_expect(!done[b][c], 0)) continue;
-                    store_dev(&y[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
+                    if (FUSE != kFuseSwiglu) store_dev(&y[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
                     store_dev(&fx_acc[word(b, c)], 0ull);  // zero at rest
                 }
+            if constexpr (FUSE == kFuseSwiglu) {
+                // As in the one-token kernel: a slice whose columns this wavefront finished for every token is gated from
+                // registers; otherwise finished columns are parked in memory and counted on the slice's ticket, and whoever
+                // completes the count fetches the slice and gates it.
+                const int live_cols = min(max(N - (tile * TILE + w * SLICE), 0), SLICE);  // columns of this slice that exist
+                if (live_cols == 0) return;
+                bool all_done = true, any_done = false;
+                int n_done = 0;
+#pragma unroll
+                for (int b = 0; b < BT; ++b)
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        if (b < B && fcol + c * CSTR < N) all_done &= done[b][c];
+                        any_done |= done[b][c];
+                        n_done += done[b][c] ? 1 : 0;
+                    }
+                if (__ballot(!all_done) == 0ull && !(flags & kG1FlagParkSlices)) {
+                    gate(yv);
+                    return;
+                }
+                if (__ballot(any_done) == 0ull) return;
+                float* park = partial + (size_t)S * T * B * TILE;  // behind the partial-sum slots (room checked on the host)
+                auto place = [&](int b, int c) { return park + (size_t)b * T * TILE + fcol + c * CSTR; };
+#pragma unroll
+                for (int b = 0; b < BT; ++b)
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c)
+                        if (done[b][c]) store_dev(place(b, c), yv[b][c]);
+                wait_memory_ops();
+                n_done = wave_sum(n_done);
+                unsigned long long* st = reinterpret_cast<unsigned long long*>(counters + tile * kCounterStride + w * kG1TicketWords);
+                unsigned long long got = 0;
+                if (lane == 0) got = __hip_atomic_fetch_add(st, (unsigned long long)n_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + (unsigned long long)n_done;
+                if (__builtin_amdgcn_readfirstlane((int)(uint32_t)got) != live_cols * B) return;
+                if (lane == 0) store_dev(st, 0ull);
+#pragma unroll
+                for (int b = 0; b < BT; ++b)
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) yv[b][c] = b < B && fcol + c * CSTR < N ? load_dev(place(b, c)) : 0.f;
+                gate(yv);
+                return;
+            }
             if (!want_lists || S == 1) return;
             // token w's list (tile 0, wavefront w < B) still needs the last of its writers to close the gaps: they
             // stored their pieces and counts before taking this ticket
@@ -648,7 +717,7 @@ static int launch_gemv1b_one(const Gemv1bArgs& g, size_t lds, hipStream_t stream
     hipLaunchKernelGGL((gemv1b_kernel<WDT, NCH, BT, FUSE>), grid, block, lds, stream, a.x, a.W, a.K, a.N, a.Kc, a.S, a.T, g.B,
                        a.mode, a.xdt, a.m, a.tau, a.flags, a.bias, a.y, a.partial, a.counters, a.col_scale, a.idx_out,
                        a.nnz_out, a.union_nnz_out, a.seg_cnt, a.m2, a.tau2, a.z_out, a.zl_idx, a.zl_d, a.zl_cnt, a.F,
-                       FUSE == kFuseSwiglu ? nullptr : a.fx_acc);
+                       a.fx_acc);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
@@ -674,17 +743,18 @@ int launch_gemv1b_wdt(const Gemv1bArgs& g, hipStream_t stream) {
     return SCAP_ERR_CONFIG;
 }
 
-// the launches of the fused block of two tokens (fuse: kFuseSwiglu -- 16-byte int8 lanes only -- or kFuseList), and
+// the launches of the fused block of two tokens (kFuseSwiglu, and the list of its 8-byte slices kFuseList32: int8 weights) and
 // the down launch of a 16-bit block of 3-4 tokens (kFuseList, four slots)
 template <int WDT>
 int launch_gemv1b_block_wdt(const Gemv1bArgs& g, int fuse, hipStream_t stream) {
-    if constexpr (WDT == kF16 || WDT == kBF16) {  // four slots: the down launch of a 16-bit block of 3-4 tokens
+    if constexpr (WDT == kF16 || WDT == kBF16) {
         if (g.bt == 4 && fuse == kFuseList) return launch_gemv1b_nch<WDT, 4, kFuseList>(g, stream);
     }
     if (g.bt != 2) return SCAP_ERR_CONFIG;
     if (fuse == kFuseList) return launch_gemv1b_nch<WDT, 2, kFuseList>(g, stream);
-    if constexpr (WDT == kI8) {
+    if constexpr (is_int8(WDT)) {
         if (fuse == kFuseSwiglu) return launch_gemv1b_nch<WDT, 2, kFuseSwiglu>(g, stream);
+        if (fuse == kFuseList32) return launch_gemv1b_nch<WDT, 2, kFuseList32>(g, stream);
     }
     return SCAP_ERR_CONFIG;
 }

@@ -32,6 +32,10 @@ template <int WDT, int BT>
 static int launch_block(GemvArgs up, GemvArgs dn, int wdt, int flags, hipStream_t stream) {
     const GemvArgs up_in = up, dn_in = dn;
     const bool two = (BT == 2 || BT == 4) && up.B >= 2 && !(flags & SCAP_CFG_GENERAL_KERNEL);
+    if (two) {
+        const int rc = launch_swiglu_block2_pair(up_in, dn_in, wdt, flags, stream);
+        if (rc != kG1NotApplicable) return rc;
+    }
     const bool up_two = two && swiglu_block2_part_applies(up_in, dn_in, wdt, 0);
     const bool dn_two = two && swiglu_block2_part_applies(up_in, dn_in, wdt, 1);
     constexpr int TILE = kWave * Vec<WDT>::kElems;
@@ -60,13 +64,13 @@ static int launch_block(GemvArgs up, GemvArgs dn, int wdt, int flags, hipStream_
     if (lds_up > 64 * 1024 || lds_dn > 64 * 1024) return SCAP_ERR_SHAPE;
 
     if (up_two) {
-        rc = launch_swiglu_block2_part(up_in, dn_in, wdt, 0, stream);
+        rc = launch_swiglu_block2_part(up_in, dn_in, wdt, 0, flags, stream);
         if (rc != SCAP_OK) return rc;
     } else {
         hipLaunchKernelGGL((swiglu_up_kernel<WDT, BT>), dim3((unsigned)(up.S * up.T)), dim3(NT), lds_up, stream, up);
         if (hipGetLastError() != hipSuccess) return SCAP_ERR_HIP;
     }
-    if (dn_two) return launch_swiglu_block2_part(up_in, dn_in, wdt, 1, stream);
+    if (dn_two) return launch_swiglu_block2_part(up_in, dn_in, wdt, 1, flags, stream);
     if (half) {
         hipLaunchKernelGGL((swiglu_down_kernel<WDT, BT, kWave / 2>), dim3((unsigned)(dn.S * dn.T)), dim3(NT), lds_dn,
                            stream, dn);

@@ -327,3 +327,32 @@ def test_int8_blocks_of_both_lane_widths(K, F, N):
         X = wl.laplace(B, K, 1311 + B, BF16, loc=0.0, scale=0.5)
         print(f"int8 block lanes {K}->{F}->{N} B={B}", flush=True)
         blk.check_batch(X, BF16, 0.0, 0.3, None, None, 0.0, 0.004, None, what=f"{K} {F} {N} B={B}")
+
+
+# the two-token block over int8 weights on 8-byte lanes: list segments of 32 channels, the gate|up launch in fixed point.
+# The last segment cut, fewer channels than one, one tile and many; slices gated from registers and through memory (the same
+# bits); sums that escape the fixed point (gate and up weights times 2^12 over large inputs)
+@pytest.mark.parametrize("K,F,N", [(256, 8, 16), (300, 72, 144), (1000, 2056, 1040), (520, 4104, 2064), (136, 16416, 528), (2000, 1032, 4112)])
+def test_int8_blocks_of_two_tokens(K, F, N):
+    for std, loc in ((0.05, 0.1), (0.05 * 2.0 ** 12, 30.0)):
+        blk = Block(K, F, N, I8, 1400 + K, std=std, B=2)
+        X = wl.laplace(2, K, 1401 + K, BF16, loc=loc, scale=5 * loc)
+        for tau_x, tau_z in ((0.0, 0.0), (5 * loc, 0.02), (1e9, 0.0)):
+            if std > 1 and tau_x != 5 * loc:
+                continue
+            print(f"int8 block of two {K}->{F}->{N} std={std} tau_x={tau_x} tau_z={tau_z}", flush=True)
+            args = (X, BF16, loc, tau_x, None, None, 0.01, tau_z, None)
+            got = blk.run_batch(*args) if std > 1 else blk.check_batch(*args, what=f"{K} {F} {N} {tau_x} {tau_z}")
+            for other in (blk.run_batch(*args), blk.run_batch(*args, cfg=(0, 0, 0, 0, scap.CFG_PARK_SLICES))):
+                for b in range(2):
+                    assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
+                    assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
+            if std > 1:  # both sides are far beyond the fixed point's range; z against double precision
+                f = lambda w, s: w.astype(np.float64) * wl.decode(s, F16).astype(np.float64)
+                d = (wl.decode(X, BF16).astype(np.float32) - np.float32(loc))
+                d = np.where(np.abs(d) > np.float32(tau_x), d, np.float32(0)).astype(np.float64)
+                g, u = d @ f(blk.Wg, blk.sg), d @ f(blk.Wu, blk.su)
+                with np.errstate(over="ignore"):
+                    z = g / (1 + np.exp(-g)) * u
+                for b in range(2):
+                    assert _rel(got[b]["z"], z[b]) <= 2e-6, (K, F, N, b, _rel(got[b]["z"], z[b]))
