@@ -55,7 +55,7 @@ int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int wav
     out->tile = kWave * out->elems;
     GemvArgs p = g;
     // LDS: header, the wavefronts' sums, then 8 bytes per listed channel (16 with 2 token slots)
-    const int entry = bt == 1 ? 8 : (bt == 2 ? 16 : 32);
+    const int entry = bt == 1 ? 8 : g1b_entry_bytes(bt);
     const int64_t fixed_lds = bt == 1 ? (int64_t)waves * out->tile * 4 + 64 + kG1HdrBytes
                                       : (int64_t)bt * kG1HdrBytes + (int64_t)kG1bWaves * bt * out->tile * 4 + (int64_t)kG1bWaves * 4 * entry;
     const int64_t lds_max = bt == 1 ? 64 * 1024 : kG1bMaxLds;
@@ -87,7 +87,7 @@ int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int wav
 }
 
 // K split and lane width of one launch.  SCAP_OK, kG1NotApplicable or a scap_status.
-// bt = token slots: 1 (one-token kernel), 2 or 4 (its multi-token forms, 8 wavefronts).
+// bt = token slots: 1 (one-token kernel), 2, 3 or 4 (its multi-token forms, 8 wavefronts).
 // wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
 // must: no other kernel does what the call asks for (y += result)
 // lanes8: int8 weights in 8-byte lanes whatever the columns
@@ -166,7 +166,7 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
     return SCAP_ERR_DTYPE;
 }
 
-// Two tokens, or three to four (int8 weights: in 8-byte lanes only), through the two- /
+// Two to four tokens (three and four over int8 weights: in 8-byte lanes only), through the two-, three- or
 // four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, more than 2048
 // channels per workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
 int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
@@ -176,14 +176,15 @@ int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
 
     Gemv1bArgs b;
     b.B = g.B;
-    b.bt = g.B == 2 ? 2 : 4;
+    b.bt = (int)g.B;
     Plan1 pl;
     const int rc = plan_gemv1(g, wdt, 0, false, kG1bWaves, 8, b.bt, &pl);
     if (rc != SCAP_OK) return rc;
+    if (wdt == kI8 && b.bt > 2 && !pl.i8_half) return kG1NotApplicable;  // 16-byte lanes: two slots only
     b.a = args_of(g, pl, flags);
     if ((size_t)g.B * (size_t)g.N > (size_t)kFxCols) b.a.fx_acc = nullptr;  // one fixed-point word per (token, column)
-    // with four slots the partial-sum hand-over loses to the other kernels (its last arrivals fetch 4 S slices)
-    if (b.bt == 4 && b.a.fx_acc == nullptr) return kG1NotApplicable;
+    // with more slots the partial-sum hand-over loses to the other kernels (its last arrivals fetch 4 S slices)
+    if (b.bt > 2 && b.a.fx_acc == nullptr) return kG1NotApplicable;
     switch (wdt) {
         case kF16: return launch_gemv1b_wdt<kF16>(b, stream);
         case kBF16: return launch_gemv1b_wdt<kBF16>(b, stream);

@@ -9,10 +9,13 @@
 // the list format of the batched block kernels (scap_gemv_parts.hpp, "list input"), 32 channels with the counts packed
 // into one word from 8-byte lanes --; kFuseList (2 or 4 slots) and kFuseList32 (2) -- the down launch takes its channels
 // and centred values from those segments instead of x.
-// BT = 2 token slots, and 4 (3-4 tokens) for 16-bit weights and for plain calls with int8 weights in 8-byte lanes.
+// BT = 2 token slots, and 3 and 4 for 16-bit weights and for plain calls with int8 weights in 8-byte lanes.
 // With the partial-sum hand-over the kernel's fixed part grows with the token slots -- the last arrival of a tile
 // pulls S x BT partial slices through one compute unit's L1 (14336 x 4096 bf16: 0.9 us for one token, 2.1 for two,
-// 3.8 for four); the fixed-point hand-over has nothing to pull, and four slots run with it only.
+// 3.8 for four); the fixed-point hand-over has nothing to pull, and three and four slots run with it only.
+// Three slots: a list entry of 16 instead of 32 bytes and a quarter of the tests, FMAs, sums and atomics less than the
+// four-slot form that ran three tokens before (us at 60 %, four / three slots: bf16 1024 x 4096 9.1 / 8.3, 5461 x 2752 11.8 /
+// 11.1, 14336 x 4096 21.7 / 21.1; int8 4096 x 11008 16.6 / 14.5).
 #pragma once
 
 #include <atomic>
@@ -40,6 +43,21 @@ template <> struct G1bList<2> {
         d[1] = __int_as_float(t.z);
     }
 };
+template <> struct G1bList<3> {
+    int4* e;
+    static constexpr int kBytes = 16;
+    __device__ __forceinline__ G1bList(char* base, int w, int slots) : e(reinterpret_cast<int4*>(base) + w * slots) {}
+    __device__ __forceinline__ void put(int p, int idx, const float* d) const {
+        e[p] = make_int4(idx, __float_as_int(d[0]), __float_as_int(d[1]), __float_as_int(d[2]));
+    }
+    __device__ __forceinline__ void get(int p, int& idx, float* d) const {
+        const int4 t = e[p];
+        idx = t.x;
+        d[0] = __int_as_float(t.y);
+        d[1] = __int_as_float(t.z);
+        d[2] = __int_as_float(t.w);
+    }
+};
 template <> struct G1bList<4> {  // two 16-byte halves per entry
     int4* e;
     static constexpr int kBytes = 32;
@@ -60,8 +78,9 @@ template <> struct G1bList<4> {  // two 16-byte halves per entry
 // list slots per wavefront: a multiple of 4, so that the 16-byte parts of the lists stay aligned
 __host__ __device__ inline int g1b_slots(int Kc) { return (Kc / kG1bWaves + 4) & ~3; }
 
+__host__ __device__ constexpr int g1b_entry_bytes(int bt) { return bt == 4 ? 32 : 16; }
 inline size_t gemv1b_lds_bytes(int tile_cols, int Kc, int bt) {
-    return (size_t)kG1HdrBytes * bt + (size_t)kG1bWaves * bt * tile_cols * 4 + (size_t)kG1bWaves * g1b_slots(Kc) * (bt == 2 ? 16 : 32);
+    return (size_t)kG1HdrBytes * bt + (size_t)kG1bWaves * bt * tile_cols * 4 + (size_t)kG1bWaves * g1b_slots(Kc) * g1b_entry_bytes(bt);
 }
 
 template <int WDT, int NCH, int BT, int FUSE = kFusePlain>
@@ -81,7 +100,8 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     constexpr int CPL = ELEMS / WAVES;  // columns per lane of a wavefront's slice
     constexpr int SLICE = kWave * CPL;
     static_assert(CPL == 1 || CPL == 2, "a slice is 4 or 8 bytes per lane");
-    static_assert(BT == 2 || (BT == 4 && FUSE != kFuseSwiglu && FUSE != kFuseList32), "two token slots; four without the gating epilogue");
+    static_assert(BT == 2 || (BT == 3 && FUSE == kFusePlain) || (BT == 4 && FUSE != kFuseSwiglu && FUSE != kFuseList32),
+                  "two token slots; four without the gating epilogue, three without lists");
     constexpr bool LIST = FUSE == kFuseList || FUSE == kFuseList32;
     // channels of a list segment: what a wavefront's slice of the gate|up launch holds, 32 or 64
     constexpr int SEGZ = FUSE == kFuseSwiglu ? SLICE / 2 : (FUSE == kFuseList32 ? 32 : 64);
@@ -98,7 +118,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     float* s_red = reinterpret_cast<float*>(smem + BT * kG1HdrBytes);  // [WAVES][BT][TILE]
     const int slots = g1b_slots(Kc);
     const G1bList<BT> mylist(smem + BT * kG1HdrBytes + WAVES * BT * TILE * 4, w, slots);
-    static_assert(G1bList<BT>::kBytes == (BT == 2 ? 16 : 32), "entry size assumed by gemv1b_lds_bytes");
+    static_assert(G1bList<BT>::kBytes == g1b_entry_bytes(BT), "entry size assumed by gemv1b_lds_bytes");
 
     const int tile = blockIdx.x % T;
     const int split = blockIdx.x / T;
@@ -623,71 +643,75 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     }
 
     // ------------------------------------------------------------------ 4. split-K hand-over per (tile, slice)
-    // partials [S][T][B][TILE]: as in the one-token kernel, B slices per arrival
-    const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(partial, (uint32_t)S * T * B * TILE * 4u);
-    const uint32_t pstride = (uint32_t)T * B * TILE * 4u;  // bytes between consecutive splits
-    const uint32_t pmine = (uint32_t)((tile * B * TILE + w * SLICE + lane * CPL) * 4);
-    const uint32_t ptok = (uint32_t)TILE * 4u;  // bytes between consecutive tokens
+    // Two slots.  (Three and four hand over in fixed point only, as the host has checked; what the compiler makes of the
+    // four-slot kernel without this code behind it is 1 % slower.)
+    if constexpr (BT != 3) {
+        // partials [S][T][B][TILE]: as in the one-token kernel, B slices per arrival
+        const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(partial, (uint32_t)S * T * B * TILE * 4u);
+        const uint32_t pstride = (uint32_t)T * B * TILE * 4u;  // bytes between consecutive splits
+        const uint32_t pmine = (uint32_t)((tile * B * TILE + w * SLICE + lane * CPL) * 4);
+        const uint32_t ptok = (uint32_t)TILE * 4u;  // bytes between consecutive tokens
 #pragma unroll
-    for (int b = 0; b < BT; ++b)
-        if (b < B) sum[b].store_coherent(pbuf, split * pstride + pmine + b * ptok);
-    wait_memory_ops();  // the wavefront's stores have been acknowledged
-    unsigned long long* ticket = reinterpret_cast<unsigned long long*>(counters + tile * kCounterStride + w * kG1TicketWords);
-    unsigned long long seen = 0;
-    if (lane == 0)
-        seen = __hip_atomic_fetch_add(ticket, ticket_increment(xcc_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-               ticket_increment(xcc_id());
-    const uint32_t seen_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seen);
-    const uint32_t seen_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seen >> 32));
-    seen = ((unsigned long long)seen_hi << 32) | seen_lo;
-    if ((int)(seen & 0xFFFFull) != S) return;  // not the last arrival of this slice
+        for (int b = 0; b < BT; ++b)
+            if (b < B) sum[b].store_coherent(pbuf, split * pstride + pmine + b * ptok);
+        wait_memory_ops();  // the wavefront's stores have been acknowledged
+        unsigned long long* ticket = reinterpret_cast<unsigned long long*>(counters + tile * kCounterStride + w * kG1TicketWords);
+        unsigned long long seen = 0;
+        if (lane == 0)
+            seen = __hip_atomic_fetch_add(ticket, ticket_increment(xcc_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                   ticket_increment(xcc_id());
+        const uint32_t seen_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seen);
+        const uint32_t seen_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seen >> 32));
+        seen = ((unsigned long long)seen_hi << 32) | seen_lo;
+        if ((int)(seen & 0xFFFFull) != S) return;  // not the last arrival of this slice
 
-    const bool near = ticket_all_one_xcd(seen) && !(flags & kG1FlagDeviceScope);
-    if (near) asm volatile("buffer_inv sc0" ::: "memory");  // this compute unit's vector L1 holds nothing older
-    constexpr int FLY = CPL == 1 ? 32 : 16;  // partial loads in flight per token, two tokens at a time
+        const bool near = ticket_all_one_xcd(seen) && !(flags & kG1FlagDeviceScope);
+        if (near) asm volatile("buffer_inv sc0" ::: "memory");  // this compute unit's vector L1 holds nothing older
+        constexpr int FLY = CPL == 1 ? 32 : 16;  // partial loads in flight per token
 #pragma unroll
-    for (int b0 = 0; b0 < BT; b0 += 2) {
-        if (b0 >= B) break;
-        slice_t total[2];
+        for (int b0 = 0; b0 < BT; b0 += 2) {
+            if (b0 >= B) break;
+            slice_t total[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) total[t].v[c] = 0.f;
-        for (int sp0 = 0; sp0 < S; sp0 += FLY) {
-            slice_t v[2][FLY];
+                for (int c = 0; c < CPL; ++c) total[t].v[c] = 0.f;
+            for (int sp0 = 0; sp0 < S; sp0 += FLY) {
+                slice_t v[2][FLY];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const uint32_t tok = (uint32_t)min(b0 + t, B - 1) * ptok;  // a slot past the last token re-reads it
-                if (near) {
+                for (int t = 0; t < 2; ++t) {
+                    const uint32_t tok = (uint32_t)min(b0 + t, B - 1) * ptok;  // a slot past the last token re-reads it
+                    if (near) {
 #pragma unroll
-                    for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_plain(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
-                } else {
+                        for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_plain(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
+                    } else {
 #pragma unroll
-                    for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_coherent(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
+                        for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_coherent(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                    for (int j = 0; j < FLY; ++j) {
+                        const bool in = sp0 + j < S;  // a slot past the last split re-read it: not added
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) total[t].v[c] += in ? v[t][j].v[c] : 0.f;
+                    }
                 }
             }
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                for (int j = 0; j < FLY; ++j) {
-                    const bool in = sp0 + j < S;  // a slot past the last split re-read it: not added
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) total[t].v[c] += in ? v[t][j].v[c] : 0.f;
-                }
-            }
+            finish(total);
         }
-        finish(total);
-    }
-    if (lane == 0) store_dev(ticket, 0ull);  // ready for the next call
-    if (want_lists) {
-        // token w's lists of all splits are complete: their writers stored them before taking this slice's ticket
-        const int run = close_list_rows(seg_cnt + (1 + w) * kMaxSplits, idx_out ? idx_out + (int64_t)w * K : nullptr, S, K, Kc, s_off, s_cnt);
-        if (lane == 0 && nnz_out) nnz_out[w] = run;
-        if (w == 0 && union_nnz_out) {
-            int u = 0;
-            for (int s0 = 0; s0 < S; s0 += kWave) u += s0 + lane < S ? load_dev(&seg_cnt[s0 + lane]) : 0;
-            u = wave_sum(u);
-            if (lane == 0) union_nnz_out[0] = u;
+        if (lane == 0) store_dev(ticket, 0ull);  // ready for the next call
+        if (want_lists) {
+            // token w's lists of all splits are complete: their writers stored them before taking this slice's ticket
+            const int run = close_list_rows(seg_cnt + (1 + w) * kMaxSplits, idx_out ? idx_out + (int64_t)w * K : nullptr, S, K, Kc, s_off, s_cnt);
+            if (lane == 0 && nnz_out) nnz_out[w] = run;
+            if (w == 0 && union_nnz_out) {
+                int u = 0;
+                for (int s0 = 0; s0 < S; s0 += kWave) u += s0 + lane < S ? load_dev(&seg_cnt[s0 + lane]) : 0;
+                u = wave_sum(u);
+                if (lane == 0) union_nnz_out[0] = u;
+            }
         }
     }
 }
@@ -735,9 +759,10 @@ static int launch_gemv1b_nch(const Gemv1bArgs& g, hipStream_t stream) {
 template <int WDT>
 int launch_gemv1b_wdt(const Gemv1bArgs& g, hipStream_t stream) {
     if (g.bt == 2) return launch_gemv1b_nch<WDT, 2, kFusePlain>(g, stream);
-    // four slots: 16-bit weights and int8 in 8-byte lanes (with 16-byte int8 lanes the wavefronts' sums of four tokens
+    // three and four slots: 16-bit weights and int8 in 8-byte lanes (with 16-byte int8 lanes the wavefronts' sums of four tokens
     // do not fit LDS; those batches go to the matrix cores)
     if constexpr (WDT == kF16 || WDT == kBF16 || WDT == kI8Half) {
+        if (g.bt == 3) return launch_gemv1b_nch<WDT, 3, kFusePlain>(g, stream);
         if (g.bt == 4) return launch_gemv1b_nch<WDT, 4, kFusePlain>(g, stream);
     }
     return SCAP_ERR_CONFIG;
