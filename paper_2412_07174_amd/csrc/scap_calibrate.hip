@@ -425,7 +425,8 @@ float histogram_mode(const Table& t, int64_t M) {
         const float v = t.val[i];
         if (v < lo || v > hi) continue;
         const double pos = std::floor(((double)v - (double)lo) / width);
-        const int bin = pos >= (double)kHistBins ? kHistBins - 1 : (int)pos;
+        // an infinite order statistic makes the width infinite and positions 0 or NaN: those values count in bin 0
+        const int bin = !(pos > 0.0) ? 0 : (pos >= (double)kHistBins ? kHistBins - 1 : (int)pos);
         upto[bin + 1] += t.cnt[i];
     }
     for (int b = 0; b < kHistBins; ++b) upto[b + 1] += upto[b];

@@ -356,3 +356,24 @@ def test_int8_blocks_of_two_tokens(K, F, N):
                     z = g / (1 + np.exp(-g)) * u
                 for b in range(2):
                     assert _rel(got[b]["z"], z[b]) <= 2e-6, (K, F, N, b, _rel(got[b]["z"], z[b]))
+
+
+# the histogram estimator where the range it bins is infinite: every finite value counts in bin 0 and the estimate is the
+# centre of an infinitely wide bin (lo + inf), or NaN where the lower end is -inf; a few infinities beyond the 0.1 % that the
+# range leaves out change nothing about it
+@pytest.mark.parametrize("dt", [F16, BF16])
+def test_histogram_mode_of_a_sample_with_infinities(dt):
+    inf, neg = (0x7C00, 0xFC00) if dt == F16 else (0x7F80, 0xFF80)
+    base = wl.laplace(1, 4000, 1500 + dt, dt, loc=0.1, scale=0.5)
+    ws = scap.Workspace(4000, 0, 1)
+    for at, want in (({inf: 40}, (np.inf, np.inf)), ({neg: 40}, (np.nan, np.nan)), ({inf: 40, neg: 40}, (np.nan, np.nan)),
+                     ({inf: 4000}, (np.inf, np.nan)), ({inf: 2, neg: 2}, None)):
+        X, p = base.copy(), 0
+        for code, n in at.items():
+            X[0, p:p + n] = code
+            p += n
+        print(f"hist with infinities dt={dt} {at}", flush=True)
+        got = scap.calibrate(to_dev(X, dt), 0.5, scap.MODE_HIST, workspace=ws)
+        assert np.array_equal(got, oracle.calibrate(X, dt, 0.5, oracle.MODE_HIST), equal_nan=True), (at, got)
+        assert want is None or np.array_equal(got, want, equal_nan=True), (at, got)
+        assert want is not None or np.isfinite(got).all()
