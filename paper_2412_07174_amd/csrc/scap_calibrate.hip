@@ -100,18 +100,20 @@ __global__ __launch_bounds__(kHistThreads) void code_hist_kernel(const uint16_t*
 // m = median of the sample (or 0) and tau = k-th smallest |value - m| from the counts, by one workgroup (M < 2^32): each
 // selection is a radix select over LDS bins.  The groups of 64 codes that have counts at all (most samples touch a tenth
 // of the bf16 codes, and neighbouring ones) are known from the counting kernel's bits; their counts are fetched once, into
-// LDS, and every pass reads them there (groups past its room from memory).  A pass's work is shared out by runs of codes,
-// one per thread, not by groups, one per wavefront: a few instructions per code and wavefront are what one compute unit
-// spends its time on where many codes occur (fp16).  The loops are rolled: with the counts in registers and every loop
-// unrolled the kernel waited for its own 100 KB of instructions.  16384 x 4096 sample, before (every pass read 64-bit counts
-// from L2, behind one that looked for the groups) / now: bf16 35.6 / 21.7 us, fp16 98 / 61; the whole call with the median
-// 94 / 81 and 157 / 119.
+// LDS, and every pass reads them there.  A pass's work is shared out by runs of codes, one per thread, not by groups, one
+// per wavefront: a few instructions per code and wavefront are what one compute unit spends its time on where many codes
+// occur (fp16).  The groups past the LDS room are read from memory, a wavefront per group and eight in flight; taken as runs
+// they were a second round of 32 loads in a row for few threads (a whole call over fp16, us, runs / this: 3 x 333 with 586
+// groups, ZERO, 81.3 / 65.4; 64 x 1024 with almost all, ZERO 99.8 / 87.2, MEDIAN 117.8 / 99.6).  The loops are rolled: with the
+// counts in registers and every loop unrolled the kernel waited for its own 100 KB of instructions.  16384 x 4096 sample,
+// before (every pass read 64-bit counts from L2, behind one that looked for the groups) / now: bf16 35.6 / 21.7 us, fp16
+// 98 / 61; the whole call with the median 94 / 81 and 157 / 119.
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kGroups = kCodes / kWave;
 constexpr int kSelBins = 2048;
 constexpr int kSelFly = 8;  // groups in flight per wavefront
-constexpr int kSelGroups = 560;  // groups whose counts are kept in LDS (140 of gfx950's 160 KB)
+constexpr int kSelGroups = 512;  // groups whose counts are kept in LDS: as many as make one run of 32 codes per thread
 constexpr uint32_t kNoRank = 0xFFFFFFFFu;
 
 struct SelLds {
@@ -123,6 +125,15 @@ struct SelLds {
     uint32_t bin, rank;  // where a rank fell: its bin and the rank inside it
     uint32_t counts[kSelGroups * kWave];  // counts of the first kSelGroups listed groups
 };
+
+// sum over each row of 16 lanes, in every lane
+__device__ __forceinline__ uint32_t row_total(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lanes 1,0,3,2 of a quad
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lanes 2,3,0,1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // mirrored in each half row
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // mirrored in each row
+    return v;
+}
 
 __device__ __forceinline__ void sel_clear(SelLds& s) {
     for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) s.bins[i] = 0;
@@ -198,14 +209,14 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const uint32_t* __r
     const int run = n <= kSelThreads / 4 ? 16 : 32;
     auto add_to_bins = [&](auto bin) {
         const int per_group = kWave / run;
-        for (int r = tid; r < n * per_group; r += kSelThreads) {
+        for (int r = tid; r < min(n, kSelGroups) * per_group; r += kSelThreads) {
             const int g = r / per_group, e0 = (r % per_group) * run;
             const uint32_t c0 = (uint32_t)s.live[g] * kWave;
             uint32_t cur = kNoRank, sum = 0;
 #pragma unroll 4
             for (int j = 0; j < run; ++j) {
                 const int e = e0 + ((j + lane) & (run - 1));  // lanes start at different places: fewer meet on one LDS bank
-                const uint32_t c = g < kSelGroups ? s.counts[g * kWave + e] : counted(c0 + e);
+                const uint32_t c = s.counts[g * kWave + e];
                 const uint32_t b = c != 0 ? bin(c0 + e) : kNoRank;
                 if (b != cur) {
                     if (sum != 0) atomicAdd(&s.bins[cur], sum);
@@ -215,6 +226,26 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const uint32_t* __r
                 sum += b != kNoRank ? c : 0u;
             }
             if (sum != 0) atomicAdd(&s.bins[cur], sum);
+        }
+        // the others: one code per lane
+        for (int g0 = kSelGroups + w * kSelFly; g0 < n; g0 += kSelWaves * kSelFly) {
+            uint32_t code[kSelFly], c[kSelFly];
+#pragma unroll
+            for (int u = 0; u < kSelFly; ++u) {
+                code[u] = (uint32_t)s.live[min(g0 + u, n - 1)] * kWave + lane;
+                c[u] = counted(code[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kSelFly; ++u) {
+                const uint32_t b = bin(code[u]);
+                const uint32_t k = g0 + u < n && b != kNoRank ? c[u] : 0u;
+                if (__ballot(b != (uint32_t)__shfl((int)b, lane & ~15, kWave)) == 0) {  // one bin per row of 16 lanes: one add
+                    const uint32_t sum = row_total(k);
+                    if ((lane & 15) == 0 && sum != 0) atomicAdd(&s.bins[b], sum);
+                } else if (k != 0) {
+                    atomicAdd(&s.bins[b], k);
+                }
+            }
         }
     };
     float m = 0.f;

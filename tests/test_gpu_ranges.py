@@ -377,3 +377,19 @@ def test_histogram_mode_of_a_sample_with_infinities(dt):
         assert np.array_equal(got, oracle.calibrate(X, dt, 0.5, oracle.MODE_HIST), equal_nan=True), (at, got)
         assert want is None or np.array_equal(got, want, equal_nan=True), (at, got)
         assert want is not None or np.isfinite(got).all()
+
+
+# the selection's groups of 64 codes: runs of 16 and of 32 codes, the last group whose counts LDS holds and the first that is
+# read from memory, all of them
+@pytest.mark.parametrize("groups", [1, 255, 256, 257, 511, 512, 513, 640, 1024])
+def test_calibrate_selects_among_any_number_of_groups(groups):
+    rng = np.random.default_rng(1600 + groups)
+    for dt in (F16, BF16):
+        X = np.repeat(rng.permutation(1024)[:groups].astype(np.uint16) * 64, 7)
+        X = (X + rng.integers(0, 64, X.size).astype(np.uint16))[None]
+        ws = scap.Workspace(X.shape[1], 0, 1)
+        for est, oest in ((scap.MODE_ZERO, oracle.MODE_ZERO), (scap.MODE_MEDIAN, oracle.MODE_MEDIAN)):
+            for s in (0.02, 0.5, 0.97):
+                print(f"groups={groups} dt={dt} est={est} s={s}", flush=True)
+                got = scap.calibrate(to_dev(X, dt), s, est, workspace=ws)
+                assert np.array_equal(got, oracle.calibrate(X, dt, s, oest), equal_nan=True), (groups, dt, est, s, got)
