@@ -148,8 +148,12 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // Not over an input length that is not a multiple of 8: int8 weights keep the 4-slot lists beyond 2048 channels (4
     // tokens at 70 %, lists / here: 1023 x 28672 14.9 / 11.0, 2047 x 28672 18.5 / 17.4, 4097 x 20480 21.7 / 23.9, 8193 x 16384
     // 27.9 / 30.0), and bf16 calls that the four-slot kernel does not take the general vector kernel with its fp32 operands.
-    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 && (a.K % 8 == 0 || (wdt == kI8 && a.K <= 2048)) &&
-        (wdt == kI8 || (wdt == kBF16 && (int64_t)a.K >= 2 * (int64_t)a.N))) {
+    // A call that names its rows per workgroup keeps the lists in wide layers (N > 4 K) and over odd lengths: they take up to 4096
+    // rows where this kernel's LDS holds 2368.
+    const bool by_16 = wdt == kI8 ? (a.K % 8 == 0 && (int64_t)a.N <= 4 * (int64_t)a.K) ||
+                                        (!(cfg && cfg->rows_per_group) && (a.K % 8 == 0 || a.K <= 2048))
+                                  : wdt == kBF16 && a.K % 8 == 0 && (int64_t)a.K >= 2 * (int64_t)a.N;
+    if (mfma_ok && lanes == 0 && a.B >= 3 && a.B <= 4 && by_16) {
         const int rc = launch_gemm_inline(a, wdt, cfg, stream, true);
         if (rc != SCAP_ERR_SHAPE) return rc;
     }

@@ -393,3 +393,20 @@ def test_calibrate_selects_among_any_number_of_groups(groups):
                 print(f"groups={groups} dt={dt} est={est} s={s}", flush=True)
                 got = scap.calibrate(to_dev(X, dt), s, est, workspace=ws)
                 assert np.array_equal(got, oracle.calibrate(X, dt, s, oest), equal_nan=True), (groups, dt, est, s, got)
+
+
+# int8, 3-4 tokens, a call that names its rows per workgroup: up to 4096 of them in wide layers and over odd lengths, whose
+# lists have room for as many; beyond that, and past 2368 where the staged tile runs, the call is refused
+@pytest.mark.parametrize("K,N,rows,ok", [(1024, 8192, 4096, True), (3000, 12288, 2432, True), (4160, 17408, 4096, True),
+                                         (1023, 1040, 2432, True), (2047, 4112, 4096, True), (1024, 8192, 4160, False),
+                                         (1024, 8192, 64, True), (2048, 8192, 2432, False), (2048, 8192, 2368, True)])
+def test_int8_rows_per_group_of_three_and_four_tokens(K, N, rows, ok):
+    layer, xdt = _layer(K, N, I8, 1700 + K + rows)
+    for B in (3, 4):
+        X = wl.laplace(B, K, 1701 + K, xdt, loc=0.1, scale=0.5)
+        print(f"int8 rows K={K} N={N} rows={rows} B={B}", flush=True)
+        if ok:
+            check_against_oracle(layer, X, xdt, 0.1, 0.8, None, cfg=(0, rows, 0, 0), what=f"K={K} N={N} rows={rows} B={B}")
+        else:
+            with pytest.raises(scap.ScapError, match="status -9"):
+                gpu_sparse_fc(layer, X, xdt, 0.1, 0.8, None, cfg=(0, rows, 0, 0))
