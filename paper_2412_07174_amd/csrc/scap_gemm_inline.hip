@@ -100,7 +100,10 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 
     // Three stages per wavefront: list entries of block n+2 come out of LDS while the weight rows of block
     // n+1 are in flight and the MFMAs of block n run.  A slot past the end of the list reads LDS at a clamped position
-    // and no weights.  The loop stops issuing with the last block (see the staged-tile kernel: TAIL).
+    // and no weights.  16 slots: the loop stops issuing with the last block (see the staged-tile kernel: TAIL).  4 slots: it
+    // issues one stage past it, for that loop's second copy of the multiply takes int8 weights from 127 to 183 registers, i.e.
+    // to one workgroup per compute unit instead of two (us, that loop / this: 4097 x 17408 int8, 3 tokens, 22.6 / 21.3, 9001 x
+    // 9600 24.2 / 22.8, blocks 4096 -> 11008 -> 4096 48.7 / 40.2 and 1024 -> 20480 -> 1024 40.5 / 32.1).
     struct Entries {
         int4 rows;
         float4 d;
@@ -135,7 +138,24 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
         mfma_block<WDT>(acc, a_hi, a_lo, st.r);
     };
 
-    if (w < n_blocks) {
+    if constexpr (BT <= 4) {
+        Entries E0, E1;
+        Stage A, Bs;
+        entries(w, E0);
+        entries(w + WAVES, E1);
+        issue(E0, A);
+        for (int blk = w; blk < n_blocks;) {
+            entries(blk + 2 * WAVES, E0);
+            issue(E1, Bs);
+            compute(A);
+            blk += WAVES;
+            if (blk >= n_blocks) break;
+            entries(blk + 2 * WAVES, E1);
+            issue(E0, A);
+            compute(Bs);
+            blk += WAVES;
+        }
+    } else if (w < n_blocks) {
         Entries E;
         Stage A, Bs;
         entries(w, E);
