@@ -101,9 +101,9 @@ typedef struct {
                                 of adding them as fixed-point integers with one atomic per column (both are
                                 bit-reproducible; they differ in the last bits of y).  Bit 0 implies it;
                                 bit 4 (SCAP_CFG_PARK_SLICES, scap_swiglu_block_ex only, for tests): the first launch
-                                of a one-token block, or of a two-token block over int8 weights, gates every slice by
-                                the way a slice takes when its columns were finished by more than one wavefront
-                                (through memory) */
+                                of a one-token block, or of a two-token block over int8 weights in 8-byte lanes,
+                                gates every slice by the way a slice takes when its columns were finished by more
+                                than one wavefront (through memory) */
 } scap_launch_cfg;
 #define SCAP_CFG_DEVICE_SCOPE_LOADS 1
 #define SCAP_CFG_GENERAL_KERNEL 2

@@ -90,7 +90,7 @@ int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int wav
 // bt = token slots: 1 (one-token kernel), 2, 3 or 4 (its multi-token forms, 8 wavefronts).
 // wide_lanes: int8 weights in 16-byte lanes wherever there are more than 4 tiles of them
 // must: no other kernel does what the call asks for (y += result)
-// lanes8: int8 weights in 8-byte lanes whatever the columns
+// lanes8: int8 weights in 8-byte lanes whatever the columns, in the second plan too
 int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, int granule_min, int bt, Plan1* out,
                bool wide_lanes = false, bool must = false, bool lanes8 = false) {
     const bool half = lanes8 || (wdt == kI8 && g.N <= (wide_lanes ? kI8WideCols : kI8HalfCols));
@@ -101,7 +101,7 @@ int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, in
     // fixed-point hand-over (us, general kernel / here, one and two tokens at 50 %: 62238 x 4592 int8 39.9 / 37.3 and 54.2 /
     // 51.6, 22968 x 11200 int8 33.8 / 32.4 and 45.9 / 44.2), not otherwise (132456 x 1040 int8, 83 splits, 29.2 / 30.9 and 39.2 /
     // 42.6; 98580 x 9328 int8, 500 workgroups, 94.2 / 96.1 and 135.5 / 138.9).
-    const int rc2 = plan_gemv1_lanes(g, wdt, kc, kc_forced, waves, granule_min, bt, wdt == kI8 && g.N <= kI8WideCols, false, out);
+    const int rc2 = plan_gemv1_lanes(g, wdt, kc, kc_forced, waves, granule_min, bt, lanes8 || (wdt == kI8 && g.N <= kI8WideCols), false, out);
     if (rc2 != SCAP_OK || must) return rc2;
     return out->S <= kFxMaxSplits && (int64_t)out->S * out->T <= 256 ? SCAP_OK : kG1NotApplicable;
 }
@@ -248,6 +248,7 @@ int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& dn, int wdt, int up
 // Measured on 4096 -> 14336 -> 4096, two tokens, both launches general / these (us): int8 45.8 / 41.9 with nothing
 // pruned, 38.0 / 34.5 at 50 %, 21.8 / 19.6 at 90 %; bf16 (down launch only) 65.3 / 64.3, 55.9 / 54.7, 25.9 / 24.8.
 // Fills *g and returns SCAP_OK, or kG1NotApplicable.
+// flags: kG1FlagParkSlices (8-byte lanes of part 0; 16-byte lanes hand partial sums over, where every slice is finished at once).
 static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, bool lanes8, int flags, Gemv1bArgs* g,
                             bool* i8_half) {
     // 3-4 tokens: the down launch only, 16-bit weights, on the four-slot form (the lists then carry 4 token slots)
@@ -297,8 +298,8 @@ static int launch_block2(const Gemv1bArgs& g, int wdt, bool half, int fuse, hipS
 }
 
 // One of the launches in the batched block kernels' list format.
-static int plan_block2_64(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, int flags, Gemv1bArgs* g, bool* half) {
-    const int rc = plan_block2_part(up, dn, wdt, part, false, flags, g, half);
+static int plan_block2_64(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, Gemv1bArgs* g, bool* half) {
+    const int rc = plan_block2_part(up, dn, wdt, part, false, 0, g, half);
     if (rc != SCAP_OK) return rc;
     return part == 0 && *half ? kG1NotApplicable : SCAP_OK;
 }
@@ -306,28 +307,48 @@ static int plan_block2_64(const GemvArgs& up, const GemvArgs& dn, int wdt, int p
 bool swiglu_block2_part_applies(const GemvArgs& up, const GemvArgs& dn, int wdt, int part) {
     Gemv1bArgs g;
     bool half = false;
-    return plan_block2_64(up, dn, wdt, part, 0, &g, &half) == SCAP_OK;
+    return plan_block2_64(up, dn, wdt, part, &g, &half) == SCAP_OK;
 }
 
-int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, int flags, hipStream_t stream) {
+int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int part, hipStream_t stream) {
     Gemv1bArgs g;
     bool half = false;
-    const int rc = plan_block2_64(up, dn, wdt, part, part == 0 ? flags & kG1FlagParkSlices : 0, &g, &half);
+    const int rc = plan_block2_64(up, dn, wdt, part, &g, &half);
     if (rc != SCAP_OK) return rc;
     return launch_block2(g, wdt, half, part == 0 ? kFuseSwiglu : kFuseList, stream);
 }
 
-// Both launches, lists of 32-channel segments between them; kG1NotApplicable where either does not run here so.  8-byte
-// lanes have one column per lane and slice, so the gate|up launch hands over in fixed point, and small blocks have tiles
-// enough (2F <= 4096 ran on the general kernel).  us, two tokens, before / now (40 / 70 % and 80 / 80 %): 4096 -> 2048 ->
-// 4096 23.7 / 18.2 and 22.1 / 16.4, 2048 -> 8192 -> 2048 22.3 / 20.7 and 20.0 / 18.5, 8192 -> 16384 -> 8192 72.7 / 69.2 and
-// 45.3 / 43.6, 4096 -> 14336 -> 4096 37.0 / 37.1 and 27.6 / 26.8, 4096 -> 11008 -> 4096 32.4 / 32.9 and 25.0 / 24.6.
+// Whether the gate|up launch of a two-token block over int8 weights is planned better in 8-byte lanes (`half`) than in 16-byte
+// lanes (`wide`).  8-byte lanes save in the fixed part (half the sums of the wavefronts and half the splits, handed over in fixed
+// point) and lose in the stream: they read rows in pieces of 512 instead of 1024 bytes.  From 110 blocks K -> F at 2-80 %
+// sparsity (us per block, wide / half):
+//  - up to 13312 gate|up columns, or pieces of at most 512 rows, half is faster however the tiles fall: 16384 -> 4096 37.3 / 34.6,
+//    14976 -> 2688 33.7 / 30.0, 4096 -> 8192 25.6 / 24.0, 2048 -> 16384 26.6 / 24.8, 1064 -> 13848 22.3 / 21.8;
+//  - pieces of up to 1024 rows: where the busiest unit reads no more bytes than in the wide plan (4096 -> 12800 34.9 / 33.9, 4096 ->
+//    14336 37.1 / 37.0, 6144 -> 24576 76.8 / 76.0), not where a smaller share of the units is busy (4096 -> 11008 at 40 % 32.0 /
+//    32.5, 4096 -> 18368 at 30 % 45.9 / 47.1);
+//  - longer ones lose: 8192 -> 12288 54.7 / 56.6, 8192 -> 13568 62.1 / 65.1, 4096 -> 28672 60.9 / 61.7, 3584 -> 31680 60.5 / 61.2;
+//  - pieces of 1024 rows or more that lie a multiple of 32 MiB apart meet on the same memory channels: half then 36.2 / 38.9 on
+//    4096 -> 16384 and 38.6 / 42.3 on 2048 -> 32768.  Where the wide plan's do, half is the faster one (8192 -> 16384 78.4 / 75.0).
+static bool half_lanes_are_faster(const Gemv1bArgs& half, const Gemv1bArgs& wide) {
+    auto bytes = [](const Gemv1bArgs& g, int tile) { return ((int64_t)g.a.S * g.a.T + 255) / 256 * g.a.Kc * tile; };
+    auto meet = [](const Gemv1bArgs& g) { return g.a.Kc >= 1024 && (int64_t)g.a.Kc * g.a.N % ((int64_t)1 << 25) == 0; };
+    if (meet(half) || meet(wide)) return meet(wide);
+    return half.a.N <= 13312 || half.a.Kc <= 512 ||
+           (half.a.Kc <= 1024 && bytes(half, kWave * Vec<kI8Half>::kElems) <= bytes(wide, kWave * Vec<kI8>::kElems));
+}
+
+// Both launches, lists of 32-channel segments between them; kG1NotApplicable where either does not run here so, or the gate|up
+// launch is faster in 16-byte lanes.  8-byte lanes have one column per lane and slice, so the gate|up launch hands over in
+// fixed point, and small blocks have tiles enough (2F <= 4096 ran on the general kernel: 4096 -> 2048 -> 4096 23.7 / 18.2 us at
+// 40 / 70 %).
 int launch_swiglu_block2_pair(const GemvArgs& up, const GemvArgs& dn, int wdt, int flags, hipStream_t stream) {
-    Gemv1bArgs gu, gd;
-    bool hu = false, hd = false;
+    Gemv1bArgs gu, gd, wide;
+    bool hu = false, hd = false, hw = false;
     if (plan_block2_part(up, dn, wdt, 0, true, flags & kG1FlagParkSlices, &gu, &hu) != SCAP_OK || !hu || gu.a.fx_acc == nullptr ||
         plan_block2_part(up, dn, wdt, 1, true, 0, &gd, &hd) != SCAP_OK)
         return kG1NotApplicable;
+    if (plan_block2_64(up, dn, wdt, 0, &wide, &hw) == SCAP_OK && !half_lanes_are_faster(gu, wide)) return kG1NotApplicable;
     const int rc = launch_block2(gu, wdt, hu, kFuseSwiglu, stream);
     if (rc != SCAP_OK) return rc;
     return launch_block2(gd, wdt, hd, kFuseList32, stream);

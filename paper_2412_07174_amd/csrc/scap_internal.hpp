@@ -104,8 +104,9 @@ int launch_gemv1b(const GemvArgs& a, int wdt, int flags, hipStream_t stream);
 // Two-token block: whether launch `part` (0: gate|up with the gating epilogue, 1: down reading the lists) can run on the
 // two- / four-slot kernel, and that launch.  Both use the batched block kernels' list format, so the parts mix with theirs.
 bool swiglu_block2_part_applies(const GemvArgs& up, const GemvArgs& down, int wdt, int part);
-int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& down, int wdt, int part, int flags, hipStream_t stream);
-// Block of two tokens (int8 weights) with both launches on that kernel, in a list format of their own; kG1NotApplicable likewise.
+int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& down, int wdt, int part, hipStream_t stream);
+// Block of two tokens (int8 weights) with both launches on that kernel, in a list format of their own; kG1NotApplicable likewise,
+// and where the format above is the faster one.
 int launch_swiglu_block2_pair(const GemvArgs& up, const GemvArgs& down, int wdt, int flags, hipStream_t stream);
 int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& down, int wdt, int up_flags, int down_flags,
                          hipStream_t stream);

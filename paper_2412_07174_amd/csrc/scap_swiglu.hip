@@ -64,13 +64,13 @@ static int launch_block(GemvArgs up, GemvArgs dn, int wdt, int flags, hipStream_
     if (lds_up > 64 * 1024 || lds_dn > 64 * 1024) return SCAP_ERR_SHAPE;
 
     if (up_two) {
-        rc = launch_swiglu_block2_part(up_in, dn_in, wdt, 0, flags, stream);
+        rc = launch_swiglu_block2_part(up_in, dn_in, wdt, 0, stream);
         if (rc != SCAP_OK) return rc;
     } else {
         hipLaunchKernelGGL((swiglu_up_kernel<WDT, BT>), dim3((unsigned)(up.S * up.T)), dim3(NT), lds_up, stream, up);
         if (hipGetLastError() != hipSuccess) return SCAP_ERR_HIP;
     }
-    if (dn_two) return launch_swiglu_block2_part(up_in, dn_in, wdt, 1, flags, stream);
+    if (dn_two) return launch_swiglu_block2_part(up_in, dn_in, wdt, 1, stream);
     if (half) {
         hipLaunchKernelGGL((swiglu_down_kernel<WDT, BT, kWave / 2>), dim3((unsigned)(dn.S * dn.T)), dim3(NT), lds_dn,
                            stream, dn);

@@ -410,3 +410,24 @@ def test_int8_rows_per_group_of_three_and_four_tokens(K, N, rows, ok):
         else:
             with pytest.raises(scap.ScapError, match="status -9"):
                 gpu_sparse_fc(layer, X, xdt, 0.1, 0.8, None, cfg=(0, rows, 0, 0))
+
+
+# ... and where the gate|up launch runs in 16-byte lanes (64-channel segments, partial sums): pieces of more than 512 rows that
+# would be heavier in 8-byte lanes, the last segment cut, an odd input length; more columns than there are fixed-point words;
+# paired with the general kernels, where the input of the down launch, or of the gate|up launch, is too long; and a down launch
+# in wide lanes behind a gate|up launch in 8-byte lanes
+@pytest.mark.parametrize("K,F,N", [(136, 2056, 16400), (1040, 22088, 144), (1041, 22088, 2064), (136, 32776, 528), (8, 131080, 1040), (140000, 8, 528)])
+def test_int8_blocks_of_two_tokens_in_wide_lanes(K, F, N):
+    blk = Block(K, F, N, I8, 1800 + K, std=0.02 if K > 2000 else 0.05, B=2)
+    X = wl.laplace(2, K, 1801 + K, BF16, loc=0.1, scale=0.5)
+    rng = np.random.default_rng(1802 + K)
+    bg, bu, bd = (rng.standard_normal(n).astype(np.float32) * 0.05 for n in (F, F, N))
+    for tau_x, tau_z in ((0.0, 0.0), (0.5, 0.02), (1e9, 0.0)):
+        print(f"int8 block of two, wide lanes {K}->{F}->{N} tau_x={tau_x} tau_z={tau_z}", flush=True)
+        args = (X, BF16, 0.1, tau_x, bg, bu, 0.01, tau_z, bd)
+        got = blk.check_batch(*args, what=f"{K} {F} {N} {tau_x} {tau_z}")
+        blk.check_batch(*args, what=f"{K} {F} {N} {tau_x} {tau_z} general kernels", cfg=(0, 0, 0, 0, scap.CFG_GENERAL_KERNEL))
+        for other in (blk.run_batch(*args), blk.run_batch(*args, cfg=(0, 0, 0, 0, scap.CFG_PARK_SLICES))):
+            for b in range(2):
+                assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
+                assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
