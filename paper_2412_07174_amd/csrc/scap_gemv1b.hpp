@@ -497,6 +497,13 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     // travel so (fx_escapes; each token's slice by itself) goes as fp32 through its partial-sum slot and the column's escape mask.
     if constexpr (FIXED) {
         if (fx_acc != nullptr) {
+            // y in scalar registers of its own from here on: at four slots the compiler otherwise keeps it, with the arguments
+            // loaded beside it, in lanes of a vector register and reads all eight back before every token's store (us, so /
+            // now: 4096 x 11008 int8, 70 %, 16.9 / 16.7, 8192 x 8192 20.0 / 19.8, 2048 x 2048 10.35 / 10.2)
+            typedef __attribute__((address_space(1))) float global_f32_t;
+            global_f32_t* yg = (global_f32_t*)y;
+            if constexpr (BT == 4) asm("" : "+s"(yg));
+            float* y_out = (float*)yg;
             const int limit_bits = fx_limit_bits(S);
             const int frac = limit_bits - fx_range_bits(IS_I8);
             const double to_fixed = __hiloint2double((1023 + frac) << 20, 0);    // 2^frac
@@ -576,7 +583,7 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
                 for (int c = 0; c < CPL; ++c) {
                     if (FUSE == kFuseSwiglu) yv[b][c] = done[b][c] ? (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c] : 0.f;
                     if (__builtin_expect(!done[b][c], 0)) continue;
-                    if (FUSE != kFuseSwiglu) store_dev(&y[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
+                    if (FUSE != kFuseSwiglu) store_dev(&y_out[word(b, c)], (IS_I8 ? yv[b][c] * cscale[c] : yv[b][c]) + cbias[c]);
                     store_dev(&fx_acc[word(b, c)], 0ull);  // zero at rest
                 }
             if constexpr (FUSE == kFuseSwiglu) {
@@ -643,9 +650,8 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     }
 
     // ------------------------------------------------------------------ 4. split-K hand-over per (tile, slice)
-    // Two slots.  (Three and four hand over in fixed point only, as the host has checked; what the compiler makes of the
-    // four-slot kernel without this code behind it is 1 % slower.)
-    if constexpr (BT != 3) {
+    // two slots: three and four hand over in fixed point only (launch_gemv1b_nch refuses them without)
+    if constexpr (BT == 2) {
         // partials [S][T][B][TILE]: as in the one-token kernel, B slices per arrival
         const __amdgpu_buffer_rsrc_t pbuf = make_raw_buffer(partial, (uint32_t)S * T * B * TILE * 4u);
         const uint32_t pstride = (uint32_t)T * B * TILE * 4u;  // bytes between consecutive splits
@@ -668,39 +674,35 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
         const bool near = ticket_all_one_xcd(seen) && !(flags & kG1FlagDeviceScope);
         if (near) asm volatile("buffer_inv sc0" ::: "memory");  // this compute unit's vector L1 holds nothing older
         constexpr int FLY = CPL == 1 ? 32 : 16;  // partial loads in flight per token
+        slice_t total[2];
 #pragma unroll
-        for (int b0 = 0; b0 < BT; b0 += 2) {
-            if (b0 >= B) break;
-            slice_t total[2];
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int c = 0; c < CPL; ++c) total[t].v[c] = 0.f;
+        for (int sp0 = 0; sp0 < S; sp0 += FLY) {
+            slice_t v[2][FLY];
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) total[t].v[c] = 0.f;
-            for (int sp0 = 0; sp0 < S; sp0 += FLY) {
-                slice_t v[2][FLY];
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t tok = (uint32_t)min(t, B - 1) * ptok;  // a slot past the last token re-reads it
+                if (near) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint32_t tok = (uint32_t)min(b0 + t, B - 1) * ptok;  // a slot past the last token re-reads it
-                    if (near) {
+                    for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_plain(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
+                } else {
 #pragma unroll
-                        for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_plain(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_coherent(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
-                    }
-                }
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                    for (int j = 0; j < FLY; ++j) {
-                        const bool in = sp0 + j < S;  // a slot past the last split re-read it: not added
-#pragma unroll
-                        for (int c = 0; c < CPL; ++c) total[t].v[c] += in ? v[t][j].v[c] : 0.f;
-                    }
+                    for (int j = 0; j < FLY; ++j) v[t][j] = slice_t::load_coherent(pbuf, min(sp0 + j, S - 1) * pstride + pmine + tok);
                 }
             }
-            finish(total);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int j = 0; j < FLY; ++j) {
+                    const bool in = sp0 + j < S;  // a slot past the last split re-read it: not added
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) total[t].v[c] += in ? v[t][j].v[c] : 0.f;
+                }
+            }
         }
+        finish(total);
         if (lane == 0) store_dev(ticket, 0ull);  // ready for the next call
         if (want_lists) {
             // token w's lists of all splits are complete: their writers stored them before taking this slice's ticket
@@ -750,6 +752,7 @@ static int launch_gemv1b_nch(const Gemv1bArgs& g, hipStream_t stream) {
     constexpr int TILE = kWave * Vec<WDT>::kElems;
     const size_t lds = gemv1b_lds_bytes(TILE, g.a.Kc, BT);
     if (lds > (size_t)kG1bMaxLds) return SCAP_ERR_CONFIG;
+    if (BT > 2 && g.a.S > 1 && g.a.fx_acc == nullptr) return SCAP_ERR_CONFIG;  // fixed-point hand-over only
     if (g.a.Kc <= kG1Chunk) return launch_gemv1b_one<WDT, 1, BT, FUSE>(g, lds, stream);
     if (g.a.Kc <= 2 * kG1Chunk) return launch_gemv1b_one<WDT, 2, BT, FUSE>(g, lds, stream);
     if (g.a.Kc <= 4 * kG1Chunk) return launch_gemv1b_one<WDT, 4, BT, FUSE>(g, lds, stream);
