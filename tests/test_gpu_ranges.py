@@ -330,32 +330,60 @@ def test_int8_blocks_of_both_lane_widths(K, F, N):
 
 
 # the two-token block over int8 weights on 8-byte lanes: list segments of 32 channels, the gate|up launch in fixed point.
-# The last segment cut, fewer channels than one, one tile and many; slices gated from registers and through memory (the same
-# bits); sums that escape the fixed point (gate and up weights times 2^12 over large inputs)
-@pytest.mark.parametrize("K,F,N", [(256, 8, 16), (300, 72, 144), (1000, 2056, 1040), (520, 4104, 2064), (136, 16416, 528), (2000, 1032, 4112)])
+# The last segment cut, fewer channels than one, one tile and many; slices gated from registers and through memory (the same bits)
+TWO_TOKEN_INT8 = [(256, 8, 16), (300, 72, 144), (1000, 2056, 1040), (520, 4104, 2064), (136, 16416, 528), (2000, 1032, 4112)]
+
+
+@pytest.mark.parametrize("K,F,N", TWO_TOKEN_INT8)
 def test_int8_blocks_of_two_tokens(K, F, N):
-    for std, loc in ((0.05, 0.1), (0.05 * 2.0 ** 12, 30.0)):
-        blk = Block(K, F, N, I8, 1400 + K, std=std, B=2)
-        X = wl.laplace(2, K, 1401 + K, BF16, loc=loc, scale=5 * loc)
-        for tau_x, tau_z in ((0.0, 0.0), (5 * loc, 0.02), (1e9, 0.0)):
-            if std > 1 and tau_x != 5 * loc:
-                continue
-            print(f"int8 block of two {K}->{F}->{N} std={std} tau_x={tau_x} tau_z={tau_z}", flush=True)
-            args = (X, BF16, loc, tau_x, None, None, 0.01, tau_z, None)
-            got = blk.run_batch(*args) if std > 1 else blk.check_batch(*args, what=f"{K} {F} {N} {tau_x} {tau_z}")
-            for other in (blk.run_batch(*args), blk.run_batch(*args, cfg=(0, 0, 0, 0, scap.CFG_PARK_SLICES))):
-                for b in range(2):
-                    assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
-                    assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
-            if std > 1:  # both sides are far beyond the fixed point's range; z against double precision
-                f = lambda w, s: w.astype(np.float64) * wl.decode(s, F16).astype(np.float64)
-                d = (wl.decode(X, BF16).astype(np.float32) - np.float32(loc))
-                d = np.where(np.abs(d) > np.float32(tau_x), d, np.float32(0)).astype(np.float64)
-                g, u = d @ f(blk.Wg, blk.sg), d @ f(blk.Wu, blk.su)
-                with np.errstate(over="ignore"):
-                    z = g / (1 + np.exp(-g)) * u
-                for b in range(2):
-                    assert _rel(got[b]["z"], z[b]) <= 2e-6, (K, F, N, b, _rel(got[b]["z"], z[b]))
+    blk = Block(K, F, N, I8, 1400 + K, std=0.05, B=2)
+    X = wl.laplace(2, K, 1401 + K, BF16, loc=0.1, scale=0.5)
+    for tau_x, tau_z in ((0.0, 0.0), (0.5, 0.02), (1e9, 0.0)):
+        print(f"int8 block of two {K}->{F}->{N} tau_x={tau_x} tau_z={tau_z}", flush=True)
+        args = (X, BF16, 0.1, tau_x, None, None, 0.01, tau_z, None)
+        got = blk.check_batch(*args, what=f"{K} {F} {N} {tau_x} {tau_z}")
+        for other in (blk.run_batch(*args), blk.run_batch(*args, cfg=(0, 0, 0, 0, scap.CFG_PARK_SLICES))):
+            for b in range(2):
+                assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
+                assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
+
+
+# ... with partial sums that escape the fixed point: 2^18 and more in magnitude before the column scale, i.e. large inputs over
+# columns of a small scale.  "some": a few columns of a slice; "most": already 8 rows are mostly beyond the range.  Both are
+# beyond what the oracle's fp32 sums are compared at, so z against double precision (the errors of 32-bit sums; no cancellation in
+# silu(g) u), the lists against the z returned, y against double precision over those lists
+@pytest.mark.parametrize("share", ["some", "most"])
+@pytest.mark.parametrize("K,F,N", TWO_TOKEN_INT8)
+def test_int8_blocks_of_two_tokens_beyond_the_fixed_point(K, F, N, share):
+    up = 2.0 ** (2 if share == "some" else 10)
+    blk = Block(K, F, N, I8, 1400 + K, std=0.05 / up / 64, B=2)
+    X = wl.laplace(2, K, 1401 + K, BF16, loc=30.0 * up, scale=150.0 * up)
+    m_x, tau_x, m_z, tau_z = np.float32(30.0 * up), np.float32(150.0 * up), np.float32(0.01), np.float32(0.02)
+    d = wl.decode(X, BF16).astype(np.float32) - m_x
+    d = np.where(np.abs(d) > tau_x, d, np.float32(0)).astype(np.float64)
+    def beyond(rows):  # share of the partial sums of `rows` rows that lie beyond the range
+        whole = K // rows * rows
+        part = lambda W: np.einsum("bcr,crn->bcn", d[:, :whole].reshape(2, -1, rows), W[:whole].astype(np.float64).reshape(-1, rows, F))
+        return np.mean([np.abs(part(W)) >= 2.0 ** 18 for W in (blk.Wg, blk.Wu)])
+    # pieces have 24 to 80 rows here: more rows, more of them
+    assert beyond(8) > 0.5 if share == "most" else beyond(24) > 0.005 and beyond(80) < 0.95, (beyond(8), beyond(24), beyond(80))
+    f = lambda w, s: w.astype(np.float64) * wl.decode(s, F16).astype(np.float64)
+    g, u = d @ f(blk.Wg, blk.sg), d @ f(blk.Wu, blk.su)
+    z = g / (1 + np.exp(-g)) * u
+    print(f"int8 block of two beyond the range {K}->{F}->{N} {share} |g| up to {np.abs(g).max():.3g}", flush=True)
+    args = (X, BF16, float(m_x), float(tau_x), None, None, float(m_z), float(tau_z), None)
+    got = blk.run_batch(*args)
+    for b in range(2):
+        assert np.isfinite(z[b]).all() and _rel(got[b]["z"], z[b]) <= 2e-6, (K, F, N, b, _rel(got[b]["z"], z[b]))
+        dz = got[b]["z"] - m_z  # one fp32 subtraction
+        kept = np.nonzero(np.abs(dz) > tau_z)[0]
+        assert np.array_equal(got[b]["idx_z"], kept), (K, F, N, b)
+        y = dz[kept].astype(np.float64) @ f(blk.Wd[kept], blk.sd)
+        assert _rel(got[b]["y"], y) <= 2e-6, (K, F, N, b, _rel(got[b]["y"], y))
+    for other in (blk.run_batch(*args), blk.run_batch(*args, cfg=(0, 0, 0, 0, scap.CFG_PARK_SLICES))):
+        for b in range(2):
+            assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
+            assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
 
 
 # the histogram estimator where the range it bins is infinite: every finite value counts in bin 0 and the estimate is the
