@@ -872,29 +872,52 @@ static int64_t inline_cost(const GemvArgs& a, int tile_cols) {
     return (((int64_t)a.S * a.T + 255) / 256 * (a.Kc + 128) + (int64_t)a.S * kInlineSplitRows) * tile_cols;
 }
 
+// The cost weighs a workgroup's fixed part like rows, but its prologue tests Kc channels whatever its tile: narrow tiles pay when
+// they all run at once, otherwise only while the launch does not grow by more than the units can hide, and rows that start
+// inside a cache line (N not a multiple of 128) are read in pieces that straddle two.  From 100 layers of more than 256 narrow
+// workgroups (us, 16- / 8-byte lanes, with the workgroups of either): 24728 x 9856, 5 tokens, 51.3 / 48.7 (508 / 1001), 832 x 20096
+// 11.5 / 10.4 (237 / 471), 520 x 17824 (pieces of 192 rows) 10.7 / 9.3, 4016 x 22128, 16 tokens, 37.3 / 34.7 (435 / 692), 2056 x
+// 16624 (pieces of 704) 19.2 / 17.9, but with 5 tokens 16.4 / 17.0; 1024 x 43680, 4 tokens, 16.0 / 20.8 (171 / 684), 24288 x 5120, 5
+// tokens, 30.1 / 32.1 (240 / 760), 2904 x 19312, 8 tokens, 22.6 / 25.7 (228 / 453, pieces of 1024), 62240 x 4592, 4 tokens, 76.0 /
+// 95.7 (504 / 1008).
+static bool narrow_tiles_fit(const GemvArgs& narrow, const GemvArgs& wide) {
+    const int64_t n = (int64_t)narrow.S * narrow.T, w = (int64_t)wide.S * wide.T;
+    if (n <= 256) return true;
+    if (narrow.N % kMfmaTile == 0 || narrow.Kc <= (narrow.B > 8 ? 768 : 640)) return n < 3 * w;
+    return narrow.Kc <= 1792 && 5 * n <= 8 * w;
+}
+
 // The same with the lane width of int8 weights chosen on the way (*wdt becomes kI8Half: 8-byte lanes, 128-column tiles).
 // Narrow tiles halve the K splits, the wavefronts' sums and what a tile's last arrival collects, wide ones halve the
 // prologues and read rows in pieces of 256 instead of 128 bytes.  Which is faster follows what the two plans cost (16
 // tokens, wide / narrow, us: 1024 x 4096 12.0 / 8.5, 4096 x 4096 14.0 / 10.9, 14336 x 4096 21.5 / 19.6, 4096 x 24576 35.3 /
-// 30.3, 16384 x 16384 69.7 / 66.4; 5 tokens 18.9 / 18.2 on 14336 x 4096, but 29.3 / 30.9 on 4096 x 28672, where both plans
-// cost the same).  The launch that reads lists gains less from the narrow tiles (block 2048 -> 8192 -> 2048, 16 tokens,
+// 30.3, 16384 x 16384 69.7 / 66.4), where narrow tiles fit; where the two cost the same (4096 x 28672) so do the launches.  At
+// 97-99 % of the cost few tokens gain less than many: 8192 x 16384, 5 tokens, 32.3 / 33.5, 16 tokens 36.3 / 35.9.
+// The launch that reads lists gains less from the narrow tiles (block 2048 -> 8192 -> 2048, 16 tokens,
 // 34.1 / 28.9, 4096 -> 8192 -> 4096 40.5 / 39.3, but 4096 -> 11008 -> 4096 48.9 / 49.4 and 8192 -> 16384 -> 8192 99.5 / 109.7).
-// An input length that is not a multiple of 8: the staged tile exists for narrow tiles only, and beats the value lists
-// (16 tokens, lists / tile: 513 x 1024 17.0 / 8.8, 5461 x 2752 23.3 / 12.5, 14337 x 4096 27.3 / 24.2; 5 tokens 4097 x 28672
-// 36.7 / 33.0) but for more than 8 tokens and a long stream (16 tokens 4097 x 28672 40.0 / 43.2, 10 tokens 36.4 / 37.4).
+// An input length that is not a multiple of 8: the staged tile exists for narrow tiles only.  It beats the value lists up to 2^26
+// weights (16 tokens, lists / tile: 513 x 1024 17.0 / 8.8, 5461 x 2752 23.3 / 12.5, 14337 x 4096 27.3 / 24.2; not with four times the
+// workgroups: 1023 x 48016, 12 tokens, 25.1 / 26.4); beyond, with up to 8 tokens, where rows start on a cache line or the pieces are
+// not long and many (6 tokens 5461 x 26128 70.0 / 53.4, 9001 x 9600, 5 tokens, 30.7 / 25.5, 2047 x 40000 43.0 / 32.0, but 16385 x
+// 8784 48.3 / 58.3 and 62241 x 4592 95.7 / 111.6), and with more not (16 tokens 4097 x 28672 40.0 / 43.2, 10 tokens 36.4 / 37.4).
 static int plan_inline_lanes(GemvArgs& a, int* wdt, int kc, bool kc_forced, int fuse, int* bt_out, size_t* lds_out,
                              bool slots16 = false) {
     const GemvArgs in = a;
     const int rc = plan_inline(a, *wdt, kc, kc_forced, fuse, bt_out, lds_out, slots16);
     if (rc != SCAP_OK || *wdt != kI8 || *bt_out != kMfmaTokens) return rc;
-    const bool ragged = fuse != kFuseList && in.K % 8 != 0;
-    if (ragged && in.B > 8 && (int64_t)in.K * in.N > ((int64_t)1 << 26)) return rc;
     GemvArgs h = in;
     int bt = 0;
     size_t lds = 0;
     if (plan_inline(h, kI8Half, kc, kc_forced, fuse, &bt, &lds, slots16) != SCAP_OK) return rc;
-    const int percent = fuse == kFuseList ? 77 : 99;
-    if (!ragged && inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * percent) return rc;
+    if (fuse != kFuseList && in.K % 8 != 0) {
+        const int64_t n = (int64_t)h.S * h.T, w = (int64_t)a.S * a.T;
+        const bool little = (int64_t)in.K * in.N <= ((int64_t)1 << 26) && (n < 4 * w || h.Kc < 512);
+        const bool few = in.N % kMfmaTile == 0 || h.Kc <= 640 || (h.Kc <= 1536 && n <= 2 * w);
+        if (!(little || (in.B <= 8 && few))) return rc;
+    } else {
+        const int percent = fuse == kFuseList ? 77 : 99;
+        if (inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * percent || !narrow_tiles_fit(h, a)) return rc;
+    }
     a = h;
     *lds_out = lds;
     *wdt = kI8Half;

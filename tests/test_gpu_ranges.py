@@ -459,3 +459,16 @@ def test_int8_blocks_of_two_tokens_in_wide_lanes(K, F, N):
             for b in range(2):
                 assert np.array_equal(got[b]["y"].view(np.uint32), other[b]["y"].view(np.uint32)), (K, F, N, b)
                 assert np.array_equal(got[b]["idx_z"], other[b]["idx_z"])
+
+
+# ... and where more narrow workgroups than compute units would be needed: rows that start on a cache line, or short pieces, and
+# less than three times the wide ones, or not; longer pieces over other rows; 3-4 tokens on the 4-slot lists of pieces that the
+# tile's LDS does not hold, and instead of more than 256 wide workgroups; odd lengths on either side
+@pytest.mark.parametrize("K,N", [(64, 33280), (344, 33280), (64, 32864), (344, 32864), (1968, 16432), (1352, 32864), (2400, 49632),
+                                 (1560, 39216), (343, 32864), (513, 43680), (1231, 56960), (6001, 11280)])
+def test_int8_batches_of_more_tiles_than_compute_units(K, N):
+    layer, xdt = _layer(K, N, I8, 1250 + K)
+    for B in (3, 4, 5, 16):
+        X = wl.laplace(B, K, 1251 + K, xdt, loc=0.1, scale=0.5)
+        print(f"int8 lanes, many tiles K={K} N={N} B={B}", flush=True)
+        check_against_oracle(layer, X, xdt, 0.1, 0.8, None, what=f"K={K} N={N} B={B}")
