@@ -24,6 +24,7 @@ namespace scap {
 
 constexpr size_t kInlineLdsBudget = 160 * 1024;
 constexpr int kInlineWaves = 8;
+constexpr int kTileRows = 2368;       // rows of a workgroup whose 16 token slots fit LDS
 constexpr int kInlineSplitRows = 12;  // rows' time that a K split's hand-over costs (16 token slots)
 // chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
 constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
@@ -913,7 +914,8 @@ static int plan_inline_lanes(GemvArgs& a, int* wdt, int kc, bool kc_forced, int 
         const int64_t n = (int64_t)h.S * h.T, w = (int64_t)a.S * a.T;
         const bool little = (int64_t)in.K * in.N <= ((int64_t)1 << 26) && (n < 4 * w || h.Kc < 512);
         const bool few = in.N % kMfmaTile == 0 || h.Kc <= 640 || (h.Kc <= 1536 && n <= 2 * w);
-        if (!(little || (in.B <= 8 && few))) return rc;
+        // (3-4 tokens: against the 4-slot lists, which launch_gemm_inline takes where this stays wide)
+        if (!(in.B <= 4 ? little && narrow_tiles_fit(h, a) : little || (in.B <= 8 && few))) return rc;
     } else {
         const int percent = fuse == kFuseList ? 77 : 99;
         if (inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * percent || !narrow_tiles_fit(h, a)) return rc;
@@ -934,10 +936,27 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
         if (kc < 0 || (kc % kWave) != 0) return SCAP_ERR_CONFIG;
         if (cfg->waves_per_group && cfg->waves_per_group != kInlineWaves) return SCAP_ERR_CONFIG;
     }
+    const int wdt_in = wdt;
     int bt = 0;
     size_t lds = 0;
     const int rc = plan_inline_lanes(a, &wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
+    // Layers wider than 4 K and odd lengths: the 4-slot lists where they need fewer workgroups than the tile's LDS allows, or where
+    // the tile would run in 16-byte lanes, one workgroup per compute unit, on more of them (or does not exist); two of the lists'
+    // share a unit.  3 tokens at 70 %, tile / lists, us: 4096 x 57344 43.8 / 35.4, 6144 x 28672 38.1 / 32.3, 2664 x 56944 39.2 / 32.3,
+    // 7912 x 33408 58.2 / 46.8, 5896 x 34816 47.0 / 40.8; elsewhere 4096 x 24576 21.7 / 23.2, 2048 x 20480 12.6 / 15.8, 512 x 24576 6.4 / 12.0.
+    if (slots16 && wdt_in == kI8 && ((int64_t)a.N > 4 * (int64_t)a.K || a.K % 8 != 0)) {
+        GemvArgs l = a_in;
+        int bt_l = 0;
+        size_t lds_l = 0;
+        if (plan_inline(l, kI8, kc, kc != 0, kFusePlain, &bt_l, &lds_l) == SCAP_OK &&
+            ((a.K % 8 == 0 && l.Kc > kTileRows) || (wdt == kI8 && (a.K % 8 != 0 || (int64_t)a.S * a.T > 256)))) {
+            a = l;
+            wdt = kI8;
+            bt = bt_l;
+            lds = lds_l;
+        }
+    }
     a.Kl = a.Kc;
     a.Sl = a.S;
     return launch_inline_any<kFusePlain>(a, wdt, bt, lds, stream);
