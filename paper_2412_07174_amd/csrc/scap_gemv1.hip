@@ -61,7 +61,11 @@ int plan_gemv1_lanes(const GemvArgs& g, int wdt, int kc, bool kc_forced, int wav
     const int64_t lds_max = bt == 1 ? 64 * 1024 : kG1bMaxLds;
     // (four slots of 1024-column tiles: the wavefronts' sums alone would fill LDS)
     if (fixed_lds + (int64_t)kWave * (4 + entry) > lds_max) return kG1NotApplicable;
-    const size_t lds_budget = (size_t)(lds_max - fixed_lds) + kHdrBytes;
+    size_t lds_budget = (size_t)(lds_max - fixed_lds) + kHdrBytes;
+    // Three slots have room for more channels than the kernel tests: shorter pieces in two rounds rather than another kernel (3
+    // tokens at 60 %, us, staged tile or general kernel / here: 62240 x 4592 bf16 122.1 / 92.1, fp16 93.7 / 92.7, 40000 x 8192 bf16
+    // 103 / 92.2), as four slots do.
+    if (bt == 3) lds_budget = std::min(lds_budget, (size_t)kHdrBytes + (size_t)kG1MaxChunks * kG1Chunk * entry);
     // Rows per workgroup in multiples of 64, unless the input is so short that 64-row pieces would leave compute
     // units without a workgroup (finer pieces elsewhere gained and lost 2 % by turns)
     p.T = (p.N + out->tile - 1) / out->tile;

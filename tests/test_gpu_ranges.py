@@ -472,3 +472,13 @@ def test_int8_batches_of_more_tiles_than_compute_units(K, N):
         X = wl.laplace(B, K, 1251 + K, xdt, loc=0.1, scale=0.5)
         print(f"int8 lanes, many tiles K={K} N={N} B={B}", flush=True)
         check_against_oracle(layer, X, xdt, 0.1, 0.8, None, what=f"K={K} N={N} B={B}")
+
+
+# three tokens where the pieces that fill the chip are longer than the kernel tests, but not than its LDS holds
+def test_three_tokens_over_pieces_past_the_kernels_limit():
+    K, N = 4104, 43528
+    layer, xdt = _layer(K, N, BF16, 1900, B=4)
+    X = wl.laplace(4, K, 1901, xdt, loc=0.1, scale=0.5)
+    for B in (3, 4):
+        print(f"long pieces K={K} N={N} B={B}", flush=True)
+        check_against_oracle(layer, X[:B], xdt, 0.1, 0.9, None, what=f"K={K} N={N} B={B}")
