@@ -482,7 +482,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
 
 // X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 180 registers per lane against 123, i.e. one
 // workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
-template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC>
+template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC, bool LONG>
 __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
@@ -515,12 +515,14 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
     const int kg = lane >> 4;  // row group: list rows 4*kg .. 4*kg+3 of a block
     const int col0 = tile * TILE + cg * ELEMS;
-    // Two forms of the row loads.  LONG -- 16-bit weights, two workgroups per compute unit, pieces of more than 1024 rows
-    // -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in registers:
-    // with the other form's loads and order 4096 x 28672 bf16, 16 tokens, took 50.4 instead of 49.8 us and fp16 50.4
-    // instead of 48.2, 8192 x 16384 53.0 instead of 52.2; with shorter pieces it is the slower one (4096 x 22016 44.3
-    // against 40.0, fp16 47.4 against 40.1), and over odd input lengths (14337 x 4096 fp16, 10 tokens, 34.6 against 31.1).
-        constexpr bool LONG = !X32 && !is_int8(WDT) && MAXC >= 4 && !RAGGED;
+    // Two forms of the row loads.  LONG -- fp16 weights, pieces of 1537-2048 rows, all workgroups on the chip at once (up to two
+    // per compute unit) -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in
+    // registers: 4096 x 28672, 16 tokens, takes 49.9 us instead of 51.1, 8192 x 16384 56.0 instead of 56.5, 14336 x 8192 48.4 instead
+    // of 49.0 (over bf16 weights they take the same).  With shorter pieces it is the slower form (11584 x 7040 38.2 against 37.0, 4096
+    // x 22016 47.4 against 40.1), over odd input lengths (14337 x 4096, 10 tokens, 34.6 against 31.1), and in launches of more
+    // workgroups or of one per unit (12280 x 15296 83.3 against 73.2, 30424 x 4672 77.6 against 61.0; bf16 69.2 and 60.8, 16384 x 28672
+    // 185 and 161).
+    static_assert(!LONG || (!X32 && WDT == kF16 && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
     const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const char* wbase = reinterpret_cast<const char*>(a.W);
@@ -762,7 +764,7 @@ static int launch_inline(const GemvArgs& a, size_t lds, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC>
+template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC, bool LONG = false>
 static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
     if (lds > 64 * 1024) {
@@ -771,14 +773,14 @@ static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t s
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC, LONG>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave),
-                       lds, stream, a);
+    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC, LONG>), dim3((unsigned)(a.S * a.T)),
+                       dim3(kInlineWaves * kWave), lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
@@ -787,7 +789,12 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
     if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
     if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
     if constexpr (!RAGGED || is_int8(WDT)) {
-        if (a.Kc <= 4 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);
+        if (a.Kc <= 4 * kInlineWaves * kWave) {
+            if constexpr (!RAGGED && !X32 && WDT == kF16) {
+                if (a.Kc > 3 * kInlineWaves * kWave && (long)a.S * a.T <= 512) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4, true>(a, lds, stream);
+            }
+            return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);
+        }
     }
     return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, kRawChunks>(a, lds, stream);
 }

@@ -482,3 +482,15 @@ def test_three_tokens_over_pieces_past_the_kernels_limit():
     for B in (3, 4):
         print(f"long pieces K={K} N={N} B={B}", flush=True)
         check_against_oracle(layer, X[:B], xdt, 0.1, 0.9, None, what=f"K={K} N={N} B={B}")
+
+
+# 16-bit batches in pieces of more than 1024 rows and more than 256 workgroups: up to 512 of them in pieces on either side of 1536
+# rows, more of them, pieces of more than 2048
+@pytest.mark.parametrize("wdt", [BF16, F16])
+@pytest.mark.parametrize("K,N,rows", [(2048, 33000, 2048), (1600, 33000, 1600), (1536, 33000, 1536), (4096, 33000, 2048), (2368, 33000, 2368)])
+def test_batches_of_long_pieces_and_many_workgroups(K, N, rows, wdt):
+    layer, xdt = _layer(K, N, wdt, 1950 + K)
+    for B in (5, 16):
+        X = wl.laplace(B, K, 1951 + K, xdt, loc=0.1, scale=0.5)
+        print(f"long pieces of a batch K={K} N={N} rows={rows} wdt={wdt} B={B}", flush=True)
+        check_against_oracle(layer, X, xdt, 0.1, 1.1, None, cfg=(0, rows, 0, 16), what=f"K={K} N={N} rows={rows} wdt={wdt} B={B}")
