@@ -77,8 +77,10 @@ typedef enum {
  * two-launch form also takes 16 with bf16 -- and rows_per_group is a multiple of 64, rounded up to whole
  * 512-channel list segments by the two-launch form, whose unroll (1, 2, 4; int8: 1, 2) counts 16-row blocks
  * in flight per wavefront).  By default batches of 5 or more tokens run on
- * the matrix cores, and of 3-4 tokens those over wide int8 layers and those over bf16 layers with K >= 2 N whose input is
- * dense or that have at most 1024 columns. */
+ * the matrix cores, and of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
+ * 16384 columns, and those over bf16 layers with K >= 2 N (K a multiple of 8) whose input is dense or that have at most 1024
+ * columns and K > 512.  Over int8 weights they also run there when rows_per_group is given, which may then be up to 4096 in
+ * layers with N > 4 K or a K that is not a multiple of 8. */
 typedef struct {
     int32_t waves_per_group; /* 4, 8 or 16 wavefronts per workgroup */
     int32_t rows_per_group;  /* input channels owned by one workgroup; multiple of 64 */
@@ -88,7 +90,7 @@ typedef struct {
                                 with device-coherent loads even when all their writers ran on the reader's own
                                 accelerator die (results are identical; for tests and measurements);
                                 bit 1 (SCAP_CFG_GENERAL_KERNEL): one to four tokens through the general kernels
-                                instead of the one-token kernel and its two- and four-slot forms;
+                                instead of the one-token kernel and its two- to four-slot forms;
                                 bit 2 (SCAP_CFG_ACCUMULATE): NOT a tuning knob -- y += result instead of y = result.
                                 y must hold the addend (a residual stream, say) when the call is enqueued; every
                                 workgroup adds its share with fp32 atomic adds, which removes the split-K hand-over
@@ -267,7 +269,7 @@ int scap_swiglu_block(const void* W_gu, const void* gu_scale, const void* W_down
 
 /* Same as scap_swiglu_block with launch flags for its one-token form (cfg may be NULL): of cfg only the flags
  * SCAP_CFG_PARTIAL_SUMS (B == 1), SCAP_CFG_PARK_SLICES (B <= 2) and SCAP_CFG_GENERAL_KERNEL (B <= 4: both launches on the
- * general kernels instead of the one-token kernel and its two- and four-slot forms) are read.  For tests and measurements. */
+ * general kernels instead of the one-token kernel and its two- to four-slot forms) are read.  For tests and measurements. */
 int scap_swiglu_block_ex(const void* W_gu, const void* gu_scale, const void* W_down, const void* down_scale, int64_t K,
                          int64_t F, int64_t N, int wdt, const void* x, int xdt, int64_t B, float m_x, float tau_x,
                          const float* b_gu_fused, float m_z, float tau_z, const float* b_down_fused, float* y,

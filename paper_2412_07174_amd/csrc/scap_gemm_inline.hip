@@ -12,7 +12,7 @@
 // the separate union launch of scap_gemm_mfma.hip, its kernel boundary and its lists in memory are not
 // needed; that form remains for inputs too long to split into LDS-sized pieces.
 //
-// The column tile is narrow (128 columns for bf16, 256 for int8), so the prologue is repeated by more
+// The column tile is narrow (128 columns for 16-bit weights, 128 or 256 for int8), so the prologue is repeated by more
 // workgroups than in the vector kernel; it is loads from L2 and a few hundred ALU operations per thread
 // and costs less than the kernel boundary it replaces.
 #include <atomic>
@@ -480,7 +480,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     return cnt;
 }
 
-// X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 180 registers per lane against 123, i.e. one
+// X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 178-180 registers per lane against 109-125, i.e. one
 // workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
 template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC, bool LONG>
 __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
         st.d = make_float4(dm[0], dm[1], dm[2], dm[3]);
     };
     if constexpr (!X32) {
-        // (int8 weights always: with 16 columns per lane the 32-deep form needs 180 registers and measured slower,
+        // (int8 weights always: with 16 columns per lane the 32-deep form measured slower,
         // 14336 x 4096, 16 tokens: 23.3 against 24.8 us; with 8 columns 14336 x 4096, 5 tokens, 18.3 against 19.4)
         auto compute = [&](const Stage& st) {
             s16x4_t a_hi, a_lo;

@@ -122,8 +122,8 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
     // (dense / 50 / 90 %, us): 4 tokens 4096 x 14336 bf16 24.4 / 23.0 / 13.4 against 26.1 / 24.9 / 14.8, 4096 x 6144
     // 15.2 / 14.5 / 10.5 against 18.1 / 17.2 / 12.4, 14336 x 4096 25.5 / 24.6 / 14.9 against 24.7 / 25.5 / 15.6 -- so a
     // dense call with a long input into a narrow layer stays on the staged-tile kernel.  int8 weights in 8-byte lanes
-    // (up to 16384 columns, beyond 4096 up to 2^26 weights; others fall through to the matrix cores): 14336 x 4096, 4 tokens,
-    // 19.7 / 17.7 / 12.9 at 50 / 70 / 90 % against 19.9 / 18.3 / 14.0, 3 tokens 18.1 / 15.8 / 11.9 against 19.1 / 17.0 / 12.9.
+    // (up to 16384 columns, beyond 4096 up to 2^26 weights; others fall through to the matrix cores): for their fp32 operands,
+    // faster than the matrix cores only for three tokens over large layers (kI8FourSlotWeights).
     // bf16 layers of at most 1024 columns with K >= 2 N go to the staged-tile kernel below: 4 tokens at 50 / 90 %, there
     // against here, 4096 x 1024 8.5 / 7.9 us against 10.3 / 8.7, 768 x 256 7.1 / 6.6 against 8.0 / 7.1.  That kernel
     // carries x - m as two bf16 halves (error with m != 0 about 1.8e-6 instead of 1.3e-7), so only from 512 channels on and
@@ -142,8 +142,9 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
         if (rc != kG1NotApplicable) return rc;
     }
     // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot lists for int8 weights (3 tokens at 50 %, lists /
-    // here, us: 512 x 24576 13.4 / 7.2, 1024 x 28672 15.9 / 10.3, 4096 x 24576 34.2 / 25.8, 4096 x 28672 29.2 / 27.5, 8192 x
-    // 28672 53.3 / 53.0), and than the vector kernel for a long input into a narrow bf16 layer (14336 x 4096, 4 tokens:
+    // here, us: 512 x 24576 13.4 / 7.2, 1024 x 28672 15.9 / 10.3, 4096 x 24576 34.2 / 25.8, 4096 x 28672 29.2 / 27.5; in layers
+    // wider than 4 K and over odd lengths launch_gemm_inline still takes the lists where they are the better plan), and than the
+    // vector kernel for a long input into a narrow bf16 layer (14336 x 4096, 4 tokens:
     // 28.7 -> 27.3 us dense, 22.2 -> 20.0 at 90 %).
     // Not over an input length that is not a multiple of 8: int8 weights keep the 4-slot lists beyond 2048 channels (4
     // tokens at 70 %, lists / here: 1023 x 28672 14.9 / 11.0, 2047 x 28672 18.5 / 17.4, 4097 x 20480 21.7 / 23.9, 8193 x 16384

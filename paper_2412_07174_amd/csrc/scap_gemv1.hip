@@ -40,10 +40,13 @@ struct Plan1 {
 // 4096 x 16384 11.5 / 10.4 and 16.5 / 14.4; 4096 x 28672 14.7 / 15.2 and 21.4 / 22.3.
 constexpr int kI8HalfCols = 16384;
 constexpr int kI8WideCols = 4096;
-// Four slots over int8 weights issue four FMAs per weight and token: as the stream gets longer the matrix cores win (3 / 4
-// tokens at 50 %, matrix cores / here: 4096 x 11008 18.3 / 16.7 and 19.2 / 17.9, 8192 x 8192 21.0 / 20.1 and 21.9 / 21.4,
-// 4096 x 16384 dense 22.8 / 22.2 and 23.2 / 23.4, 14336 x 8192 29.4 / 30.7 and 30.5 / 32.8); up to kI8WideCols columns
-// they never do.
+// Three and four slots over int8 weights spend one FMA per weight and token beside the widening; the staged tile on the matrix
+// cores is the faster one for four tokens and for small layers, this kernel for three tokens over large ones (50 / 90 %, here /
+// staged tile, us: 4 tokens 14336 x 4096 20.6 / 18.5 and 13.8 / 12.4, 4096 x 11008 18.7 / 16.2 and 12.8 / 10.9, 8192 x 8192
+// 21.9 / 20.0 and 14.6 / 13.1, 4096 x 4096 13.7 / 9.6 and 11.2 / 7.7; 3 tokens 14336 x 4096 16.7 / 17.3 and 11.4 / 11.6,
+// 4096 x 11008 15.0 / 15.7 and 10.6 / 10.4, 8192 x 8192 18.3 / 19.3 and 11.5 / 12.0, 4096 x 4096 11.4 / 9.3 and 9.1 / 7.5).  Up to
+// this many weights, and up to kI8WideCols columns, calls run here all the same: x - m is an fp32 operand here and two bf16
+// halves there (error with m != 0 about 1.8e-6 instead of 1.3e-7).
 constexpr int64_t kI8FourSlotWeights = (int64_t)1 << 26;
 
 // K split of one launch with the given lane width and split cost; SCAP_OK, kG1NotApplicable (also for more channels per
@@ -170,9 +173,9 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
     return SCAP_ERR_DTYPE;
 }
 
-// Two to four tokens (three and four over int8 weights: in 8-byte lanes only), through the two-, three- or
-// four-slot form of the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding, more than 2048
-// channels per workgroup, or four slots without the fixed-point hand-over.  flags as for launch_gemv1.
+// Two to four tokens (three and four over int8 weights: in 8-byte lanes only), through the two-, three- or four-slot form of
+// the one-token kernel (sparse or dense mode).  Returns a scap_status, or kG1NotApplicable: another token count, bias folding,
+// more than 2048 channels per workgroup, or three or four tokens without the fixed-point hand-over.  flags as for launch_gemv1.
 int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
     if (g.B < 2 || g.B > 4 || g.mode == kModeFold) return kG1NotApplicable;
 

@@ -14,7 +14,7 @@ constexpr int kFusePlain = 0;   // inputs from x, outputs to y
 constexpr int kFuseSwiglu = 1;  // columns are gate|up interleaved in groups of 4; the tile's last arrival forms
                                 // z = silu(gate) * up, centres and thresholds it and leaves compacted lists
 constexpr int kFuseList = 2;    // inputs are those lists instead of x
-constexpr int kFuseList32 = 3;  // the same from 32-channel segments with packed counts (two- / four-slot kernel only)
+constexpr int kFuseList32 = 3;  // the same from 32-channel segments with packed counts (two-slot kernel over int8 weights only)
 
 // Data handed from one workgroup to another inside a launch (split-K partials, per-split index lists,
 // arrival counters) bypasses the non-coherent cache levels: device-scope relaxed atomics for single

@@ -28,8 +28,9 @@ constexpr int kModeFold = 2;    // d = m for every channel            (Eq. 6, et
 //   [1179648, +2 MiB)    one-token kernel, fixed-point hand-over: uint64 acc[131072] (per output column: arrival
 //                        count, escape count and the biased fixed-point sum of the arrivals' partial sums), then
 //                        uint64 esc[131072] (which splits handed their partial over as fp32 instead); zero at rest
-//   [3276800, +4*B*cap)  float partial[B][S][T][tile]   split-K partial sums; during calibration the first
-//                        512 KiB hold the uint64 count of every 16-bit code
+//   [3276800, +4*B*cap)  float partial[B][S][T][tile]   split-K partial sums; calibration: the count of every
+//                        16-bit code in the first 512 KiB, uint64 -- or, for less than 2^32 values with m = 0 or
+//                        the median, uint32 and behind them one bit per group of 64 codes that occur (32 words)
 //   [.., +68*(K+16384))  batched path (B >= 2): union list of every list segment (64 bytes of A operands and
 //                        the channel index per entry)
 // ---------------------------------------------------------------------------------------------
@@ -84,9 +85,12 @@ struct GemvArgs {
     // as one compacted list per 64 channels; the down launch takes those lists as its input.
     float m2, tau2;   // mode estimate and threshold of the gated product
     float* z_out;     // optional fp32 [B][F]: the gated product itself
-    int32_t* zl_idx;  // [ceil(F/64)][64] channels of each 64-channel segment kept by any token, ascending
-    float* zl_d;      // [ceil(F/64)][64][BT] their centred values per token (BT = B rounded up to 1, 2 or 4)
-    int32_t* zl_cnt;  // [1 + BT][ceil(F/64)] entries per segment: union first, then per token
+    // More than one token: 64-channel segments -- except between the two launches of a two-token block over int8 weights in
+    // 8-byte lanes: ceil(F/32) segments of 32 channels.  (One token: see Gemv1Args.)
+    int32_t* zl_idx;  // [ceil(F/64)][64] channels of each segment kept by any token, ascending; [ceil(F/32)][32]
+    float* zl_d;      // [ceil(F/64)][64][BT] their centred values per token (BT = 2, 4 or 16 slots); [ceil(F/32)][32][2]
+    int32_t* zl_cnt;  // [1 + BT][ceil(F/64)] entries per segment: union first, then per token; [ceil(F/32)]: the three
+                      // counts in the low bytes of one word, union lowest
     int F;            // channels of the gated product (half the columns of the gate|up launch)
 };
 
@@ -97,17 +101,18 @@ int launch_gemv(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStrea
 // workgroup would own more channels than that kernel tests per wavefront: the caller takes launch_gemv's kernel.
 constexpr int kG1NotApplicable = 1;
 int launch_gemv1(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStream_t stream);
-// Two to four tokens through that kernel's two- / four-slot form; kG1NotApplicable likewise (also for another token count and
-// bias folding).
+// Two to four tokens through that kernel's two- to four-slot forms; kG1NotApplicable likewise (also for another token count,
+// bias folding, and three or four tokens that it cannot hand over in fixed point).
 int launch_gemv1b(const GemvArgs& a, int wdt, int flags, hipStream_t stream);
-// The fused block of one token on the same kernel (two launches); kG1NotApplicable likewise.
-// Two-token block: whether launch `part` (0: gate|up with the gating epilogue, 1: down reading the lists) can run on the
-// two- / four-slot kernel, and that launch.  Both use the batched block kernels' list format, so the parts mix with theirs.
+// Block of 2-4 tokens: whether launch `part` (0: gate|up with the gating epilogue, two tokens over int8 weights; 1: down reading
+// the lists, two tokens, or up to four over 16-bit weights) can run on the two- or four-slot kernel, and that launch.  Both use
+// the batched block kernels' list format, so the parts mix with theirs.
 bool swiglu_block2_part_applies(const GemvArgs& up, const GemvArgs& down, int wdt, int part);
 int launch_swiglu_block2_part(const GemvArgs& up, const GemvArgs& down, int wdt, int part, hipStream_t stream);
 // Block of two tokens (int8 weights) with both launches on that kernel, in a list format of their own; kG1NotApplicable likewise,
 // and where the format above is the faster one.
 int launch_swiglu_block2_pair(const GemvArgs& up, const GemvArgs& down, int wdt, int flags, hipStream_t stream);
+// The fused block of one token on the one-token kernel (two launches); kG1NotApplicable likewise.
 int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& down, int wdt, int up_flags, int down_flags,
                          hipStream_t stream);
 
