@@ -515,14 +515,16 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
     const int kg = lane >> 4;  // row group: list rows 4*kg .. 4*kg+3 of a block
     const int col0 = tile * TILE + cg * ELEMS;
-    // Two forms of the row loads.  LONG -- fp16 weights, pieces of 1537-2048 rows, all workgroups on the chip at once (up to two
+    // Two forms of the row loads.  LONG -- fp16 weights and the gate|up launch of a bf16 block, pieces of 1537-2048 rows, all workgroups on the chip at once (up to two
     // per compute unit) -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in
     // registers: 4096 x 28672, 16 tokens, takes 49.9 us instead of 51.1, 8192 x 16384 56.0 instead of 56.5, 14336 x 8192 48.4 instead
-    // of 49.0 (over bf16 weights they take the same).  With shorter pieces it is the slower form (11584 x 7040 38.2 against 37.0, 4096
+    // of 49.0 (over bf16 weights they take the same, but the gating launch, whose epilogue leaves the compiler less room, gains:
+    // block 4096 -> 14336 -> 1024, 16 tokens, 64.9 instead of 65.8, 4096 -> 11008 55.6 / 55.8; 8192 -> 28672, three rounds of
+    // workgroups, 197 against 190 without).  With shorter pieces it is the slower form (11584 x 7040 38.2 against 37.0, 4096
     // x 22016 47.4 against 40.1), over odd input lengths (14337 x 4096, 10 tokens, 34.6 against 31.1), and in launches of more
     // workgroups or of one per unit (12280 x 15296 83.3 against 73.2, 30424 x 4672 77.6 against 61.0; bf16 69.2 and 60.8, 16384 x 28672
     // 185 and 161).
-    static_assert(!LONG || (!X32 && WDT == kF16 && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
+    static_assert(!LONG || (!X32 && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu)) && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
     const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const char* wbase = reinterpret_cast<const char*>(a.W);
@@ -790,7 +792,7 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
     if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
     if constexpr (!RAGGED || is_int8(WDT)) {
         if (a.Kc <= 4 * kInlineWaves * kWave) {
-            if constexpr (!RAGGED && !X32 && WDT == kF16) {
+            if constexpr (!RAGGED && !X32 && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu))) {
                 if (a.Kc > 3 * kInlineWaves * kWave && (long)a.S * a.T <= 512) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4, true>(a, lds, stream);
             }
             return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);

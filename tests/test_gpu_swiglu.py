@@ -430,6 +430,22 @@ def test_ffn_block_full_size_batched(dt, B):
         assert abs(gots[b]["idx_z"].size / F - 0.4) < 0.06
 
 
+# bf16 batches whose gate|up launch runs two workgroups per compute unit, in pieces of more than 1024 rows: up to 512 workgroups
+# in pieces on either side of 1536 rows, and more of them
+@pytest.mark.parametrize("K,F", [(1088, 16448), (1600, 16448), (1600, 32832)])
+def test_blocks_of_long_pieces_and_many_workgroups(K, F):
+    N = 64
+    blk = Block(K, F, N, BF16, seed=3200 + K, std=0.03, B=5)
+    X = wl.laplace(5, K, 3201 + K, BF16, loc=0.1, scale=0.5)
+    zc = oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[0], 0.1, 0.5, 0.0, 0.0, BF16, BF16, nthreads=8)["z"]
+    tau_z = float(np.median(np.abs(zc)))
+    say(f"block of long pieces K={K} F={F}")
+    gots = blk.run_batch(X, BF16, 0.1, 0.5, None, None, 0.0, tau_z, None)
+    for b in (0, 4):
+        want = oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[b], 0.1, 0.5, 0.0, tau_z, BF16, BF16, nthreads=8)
+        blk.compare(gots[b], want, 0.0, tau_z, f"block of long pieces K={K} F={F} token {b}", matrix_cores=True)
+
+
 def test_blocks_on_two_streams_with_their_own_workspaces():
     """Independent blocks (experts of a mixture) may overlap in time when each stream has its own workspace:
     results equal the one-after-the-other results bit for bit."""
