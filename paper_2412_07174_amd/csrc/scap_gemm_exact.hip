@@ -1,0 +1,392 @@
+// Batched sparse FC on the matrix cores where the centred input IS the 16-bit input: m = 0 (inputs that are already
+// centred: everything behind a norm, a GLU block's inputs) or dense mode, activations of the operand's own type (bf16
+// over bf16 and int8 weights, fp16 over fp16 weights).  Then x - m needs no second half, and the pruner can decide on
+// the 16-bit codes:
+//
+//   |x| > tau  <=>  (code & 0x7fff) > code(tau), and no NaN  <=>  (code & 0x7fff) - lo < len  as unsigned 16-bit numbers
+//
+// with code(tau) the largest 16-bit value that is not above tau (exact: a value above tau is above code(tau), too): two
+// elements a lane and instruction.
+//
+// No list and no staging: a wavefront takes steps of 32 rows.  Lane l loads 8 consecutive inputs of token l % 16 (16 bytes; the
+// operand layout of the 32-deep matrix instruction), prunes them in registers -- that is the operand --, ORs the tokens' keep bits
+// over its row of 16 lanes, and asks for its part of the 8 rows; a row that no token keeps is asked for at an offset behind
+// the buffer and costs an issue slot, no memory traffic.  Nothing is exchanged between wavefronts before the sums are added, so the
+// first weight rows are asked for one memory latency after the kernel starts, and a piece may be as long as the layer.
+// The staged-tile kernel (scap_gemm_inline.hip: m != 0) tests and lists a piece before its first row: 3.6 us of 18.7 on 14336 x 4096
+// int8, 12 tokens, 4.3-6.7 of 46 on 4096 x 28672 bf16, 16 tokens, and its pieces have to fit LDS.  Here inputs are 1 KB more per
+// 8 KB of rows (int8: per 4), out of L2.
+//
+// What bounds it: the row stream (6.3 TB/s in 256-byte pieces over a long launch, 7.1 over a short one), then the reduction of eight
+// wavefronts (1 us) and the hand-over (2-3 us).  us per call, staged tile / here: 4096 x 28672 bf16, 16 tokens at 70 %, 47.4 / 39.9;
+// 14336 x 4096 26.2 / 24.7; 4096 x 11008 fp16, 8 tokens at 50 %, 23.5 / 20.0; 14336 x 4096 int8, 12 tokens at 70 %, 19.0 / 16.0;
+// 4096 x 4096 bf16, 8 tokens, 13.1 / 10.2.
+//
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+#include "scap_mfma_parts.hpp"
+
+namespace scap {
+
+constexpr int kStepRows = 32;  // rows of one matrix instruction
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+
+// Elements of the two halves of a word that the pruner drops become 0; flags: 1 in each half that is kept.
+__device__ __forceinline__ uint32_t keep_pair(uint32_t v, u16x2_t lo, u16x2_t len, u16x2_t one, uint32_t& flags) {
+    union { uint32_t u; u16x2_t h; } a, x, f, r;
+    a.u = v & 0x7fff7fffu;
+    x.u = v;
+    f.h = __builtin_elementwise_min(__builtin_elementwise_sub_sat(len, (u16x2_t)(a.h - lo)), one);
+    r.h = x.h * f.h;
+    flags = f.u;
+    return r.u;
+}
+
+// OR over the sixteen lanes of a row
+__device__ __forceinline__ uint32_t or_of_sixteen(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lanes 1,0,3,2 of a quad
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lanes 2,3,0,1
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // mirrored in each half row
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // mirrored in each row
+    return v;
+}
+
+// Per-token counts and lists and the size of the union, on request (the tile's own tokens; the union: tile 0).  kept_tok, kept_any:
+// the calling lane's counts over its rows (lane = token l % 16, row group l / 16).  The lists are read off the inputs once more.
+template <int WAVES, bool RAGGED>
+__device__ __forceinline__ void leave_lists(const GemvArgs& a, int tile, int split, int k0, int kend, int kept_tok, int kept_any,
+                                            const Lds& L) {
+    const uint32_t own = owned_tokens(a, tile);
+    const bool own_union = tile == 0 && a.union_nnz_out != nullptr;
+    if (own == 0 && !own_union) return;
+    const int tid = threadIdx.x;
+    const int w = uniform(tid >> 6);
+    const int lane = tid & 63;
+    const bool dense = a.mode == kModeDense;
+    kept_tok += __shfl_xor(kept_tok, 16, kWave);
+    kept_tok += __shfl_xor(kept_tok, 32, kWave);
+    kept_any += __shfl_xor(kept_any, 16, kWave);
+    kept_any += __shfl_xor(kept_any, 32, kWave);
+    if (lane < kMfmaTokens) L.hdr[(1 + lane) * WAVES + w] = kept_tok;
+    if (lane == 0) L.hdr[w] = kept_any;
+    __syncthreads();
+    if (tid < kMfmaTokens + 1) {
+        int sum = 0;
+        for (int i = 0; i < WAVES; ++i) sum += L.hdr[tid * WAVES + i];
+        if (dense) sum = kend - k0;  // (rows past the last channel were counted)
+        if (tid == 0 ? own_union : (own >> (tid - 1)) & 1u) store_dev(&a.seg_cnt[(tid == 0 ? a.B : tid - 1) * a.Sl + split], sum);
+    }
+    if (a.idx_out == nullptr || own == 0) return;
+    // ascending lists: a wavefront takes a run of 64-channel chunks, its counts first, then the entries
+    const int nchunk = (kend - k0 + kWave - 1) / kWave;
+    const int cpw = (nchunk + WAVES - 1) / WAVES;
+    const int c_begin = min(w * cpw, nchunk), c_end = min(c_begin + cpw, nchunk);
+    auto kept_at = [&](int c, int b) {
+        const int k = k0 + c * kWave + lane;
+        const uint32_t mag = k < kend ? (uint32_t)a.x[(int64_t)b * a.K + k] & 0x7fffu : 0u;
+        return k < kend && (dense || ((mag - a.keep_lo) & 0xffffu) < a.keep_len);
+    };
+    for (int b = 0; b < a.B; ++b) {
+        if (!((own >> b) & 1u)) continue;
+        int n = 0;
+        for (int c = c_begin; c < c_end; ++c) n += __popcll(__ballot(kept_at(c, b)));
+        __syncthreads();  // the counts above, or the token before, have been read
+        if (lane == 0) L.hdr[w] = n;
+        __syncthreads();
+        int at = 0;
+        for (int i = 0; i < w; ++i) at += L.hdr[i];
+        for (int c = c_begin; c < c_end; ++c) {
+            const bool keep = kept_at(c, b);
+            const uint64_t bal = __ballot(keep);
+            if (keep) store_dev(&a.idx_out[(int64_t)b * a.K + k0 + at + lanes_below(bal)], k0 + c * kWave + lane);
+            at += __popcll(bal);
+        }
+    }
+}
+
+// 32 rows against the operand `av`: acc[e] += A * B_e for the ELEMS column elements.  r[j] = this lane's part of row 8*(l/16) + j.
+template <int WDT>
+__device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint32_t (&av)[4], const uint4 (&r)[8]) {
+    constexpr int ELEMS = Vec<WDT>::kElems;
+    uint32_t q[8][4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        q[j][0] = r[j].x;
+        q[j][1] = r[j].y;
+        q[j][2] = r[j].z;
+        q[j][3] = r[j].w;
+    }
+    union Op { uint32_t u[4]; bf16x8_t b; f16x8_t f; } ao;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ao.u[i] = av[i];
+#pragma unroll
+    for (int e = 0; e < ELEMS; ++e) {
+        Op bo;  // rows (0,1), (2,3), ... of column element e
+#pragma unroll
+        for (int pr = 0; pr < 4; ++pr) {
+            const uint32_t* x0 = q[2 * pr];
+            const uint32_t* x1 = q[2 * pr + 1];
+            if constexpr (is_int8(WDT)) {
+                // byte e of each row, sign-extended, as a float: its low 16 bits are zero (|v| <= 128)
+                const int c = e >> 2, sh = 24 - 8 * (e & 3);
+                const uint32_t f0 = __float_as_uint((float)(((int)(x0[c] << sh)) >> 24));
+                const uint32_t f1 = __float_as_uint((float)(((int)(x1[c] << sh)) >> 24));
+                bo.u[pr] = __builtin_amdgcn_perm(f1, f0, 0x07060302u);
+            } else {
+                const int c = e >> 1;
+                bo.u[pr] = __builtin_amdgcn_perm(x1[c], x0[c], (e & 1) ? 0x07060302u : 0x05040100u);
+            }
+        }
+        if constexpr (WDT == kF16)
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ao.f, bo.f, acc[e], 0, 0, 0);
+        else
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao.b, bo.b, acc[e], 0, 0, 0);
+    }
+}
+
+template <int WDT, int FUSE, int BT, bool RAGGED>
+__global__ __launch_bounds__(kInlineWaves* kWave, RAGGED && WDT != kI8Half ? 2 : 4) void gemm_exact_kernel(const GemvArgs a) {
+    constexpr int WAVES = kInlineWaves;
+    constexpr int ELEMS = Vec<WDT>::kElems;
+    constexpr int TILE = 16 * ELEMS;
+
+    extern __shared__ uint4 smem_raw[];
+    Lds L = carve_lds<WAVES, kMfmaTokens>(reinterpret_cast<char*>(smem_raw), 0);
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(true);
+    const int tid = threadIdx.x;
+    const int w = uniform(tid >> 6);
+    const int lane = tid & 63;
+    const int tile = blockIdx.x % a.T;
+    const int split = blockIdx.x / a.T;
+    const int k0 = split * a.Kc;
+    const int kend = min(k0 + a.Kc, a.K);
+
+    const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
+    const int kg = lane >> 4;  // row group: rows 8*kg .. 8*kg+7 of a step
+    const int col0 = tile * TILE + cg * ELEMS;
+    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : kNoRow;
+    const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
+    const __amdgpu_buffer_rsrc_t wbuf = weight_rows(a, k0, row_bytes);
+    const __amdgpu_buffer_rsrc_t xbuf = make_raw_buffer(const_cast<uint16_t*>(a.x), (uint32_t)a.B * (uint32_t)a.K * 2u);
+    const u16x2_t lo = (u16x2_t)((unsigned short)a.keep_lo), len = (u16x2_t)((unsigned short)a.keep_len);
+    // (a 1 that the compiler does not know: it would turn the packed steps into compares and selects, element by element)
+    union { uint32_t u; u16x2_t h; } one = {0x00010001u};
+    asm("" : "+v"(one.u));
+
+    f32x4_t acc[ELEMS];
+#pragma unroll
+    for (int e = 0; e < ELEMS; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    struct Stage {
+        uint4 r[8];
+        uint32_t op[4];
+    };
+    const int n_all = (kend - k0 + kStepRows - 1) / kStepRows;
+    const int n_steps = n_all > w ? (n_all - w + WAVES - 1) / WAVES : 0;  // steps w, w + WAVES, ... of 32 rows
+    int kept_tok = 0, kept_any = 0;  // rows of this lane's group that its token keeps, that any token keeps
+    // inputs of a step: 8 channels of the lane's token; 0 past the last channel and for slots past the batch
+    auto load_x = [&](int st) {
+        const int k = k0 + (w + st * WAVES) * kStepRows + 8 * kg;
+        if constexpr (!RAGGED) {
+            const uint32_t off = k < a.K && cg < a.B ? (uint32_t)(cg * a.K + k) * 2u : kNoRow;
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)off, 0, 0);
+            return make_uint4(v[0], v[1], v[2], v[3]);
+        } else {
+            // rows that start at any 2-byte boundary; the last octet of a token runs into the next token's values, that of the last
+            // token is read element by element
+            const int total = a.B * a.K, p = min(cg, a.B - 1) * a.K + min(k, a.K - 1);
+            uint4 v = total >= 8 ? load_octet(a.x + min(p, total - 8)) : make_uint4(0u, 0u, 0u, 0u);
+            if (p > total - 8) v = load_octet_cut(a.x + p, total - p);
+            const int n = cg < a.B ? a.K - k : 0;  // elements of the octet that exist
+            uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wd[q] = n >= 2 * q + 2 ? wd[q] : (n == 2 * q + 1 ? wd[q] & 0xffffu : 0u);
+            return make_uint4(wd[0], wd[1], wd[2], wd[3]);
+        }
+    };
+    // (Registers: 128 at two workgroups per compute unit, which shapes of more than 256 workgroups need -- 8192 x 28672, 6 tokens, 512-row
+    // pieces 82.3 us against 88.4 with one.  An odd input length takes a few more and runs one.)
+    // Prune the inputs of step st, replace them by those of step `ahead`, and fetch the rows that some token keeps; the others ask
+    // for an offset behind the buffer: nothing is read.  (The inputs go first: loads come back in order, and the next step's test must
+    // not wait for rows.)
+    auto issue = [&](int st, uint4& x, int ahead, Stage& sg) {
+        const uint32_t wd[4] = {x.x, x.y, x.z, x.w};
+        uint32_t f[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sg.op[q] = keep_pair(wd[q], lo, len, one.h, f[q]);
+        const uint32_t t = f[0] | (f[1] << 2) | (f[2] << 4) | (f[3] << 6);
+        const uint32_t mine = (t | (t >> 15)) & 0xffu;  // bit j: row 8*kg + j kept by this token
+        const uint32_t any = or_of_sixteen(mine);
+        kept_tok += __popc(mine);
+        kept_any += __popc(any);
+        x = load_x(ahead);
+        const uint32_t drop = ~any;
+        const uint32_t base = __umul24((uint32_t)((w + st * WAVES) * kStepRows + 8 * kg), row_bytes) + lane_off;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            sg.r[j] = load_row_part<WDT>(wbuf, (base + j * row_bytes) | ((drop << (31 - j)) & kNoRow));
+    };
+    if (n_steps > 0) {
+        uint4 X = load_x(0), Y = load_x(1);
+        Stage A, Bs;
+        issue(0, X, 2, A);
+        int st = 0;
+        for (; st + 2 < n_steps; st += 2) {  // Y: inputs of step st + 1, X: of step st + 2
+            issue(st + 1, Y, st + 3, Bs);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_rows<WDT>(acc, A.op, A.r);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(st + 2, X, st + 4, A);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_rows<WDT>(acc, Bs.op, Bs.r);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // (one way out of the loop: where it also ended between its halves, the compiler waited for all loads in each turn)
+        if (st + 1 < n_steps) {
+            issue(st + 1, Y, st + 3, Bs);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_rows<WDT>(acc, A.op, A.r);
+            mfma_rows<WDT>(acc, Bs.op, Bs.r);
+        } else {
+            mfma_rows<WDT>(acc, A.op, A.r);
+        }
+    }
+
+    leave_lists<WAVES, RAGGED>(a, tile, split, k0, kend, kept_tok, kept_any, L);
+    // constants of the column group this thread finishes if its workgroup is the tile's last arrival
+    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
+    const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
+    reduce_waves_and_emit<WDT, WAVES, FUSE, true, true>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
+    finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
+}
+
+// ---------------------------------------------------------------------------------------------- launch
+bool exact_operand(const GemvArgs& a, int wdt) {
+    if (a.xdt != (wdt == kF16 ? kF16 : kBF16)) return false;
+    return a.mode == kModeDense || (a.mode == kModeSparse && a.m == 0.f);
+}
+
+// The interval of magnitude codes that the pruner keeps: [lo, lo + len) of the 16-bit patterns without their sign.
+void keep_codes(const GemvArgs& a, uint32_t* lo, uint32_t* len) {
+    if (a.mode == kModeDense) {
+        *lo = 0;
+        *len = 0x8000;
+        return;
+    }
+    union { float f; uint32_t u; } t;
+    t.f = a.tau;
+    uint32_t code = (t.u & 0x7fffffffu) >> 16;  // the largest bf16 that is not above tau
+    uint32_t inf = 0x7f80;
+    if (a.xdt == kF16) {
+        const float tau = t.f < 0.f ? 0.f : t.f;  // (-0)
+        inf = 0x7c00;
+        if (tau >= 65504.f) {
+            code = 0x7bff;
+        } else if (tau < 6.103515625e-05f) {
+            code = (uint32_t)(tau * 16777216.f);  // multiples of 2^-24
+        } else {
+            const uint32_t u = t.u & 0x7fffffffu;
+            code = ((u >> 23) - 112u) << 10 | ((u >> 13) & 0x3ffu);
+        }
+    }
+    *lo = code + 1;
+    *len = inf - code;
+}
+
+template <int WDT, int FUSE, int BT, bool RAGGED>
+static int launch_exact_kernel(const GemvArgs& a, size_t lds, hipStream_t stream) {
+    if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
+    if (lds > 64 * 1024) {
+        // more dynamic LDS than the default limit: ask once per kernel and device
+        constexpr int kMaxDevices = 64;
+        static std::atomic<bool> asked[kMaxDevices];
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
+        if (!asked[dev].load(std::memory_order_acquire)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_exact_kernel<WDT, FUSE, BT, RAGGED>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
+                return SCAP_ERR_HIP;
+            asked[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL((gemm_exact_kernel<WDT, FUSE, BT, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave), lds, stream, a);
+    return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
+}
+
+template <int WDT, int FUSE, int BT>
+static int launch_exact_wdt(const GemvArgs& a, size_t lds, hipStream_t stream) {
+    return a.K % 8 == 0 ? launch_exact_kernel<WDT, FUSE, BT, false>(a, lds, stream) : launch_exact_kernel<WDT, FUSE, BT, true>(a, lds, stream);
+}
+
+template <int FUSE, int BT>
+static int launch_exact(const GemvArgs& a, int wdt, size_t lds, hipStream_t stream) {
+    if (wdt == kBF16) return launch_exact_wdt<kBF16, FUSE, BT>(a, lds, stream);
+    if (wdt == kF16) return launch_exact_wdt<kF16, FUSE, BT>(a, lds, stream);
+    return launch_exact_wdt<kI8Half, FUSE, BT>(a, lds, stream);
+}
+
+// K split: fills a.T, a.Kc, a.S (and the list segmentation); kc: the caller's rows per workgroup, or 0.  SCAP_ERR_SHAPE where the
+// layer has more tiles than there are arrival counters.
+//
+// The cost of a split in rows of one workgroup at the rate of a full chip.  Nothing but the weight buffer's offsets bounds a piece
+// (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
+// take: 46 GB/s x 1000 where a full chip has 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
+// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s).  Hence `part` below.  Prologue, reduction and the launch's ends are worth about 192 rows of
+// 256 bytes, half of that for each further round (two workgroups share a unit), and a split's hand-over 7.  From sweeps of all splits
+// over 20 layers, us at the split chosen / the next best: 4096 x 28672 bf16, 16 tokens, S = 1 39.5 / S = 2 44.7; 4096 x 11008, 8
+// tokens, S = 2 19.8 / S = 5 20.1 / S = 3 24.5; 14336 x 4096 S = 8 24.6 / S = 6 26.5; 2048 x 2048 S = 8 7.1 / S = 16 7.5; 8192 x 28672,
+// 6 tokens, S = 1 77.8 / S = 2 81.8, over int8 weights (whose 128-byte pieces leave one workgroup per unit less in flight: 3 % more)
+// S = 2 46.0 / S = 1 49.1.
+static int plan_exact(GemvArgs& a, int wdt, int kc) {
+    a.T = (a.N + kMfmaTile - 1) / kMfmaTile;
+    if (a.T > kMaxTiles) return SCAP_ERR_SHAPE;
+    const bool i8 = wdt == kI8;
+    const int64_t row_bytes = (int64_t)a.N * (i8 ? 1 : 2);
+    const int64_t kc_max = (((int64_t)1 << 31) / row_bytes - 2 * kWave) / kWave * kWave;
+    int64_t s_max = (int64_t)(partial_capacity(a.N) / ((size_t)a.T * kMfmaTile));
+    if (s_max > kMaxSplits) s_max = kMaxSplits;
+    if (kc == 0) {
+        const int fixed = i8 ? 384 : 192, split = i8 ? 14 : 7;
+        double best = 0.0;
+        for (int64_t sp = 1; sp <= s_max; ++sp) {
+            const int64_t c = (int64_t)align_up((size_t)((a.K + sp - 1) / sp), kWave);
+            if (c > kc_max) continue;
+            const int64_t s = (a.K + c - 1) / c, n = s * a.T, rounds = (n + 255) / 256;
+            auto part = [&](int64_t m) { return m == 0 ? 0.0 : std::max(0.55, (i8 && n <= 256 ? 0.28 : 0.25) + 0.75 * (double)m / 256.0); };
+            const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + fixed + fixed * 0.5 * (double)(rounds - 1) + (double)(split * s);
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                kc = (int)c;
+            }
+            if (c == kWave) break;
+        }
+        if (kc == 0) return SCAP_ERR_SHAPE;
+    }
+    if (kc % kWave != 0) return SCAP_ERR_CONFIG;
+    a.S = (a.K + kc - 1) / kc;
+    if (kc > kc_max || a.S > s_max) return SCAP_ERR_SHAPE;
+    a.Kc = kc;
+    a.Kl = a.Kc;
+    a.Sl = a.S;
+    return SCAP_OK;
+}
+
+bool gemm_exact_plans(const GemvArgs& a_in, int wdt) {
+    GemvArgs a = a_in;
+    return plan_exact(a, wdt, 0) == SCAP_OK;
+}
+
+int launch_gemm_exact(const GemvArgs& a_in, int wdt, int fuse, int kc, hipStream_t stream) {
+    GemvArgs a = a_in;
+    if (!exact_operand(a, wdt) || a.B < 1 || a.B > kMfmaTokens) return SCAP_ERR_CONFIG;
+    const int rc = plan_exact(a, wdt, kc);
+    if (rc != SCAP_OK) return rc;
+    keep_codes(a, &a.keep_lo, &a.keep_len);
+    const size_t lds = kHdrBytes + (size_t)tree_floats(true) * 4 + (fuse == kFuseSwiglu ? (size_t)kMfmaTokens * kMfmaTile * 4 : 0);
+    return fuse == kFuseSwiglu ? launch_exact<kFuseSwiglu, kMfmaTokens>(a, wdt, lds, stream)
+                               : launch_exact<kFusePlain, kMfmaTokens>(a, wdt, lds, stream);
+}
+
+}  // namespace scap

@@ -22,42 +22,6 @@
 
 namespace scap {
 
-constexpr size_t kInlineLdsBudget = 160 * 1024;
-constexpr int kInlineWaves = 8;
-constexpr int kTileRows = 2368;       // rows of a workgroup whose 16 token slots fit LDS
-constexpr int kInlineSplitRows = 12;  // rows' time that a K split's hand-over costs (16 token slots)
-// chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
-constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
-
-// LDS floats of the reduction of the wavefronts' sums (and of the final one).  Kernels that run one workgroup per compute
-// unit anyway take all eight wavefronts' sums at once, 64 KB: two barriers and one turn fewer (reduce_waves_and_emit).
-constexpr int tree_floats(bool whole) { return (whole ? 64 : 32) * 1024 / 4; }
-// ... which are the 16-slot launch that reads lists (158 registers) and the 32-deep staged-tile form, 16-bit weights
-__host__ __device__ constexpr bool whole_reduction(int wdt, int bt, int fuse, bool x32) {
-    return wdt != kI8 && bt == 16 && (fuse == kFuseList || x32);
-}
-
-// A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
-// offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
-// were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay
-// below kNoRow: at most 4096 rows of 1024 tiles x 256 bytes.
-constexpr uint32_t kNoRow = 0x80000000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const GemvArgs& a, int k0, uint32_t row_bytes) {
-    return make_raw_buffer(const_cast<char*>(reinterpret_cast<const char*>(a.W)) + (uint64_t)k0 * row_bytes,
-                           (uint32_t)min(a.Kc, a.K - k0) * row_bytes);
-}
-constexpr int kAuxNonTemporal = 1 << 1;  // "nt" bit of the buffer cache policy: see load_weights16
-template <int WDT>
-__device__ __forceinline__ uint4 load_row_part(__amdgpu_buffer_rsrc_t rows, uint32_t off) {
-    if constexpr (WDT == kI8Half) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rows, (int)off, 0, kAuxNonTemporal);
-        return make_uint4(v[0], v[1], 0u, 0u);
-    } else {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, kAuxNonTemporal);
-        return make_uint4(v[0], v[1], v[2], v[3]);
-    }
-}
-
 // FUSE (kFusePlain / kFuseSwiglu / kFuseList) as in the vector kernel: where the inputs come from and what the
 // tile's last arrival does with the finished columns (the two launches of the fused SwiGLU block, Alg. 2).
 template <int WDT, int BT, int FUSE>
@@ -948,8 +912,19 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     const int wdt_in = wdt;
     int bt = 0;
     size_t lds = 0;
+    // 16 token slots, and the centred input is the operand: a kernel of its own.  (Rows that the caller names have to fit here all
+    // the same.)
+    const bool exact = (a.B > 4 || slots16) && exact_operand(a, wdt);
+    if (exact && kc == 0) {
+        const int rc = launch_gemm_exact(a, wdt, kFusePlain, 0, stream);
+        if (rc != SCAP_ERR_SHAPE) return rc;
+    }
     const int rc = plan_inline_lanes(a, &wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
+    if (exact && kc != 0) {
+        const int rc2 = launch_gemm_exact(a_in, wdt_in, kFusePlain, kc, stream);
+        if (rc2 != SCAP_ERR_SHAPE) return rc2;
+    }
     // Layers wider than 4 K and odd lengths: the 4-slot lists where they need fewer workgroups than the tile's LDS allows, or where
     // the tile would run in 16-byte lanes, one workgroup per compute unit, on more of them (or does not exist); two of the lists'
     // share a unit.  3 tokens at 70 %, tile / lists, us: 4096 x 57344 43.8 / 35.4, 6144 x 28672 38.1 / 32.3, 2664 x 56944 39.2 / 32.3,
@@ -977,17 +952,21 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
     int wup = wdt, wdn = wdt;
-    int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
-    if (rc != SCAP_OK) return rc;
-    up.Kl = up.Kc;
-    up.Sl = up.S;
+    const bool up_exact = up.B > 4 && exact_operand(up, wdt) && gemm_exact_plans(up, wdt);
+    int rc = SCAP_OK;
+    if (!up_exact) {
+        rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+        if (rc != SCAP_OK) return rc;
+        up.Kl = up.Kc;
+        up.Sl = up.S;
+    }
     rc = plan_inline_lanes(dn, &wdn, 0, false, kFuseList, &bt_dn, &lds_dn);
     if (rc != SCAP_OK) return rc;
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
     const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
-    rc = launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
+    rc = up_exact ? launch_gemm_exact(up, wdt, kFuseSwiglu, 0, stream) : launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;
     return launch_inline_any<kFuseList>(dn, wdn, bt_dn, lds_dn, stream);
 }

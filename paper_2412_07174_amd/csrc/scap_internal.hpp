@@ -92,6 +92,8 @@ struct GemvArgs {
     int32_t* zl_cnt;  // [1 + BT][ceil(F/64)] entries per segment: union first, then per token; [ceil(F/32)]: the three
                       // counts in the low bytes of one word, union lowest
     int F;            // channels of the gated product (half the columns of the gate|up launch)
+    // exact-operand kernel (scap_gemm_exact.hip): the magnitude codes [keep_lo, keep_lo + keep_len) are kept
+    uint32_t keep_lo, keep_len;
 };
 
 // Enqueue one GEMV (sparse / dense / fold mode).  Returns a scap_status.
@@ -143,6 +145,12 @@ int launch_gemm_mfma(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hip
 // The same in one launch: each workgroup compacts its own inputs into LDS (up to 160 KB on gfx950).
 // SCAP_ERR_SHAPE when the input is too long to split into LDS-sized pieces.
 int launch_gemm_inline(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStream_t stream, bool slots16 = false);
+// Whether the centred input is the 16-bit operand itself (m = 0 or dense mode, activations of the operand's type), and the launch
+// for such inputs, 16 token slots (scap_gemm_exact.hip).  kc: rows per workgroup, or 0.  SCAP_ERR_SHAPE where it cannot split the layer
+// (gemm_exact_plans: whether it can by itself).
+bool exact_operand(const GemvArgs& a, int wdt);
+bool gemm_exact_plans(const GemvArgs& a, int wdt);
+int launch_gemm_exact(const GemvArgs& a, int wdt, int fuse, int kc, hipStream_t stream);
 // The fused block's two launches on the same kernel (bf16 / int8, up to 16 tokens).
 int launch_swiglu_block_inline(const GemvArgs& up, const GemvArgs& down, int wdt, hipStream_t stream);
 

@@ -180,6 +180,43 @@ __device__ __forceinline__ void mfma_block32(f32x4_t* __restrict__ acc, const s1
     }
 }
 
+// ---------------------------------------------------------------------------------------------- single-launch kernels
+constexpr size_t kInlineLdsBudget = 160 * 1024;
+constexpr int kInlineWaves = 8;
+constexpr int kTileRows = 2368;       // rows of a workgroup whose 16 token slots fit LDS
+constexpr int kInlineSplitRows = 12;  // rows' time that a K split's hand-over costs (16 token slots)
+// chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
+constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
+
+// LDS floats of the reduction of the wavefronts' sums (and of the final one).  Kernels that run one workgroup per compute
+// unit anyway take all eight wavefronts' sums at once, 64 KB: two barriers and one turn fewer (reduce_waves_and_emit).
+constexpr int tree_floats(bool whole) { return (whole ? 64 : 32) * 1024 / 4; }
+// ... which are the 16-slot launch that reads lists (158 registers) and the 32-deep staged-tile form, 16-bit weights
+__host__ __device__ constexpr bool whole_reduction(int wdt, int bt, int fuse, bool x32) {
+    return wdt != kI8 && bt == 16 && (fuse == kFuseList || x32);
+}
+
+// A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
+// offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
+// were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay
+// below kNoRow: at most 4096 rows of 1024 tiles x 256 bytes.
+constexpr uint32_t kNoRow = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const GemvArgs& a, int k0, uint32_t row_bytes) {
+    return make_raw_buffer(const_cast<char*>(reinterpret_cast<const char*>(a.W)) + (uint64_t)k0 * row_bytes,
+                           (uint32_t)min(a.Kc, a.K - k0) * row_bytes);
+}
+constexpr int kAuxNonTemporal = 1 << 1;  // "nt" bit of the buffer cache policy: see load_weights16
+template <int WDT>
+__device__ __forceinline__ uint4 load_row_part(__amdgpu_buffer_rsrc_t rows, uint32_t off) {
+    if constexpr (WDT == kI8Half) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rows, (int)off, 0, kAuxNonTemporal);
+        return make_uint4(v[0], v[1], 0u, 0u);
+    } else {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, kAuxNonTemporal);
+        return make_uint4(v[0], v[1], v[2], v[3]);
+    }
+}
+
 // Every wavefront holds a full [16 tokens x TILE columns] tile of sums in the same lane layout
 // (acc[e][i] = token 4*(l/16) + i, column ELEMS*(l%16) + e of the tile).  They are added through LDS (32 KB at
 // s_tree) in a fixed order and emitted by one thread per (token, 4-column group).  Ends with a barrier.

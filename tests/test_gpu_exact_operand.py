@@ -1,0 +1,141 @@
+"""Batches whose centred input is the matrix operand itself (m = 0 or dense mode, activations of the operand's type): the kernel that
+tests the 16-bit codes and reads its operands straight from the inputs, at the sizes where it can go wrong -- steps of 32 rows
+(remainders, fewer than eight wavefronts' worth, one row), input lengths that are not a multiple of 8, columns that end inside a
+tile, 8 and 9 tokens -- against the CPU oracle, and its rule on codes against the fp32 comparison for every code."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2412_07174_amd as scap
+import workloads as wl
+from workloads import BF16, F16, I8
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from gpu_util import Layer, check_against_oracle, f32_dev, gpu_sparse_fc, to_dev
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def layer_of(K, N, dt, seed, B=16):
+    if dt == I8:
+        W, sc = wl.quantize_i8(K, N, seed, std=0.05)
+        return Layer(W, dt, sc, B=B)
+    return Layer(wl.weights(K, N, seed, dt, std=0.05), dt, B=B)
+
+
+def wide(layer):
+    if layer.wdt == I8:
+        return layer.W_host.astype(np.float64) * wl.decode(layer.scale_host, F16).astype(np.float64)[None, :]
+    return wl.decode(layer.W_host, layer.wdt).astype(np.float64)
+
+
+def sums_within_fp32(got, layer, D, bias, what):
+    """Every result within the bound of an fp32 sum of its exact products, in any order: (terms + 2) * 2^-24 * sum |d w|, one more
+    rounding for the column scale and the bias."""
+    W = wide(layer)
+    want = D.astype(np.float64) @ W + (0.0 if bias is None else bias.astype(np.float64)[None, :])
+    bound = (np.count_nonzero(D, axis=1)[:, None] + 4) * 2.0 ** -24 * (np.abs(D) @ np.abs(W)) + 2.0 ** -22 * np.abs(want) + 1e-30
+    off = np.abs(got - want)
+    assert np.all(off <= bound), f"{what}: {np.max(off / bound)} times the bound"
+
+
+SHAPES = [
+    # K, N: one row, less than a step, around one step, around eight steps, odd lengths, ragged tiles, several splits
+    (1, 16), (8, 16), (31, 144), (32, 128), (33, 272), (255, 128), (256, 1040), (264, 2048), (777, 144), (1000, 4112), (4097, 528),
+    (4096, 1024), (2048, 128),
+]
+
+
+@pytest.mark.parametrize("dt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,N", SHAPES)
+def test_exact_operand_shapes(K, N, dt):
+    layer = layer_of(K, N, dt, 9100 + K)
+    xdt = F16 if dt == F16 else BF16
+    bias = np.random.default_rng(K + N).standard_normal(N).astype(np.float32)
+    X = wl.laplace(16, K, 9200 + K, xdt, loc=0.0, scale=0.6)
+    Xf = wl.decode(X, xdt).astype(np.float64)
+    for B, tau in ((5, 0.0), (8, 0.41), (9, 1.4), (16, 0.3), (16, 1e6)):
+        say(f"exact operand K={K} N={N} dt={dt} B={B} tau={tau}")
+        got, _ = check_against_oracle(layer, X[:B], xdt, 0.0, tau, bias, what=f"K={K} N={N} B={B} tau={tau}")
+        D = np.where(np.abs(Xf[:B]) > np.float32(tau), Xf[:B], 0.0)
+        sums_within_fp32(got["y"], layer, D, bias, f"K={K} N={N} B={B} tau={tau}")
+        plain = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
+        scap.sparse_fc(layer.W, to_dev(X[:B], xdt), 0.0, tau, f32_dev(bias), col_scale=layer.scale, y=plain, workspace=layer.ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(plain.cpu().numpy().view(np.uint32), got["y"].view(np.uint32)), "y depends on the outputs requested"
+        # the general vector kernel: the same channels
+        if K >= 64:
+            other = gpu_sparse_fc(layer, X[:B], xdt, 0.0, tau, bias, cfg=(0, 0, 0, 64))
+            assert np.array_equal(other["nnz"], got["nnz"]) and other["union_nnz"] == got["union_nnz"]
+            assert all(np.array_equal(other["idx"][b], got["idx"][b]) for b in range(B))
+    say(f"exact operand, dense mode K={K} N={N} dt={dt}")
+    y = scap.dense_fc(layer.W, to_dev(X[:7], xdt), f32_dev(bias), col_scale=layer.scale, workspace=layer.ws)
+    torch.cuda.synchronize()
+    sums_within_fp32(y.cpu().numpy(), layer, Xf[:7], bias, f"dense K={K} N={N}")
+
+
+@pytest.mark.parametrize("dt", [BF16, F16])
+def test_every_code_against_thresholds(dt):
+    """All 65536 codes as inputs (subnormals, both zeros, infinities, NaN): kept exactly where the fp32 comparison keeps them, at
+    thresholds on codes, between two codes, below the smallest and above the largest."""
+    K, B = 8192, 8
+    codes = np.arange(65536, dtype=np.uint16).reshape(B, K)
+    val = wl.decode(codes, dt).astype(np.float32)
+    layer = Layer(np.zeros((K, 16), dtype=np.uint16), dt, B=B)
+    rng = np.random.default_rng(5)
+    fin = np.abs(val[np.isfinite(val)])
+    taus = [0.0, -0.0, float(fin.max()), float(np.nextafter(np.float32(fin.max()), np.float32(0))), 3.0e38, 1e-45, 65504.0, 65503.0, 65520.0, 6.1e-5,
+            float(np.float32(2.0) ** -14), float(np.float32(2.0) ** -24)]
+    for v in rng.choice(fin, 12):
+        taus += [float(v), float(np.nextafter(v, np.float32(0))), float(np.nextafter(v, np.float32(3e38)))]
+    for tau in taus:
+        tau = float(np.float32(tau))
+        say(f"codes dt={dt} tau={tau}")
+        got = gpu_sparse_fc(layer, codes, dt, 0.0, tau, None)
+        with np.errstate(invalid="ignore"):
+            keep = np.abs(val) > np.float32(tau)
+        for b in range(B):
+            assert np.array_equal(got["idx"][b], np.nonzero(keep[b])[0]), (tau, b)
+        assert got["union_nnz"] == int(keep.any(axis=0).sum())
+
+
+def test_values_that_are_not_finite():
+    """Infinities are kept and reach every column of their token, and no other token; NaN inputs are pruned, and kept in dense mode.
+    What lies behind the last channel of an odd-length row (the next token's values) takes no part."""
+    for K, dt in ((4096, BF16), (777, F16), (1001, BF16)):
+        layer = layer_of(K, 144, dt, 9400 + K)
+        X = wl.laplace(9, K, 9401 + K, dt, loc=0.0, scale=0.6)
+        inf, nan = (0x7C00, 0x7E00) if dt == F16 else (0x7F80, 0x7FC0)
+        X[3, 5] = inf
+        X[4, 0] = nan | 0x8000
+        X[6, K - 1] = nan
+        X[8, 0] = nan
+        say(f"not finite K={K} dt={dt}")
+        check_against_oracle(layer, X, dt, 0.0, 0.3, None, what=f"not finite K={K}")
+        y = scap.dense_fc(layer.W, to_dev(X, dt), None, workspace=layer.ws)
+        torch.cuda.synchronize()
+        bad = ~np.isfinite(y.cpu().numpy()).all(axis=1)
+        assert np.array_equal(np.nonzero(bad)[0], [3, 4, 6, 8])
+
+
+@pytest.mark.parametrize("dt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
+def test_exact_operand_blocks(K, F, N, B, dt):
+    """The block's gate|up launch on this kernel (centred inputs) against the oracle, token by token."""
+    from test_gpu_swiglu import Block
+    blk = Block(K, F, N, dt, seed=9500 + K, B=B)
+    xdt = F16 if dt == F16 else BF16
+    X = wl.laplace(B, K, 9501 + K, xdt, loc=0.0, scale=0.8)
+    zs = np.abs(oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[0], 0.0, 0.5, 0.0, 0.0, dt, xdt, gate_scale=blk.sg, up_scale=blk.su,
+                                    down_scale=blk.sd)["z"])
+    for tau_x, tau_z in ((0.0, 0.0), (0.5, float(np.median(zs))), (1.1, float(np.quantile(zs, 0.9)))):
+        say(f"exact operand block K={K} F={F} N={N} B={B} dt={dt} tau_x={tau_x} tau_z={tau_z:.4g}")
+        blk.check_batch(X, xdt, 0.0, tau_x, None, None, 0.0, tau_z, None, f"exact operand block {K} {F} {N} {B}")
