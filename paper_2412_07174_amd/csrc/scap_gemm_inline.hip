@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    constexpr bool WHOLE = whole_reduction(WDT, BT, FUSE, false);
+    constexpr bool WHOLE = false;
     if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);  // behind both uses of the reduction buffer
     const int tid = threadIdx.x;
     const int w = uniform(tid >> 6);
@@ -444,10 +444,9 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
     return cnt;
 }
 
-// X32: the 32-deep matrix instruction (bf16 / fp16 weights).  It needs 178-180 registers per lane against 109-125, i.e. one
-// workgroup per compute unit instead of two, so launches of more than 256 workgroups keep the 16-deep form.
-template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC, bool LONG>
-__global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
+// ALONE: one workgroup per compute unit (int8 weights in 16-byte lanes, 194 registers); the others leave room for two.
+template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC, bool LONG>
+__global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
     constexpr int ELEMS = Vec<WDT>::kElems;
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    constexpr bool WHOLE = whole_reduction(WDT, BT, FUSE, X32);
+    constexpr bool WHOLE = false;
     if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);
     char* xs = reinterpret_cast<char*>(L.idx + a.Kc);  // staged inputs [16][Kc * 2 + pad] in place of the value lists
     const uint32_t xrow = (uint32_t)a.Kc * 2 + kRawPad;
@@ -488,7 +487,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     // x 22016 47.4 against 40.1), over odd input lengths (14337 x 4096, 10 tokens, 34.6 against 31.1), and in launches of more
     // workgroups or of one per unit (12280 x 15296 83.3 against 73.2, 30424 x 4672 77.6 against 61.0; bf16 69.2 and 60.8, 16384 x 28672
     // 185 and 161).
-    static_assert(!LONG || (!X32 && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu)) && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
+    static_assert(!LONG || (!ALONE && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu)) && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
     const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const char* wbase = reinterpret_cast<const char*>(a.W);
@@ -507,7 +506,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
     // as much time in the load pipe as a stage of rows (removing the one stage that the loop issued in vain: 1024 x 4096
     // bf16, 16 tokens, 9.7 -> 9.1 us, 4096 x 4096 13.8 -> 13.1; a second one added 1.2 us).  In the 16-deep form over 16-bit
     // weights the copy of the stage behind the loop does not fit the 128 registers of two workgroups per unit.
-    constexpr bool TAIL = X32 || is_int8(WDT);
+    constexpr bool TAIL = is_int8(WDT);
     struct Rows {
         int4 rows;
         int left;  // valid entries from this lane's first one on (<= 0: none)
@@ -555,146 +554,78 @@ __global__ __launch_bounds__(kInlineWaves* kWave, X32 || WDT == kI8 ? 2 : 4) voi
         }
         st.d = make_float4(dm[0], dm[1], dm[2], dm[3]);
     };
-    if constexpr (!X32) {
-        // (int8 weights always: with 16 columns per lane the 32-deep form measured slower,
-        // 14336 x 4096, 16 tokens: 23.3 against 24.8 us; with 8 columns 14336 x 4096, 5 tokens, 18.3 against 19.4)
-        auto compute = [&](const Stage& st) {
-            s16x4_t a_hi, a_lo;
-            split_operand<WDT>(st.d, a_hi, a_lo);
-            mfma_block<WDT>(acc, a_hi, a_lo, st.r);
-        };
-        if constexpr (LONG) {
-            Rows R;
-            Entries E0, E1;
-            Stage A, Bs;
-            rows_of(w, R);
+    auto compute = [&](const Stage& st) {
+        s16x4_t a_hi, a_lo;
+        split_operand<WDT>(st.d, a_hi, a_lo);
+        mfma_block<WDT>(acc, a_hi, a_lo, st.r);
+    };
+    if constexpr (LONG) {
+        Rows R;
+        Entries E0, E1;
+        Stage A, Bs;
+        rows_of(w, R);
+        codes_of(R, E0);
+        rows_of(w + WAVES, R);
+        codes_of(R, E1);
+        rows_of(w + 2 * WAVES, R);
+        issue(E0, A);
+        for (int blk = w; blk < n_blocks;) {
             codes_of(R, E0);
-            rows_of(w + WAVES, R);
+            rows_of(blk + 3 * WAVES, R);
+            issue(E1, Bs);
+            compute(A);
+            blk += WAVES;
+            if (blk >= n_blocks) break;
             codes_of(R, E1);
-            rows_of(w + 2 * WAVES, R);
+            rows_of(blk + 3 * WAVES, R);
             issue(E0, A);
-            for (int blk = w; blk < n_blocks;) {
-                codes_of(R, E0);
-                rows_of(blk + 3 * WAVES, R);
-                issue(E1, Bs);
-                compute(A);
-                blk += WAVES;
-                if (blk >= n_blocks) break;
-                codes_of(R, E1);
-                rows_of(blk + 3 * WAVES, R);
-                issue(E0, A);
-                compute(Bs);
-                blk += WAVES;
-            }
-        } else if (w < n_blocks) {
-            Rows R;
-            Entries E;
-            Stage A, Bs;
-            rows_of(w, R);
-            codes_of(R, E);
-            rows_of(w + WAVES, R);
-            issue(E, A);
-            codes_of(R, E);
-            rows_of(w + 2 * WAVES, R);
-            if constexpr (TAIL) {
-                int blk = w;
-                for (;;) {
-                    if (blk + WAVES >= n_blocks) break;
-                    issue(E, Bs);
-                    codes_of(R, E);
-                    rows_of(blk + 3 * WAVES, R);
-                    compute(A);
-                    blk += WAVES;
-                    if (blk + WAVES >= n_blocks) {
-                        A = Bs;
-                        break;
-                    }
-                    issue(E, A);
-                    codes_of(R, E);
-                    rows_of(blk + 3 * WAVES, R);
-                    compute(Bs);
-                    blk += WAVES;
-                }
-                compute(A);
-            } else {
-                for (int blk = w; blk < n_blocks;) {
-                    issue(E, Bs);
-                    codes_of(R, E);
-                    rows_of(blk + 3 * WAVES, R);
-                    compute(A);
-                    blk += WAVES;
-                    if (blk >= n_blocks) break;
-                    issue(E, A);
-                    codes_of(R, E);
-                    rows_of(blk + 3 * WAVES, R);
-                    compute(Bs);
-                    blk += WAVES;
-                }
-            }
+            compute(Bs);
+            blk += WAVES;
         }
-    } else {
-        // The matrix instruction is 32 rows deep (gfx950's 16x16x32): a wavefront's blocks are taken two at a time,
-        // block w + 2p*WAVES in k-slots 0-3 of every lane and block w + (2p+1)*WAVES in k-slots 4-7.  A pair whose
-        // second block lies past the end of the list carries zeros there.
-        struct Rows2 {
-            Rows a, b;
-        };
-        struct Entries2 {
-            Entries a, b;
-        };
-        struct Stage2 {
-            Stage a, b;
-        };
-        auto rows2_of = [&](int pr, Rows2& rw) {
-            rows_of(w + 2 * pr * WAVES, rw.a);
-            rows_of(w + (2 * pr + 1) * WAVES, rw.b);
-        };
-        auto codes2_of = [&](const Rows2& rw, Entries2& en) {
-            codes_of(rw.a, en.a);
-            codes_of(rw.b, en.b);
-        };
-        auto issue2 = [&](const Entries2& en, Stage2& st) {
-            issue(en.a, st.a);
-            issue(en.b, st.b);
-        };
-        auto compute2 = [&](const Stage2& st) {
-            s16x4_t a_hi[2], a_lo[2];
-            split_operand<WDT>(st.a.d, a_hi[0], a_lo[0]);
-            split_operand<WDT>(st.b.d, a_hi[1], a_lo[1]);
-            const uint4 r8[8] = {st.a.r[0], st.a.r[1], st.a.r[2], st.a.r[3], st.b.r[0], st.b.r[1], st.b.r[2], st.b.r[3]};
-            mfma_block32<WDT>(acc, a_hi, a_lo, r8);
-        };
-        const int n_mine = n_blocks > w ? (n_blocks - w + WAVES - 1) / WAVES : 0;  // blocks w, w + WAVES, ...
-        const int n_pairs = (n_mine + 1) / 2;
-
-        if (n_pairs > 0) {
-            Rows2 R;
-            Entries2 E;
-            Stage2 A, Bs;
-            rows2_of(0, R);
-            codes2_of(R, E);
-            rows2_of(1, R);
-            issue2(E, A);
-            codes2_of(R, E);
-            rows2_of(2, R);
-            int pr = 0;
+    } else if (w < n_blocks) {
+        Rows R;
+        Entries E;
+        Stage A, Bs;
+        rows_of(w, R);
+        codes_of(R, E);
+        rows_of(w + WAVES, R);
+        issue(E, A);
+        codes_of(R, E);
+        rows_of(w + 2 * WAVES, R);
+        if constexpr (TAIL) {
+            int blk = w;
             for (;;) {
-                if (pr + 1 >= n_pairs) break;
-                issue2(E, Bs);
-                codes2_of(R, E);
-                rows2_of(pr + 3, R);
-                compute2(A);
-                if (++pr + 1 >= n_pairs) {
+                if (blk + WAVES >= n_blocks) break;
+                issue(E, Bs);
+                codes_of(R, E);
+                rows_of(blk + 3 * WAVES, R);
+                compute(A);
+                blk += WAVES;
+                if (blk + WAVES >= n_blocks) {
                     A = Bs;
                     break;
                 }
-                issue2(E, A);
-                codes2_of(R, E);
-                rows2_of(pr + 3, R);
-                compute2(Bs);
-                ++pr;
+                issue(E, A);
+                codes_of(R, E);
+                rows_of(blk + 3 * WAVES, R);
+                compute(Bs);
+                blk += WAVES;
             }
-            compute2(A);
+            compute(A);
+        } else {
+            for (int blk = w; blk < n_blocks;) {
+                issue(E, Bs);
+                codes_of(R, E);
+                rows_of(blk + 3 * WAVES, R);
+                compute(A);
+                blk += WAVES;
+                if (blk >= n_blocks) break;
+                issue(E, A);
+                codes_of(R, E);
+                rows_of(blk + 3 * WAVES, R);
+                compute(Bs);
+                blk += WAVES;
+            }
         }
     }
 
@@ -730,7 +661,7 @@ static int launch_inline(const GemvArgs& a, size_t lds, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool X32, bool RAGGED, int MAXC, bool LONG = false>
+template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC, bool LONG = false>
 static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
     if (lds > 64 * 1024) {
@@ -739,30 +670,34 @@ static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t s
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC, LONG>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC, LONG>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, X32, RAGGED, MAXC, LONG>), dim3((unsigned)(a.S * a.T)),
+    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC, LONG>), dim3((unsigned)(a.S * a.T)),
                        dim3(kInlineWaves * kWave), lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool X32, bool RAGGED>
+template <int WDT, int FUSE, bool ALONE, bool RAGGED>
 static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) {
-    if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 1>(a, lds, stream);
-    if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 2>(a, lds, stream);
+    if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 1>(a, lds, stream);
+    if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 2>(a, lds, stream);
     if constexpr (!RAGGED || is_int8(WDT)) {
         if (a.Kc <= 4 * kInlineWaves * kWave) {
-            if constexpr (!RAGGED && !X32 && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu))) {
-                if (a.Kc > 3 * kInlineWaves * kWave && (long)a.S * a.T <= 512) return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4, true>(a, lds, stream);
+            if constexpr (!RAGGED && !ALONE && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu))) {
+                if (a.Kc > 3 * kInlineWaves * kWave && (long)a.S * a.T <= 512) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 4, true>(a, lds, stream);
             }
-            return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, 4>(a, lds, stream);
+            return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 4>(a, lds, stream);
         }
     }
-    return launch_inline_raw_chunks<WDT, FUSE, X32, RAGGED, kRawChunks>(a, lds, stream);
+    // (the gating launch over narrow int8 tiles: pieces of at most four chunks, plan_inline)
+    if constexpr (WDT == kI8Half && FUSE == kFuseSwiglu && !RAGGED)
+        return SCAP_ERR_SHAPE;
+    else
+        return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, kRawChunks>(a, lds, stream);
 }
 
 // 16 token slots: the staged-tile kernel, or the value-list kernel where the inputs are the gated product's lists;
@@ -776,7 +711,7 @@ template <int WDT, int FUSE>
 static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t stream) {
     if (bt == kMfmaTokens) {
         if constexpr (FUSE == kFuseList) {
-            return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
+            return SCAP_ERR_CONFIG;  // (16 slots: planes instead of lists, scap_gemm_rows.hip)
         } else {
             if constexpr (WDT == kI8) {
                 if (!staged_tile(WDT, a.K)) return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
@@ -784,9 +719,8 @@ static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t 
                 if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
             } else {
                 if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
-                if ((long)a.S * a.T <= 256) return launch_inline_raw<WDT, FUSE, true, false>(a, lds, stream);
             }
-            return launch_inline_raw<WDT, FUSE, false, false>(a, lds, stream);
+            return launch_inline_raw<WDT, FUSE, WDT == kI8, false>(a, lds, stream);
         }
     }
     if constexpr (WDT == kF16 || WDT == kI8Half)
@@ -819,6 +753,8 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
         kc_cap = 64 * kWave;  // gather_lists: at most 64 segments of 64 channels per workgroup
     } else {
         kc_cap = kInlineWaves * kWave * inline_max_chunks(bt);
+        // (a fifth chunk there takes the gating form past its scalar registers)
+        if (wdt == kI8Half && fuse == kFuseSwiglu && bt == kMfmaTokens) kc_cap = kInlineWaves * kWave * 4;
     }
     const size_t by_cap = kHdrBytes + (size_t)kc_cap * 4 * (1 + bt);
     if (by_cap < budget) budget = by_cap;
@@ -829,8 +765,7 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget, kWave, sc);
     if (rc != SCAP_OK) return rc;
     if (a.Kc > kc_cap) return SCAP_ERR_SHAPE;
-    const bool x32 = wdt != kI8Half && staged_tile(wdt, a.K) && a.K % 8 == 0 && (int64_t)a.S * a.T <= 256;  // (as launch_inline_wdt chooses)
-    size_t red = (size_t)tree_floats(whole_reduction(wdt, bt, fuse, x32)) * 4;
+    size_t red = (size_t)tree_floats(false) * 4;
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
     *lds_out = lds_bytes(a.Kc, bt, red);
@@ -914,15 +849,16 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     size_t lds = 0;
     // 16 token slots, and the centred input is the operand: a kernel of its own.  (Rows that the caller names have to fit here all
     // the same.)
-    const bool exact = (a.B > 4 || slots16) && exact_operand(a, wdt);
+    const int src = exact_operand(a, wdt) ? kRowsCodes : kRowsCentre;
+    const bool exact = a.B > 4 || (slots16 && (src == kRowsCodes || wdt != kI8 || a.B == 4));
     if (exact && kc == 0) {
-        const int rc = launch_gemm_exact(a, wdt, kFusePlain, 0, stream);
+        const int rc = launch_gemm_rows(a, wdt, src, kFusePlain, 0, stream);
         if (rc != SCAP_ERR_SHAPE) return rc;
     }
     const int rc = plan_inline_lanes(a, &wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
     if (exact && kc != 0) {
-        const int rc2 = launch_gemm_exact(a_in, wdt_in, kFusePlain, kc, stream);
+        const int rc2 = launch_gemm_rows(a_in, wdt_in, src, kFusePlain, kc, stream);
         if (rc2 != SCAP_ERR_SHAPE) return rc2;
     }
     // Layers wider than 4 K and odd lengths: the 4-slot lists where they need fewer workgroups than the tile's LDS allows, or where
@@ -952,21 +888,35 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
     int wup = wdt, wdn = wdt;
-    const bool up_exact = up.B > 4 && exact_operand(up, wdt) && gemm_exact_plans(up, wdt);
-    int rc = SCAP_OK;
-    if (!up_exact) {
-        rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+    if (up.B > 4) {
+        // 16 token slots: the gated product travels as planes of operand halves, and the down launch takes them row step by row step
+        const int src = exact_operand(up, wdt) ? kRowsCodes : kRowsCentre;
+        const bool codes = gemm_rows_plans(up, wdt, src);
+        if (!codes) {
+            const int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+            if (rc != SCAP_OK) return rc;
+            up.Kl = up.Kc;
+            up.Sl = up.S;
+        }
+        if (!gemm_rows_plans(dn, wdt, kRowsPlanes)) return SCAP_ERR_SHAPE;
+        up.zl_lo = dn.zl_lo = reinterpret_cast<uint16_t*>(up.zl_d) + (size_t)kMfmaTokens * plane_pitch(up.F);
+        dn.seg_cnt = up.seg_cnt;
+        const int rc = codes ? launch_gemm_rows(up, wdt, src, kFuseSwiglu, 0, stream)
+                             : launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
         if (rc != SCAP_OK) return rc;
-        up.Kl = up.Kc;
-        up.Sl = up.S;
+        return launch_gemm_rows(dn, wdt, kRowsPlanes, kFusePlain, 0, stream);
     }
+    int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+    if (rc != SCAP_OK) return rc;
+    up.Kl = up.Kc;
+    up.Sl = up.S;
     rc = plan_inline_lanes(dn, &wdn, 0, false, kFuseList, &bt_dn, &lds_dn);
     if (rc != SCAP_OK) return rc;
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
     const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
-    rc = up_exact ? launch_gemm_exact(up, wdt, kFuseSwiglu, 0, stream) : launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
+    rc = launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;
     return launch_inline_any<kFuseList>(dn, wdn, bt_dn, lds_dn, stream);
 }

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kCompactWaves * kWave) void batch_union_kernel(cons
                 if (e >= 0 && e < total) dv[j] = s_val[e][tok];
             }
             s16x4_t hi, lo;
-            split_bf16x4(d, hi, lo);
+            split_operand<kBF16>(d, hi, lo);
             union { uint4 q4; short h[8]; } pk;
             pk.q4 = prev;
 #pragma unroll

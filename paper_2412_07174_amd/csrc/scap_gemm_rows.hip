@@ -53,9 +53,31 @@ __device__ __forceinline__ uint32_t or_of_sixteen(uint32_t v) {
     return v;
 }
 
+template <int N> struct Words { uint32_t w[N]; };
+
+// Two centred values as a word of heads and a word of tails (split_halves, two at a time).
+template <int WDT>
+__device__ __forceinline__ void split_pair(float d0, float d1, uint32_t& hi, uint32_t& lo) {
+    if constexpr (WDT == kF16) {
+        const uint32_t a = split_halves<WDT>(d0), b = split_halves<WDT>(d1);
+        hi = (a & 0xffffu) | (b << 16);
+        lo = (a >> 16) | (b & 0xffff0000u);
+    } else {
+        typedef float f32x2_t __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+        union { bf16x2_t b; uint32_t u; } h, l;  // (round to nearest even, as split_halves does)
+        h.b = __builtin_convertvector((f32x2_t{d0, d1}), bf16x2_t);
+        const bool fin0 = (h.u & 0x7f80u) != 0x7f80u, fin1 = (h.u & 0x7f800000u) != 0x7f800000u;  // an infinite head has no tail
+        l.b = __builtin_convertvector((f32x2_t{fin0 ? d0 - __uint_as_float(h.u << 16) : 0.f,
+                                               fin1 ? d1 - __uint_as_float(h.u & 0xffff0000u) : 0.f}), bf16x2_t);
+        hi = h.u;
+        lo = l.u;
+    }
+}
+
 // Per-token counts and lists and the size of the union, on request (the tile's own tokens; the union: tile 0).  kept_tok, kept_any:
 // the calling lane's counts over its rows (lane = token l % 16, row group l / 16).  The lists are read off the inputs once more.
-template <int WAVES, bool RAGGED>
+template <int WAVES, int SRC>
 __device__ __forceinline__ void leave_lists(const GemvArgs& a, int tile, int split, int k0, int kend, int kept_tok, int kept_any,
                                             const Lds& L) {
     const uint32_t own = owned_tokens(a, tile);
@@ -85,8 +107,14 @@ __device__ __forceinline__ void leave_lists(const GemvArgs& a, int tile, int spl
     const int c_begin = min(w * cpw, nchunk), c_end = min(c_begin + cpw, nchunk);
     auto kept_at = [&](int c, int b) {
         const int k = k0 + c * kWave + lane;
-        const uint32_t mag = k < kend ? (uint32_t)a.x[(int64_t)b * a.K + k] & 0x7fffu : 0u;
-        return k < kend && (dense || ((mag - a.keep_lo) & 0xffffu) < a.keep_len);
+        if (k >= kend) return false;
+        const int64_t at = (int64_t)b * a.x_pitch + k;
+        if constexpr (SRC == kRowsPlanes)
+            return (a.x[at] | a.zl_lo[at]) != 0;
+        else if constexpr (SRC == kRowsCentre)
+            return dense || fabsf(act_to_f32(a.x, at, a.xdt) - a.m) > a.tau;
+        else
+            return dense || ((((uint32_t)a.x[at] & 0x7fffu) - a.keep_lo) & 0xffffu) < a.keep_len;
     };
     for (int b = 0; b < a.B; ++b) {
         if (!((own >> b) & 1u)) continue;
@@ -107,8 +135,9 @@ __device__ __forceinline__ void leave_lists(const GemvArgs& a, int tile, int spl
 }
 
 // 32 rows against the operand `av`: acc[e] += A * B_e for the ELEMS column elements.  r[j] = this lane's part of row 8*(l/16) + j.
-template <int WDT>
-__device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint32_t (&av)[4], const uint4 (&r)[8]) {
+// HALVES = 2: av[4..7] are the operand's tails.
+template <int WDT, int HALVES>
+__device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint32_t (&av)[4 * HALVES], const uint4 (&r)[8]) {
     constexpr int ELEMS = Vec<WDT>::kElems;
     uint32_t q[8][4];
 #pragma unroll
@@ -118,9 +147,9 @@ __device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint3
         q[j][2] = r[j].z;
         q[j][3] = r[j].w;
     }
-    union Op { uint32_t u[4]; bf16x8_t b; f16x8_t f; } ao;
+    union Op { uint32_t u[4]; bf16x8_t b; f16x8_t f; } ao[HALVES];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ao.u[i] = av[i];
+    for (int i = 0; i < 4 * HALVES; ++i) ao[i / 4].u[i % 4] = av[i];
 #pragma unroll
     for (int e = 0; e < ELEMS; ++e) {
         Op bo;  // rows (0,1), (2,3), ... of column element e
@@ -139,22 +168,33 @@ __device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint3
                 bo.u[pr] = __builtin_amdgcn_perm(x1[c], x0[c], (e & 1) ? 0x07060302u : 0x05040100u);
             }
         }
-        if constexpr (WDT == kF16)
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ao.f, bo.f, acc[e], 0, 0, 0);
-        else
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao.b, bo.b, acc[e], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) {
+            if constexpr (WDT == kF16)
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ao[h].f, bo.f, acc[e], 0, 0, 0);
+            else
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao[h].b, bo.b, acc[e], 0, 0, 0);
+        }
     }
 }
 
-template <int WDT, int FUSE, int BT, bool RAGGED>
-__global__ __launch_bounds__(kInlineWaves* kWave, RAGGED && WDT != kI8Half ? 2 : 4) void gemm_exact_kernel(const GemvArgs a) {
+// workgroups of a launch that a compute unit holds at once (registers)
+constexpr int rows_resident(int wdt, int src, bool ragged) {
+    return src == kRowsCodes ? (!ragged || wdt == kI8Half ? 2 : 1) : (src == kRowsPlanes && wdt == kI8Half ? 2 : 1);
+}
+
+template <int WDT, int FUSE, int SRC, bool RAGGED>
+__global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RAGGED)) void gemm_rows_kernel(const GemvArgs a) {
+    constexpr int HALVES = SRC == kRowsCodes ? 1 : 2;
+    constexpr int INPUTS = SRC == kRowsPlanes ? 8 : 4;  // words of a step's inputs
     constexpr int WAVES = kInlineWaves;
     constexpr int ELEMS = Vec<WDT>::kElems;
     constexpr int TILE = 16 * ELEMS;
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, kMfmaTokens>(reinterpret_cast<char*>(smem_raw), 0);
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(true);
+    constexpr bool WHOLE = WDT != kI8;  // (16-byte int8 lanes have 256 columns: the sums meet in halves, through a tree)
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);
     const int tid = threadIdx.x;
     const int w = uniform(tid >> 6);
     const int lane = tid & 63;
@@ -169,11 +209,16 @@ __global__ __launch_bounds__(kInlineWaves* kWave, RAGGED && WDT != kI8Half ? 2 :
     const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : kNoRow;
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
     const __amdgpu_buffer_rsrc_t wbuf = weight_rows(a, k0, row_bytes);
-    const __amdgpu_buffer_rsrc_t xbuf = make_raw_buffer(const_cast<uint16_t*>(a.x), (uint32_t)a.B * (uint32_t)a.K * 2u);
+    const __amdgpu_buffer_rsrc_t xbuf = make_raw_buffer(const_cast<uint16_t*>(a.x), (uint32_t)a.B * (uint32_t)a.x_pitch * 2u);
+    const __amdgpu_buffer_rsrc_t tbuf = make_raw_buffer(a.zl_lo, (uint32_t)a.B * (uint32_t)a.x_pitch * 2u);
     const u16x2_t lo = (u16x2_t)((unsigned short)a.keep_lo), len = (u16x2_t)((unsigned short)a.keep_len);
     // (a 1 that the compiler does not know: it would turn the packed steps into compares and selects, element by element)
     union { uint32_t u; u16x2_t h; } one = {0x00010001u};
     asm("" : "+v"(one.u));
+
+    const bool dense = a.mode == kModeDense;
+    const float m_eff = dense ? 0.f : a.m;  // (centred inputs) dense mode: x - 0 is x
+    const uint32_t bf16_sel = a.xdt == kBF16 ? 0xffffffffu : 0u;
 
     f32x4_t acc[ELEMS];
 #pragma unroll
@@ -181,43 +226,77 @@ __global__ __launch_bounds__(kInlineWaves* kWave, RAGGED && WDT != kI8Half ? 2 :
 
     struct Stage {
         uint4 r[8];
-        uint32_t op[4];
+        uint32_t op[4 * HALVES];
     };
+    typedef Words<INPUTS> Inputs;  // 8 values of the lane's token (and their tails)
     const int n_all = (kend - k0 + kStepRows - 1) / kStepRows;
     const int n_steps = n_all > w ? (n_all - w + WAVES - 1) / WAVES : 0;  // steps w, w + WAVES, ... of 32 rows
     int kept_tok = 0, kept_any = 0;  // rows of this lane's group that its token keeps, that any token keeps
     // inputs of a step: 8 channels of the lane's token; 0 past the last channel and for slots past the batch
     auto load_x = [&](int st) {
         const int k = k0 + (w + st * WAVES) * kStepRows + 8 * kg;
+        Inputs in;
         if constexpr (!RAGGED) {
-            const uint32_t off = k < a.K && cg < a.B ? (uint32_t)(cg * a.K + k) * 2u : kNoRow;
+            const uint32_t off = k < a.K && cg < a.B ? (uint32_t)(cg * a.x_pitch + k) * 2u : kNoRow;
             const auto v = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)off, 0, 0);
-            return make_uint4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) in.w[q] = v[q];
+            if constexpr (SRC == kRowsPlanes) {
+                const auto t = __builtin_amdgcn_raw_buffer_load_b128(tbuf, (int)off, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) in.w[4 + q] = t[q];
+            }
         } else {
+            static_assert(!RAGGED || SRC != kRowsPlanes, "planes have whole octets");
             // rows that start at any 2-byte boundary; the last octet of a token runs into the next token's values, that of the last
             // token is read element by element
             const int total = a.B * a.K, p = min(cg, a.B - 1) * a.K + min(k, a.K - 1);
             uint4 v = total >= 8 ? load_octet(a.x + min(p, total - 8)) : make_uint4(0u, 0u, 0u, 0u);
             if (p > total - 8) v = load_octet_cut(a.x + p, total - p);
             const int n = cg < a.B ? a.K - k : 0;  // elements of the octet that exist
-            uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+            const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) wd[q] = n >= 2 * q + 2 ? wd[q] : (n == 2 * q + 1 ? wd[q] & 0xffffu : 0u);
-            return make_uint4(wd[0], wd[1], wd[2], wd[3]);
+            for (int q = 0; q < 4; ++q) in.w[q] = n >= 2 * q + 2 ? wd[q] : (n == 2 * q + 1 ? wd[q] & 0xffffu : 0u);
         }
+        return in;
     };
     // (Registers: 128 at two workgroups per compute unit, which shapes of more than 256 workgroups need -- 8192 x 28672, 6 tokens, 512-row
     // pieces 82.3 us against 88.4 with one.  An odd input length takes a few more and runs one.)
     // Prune the inputs of step st, replace them by those of step `ahead`, and fetch the rows that some token keeps; the others ask
     // for an offset behind the buffer: nothing is read.  (The inputs go first: loads come back in order, and the next step's test must
     // not wait for rows.)
-    auto issue = [&](int st, uint4& x, int ahead, Stage& sg) {
-        const uint32_t wd[4] = {x.x, x.y, x.z, x.w};
-        uint32_t f[4];
+    auto issue = [&](int st, Inputs& x, int ahead, Stage& sg) {
+        uint32_t f[4], mine = 0;  // bit j: row 8*kg + j kept by this token
+        // channels of the lane's octet that exist (centred values: a missing one would be -m)
+        const int left = SRC == kRowsCentre && cg < a.B ? a.K - (k0 + (w + st * WAVES) * kStepRows + 8 * kg) : 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sg.op[q] = keep_pair(wd[q], lo, len, one.h, f[q]);
-        const uint32_t t = f[0] | (f[1] << 2) | (f[2] << 4) | (f[3] << 6);
-        const uint32_t mine = (t | (t >> 15)) & 0xffu;  // bit j: row 8*kg + j kept by this token
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (SRC == kRowsCodes) {
+                sg.op[q] = keep_pair(x.w[q], lo, len, one.h, f[q]);
+            } else if constexpr (SRC == kRowsCentre) {
+                float d[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t as_bf16 = h ? x.w[q] & 0xffff0000u : x.w[q] << 16;
+                    const uint32_t as_f16 = __float_as_uint(f16_bits_to_f32(h ? x.w[q] >> 16 : x.w[q] & 0xffffu));
+                    const float c = __uint_as_float((as_bf16 & bf16_sel) | (as_f16 & ~bf16_sel)) - m_eff;  // one fp32 subtraction
+                    const bool keep = (RAGGED ? 2 * q + h < left : left > 0) & (dense | (fabsf(c) > a.tau));  // strict; NaN is pruned
+                    d[h] = keep ? c : 0.f;
+                    mine |= keep ? 1u << (2 * q + h) : 0u;
+                }
+                split_pair<WDT>(d[0], d[1], sg.op[q], sg.op[4 + q]);
+            } else {
+                sg.op[q] = x.w[q];
+                sg.op[4 + q] = x.w[4 + q];
+                union { uint32_t u; u16x2_t h; } any = {x.w[q] | x.w[4 + q]};
+                any.h = __builtin_elementwise_min(any.h, one.h);  // a pruned channel is 0 in both planes
+                f[q] = any.u;
+            }
+        }
+        if constexpr (SRC != kRowsCentre) {
+            const uint32_t t = f[0] | (f[1] << 2) | (f[2] << 4) | (f[3] << 6);
+            mine = (t | (t >> 15)) & 0xffu;
+        }
         const uint32_t any = or_of_sixteen(mine);
         kept_tok += __popc(mine);
         kept_any += __popc(any);
@@ -229,37 +308,37 @@ __global__ __launch_bounds__(kInlineWaves* kWave, RAGGED && WDT != kI8Half ? 2 :
             sg.r[j] = load_row_part<WDT>(wbuf, (base + j * row_bytes) | ((drop << (31 - j)) & kNoRow));
     };
     if (n_steps > 0) {
-        uint4 X = load_x(0), Y = load_x(1);
+        Inputs X = load_x(0), Y = load_x(1);
         Stage A, Bs;
         issue(0, X, 2, A);
         int st = 0;
         for (; st + 2 < n_steps; st += 2) {  // Y: inputs of step st + 1, X: of step st + 2
             issue(st + 1, Y, st + 3, Bs);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT>(acc, A.op, A.r);
+            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
             __builtin_amdgcn_sched_barrier(0);
             issue(st + 2, X, st + 4, A);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT>(acc, Bs.op, Bs.r);
+            mfma_rows<WDT, HALVES>(acc, Bs.op, Bs.r);
             __builtin_amdgcn_sched_barrier(0);
         }
         // (one way out of the loop: where it also ended between its halves, the compiler waited for all loads in each turn)
         if (st + 1 < n_steps) {
             issue(st + 1, Y, st + 3, Bs);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT>(acc, A.op, A.r);
-            mfma_rows<WDT>(acc, Bs.op, Bs.r);
+            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
+            mfma_rows<WDT, HALVES>(acc, Bs.op, Bs.r);
         } else {
-            mfma_rows<WDT>(acc, A.op, A.r);
+            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
         }
     }
 
-    leave_lists<WAVES, RAGGED>(a, tile, split, k0, kend, kept_tok, kept_any, L);
+    leave_lists<WAVES, SRC>(a, tile, split, k0, kend, kept_tok, kept_any, L);
     // constants of the column group this thread finishes if its workgroup is the tile's last arrival
     const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, true, true>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
-    finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
+    reduce_waves_and_emit<WDT, WAVES, FUSE, WHOLE, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
+    finish_tile<WDT, WAVES, TILE, kMfmaTokens, FUSE>(a, pbuf, tile, L, mine);
 }
 
 // ---------------------------------------------------------------------------------------------- launch
@@ -295,9 +374,11 @@ void keep_codes(const GemvArgs& a, uint32_t* lo, uint32_t* len) {
     *len = inf - code;
 }
 
-template <int WDT, int FUSE, int BT, bool RAGGED>
-static int launch_exact_kernel(const GemvArgs& a, size_t lds, hipStream_t stream) {
-    if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
+template <int WDT, int FUSE, int SRC, bool RAGGED>
+static int launch_rows_kernel(const GemvArgs& a, hipStream_t stream) {
+    constexpr size_t lds = kHdrBytes + (size_t)tree_floats(WDT != kI8) * 4 +
+                           (FUSE == kFuseSwiglu ? (size_t)kMfmaTokens * 16 * Vec<WDT>::kElems * 4 : 0);
+    static_assert(lds <= kInlineLdsBudget && 2 * lds <= 160 * 1024, "two workgroups per compute unit");
     if (lds > 64 * 1024) {
         // more dynamic LDS than the default limit: ask once per kernel and device
         constexpr int kMaxDevices = 64;
@@ -305,26 +386,45 @@ static int launch_exact_kernel(const GemvArgs& a, size_t lds, hipStream_t stream
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_exact_kernel<WDT, FUSE, BT, RAGGED>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<WDT, FUSE, SRC, RAGGED>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_exact_kernel<WDT, FUSE, BT, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave), lds, stream, a);
+    hipLaunchKernelGGL((gemm_rows_kernel<WDT, FUSE, SRC, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave), lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, int BT>
-static int launch_exact_wdt(const GemvArgs& a, size_t lds, hipStream_t stream) {
-    return a.K % 8 == 0 ? launch_exact_kernel<WDT, FUSE, BT, false>(a, lds, stream) : launch_exact_kernel<WDT, FUSE, BT, true>(a, lds, stream);
+template <int WDT, int FUSE>
+static int launch_codes(const GemvArgs& a, hipStream_t stream) {
+    return a.K % 8 == 0 ? launch_rows_kernel<WDT, FUSE, kRowsCodes, false>(a, stream) : launch_rows_kernel<WDT, FUSE, kRowsCodes, true>(a, stream);
 }
 
-template <int FUSE, int BT>
-static int launch_exact(const GemvArgs& a, int wdt, size_t lds, hipStream_t stream) {
-    if (wdt == kBF16) return launch_exact_wdt<kBF16, FUSE, BT>(a, lds, stream);
-    if (wdt == kF16) return launch_exact_wdt<kF16, FUSE, BT>(a, lds, stream);
-    return launch_exact_wdt<kI8Half, FUSE, BT>(a, lds, stream);
+template <int WDT, int FUSE>
+static int launch_centre(const GemvArgs& a, hipStream_t stream) {
+    return a.K % 8 == 0 ? launch_rows_kernel<WDT, FUSE, kRowsCentre, false>(a, stream) : launch_rows_kernel<WDT, FUSE, kRowsCentre, true>(a, stream);
+}
+
+template <int FUSE>
+static int launch_centre_any(const GemvArgs& a, int wdt, hipStream_t stream) {
+    if (wdt == kBF16) return launch_centre<kBF16, FUSE>(a, stream);
+    if (wdt == kF16) return launch_centre<kF16, FUSE>(a, stream);
+    return wdt == kI8Half ? launch_centre<kI8Half, FUSE>(a, stream) : SCAP_ERR_CONFIG;
+}
+
+template <int FUSE>
+static int launch_codes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
+    if (wdt == kBF16) return launch_codes<kBF16, FUSE>(a, stream);
+    if (wdt == kF16) return launch_codes<kF16, FUSE>(a, stream);
+    return wdt == kI8Half ? launch_codes<kI8Half, FUSE>(a, stream) : SCAP_ERR_CONFIG;
+}
+
+static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
+    if (wdt == kBF16) return launch_rows_kernel<kBF16, kFusePlain, kRowsPlanes, false>(a, stream);
+    if (wdt == kF16) return launch_rows_kernel<kF16, kFusePlain, kRowsPlanes, false>(a, stream);
+    if (wdt == kI8Half) return launch_rows_kernel<kI8Half, kFusePlain, kRowsPlanes, false>(a, stream);
+    return wdt == kI8 ? launch_rows_kernel<kI8, kFusePlain, kRowsPlanes, false>(a, stream) : SCAP_ERR_CONFIG;
 }
 
 // K split: fills a.T, a.Kc, a.S (and the list segmentation); kc: the caller's rows per workgroup, or 0.  SCAP_ERR_SHAPE where the
@@ -334,28 +434,42 @@ static int launch_exact(const GemvArgs& a, int wdt, size_t lds, hipStream_t stre
 // (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
 // take: 46 GB/s x 1000 where a full chip has 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
 // 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s).  Hence `part` below.  Prologue, reduction and the launch's ends are worth about 192 rows of
-// 256 bytes, half of that for each further round (two workgroups share a unit), and a split's hand-over 7.  From sweeps of all splits
+// 256 bytes, half of that for each further round where two workgroups share a unit, and a split's hand-over 7.  From sweeps of all splits
 // over 20 layers, us at the split chosen / the next best: 4096 x 28672 bf16, 16 tokens, S = 1 39.5 / S = 2 44.7; 4096 x 11008, 8
 // tokens, S = 2 19.8 / S = 5 20.1 / S = 3 24.5; 14336 x 4096 S = 8 24.6 / S = 6 26.5; 2048 x 2048 S = 8 7.1 / S = 16 7.5; 8192 x 28672,
 // 6 tokens, S = 1 77.8 / S = 2 81.8, over int8 weights (whose 128-byte pieces leave one workgroup per unit less in flight: 3 % more)
 // S = 2 46.0 / S = 1 49.1.
-static int plan_exact(GemvArgs& a, int wdt, int kc) {
-    a.T = (a.N + kMfmaTile - 1) / kMfmaTile;
-    if (a.T > kMaxTiles) return SCAP_ERR_SHAPE;
-    const bool i8 = wdt == kI8;
+// int8 weights run in 8-byte lanes (128-column tiles; 5-16 tokens at 50-70 %, 16-byte / 8-byte lanes: 14336 x 4096 18.0 / 16.0, 4096 x
+// 28672 27.3 / 25.9, 4096 x 4096 10.7 / 8.1); *wdt becomes kI8Half.  Planes also in 16-byte lanes, where there are more narrow tiles than
+// arrival counters.
+static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
+    const bool i8 = *wdt == kI8;
+    int tile = kMfmaTile;
+    if (i8) {
+        if ((a.N + tile - 1) / tile <= kMaxTiles)
+            *wdt = kI8Half;
+        else if (src == kRowsPlanes)
+            tile = 2 * kMfmaTile;
+    }
+    a.T = (a.N + tile - 1) / tile;
+    // Centred inputs: one workgroup per compute unit (173-220 registers), so layers of more tiles than units stay on the staged-tile
+    // kernel, which runs two (us, there / here: 1024 x 36000 bf16, 6 tokens at 90 %, 17.4 / 20.6, 4096 x 40000, 8 tokens, 66.1 /
+    // 69.7, int8 50.1 / 55.9, 2047 x 40000 int8 33.8 / 38.7, but 4096 x 57344 bf16 91.7 / 84.9).
+    if (a.T > (src == kRowsCentre ? 256 : kMaxTiles)) return SCAP_ERR_SHAPE;
     const int64_t row_bytes = (int64_t)a.N * (i8 ? 1 : 2);
     const int64_t kc_max = (((int64_t)1 << 31) / row_bytes - 2 * kWave) / kWave * kWave;
-    int64_t s_max = (int64_t)(partial_capacity(a.N) / ((size_t)a.T * kMfmaTile));
+    int64_t s_max = (int64_t)(partial_capacity(a.N) / ((size_t)a.T * tile));
     if (s_max > kMaxSplits) s_max = kMaxSplits;
     if (kc == 0) {
         const int fixed = i8 ? 384 : 192, split = i8 ? 14 : 7;
+        const double again = rows_resident(*wdt, src, src != kRowsPlanes && a.K % 8 != 0) == 2 ? 0.5 : 1.0;
         double best = 0.0;
         for (int64_t sp = 1; sp <= s_max; ++sp) {
             const int64_t c = (int64_t)align_up((size_t)((a.K + sp - 1) / sp), kWave);
             if (c > kc_max) continue;
             const int64_t s = (a.K + c - 1) / c, n = s * a.T, rounds = (n + 255) / 256;
             auto part = [&](int64_t m) { return m == 0 ? 0.0 : std::max(0.55, (i8 && n <= 256 ? 0.28 : 0.25) + 0.75 * (double)m / 256.0); };
-            const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + fixed + fixed * 0.5 * (double)(rounds - 1) + (double)(split * s);
+            const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 kc = (int)c;
@@ -373,20 +487,26 @@ static int plan_exact(GemvArgs& a, int wdt, int kc) {
     return SCAP_OK;
 }
 
-bool gemm_exact_plans(const GemvArgs& a_in, int wdt) {
+bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src) {
     GemvArgs a = a_in;
-    return plan_exact(a, wdt, 0) == SCAP_OK;
+    return plan_rows(a, &wdt, src, 0) == SCAP_OK;
 }
 
-int launch_gemm_exact(const GemvArgs& a_in, int wdt, int fuse, int kc, hipStream_t stream) {
+int launch_gemm_rows(const GemvArgs& a_in, int wdt, int src, int fuse, int kc, hipStream_t stream) {
     GemvArgs a = a_in;
-    if (!exact_operand(a, wdt) || a.B < 1 || a.B > kMfmaTokens) return SCAP_ERR_CONFIG;
-    const int rc = plan_exact(a, wdt, kc);
+    if (a.B < 1 || a.B > kMfmaTokens || (src == kRowsCodes && !exact_operand(a, wdt))) return SCAP_ERR_CONFIG;
+    const int rc = plan_rows(a, &wdt, src, kc);
     if (rc != SCAP_OK) return rc;
+    if (src == kRowsPlanes) {
+        a.mode = kModeSparse;  // (the planes hold what is kept)
+        a.x = reinterpret_cast<const uint16_t*>(a.zl_d);
+        a.x_pitch = plane_pitch(a.K);
+        return fuse == kFusePlain ? launch_planes_any(a, wdt, stream) : SCAP_ERR_CONFIG;
+    }
+    a.x_pitch = a.K;
+    if (src == kRowsCentre) return fuse == kFuseSwiglu ? launch_centre_any<kFuseSwiglu>(a, wdt, stream) : launch_centre_any<kFusePlain>(a, wdt, stream);
     keep_codes(a, &a.keep_lo, &a.keep_len);
-    const size_t lds = kHdrBytes + (size_t)tree_floats(true) * 4 + (fuse == kFuseSwiglu ? (size_t)kMfmaTokens * kMfmaTile * 4 : 0);
-    return fuse == kFuseSwiglu ? launch_exact<kFuseSwiglu, kMfmaTokens>(a, wdt, lds, stream)
-                               : launch_exact<kFusePlain, kMfmaTokens>(a, wdt, lds, stream);
+    return fuse == kFuseSwiglu ? launch_codes_any<kFuseSwiglu>(a, wdt, stream) : launch_codes_any<kFusePlain>(a, wdt, stream);
 }
 
 }  // namespace scap

@@ -549,6 +549,67 @@ __device__ __forceinline__ void gate_and_compact(const GemvArgs& a, int tile, fl
     }
 }
 
+// ---------------------------------------------------------------------------------------------- operand halves
+// A value as head + tail in the 16-bit type that the weights' matrix instruction takes (fp16 over fp16 weights, bf16 otherwise): head
+// in the low half of the result, tail in the high half.
+__device__ __forceinline__ uint32_t bf16_rne_bits(float v) {
+    const uint32_t u = __float_as_uint(v);
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;  // finite or infinite input (NaN never reaches the list)
+}
+template <int WDT>
+__device__ __forceinline__ uint32_t split_halves(float v) {
+    if constexpr (WDT == kF16) {
+        // The head is clamped to the largest finite fp16 so that a finite value never turns into an infinite head; the tail then
+        // carries the rest (the activations are fp16 or bf16 values minus a small mode, so the rest is small).  Values below
+        // fp16's subnormal step (6e-8) lose their tail, an absolute error far inside the output tolerance.
+        const bool inf = fabsf(v) == __builtin_huge_valf();
+        union { _Float16 f; uint16_t s; } h, l;
+        h.f = (_Float16)(inf ? v : fminf(fmaxf(v, -65504.f), 65504.f));
+        l.f = (_Float16)(inf ? 0.f : v - (float)h.f);
+        return (uint32_t)h.s | ((uint32_t)l.s << 16);
+    } else {
+        const uint32_t h = bf16_rne_bits(v);
+        const float rest = ((h & 0x7FFFu) != 0x7F80u) ? v - __uint_as_float(h << 16) : 0.f;  // an infinite head has no tail
+        return h | (bf16_rne_bits(rest) << 16);
+    }
+}
+
+// Elements between the tokens' rows of a plane of the gated product, and the planes' place in the list space of a block
+inline __host__ __device__ int plane_pitch(int F) { return (F + kWave - 1) / kWave * kWave; }
+
+// kFuseSwiglu, batches on the matrix cores: the gated product of a finished tile (s_fin: per 8 columns 4 gate, then the 4
+// matching up pre-activations), centred and thresholded, as two planes of operand halves, [tokens][F rounded up to 64] each: what the
+// down launch reads as its operands.  A pruned channel is 0 in both; a kept value so small that both halves round to 0 is -0 in the
+// head, so that not 0 means kept.  Called by every thread of the tile's last arrival.
+template <int WDT, int NT, int TILE>
+__device__ __forceinline__ void gate_to_planes(const GemvArgs& a, int tile, const float* s_fin) {
+    constexpr int HALF = TILE / 2;   // gated channels of the tile
+    constexpr int PAIRS = HALF / 2;  // two channels a thread: 4-byte stores, 128 bytes or more of a row in one piece
+    const int pitch = plane_pitch(a.F);
+    uint32_t* hi = reinterpret_cast<uint32_t*>(a.zl_d);
+    uint32_t* lo = reinterpret_cast<uint32_t*>(a.zl_lo);
+#pragma nounroll
+    for (int item = threadIdx.x; item < a.B * PAIRS; item += NT) {
+        const int b = item / PAIRS, t = 2 * (item % PAIRS), c = tile * HALF + t;
+        if (c >= pitch) continue;
+        const float2 g = *reinterpret_cast<const float2*>(s_fin + b * TILE + (t >> 2) * 8 + (t & 3));
+        const float2 u = *reinterpret_cast<const float2*>(s_fin + b * TILE + (t >> 2) * 8 + 4 + (t & 3));
+        auto gated = [&](float gv, float uv, int ch) {
+            if (ch >= a.F) return 0u;
+            const float z = gv / (1.f + expf(-gv)) * uv;
+            if (a.z_out) a.z_out[(int64_t)b * a.F + ch] = z;
+            const float d = z - a.m2;
+            if (!(fabsf(d) > a.tau2)) return 0u;
+            const uint32_t h = split_halves<WDT>(d);
+            return h != 0u ? h : 0x8000u;
+        };
+        const uint32_t z0 = gated(g.x, u.x, c), z1 = gated(g.y, u.y, c + 1);
+        const int at = (b * pitch + c) >> 1;
+        hi[at] = (z0 & 0xffffu) | (z1 << 16);
+        lo[at] = (z0 >> 16) | (z1 & 0xffff0000u);
+    }
+}
+
 // kFuseList, last arrival of a tile: kept-channel count and gap-free ascending list of the tile's tokens, from the
 // segment lists (an entry belongs to token b where its centred value is non-zero: kept means |d| > tau >= 0).
 // Other workgroups may still be reading the segment lists, so those stay as they are.
@@ -747,7 +808,12 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, __amdgpu_buffer_r
     }
     if constexpr (FUSE == kFuseSwiglu) {
         __syncthreads();  // the tile's columns are complete in L.fin
-        gate_and_compact<WAVES, TILE, BT>(a, tile, L.fin);
+        if constexpr (BT == 16) {
+            gate_to_planes<WDT, WAVES * kWave, TILE>(a, tile, L.fin);
+            return;
+        } else {
+            gate_and_compact<WAVES, TILE, BT>(a, tile, L.fin);
+        }
     }
     if constexpr (FUSE == kFuseList) {
         if (own) close_block_lists<WAVES, BT>(a, L, own);

@@ -88,12 +88,17 @@ struct GemvArgs {
     // More than one token: 64-channel segments -- except between the two launches of a two-token block over int8 weights in
     // 8-byte lanes: ceil(F/32) segments of 32 channels.  (One token: see Gemv1Args.)
     int32_t* zl_idx;  // [ceil(F/64)][64] channels of each segment kept by any token, ascending; [ceil(F/32)][32]
-    float* zl_d;      // [ceil(F/64)][64][BT] their centred values per token (BT = 2, 4 or 16 slots); [ceil(F/32)][32][2]
+    float* zl_d;      // [ceil(F/64)][64][BT] their centred values per token (BT = 2 or 4 slots); [ceil(F/32)][32][2]
     int32_t* zl_cnt;  // [1 + BT][ceil(F/64)] entries per segment: union first, then per token; [ceil(F/32)]: the three
                       // counts in the low bytes of one word, union lowest
     int F;            // channels of the gated product (half the columns of the gate|up launch)
-    // exact-operand kernel (scap_gemm_exact.hip): the magnitude codes [keep_lo, keep_lo + keep_len) are kept
+    // Batches of 5 and more (gate_to_planes): zl_d is the plane of operand heads, [BT][F rounded up to 64] 16-bit values, this
+    // the plane of tails.
+    uint16_t* zl_lo;
+    // kernel over row steps (scap_gemm_rows.hip): the magnitude codes [keep_lo, keep_lo + keep_len) are kept; elements between the
+    // tokens' rows of x
     uint32_t keep_lo, keep_len;
+    int x_pitch;
 };
 
 // Enqueue one GEMV (sparse / dense / fold mode).  Returns a scap_status.
@@ -145,12 +150,15 @@ int launch_gemm_mfma(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hip
 // The same in one launch: each workgroup compacts its own inputs into LDS (up to 160 KB on gfx950).
 // SCAP_ERR_SHAPE when the input is too long to split into LDS-sized pieces.
 int launch_gemm_inline(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStream_t stream, bool slots16 = false);
-// Whether the centred input is the 16-bit operand itself (m = 0 or dense mode, activations of the operand's type), and the launch
-// for such inputs, 16 token slots (scap_gemm_exact.hip).  kc: rows per workgroup, or 0.  SCAP_ERR_SHAPE where it cannot split the layer
-// (gemm_exact_plans: whether it can by itself).
+// The same without lists or staged inputs, 16 token slots (scap_gemm_rows.hip): where the centred input is the 16-bit operand itself
+// (m = 0 or dense mode, activations of the operand's type: exact_operand), and where the inputs are planes of operand halves (the
+// gated product).  kc: rows per workgroup, or 0.  SCAP_ERR_SHAPE where it cannot split the layer.
+constexpr int kRowsCodes = 0;   // x: 16-bit inputs
+constexpr int kRowsPlanes = 1;  // x, zl_lo: heads and tails
+constexpr int kRowsCentre = 2;  // x: 16-bit inputs of any type, centred in fp32 and split
 bool exact_operand(const GemvArgs& a, int wdt);
-bool gemm_exact_plans(const GemvArgs& a, int wdt);
-int launch_gemm_exact(const GemvArgs& a, int wdt, int fuse, int kc, hipStream_t stream);
+bool gemm_rows_plans(const GemvArgs& a, int wdt, int src);
+int launch_gemm_rows(const GemvArgs& a, int wdt, int src, int fuse, int kc, hipStream_t stream);
 // The fused block's two launches on the same kernel (bf16 / int8, up to 16 tokens).
 int launch_swiglu_block_inline(const GemvArgs& up, const GemvArgs& down, int wdt, hipStream_t stream);
 

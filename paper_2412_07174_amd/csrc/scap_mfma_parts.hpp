@@ -32,51 +32,16 @@ constexpr int kMfmaTokens = 16;   // M of the MFMA; tokens beyond B are zero row
 constexpr int kMfmaBlock = 16;    // list rows per MFMA (K of the MFMA)
 constexpr int kCompactWaves = 8;
 
-__device__ __forceinline__ uint32_t bf16_rne_bits(float v) {
-    const uint32_t u = __float_as_uint(v);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;  // finite or infinite input (NaN never reaches the list)
-}
-
-// 4 centred values -> bf16 head and tail operands
-__device__ __forceinline__ void split_bf16x4(const float4& d, s16x4_t& hi, s16x4_t& lo) {
-    const float v[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t h = bf16_rne_bits(v[j]);
-        const float hf = __uint_as_float(h << 16);
-        const float rest = ((h & 0x7FFFu) != 0x7F80u) ? v[j] - hf : 0.f;  // an infinite head has no tail
-        hi[j] = (short)h;
-        lo[j] = (short)bf16_rne_bits(rest);
-    }
-}
-
-// 4 centred values -> fp16 head and tail operands (as raw 16-bit patterns).  The head is clamped to the largest
-// finite fp16 so that a finite value never turns into an infinite head; the tail then carries the rest (the
-// activations are fp16 or bf16 values minus a small mode, so the rest is small).  Values below fp16's
-// subnormal step (6e-8) lose their tail, an absolute error far inside the output tolerance.
-__device__ __forceinline__ void split_f16x4(const float4& d, s16x4_t& hi, s16x4_t& lo) {
-    const float v[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool inf = fabsf(v[j]) == __builtin_huge_valf();
-        const float c = inf ? v[j] : fminf(fmaxf(v[j], -65504.f), 65504.f);
-        const _Float16 h = (_Float16)c;
-        const _Float16 l = (_Float16)(inf ? 0.f : v[j] - (float)h);
-        union { _Float16 f; short s; } a, b;
-        a.f = h;
-        b.f = l;
-        hi[j] = a.s;
-        lo[j] = b.s;
-    }
-}
-
-// head / tail split of the A operand in the format the weights' MFMA takes
+// 4 centred values -> head and tail of the A operand in the format the weights' MFMA takes
 template <int WDT>
 __device__ __forceinline__ void split_operand(const float4& d, s16x4_t& hi, s16x4_t& lo) {
-    if constexpr (WDT == kF16)
-        split_f16x4(d, hi, lo);
-    else
-        split_bf16x4(d, hi, lo);
+    const float v[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t h = split_halves<WDT>(v[j]);
+        hi[j] = (short)h;
+        lo[j] = (short)(h >> 16);
+    }
 }
 
 // One 16-row block: r[j] = this lane's 16 bytes of list row 4*(l/16)+j (zeros for a slot past the list),
@@ -131,55 +96,6 @@ typedef short s16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 
-// Two 16-row blocks at once on the 32-deep instruction: r[0..3] = this lane's 16 bytes of rows 4*(l/16)+j of the
-// first block, r[4..7] of the second (zeros for slots past the list); a_hi / a_lo = heads and tails of the eight
-// matching centred values.  Which list row sits in which of the lane's 8 k-slots is free as long as A and B
-// agree.  acc[e] += A * B_e for the ELEMS column elements.
-template <int WDT>
-__device__ __forceinline__ void mfma_block32(f32x4_t* __restrict__ acc, const s16x4_t (&a_hi)[2], const s16x4_t (&a_lo)[2],
-                                             const uint4 (&r)[8]) {
-    constexpr int ELEMS = Vec<WDT>::kElems;
-    union { s16x4_t h[2]; bf16x8_t b; f16x8_t f; } ah, al;
-    ah.h[0] = a_hi[0];
-    ah.h[1] = a_hi[1];
-    al.h[0] = a_lo[0];
-    al.h[1] = a_lo[1];
-    uint32_t q[8][4];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        q[j][0] = r[j].x;
-        q[j][1] = r[j].y;
-        q[j][2] = r[j].z;
-        q[j][3] = r[j].w;
-    }
-#pragma unroll
-    for (int e = 0; e < ELEMS; ++e) {
-        union { uint32_t u32[4]; bf16x8_t b; f16x8_t f; } bop;  // rows (0,1), (2,3), (4,5), (6,7) of column element e
-#pragma unroll
-        for (int pr = 0; pr < 4; ++pr) {
-            const uint32_t* x0 = q[2 * pr];
-            const uint32_t* x1 = q[2 * pr + 1];
-            if constexpr (WDT == kBF16 || WDT == kF16) {
-                const int c = e >> 1;
-                bop.u32[pr] = (e & 1) == 0 ? ((x0[c] & 0xFFFFu) | (x1[c] << 16)) : ((x0[c] >> 16) | (x1[c] & 0xFFFF0000u));
-            } else {
-                // byte e of each row, sign-extended, as a float: its low 16 bits are zero (|v| <= 128)
-                const int c = e >> 2, sh = 24 - 8 * (e & 3);
-                const uint32_t f0 = __float_as_uint((float)(((int)(x0[c] << sh)) >> 24));
-                const uint32_t f1 = __float_as_uint((float)(((int)(x1[c] << sh)) >> 24));
-                bop.u32[pr] = (f0 >> 16) | f1;
-            }
-        }
-        if constexpr (WDT == kF16) {
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah.f, bop.f, acc[e], 0, 0, 0);
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al.f, bop.f, acc[e], 0, 0, 0);
-        } else {
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah.b, bop.b, acc[e], 0, 0, 0);
-            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al.b, bop.b, acc[e], 0, 0, 0);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------------------------- single-launch kernels
 constexpr size_t kInlineLdsBudget = 160 * 1024;
 constexpr int kInlineWaves = 8;
@@ -191,11 +107,6 @@ constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
 // LDS floats of the reduction of the wavefronts' sums (and of the final one).  Kernels that run one workgroup per compute
 // unit anyway take all eight wavefronts' sums at once, 64 KB: two barriers and one turn fewer (reduce_waves_and_emit).
 constexpr int tree_floats(bool whole) { return (whole ? 64 : 32) * 1024 / 4; }
-// ... which are the 16-slot launch that reads lists (158 registers) and the 32-deep staged-tile form, 16-bit weights
-__host__ __device__ constexpr bool whole_reduction(int wdt, int bt, int fuse, bool x32) {
-    return wdt != kI8 && bt == 16 && (fuse == kFuseList || x32);
-}
-
 // A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
 // offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
 // were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay

@@ -82,6 +82,32 @@ def test_exact_operand_shapes(K, N, dt):
     sums_within_fp32(y.cpu().numpy(), layer, Xf[:7], bias, f"dense K={K} N={N}")
 
 
+@pytest.mark.parametrize("dt,xdt", [(BF16, BF16), (F16, F16), (I8, BF16), (BF16, F16), (F16, BF16), (I8, F16)])
+@pytest.mark.parametrize("K,N", [(1, 16), (31, 144), (33, 272), (264, 2048), (1000, 4112), (4097, 528), (2048, 128)])
+def test_centred_operand_shapes(K, N, dt, xdt):
+    """m != 0, or activations of another type than the operand's: the same row steps with the centred values split into two halves
+    (2^-17 of each product, fp16 2^-21)."""
+    layer = layer_of(K, N, dt, 9600 + K)
+    bias = np.random.default_rng(K + N).standard_normal(N).astype(np.float32)
+    X = wl.laplace(16, K, 9700 + K, xdt, loc=0.1, scale=0.6)
+    Xf = wl.decode(X, xdt).astype(np.float32)
+    half = 2.0 ** -16 if dt != F16 else 2.0 ** -20
+    W = np.abs(wide(layer))
+    for B, m, tau in ((5, 0.1, 0.0), (8, -0.2, 0.41), (9, 0.1, 1.4), (16, 1.5, 0.3), (16, 0.0, 0.3)):
+        say(f"centred operand K={K} N={N} dt={dt} xdt={xdt} B={B} m={m} tau={tau}")
+        got, want = check_against_oracle(layer, X[:B], xdt, m, tau, bias, what=f"K={K} N={N} B={B} m={m} tau={tau}")
+        D = Xf[:B] - np.float32(m)
+        D = np.where(np.abs(D) > np.float32(tau), D, 0.0).astype(np.float64)
+        exact = D @ wide(layer) + bias[None, :]
+        bound = ((np.count_nonzero(D, axis=1)[:, None] + 4) * 2.0 ** -24 + half) * (np.abs(D) @ W) + 2.0 ** -22 * np.abs(exact) + 1e-6
+        assert np.all(np.abs(got["y"] - exact) <= bound), (K, N, B, m, tau)
+    y = scap.dense_fc(layer.W, to_dev(X[:7], xdt), f32_dev(bias), col_scale=layer.scale, workspace=layer.ws)
+    torch.cuda.synchronize()
+    exact = Xf[:7].astype(np.float64) @ wide(layer) + bias[None, :]
+    bound = ((K + 4) * 2.0 ** -24 + half) * (np.abs(Xf[:7].astype(np.float64)) @ W) + 2.0 ** -22 * np.abs(exact) + 1e-6
+    assert np.all(np.abs(y.cpu().numpy() - exact) <= bound), (K, N, "dense")
+
+
 @pytest.mark.parametrize("dt", [BF16, F16])
 def test_every_code_against_thresholds(dt):
     """All 65536 codes as inputs (subnormals, both zeros, infinities, NaN): kept exactly where the fp32 comparison keeps them, at
@@ -136,6 +162,20 @@ def test_exact_operand_blocks(K, F, N, B, dt):
     X = wl.laplace(B, K, 9501 + K, xdt, loc=0.0, scale=0.8)
     zs = np.abs(oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[0], 0.0, 0.5, 0.0, 0.0, dt, xdt, gate_scale=blk.sg, up_scale=blk.su,
                                     down_scale=blk.sd)["z"])
-    for tau_x, tau_z in ((0.0, 0.0), (0.5, float(np.median(zs))), (1.1, float(np.quantile(zs, 0.9)))):
+    for tau_x, tau_z in ((0.0, 0.0), (0.5, float(np.median(zs))), (1.1, float(np.quantile(zs, 0.9))), (0.5, 1e9)):
         say(f"exact operand block K={K} F={F} N={N} B={B} dt={dt} tau_x={tau_x} tau_z={tau_z:.4g}")
         blk.check_batch(X, xdt, 0.0, tau_x, None, None, 0.0, tau_z, None, f"exact operand block {K} {F} {N} {B}")
+        blk.check_batch(X, xdt, 0.05, tau_x, None, None, 0.001, tau_z, None, f"centred operand block {K} {F} {N} {B}")
+
+
+def test_gated_products_below_the_operand_type():
+    """Gated products so small that both halves of the operand round to 0 (fp16: below 2^-25) are kept by a threshold of 0, and counted
+    and listed as such."""
+    K, F, N, B = 64, 264, 144, 6
+    from test_gpu_swiglu import Block
+    blk = Block(K, F, N, F16, seed=9801, std=1e-4, B=B)
+    X = wl.laplace(B, K, 9802, F16, loc=0.0, scale=0.01)
+    gots = blk.run_batch(X, F16, 0.0, 0.0, None, None, 0.0, 0.0, None)
+    for b in range(B):
+        assert np.count_nonzero(np.abs(gots[b]["z"]) < 2.0 ** -26) > F // 2
+        assert np.array_equal(gots[b]["idx_z"], np.nonzero(gots[b]["z"])[0])
