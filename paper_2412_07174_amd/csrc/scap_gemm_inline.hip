@@ -850,7 +850,7 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     // 16 token slots, and the centred input is the operand: a kernel of its own.  (Rows that the caller names have to fit here all
     // the same.)
     const int src = exact_operand(a, wdt) ? kRowsCodes : kRowsCentre;
-    const bool exact = a.B > 4 || (slots16 && (src == kRowsCodes || wdt != kI8 || a.B == 4));
+    const bool exact = a.B > 4 || (slots16 && (wdt != kI8 || ((src == kRowsCodes || a.B == 4) && a.N <= kRowsFewCols && (int64_t)a.K * a.N <= kRowsFewI8Weights)));
     if (exact && kc == 0) {
         const int rc = launch_gemm_rows(a, wdt, src, kFusePlain, 0, stream);
         if (rc != SCAP_ERR_SHAPE) return rc;
@@ -888,9 +888,11 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
     int wup = wdt, wdn = wdt;
-    if (up.B > 4) {
+    const bool exact = exact_operand(up, wdt);
+    if (up.B > 4 || (exact && up.N <= kRowsFewCols && (int64_t)up.K * up.N <= kRowsFewI8Weights && gemm_rows_plans(up, wdt, kRowsCodes) &&
+                     gemm_rows_plans(dn, wdt, kRowsPlanes))) {
         // 16 token slots: the gated product travels as planes of operand halves, and the down launch takes them row step by row step
-        const int src = exact_operand(up, wdt) ? kRowsCodes : kRowsCentre;
+        const int src = exact ? kRowsCodes : kRowsCentre;
         const bool codes = gemm_rows_plans(up, wdt, src);
         if (!codes) {
             const int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
@@ -899,7 +901,7 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
             up.Sl = up.S;
         }
         if (!gemm_rows_plans(dn, wdt, kRowsPlanes)) return SCAP_ERR_SHAPE;
-        up.zl_lo = dn.zl_lo = reinterpret_cast<uint16_t*>(up.zl_d) + (size_t)kMfmaTokens * plane_pitch(up.F);
+        up.zl_lo = dn.zl_lo = reinterpret_cast<uint16_t*>(up.zl_d) + (size_t)block_token_slots(up.B) * plane_pitch(up.F);
         dn.seg_cnt = up.seg_cnt;
         const int rc = codes ? launch_gemm_rows(up, wdt, src, kFuseSwiglu, 0, stream)
                              : launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);

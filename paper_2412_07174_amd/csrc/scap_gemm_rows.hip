@@ -180,10 +180,11 @@ __device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint3
 
 // workgroups of a launch that a compute unit holds at once (registers)
 constexpr int rows_resident(int wdt, int src, bool ragged) {
-    return src == kRowsCodes ? (!ragged || wdt == kI8Half ? 2 : 1) : (src == kRowsPlanes && wdt == kI8Half ? 2 : 1);
+    return wdt == kI8Half || (src == kRowsCodes && !ragged && wdt != kI8) ? 2 : 1;
 }
 
-template <int WDT, int FUSE, int SRC, bool RAGGED>
+// SLOTS: token slots of what a gating launch leaves (2, 4: lists of centred values; 16: planes of operand halves), else 16.
+template <int WDT, int FUSE, int SRC, bool RAGGED, int SLOTS>
 __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RAGGED)) void gemm_rows_kernel(const GemvArgs a) {
     constexpr int HALVES = SRC == kRowsCodes ? 1 : 2;
     constexpr int INPUTS = SRC == kRowsPlanes ? 8 : 4;  // words of a step's inputs
@@ -224,6 +225,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
 #pragma unroll
     for (int e = 0; e < ELEMS; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+    // Steps in flight: four instead of two (207 registers, one workgroup per unit) were no faster on any of 19 layers.
+    constexpr int DEPTH = 2;
     struct Stage {
         uint4 r[8];
         uint32_t op[4 * HALVES];
@@ -308,28 +311,33 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
             sg.r[j] = load_row_part<WDT>(wbuf, (base + j * row_bytes) | ((drop << (31 - j)) & kNoRow));
     };
     if (n_steps > 0) {
-        Inputs X = load_x(0), Y = load_x(1);
-        Stage A, Bs;
-        issue(0, X, 2, A);
+        // Steps st .. st + DEPTH-1 are in flight or in work, the inputs of the DEPTH after them too (loads come back in order: a
+        // test that waited for younger inputs would wait for the rows before them).  One way out of the loop: where it also
+        // ended between its turns, the compiler waited for all loads in each.
+        Inputs X[DEPTH];
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) X[u] = load_x(u);
+        Stage S[DEPTH];
+#pragma unroll
+        for (int u = 0; u < DEPTH - 1; ++u) issue(u, X[u], u + DEPTH, S[u]);
         int st = 0;
-        for (; st + 2 < n_steps; st += 2) {  // Y: inputs of step st + 1, X: of step st + 2
-            issue(st + 1, Y, st + 3, Bs);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
-            __builtin_amdgcn_sched_barrier(0);
-            issue(st + 2, X, st + 4, A);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT, HALVES>(acc, Bs.op, Bs.r);
-            __builtin_amdgcn_sched_barrier(0);
+        for (; st + 2 * DEPTH - 1 <= n_steps; st += DEPTH) {
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
+                issue(st + u + DEPTH - 1, X[(u + DEPTH - 1) % DEPTH], st + u + 2 * DEPTH - 1, S[(u + DEPTH - 1) % DEPTH]);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_rows<WDT, HALVES>(acc, S[u].op, S[u].r);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-        // (one way out of the loop: where it also ended between its halves, the compiler waited for all loads in each turn)
-        if (st + 1 < n_steps) {
-            issue(st + 1, Y, st + 3, Bs);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
-            mfma_rows<WDT, HALVES>(acc, Bs.op, Bs.r);
-        } else {
-            mfma_rows<WDT, HALVES>(acc, A.op, A.r);
+#pragma unroll
+        for (int u = 0; u < 2 * DEPTH - 2; ++u) {  // the last ones
+            if (st + u < n_steps) {
+                if (u < DEPTH - 1 && st + u + DEPTH - 1 < n_steps)
+                    issue(st + u + DEPTH - 1, X[(u + DEPTH - 1) % DEPTH], st + u + 2 * DEPTH - 1, S[(u + DEPTH - 1) % DEPTH]);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_rows<WDT, HALVES>(acc, S[u % DEPTH].op, S[u % DEPTH].r);
+            }
         }
     }
 
@@ -338,7 +346,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
     const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
     reduce_waves_and_emit<WDT, WAVES, FUSE, WHOLE, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
-    finish_tile<WDT, WAVES, TILE, kMfmaTokens, FUSE>(a, pbuf, tile, L, mine);
+    finish_tile<WDT, WAVES, TILE, SLOTS, FUSE>(a, pbuf, tile, L, mine);
 }
 
 // ---------------------------------------------------------------------------------------------- launch
@@ -374,7 +382,7 @@ void keep_codes(const GemvArgs& a, uint32_t* lo, uint32_t* len) {
     *len = inf - code;
 }
 
-template <int WDT, int FUSE, int SRC, bool RAGGED>
+template <int WDT, int FUSE, int SRC, bool RAGGED, int SLOTS = kMfmaTokens>
 static int launch_rows_kernel(const GemvArgs& a, hipStream_t stream) {
     constexpr size_t lds = kHdrBytes + (size_t)tree_floats(WDT != kI8) * 4 +
                            (FUSE == kFuseSwiglu ? (size_t)kMfmaTokens * 16 * Vec<WDT>::kElems * 4 : 0);
@@ -386,19 +394,27 @@ static int launch_rows_kernel(const GemvArgs& a, hipStream_t stream) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<WDT, FUSE, SRC, RAGGED>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_rows_kernel<WDT, FUSE, SRC, RAGGED, SLOTS>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_rows_kernel<WDT, FUSE, SRC, RAGGED>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave), lds, stream, a);
+    hipLaunchKernelGGL((gemm_rows_kernel<WDT, FUSE, SRC, RAGGED, SLOTS>), dim3((unsigned)(a.S * a.T)), dim3(kInlineWaves * kWave), lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE>
+template <int WDT, int FUSE, int SLOTS>
 static int launch_codes(const GemvArgs& a, hipStream_t stream) {
-    return a.K % 8 == 0 ? launch_rows_kernel<WDT, FUSE, kRowsCodes, false>(a, stream) : launch_rows_kernel<WDT, FUSE, kRowsCodes, true>(a, stream);
+    return a.K % 8 == 0 ? launch_rows_kernel<WDT, FUSE, kRowsCodes, false, SLOTS>(a, stream)
+                        : launch_rows_kernel<WDT, FUSE, kRowsCodes, true, SLOTS>(a, stream);
+}
+
+template <int FUSE, int SLOTS = kMfmaTokens>
+static int launch_codes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
+    if (wdt == kBF16) return launch_codes<kBF16, FUSE, SLOTS>(a, stream);
+    if (wdt == kF16) return launch_codes<kF16, FUSE, SLOTS>(a, stream);
+    return wdt == kI8Half ? launch_codes<kI8Half, FUSE, SLOTS>(a, stream) : SCAP_ERR_CONFIG;
 }
 
 template <int WDT, int FUSE>
@@ -411,13 +427,6 @@ static int launch_centre_any(const GemvArgs& a, int wdt, hipStream_t stream) {
     if (wdt == kBF16) return launch_centre<kBF16, FUSE>(a, stream);
     if (wdt == kF16) return launch_centre<kF16, FUSE>(a, stream);
     return wdt == kI8Half ? launch_centre<kI8Half, FUSE>(a, stream) : SCAP_ERR_CONFIG;
-}
-
-template <int FUSE>
-static int launch_codes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
-    if (wdt == kBF16) return launch_codes<kBF16, FUSE>(a, stream);
-    if (wdt == kF16) return launch_codes<kF16, FUSE>(a, stream);
-    return wdt == kI8Half ? launch_codes<kI8Half, FUSE>(a, stream) : SCAP_ERR_CONFIG;
 }
 
 static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
@@ -433,7 +442,9 @@ static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
 // The cost of a split in rows of one workgroup at the rate of a full chip.  Nothing but the weight buffer's offsets bounds a piece
 // (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
 // take: 46 GB/s x 1000 where a full chip has 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
-// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s).  Hence `part` below.  Prologue, reduction and the launch's ends are worth about 192 rows of
+// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s).  Hence `part` below; a single round
+// pays a little more, for one workgroup per unit has less in flight where few of the rows are kept (4096 x 11008, 5 tokens at 50 / 90 %, S = 2
+// 19.7 / 14.8, S = 5 19.8 / 12.9).  Prologue, reduction and the launch's ends are worth about 192 rows of
 // 256 bytes, half of that for each further round where two workgroups share a unit, and a split's hand-over 7.  From sweeps of all splits
 // over 20 layers, us at the split chosen / the next best: 4096 x 28672 bf16, 16 tokens, S = 1 39.5 / S = 2 44.7; 4096 x 11008, 8
 // tokens, S = 2 19.8 / S = 5 20.1 / S = 3 24.5; 14336 x 4096 S = 8 24.6 / S = 6 26.5; 2048 x 2048 S = 8 7.1 / S = 16 7.5; 8192 x 28672,
@@ -468,7 +479,10 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
             const int64_t c = (int64_t)align_up((size_t)((a.K + sp - 1) / sp), kWave);
             if (c > kc_max) continue;
             const int64_t s = (a.K + c - 1) / c, n = s * a.T, rounds = (n + 255) / 256;
-            auto part = [&](int64_t m) { return m == 0 ? 0.0 : std::max(0.55, (i8 && n <= 256 ? 0.28 : 0.25) + 0.75 * (double)m / 256.0); };
+            auto part = [&](int64_t m) {
+                const double x = (double)m / 256.0, alone = n <= 256 ? 0.12 * x * (1.0 - x) + (i8 ? 0.03 : 0.0) : 0.0;
+                return m == 0 ? 0.0 : std::max(0.55, 0.25 + 0.75 * x + alone);
+            };
             const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s);
             if (best == 0.0 || cost < best) {
                 best = cost;
@@ -487,9 +501,11 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
     return SCAP_OK;
 }
 
-bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src) {
+bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src, int* splits) {
     GemvArgs a = a_in;
-    return plan_rows(a, &wdt, src, 0) == SCAP_OK;
+    if (plan_rows(a, &wdt, src, 0) != SCAP_OK) return false;
+    if (splits) *splits = a.S;
+    return true;
 }
 
 int launch_gemm_rows(const GemvArgs& a_in, int wdt, int src, int fuse, int kc, hipStream_t stream) {
@@ -506,7 +522,11 @@ int launch_gemm_rows(const GemvArgs& a_in, int wdt, int src, int fuse, int kc, h
     a.x_pitch = a.K;
     if (src == kRowsCentre) return fuse == kFuseSwiglu ? launch_centre_any<kFuseSwiglu>(a, wdt, stream) : launch_centre_any<kFusePlain>(a, wdt, stream);
     keep_codes(a, &a.keep_lo, &a.keep_len);
-    return fuse == kFuseSwiglu ? launch_codes_any<kFuseSwiglu>(a, wdt, stream) : launch_codes_any<kFusePlain>(a, wdt, stream);
+    if (fuse != kFuseSwiglu) return launch_codes_any<kFusePlain>(a, wdt, stream);
+    // (a gating launch leaves planes where it is told where the tails go, else the lists of 2-4 tokens)
+    if (a.zl_lo != nullptr) return launch_codes_any<kFuseSwiglu>(a, wdt, stream);
+    if (a.B > 4) return SCAP_ERR_CONFIG;
+    return a.B == 2 ? launch_codes_any<kFuseSwiglu, 2>(a, wdt, stream) : launch_codes_any<kFuseSwiglu, 4>(a, wdt, stream);
 }
 
 }  // namespace scap

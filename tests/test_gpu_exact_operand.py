@@ -152,8 +152,35 @@ def test_values_that_are_not_finite():
         assert np.array_equal(np.nonzero(bad)[0], [3, 4, 6, 8])
 
 
+# 3-4 tokens on this kernel, either side of the layer sizes where it stops (3 tokens 2^25 weights; 32768 columns)
 @pytest.mark.parametrize("dt", [BF16, F16, I8])
-@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
+@pytest.mark.parametrize("K,N", [(33, 272), (1000, 4112), (4097, 528), (2048, 16384), (2056, 16384), (40, 32768), (40, 32784)])
+def test_exact_operand_few_tokens(K, N, dt):
+    layer = layer_of(K, N, dt, 9900 + K, B=4)
+    xdt = F16 if dt == F16 else BF16
+    X = wl.laplace(4, K, 9901 + K, xdt, loc=0.0, scale=0.6)
+    if dt == F16:
+        X[1, :7] = np.arange(1, 8)  # subnormal inputs count like any other
+    Xf = wl.decode(X, xdt).astype(np.float64)
+    for B, tau in ((3, 0.4), (4, 0.4), (4, 0.0)):
+        say(f"exact operand, few tokens K={K} N={N} dt={dt} B={B} tau={tau}")
+        got, _ = check_against_oracle(layer, X[:B], xdt, 0.0, tau, None, what=f"K={K} N={N} B={B} tau={tau}")
+        sums_within_fp32(got["y"], layer, np.where(np.abs(Xf[:B]) > np.float32(tau), Xf[:B], 0.0), None, f"K={K} N={N} B={B} tau={tau}")
+
+
+def test_subnormal_inputs_keep_their_products():
+    """fp16 inputs below 2^-14 alone: the matrix instruction does not flush them."""
+    layer = layer_of(512, 144, F16, 9950, B=8)
+    X = (np.arange(8 * 512, dtype=np.uint16) % 1000).reshape(8, 512)
+    Xf = wl.decode(X, F16).astype(np.float64)
+    for B in (4, 8):
+        say(f"subnormal inputs B={B}")
+        y = gpu_sparse_fc(layer, X[:B], F16, 0.0, 0.0, None)["y"]
+        sums_within_fp32(y, layer, Xf[:B], None, f"subnormal inputs B={B}")
+
+
+@pytest.mark.parametrize("dt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (264, 520, 144, 2), (1001, 1032, 272, 3), (2048, 4104, 512, 4), (8, 16384, 144, 2), (8, 16392, 144, 4), (2048, 8200, 144, 2), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
 def test_exact_operand_blocks(K, F, N, B, dt):
     """The block's gate|up launch on this kernel (centred inputs) against the oracle, token by token."""
     from test_gpu_swiglu import Block
