@@ -113,7 +113,7 @@ int plan_gemv1(const GemvArgs& g, int wdt, int kc, bool kc_forced, int waves, in
     return out->S <= kFxMaxSplits && (int64_t)out->S * out->T <= 256 ? SCAP_OK : kG1NotApplicable;
 }
 
-Gemv1Args args_of(const GemvArgs& g, const Plan1& pl, int flags) {
+Gemv1Args args_of(const GemvArgs& g, const Plan1& pl, int wdt, int flags) {
     Gemv1Args a{};
     a.W = g.W;
     a.x = g.x;
@@ -133,7 +133,12 @@ Gemv1Args args_of(const GemvArgs& g, const Plan1& pl, int flags) {
     a.T = pl.T;
     a.mode = g.mode;
     a.xdt = g.xdt;
-    a.flags = flags;
+    // (turned_start) eight or more pieces that lie a power of two apart: from 4 MiB, long ones from 2 MiB.  Shorter pieces closer by lose as
+    // much as they gain (dense, us, without / with: 8192 x 4096 bf16, 256 rows 2 MiB apart, 14.8 / 15.1, 8192 x 2048, 128 rows 0.5 MiB apart,
+    // 9.7 / 10.5, but 16384 x 4096 int8, 512 rows 2 MiB apart, 16.1 / 15.0; 4096 x 8192 bf16, 256 rows 4 MiB apart, 15.8 / 14.5).
+    const int64_t apart = (int64_t)pl.Kc * g.N * (wdt == kI8 ? 1 : 2), mib = (int64_t)1 << 20;
+    const bool turn = pl.S >= 8 && (apart & (apart - 1)) == 0 && (apart >= 4 * mib || (apart >= 2 * mib && pl.Kc >= 512));
+    a.flags = flags | (turn ? kG1FlagTurn : 0);
     a.m = g.m;
     a.tau = g.tau;
     // fixed-point hand-over unless the caller asks for partial sums (either flag), the layer is wider than the
@@ -164,7 +169,7 @@ int launch_gemv1(const GemvArgs& g, int wdt, const scap_launch_cfg* cfg, hipStre
     if (rc != SCAP_OK) return rc;
     // rows in flight per wavefront: 4 x 1 KB (16-byte lanes), 8 x 512 bytes (8-byte lanes)
     if (unroll == 0) unroll = pl.i8_half ? 8 : 4;
-    const Gemv1Args a = args_of(g, pl, flags);
+    const Gemv1Args a = args_of(g, pl, wdt, flags);
     switch (wdt) {
         case kF16: return launch_gemv1_wdt<kF16>(a, waves, unroll, stream);
         case kBF16: return launch_gemv1_wdt<kBF16>(a, waves, unroll, stream);
@@ -188,7 +193,7 @@ int launch_gemv1b(const GemvArgs& g, int wdt, int flags, hipStream_t stream) {
     const int rc = plan_gemv1(g, wdt, 0, false, kG1bWaves, 8, b.bt, &pl);
     if (rc != SCAP_OK) return rc;
     if (wdt == kI8 && b.bt > 2 && !pl.i8_half) return kG1NotApplicable;  // 16-byte lanes: two slots only
-    b.a = args_of(g, pl, flags);
+    b.a = args_of(g, pl, wdt, flags);
     if ((size_t)g.B * (size_t)g.N > (size_t)kFxCols) b.a.fx_acc = nullptr;  // one fixed-point word per (token, column)
     // with more slots the partial-sum hand-over loses to the other kernels (its last arrivals fetch 4 S slices)
     if (b.bt > 2 && b.a.fx_acc == nullptr) return kG1NotApplicable;
@@ -224,8 +229,8 @@ int launch_swiglu_block1(const GemvArgs& up, const GemvArgs& dn, int wdt, int up
     if (rc != SCAP_OK) return rc;
     const int segz = pu.tile / 8 / 2;  // gated channels a wavefront slice of the gate|up launch finishes: 32 or 64
     if (pd.Kc % segz != 0 || pd.Kc / segz > kWave) return kG1NotApplicable;
-    Gemv1Args a = args_of(up, pu, up_flags);
-    Gemv1Args b = args_of(dn, pd, down_flags);
+    Gemv1Args a = args_of(up, pu, wdt, up_flags);
+    Gemv1Args b = args_of(dn, pd, wdt, down_flags);
     for (Gemv1Args* q : {&a, &b}) {
         q->m2 = up.m2;
         q->tau2 = up.tau2;
@@ -273,7 +278,7 @@ static int plan_block2_part(const GemvArgs& up, const GemvArgs& dn, int wdt, int
     if (part == 1 && (pl.Kc % kWave) != 0) return kG1NotApplicable;
     g->B = (int)up.B;
     g->bt = four ? 4 : 2;
-    g->a = args_of(src, pl, flags);
+    g->a = args_of(src, pl, wdt, flags);
     if (!fits_fx || (part == 0 && !pl.i8_half)) g->a.fx_acc = nullptr;
     // the gating epilogue parks finished columns behind the partial-sum slots when a slice is finished piecemeal
     if (part == 0 && (size_t)(pl.S + 1) * pl.T * pl.tile > partial_capacity(src.N)) g->a.fx_acc = nullptr;

@@ -42,6 +42,7 @@ constexpr int kG1TicketWords = 32;   // int32 words between the tickets of a til
 constexpr int kG1FlagDeviceScope = 1;  // always fetch the partials with device-coherent loads
 constexpr int kG1FlagAccumulate = 4;   // y += result: every workgroup adds its share to y with fp32 atomics
 constexpr int kG1FlagPartials = 8;     // hand split-K partial sums over as fp32 values (not as fixed-point atomics)
+constexpr int kG1FlagTurn = 1 << 16;    // (set by the launch) the splits begin their lists at different places: turned_start
 constexpr int kG1FlagParkSlices = 16;  // gating epilogue: always take the way through memory (for tests)
 
 // Fixed-point hand-over: one 64-bit word per output column, updated by ONE atomic add per arrival:
@@ -277,6 +278,15 @@ __device__ __forceinline__ void fx_add_escaped(float (&yv)[CPL], const int (&n_e
 
 // exclusive prefix sum across the 64 lanes of a wave
 __device__ __forceinline__ int wave_exclusive_scan(int v) { return wave_inclusive_scan(v) - v; }
+
+// Where a wavefront of `n` listed rows begins (it takes them in a ring).  The K splits run in step, so pieces that lie a power of two
+// apart ask the same memory channels for their rows at the same time; there each split begins somewhere else: at the golden section's
+// multiples, which are spread evenly however many splits there are.  us, without / with: 16384 x 4096 bf16 dense (4 MiB apart)
+// 31.0 / 25.4, 8192 x 8192 27.8 / 24.9.  Elsewhere the pieces' rows are on different channels already, and a ring costs the rows of a piece their
+// neighbours (a bare sweep of 14336 x 4096, 3.5 MiB apart, 23.0 / 23.7): the launch decides (args_of).
+__device__ __forceinline__ int turned_start(int flags, int split, int n) {
+    return (flags & kG1FlagTurn) ? (int)(((uint32_t)n * (((uint32_t)split * 40503u) & 0xffffu)) >> 16) : 0;
+}
 
 // Close the gaps of one token's list: every split's ascending list sits at idx[split*Kc ...] with its count in
 // seg_cnt[split].  Returns the total (in every lane).  One wavefront; entries only move left, and a block of source
@@ -543,9 +553,11 @@ __global__ __launch_bounds__(WAVES * kWave) void gemv1_kernel(const uint16_t* x,
     const char* wbase = reinterpret_cast<const char*>(a.W);
     const int n_w = cnt > w ? (cnt - w + WAVES - 1) / WAVES : 0;  // positions w, w + WAVES, ...
 
+    const int first = turned_start(a.flags, split, n_w);
+
     for (int i0 = 0; i0 < n_w; i0 += kWave) {
-        const int e = i0 + lane;
-        const int2 ent = e < n_w ? mylist[e] : make_int2(0, 0);
+        const int e = i0 + lane, at = e + first < n_w ? e + first : e + first - n_w;
+        const int2 ent = e < n_w ? mylist[at] : make_int2(0, 0);
         const int vidx = ent.x;
         const float vd = __int_as_float(ent.y);
         const int nb = min((int)kWave, n_w - i0);

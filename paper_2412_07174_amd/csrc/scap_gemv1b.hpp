@@ -336,13 +336,15 @@ __global__ __launch_bounds__(kG1bWaves * kWave) void gemv1b_kernel(const uint16_
     const char* wbase = reinterpret_cast<const char*>(W);
     const int n_w = cnt > w ? (cnt - w + WAVES - 1) / WAVES : 0;  // positions w, w + WAVES, ...
 
+    const int first = turned_start(flags, split, n_w);
+
     for (int i0 = 0; i0 < n_w; i0 += kWave) {
         const int e = i0 + lane;
         int vidx = 0;
         float vd[BT];
 #pragma unroll
         for (int b = 0; b < BT; ++b) vd[b] = 0.f;
-        if (e < n_w) mylist.get(e, vidx, vd);
+        if (e < n_w) mylist.get(e + first < n_w ? e + first : e + first - n_w, vidx, vd);
         const int nb = min((int)kWave, n_w - i0);
         auto row_load = [&](int i) {
             return load_row<WDT>(wbase, (uint32_t)__builtin_amdgcn_readlane(vidx, i), row_bytes, lane_off);

@@ -494,3 +494,15 @@ def test_batches_of_long_pieces_and_many_workgroups(K, N, rows, wdt):
         X = wl.laplace(B, K, 1951 + K, xdt, loc=0.1, scale=0.5)
         print(f"long pieces of a batch K={K} N={N} rows={rows} wdt={wdt} B={B}", flush=True)
         check_against_oracle(layer, X, xdt, 0.1, 1.1, None, cfg=(0, rows, 0, 16), what=f"K={K} N={N} rows={rows} wdt={wdt} B={B}")
+
+
+# one and two tokens over layers whose K splits lie a power of two of bytes apart: each split takes its list in a ring from a place of its
+# own.  Dense, sparse with the caller's lists, few rows left per wavefront, none
+@pytest.mark.parametrize("K,N,dt", [(4096, 8192, BF16), (16384, 4096, I8)])
+def test_splits_that_start_their_lists_in_turn(K, N, dt):
+    layer, xdt = _layer(K, N, dt, 2100 + K)
+    X = wl.laplace(2, K, 2101 + K, xdt, loc=0.1, scale=0.5)
+    for B in (1, 2):
+        for tau in (0.0, 0.6, 2.6, 1e9):
+            print(f"splits in turn K={K} N={N} B={B} tau={tau}", flush=True)
+            check_against_oracle(layer, X[:B], xdt, 0.1, tau, None, what=f"K={K} N={N} B={B} tau={tau}")
