@@ -160,23 +160,27 @@ __device__ __forceinline__ void reduce_waves_and_emit(const GemvArgs& a, __amdgp
 #pragma unroll
         for (int c0 = 0; c0 < ELEMS; c0 += 8) {
             f32x4_t t = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            const int b = tid >> 5, gi = tid & 31;
 #pragma unroll
             for (int hw = 0; hw < WAVES / H; ++hw) {
                 __syncthreads();  // the buffer is free (the list, or the previous values, have been read)
                 if (w / H == hw) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
+                        if (4 * kg + i < a.B) {  // (tokens that exist: a quarter of the LDS traffic at four)
 #pragma unroll
-                        for (int v = 0; v < 2; ++v)
-                            s_tree[(w % H) * ITEMS + (4 * kg + i) * 32 + 2 * cg + v] =
-                                f32x4_t{acc[c0 + 4 * v][i], acc[c0 + 4 * v + 1][i], acc[c0 + 4 * v + 2][i], acc[c0 + 4 * v + 3][i]};
+                            for (int v = 0; v < 2; ++v)
+                                s_tree[(w % H) * ITEMS + (4 * kg + i) * 32 + 2 * cg + v] =
+                                    f32x4_t{acc[c0 + 4 * v][i], acc[c0 + 4 * v + 1][i], acc[c0 + 4 * v + 2][i], acc[c0 + 4 * v + 3][i]};
+                        }
                     }
                 }
                 __syncthreads();
+                if (b < a.B) {
 #pragma unroll
-                for (int ww = 0; ww < H; ++ww) t += s_tree[ww * ITEMS + tid];
+                    for (int ww = 0; ww < H; ++ww) t += s_tree[ww * ITEMS + tid];
+                }
             }
-            const int b = tid >> 5, gi = tid & 31;
             if (b < a.B) {
                 const int g = ((gi >> 1) * ELEMS + c0) / 4 + (gi & 1);
                 // one split: this is the finished value, and the group's constants are loaded here
