@@ -77,7 +77,8 @@ typedef enum {
  * two-launch form also takes 16 with bf16 -- and rows_per_group is a multiple of 64, rounded up to whole
  * 512-channel list segments by the two-launch form, whose unroll (1, 2, 4; int8: 1, 2) counts 16-row blocks
  * in flight per wavefront).  By default batches of 5 or more tokens run on
- * the matrix cores, and of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
+ * the matrix cores, and so do 4 tokens (3 up to 2^25 weights) with m = 0 or dense mode and activations of the weights' type (int8: bf16)
+ * over at most 32768 columns (int8: and 2^27 weights); of the other calls of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
  * 16384 columns, and those over bf16 layers with K >= 2 N (K a multiple of 8) whose input is dense or that have at most 1024
  * columns and K > 512.  Over int8 weights they also run there when rows_per_group is given, which may then be up to 4096 in
  * layers with N > 4 K or a K that is not a multiple of 8. */
@@ -247,7 +248,7 @@ size_t scap_swiglu_workspace_bytes(int64_t K, int64_t F, int64_t N, int64_t B);
  * its input.  z is never rounded to 16 bits.
  *   W_gu, gu_scale   DEVICE  [K, 2F] from scap_pack_gate_up (and its packed fp16 scales for int8, else NULL).
  *   W_down, down_scale DEVICE [F, N] K-major (scales for int8, else NULL); same dtype wdt as W_gu.
- *   x                DEVICE  [B, K], dtype xdt.   B <= 16 (matrix cores from 5 tokens, int8 from 3); each token
+ *   x                DEVICE  [B, K], dtype xdt.   B <= 16 (matrix cores from 5 tokens, int8 from 3, and the first launch of 2-4 with m_x = 0); each token
  *                            has its own masks, a weight row is read when any token keeps its channel
  *                            (Appendix C).
  *   m_x, tau_x       constants of the block input;  b_gu_fused  DEVICE fp32 [2F] packed fused bias or NULL

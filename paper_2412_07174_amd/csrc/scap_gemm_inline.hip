@@ -1,7 +1,8 @@
-// Batched sparse FC on the matrix cores in ONE launch (gfx950 MFMA): bf16 or int8 weights from 2 tokens, fp16
-// weights from 5, up to 16 tokens.  Two kernels: gemm_inline_kernel (below) keeps per-token value lists in LDS (four
-// token slots, and the launch that reads the lists of the gated product); gemm_inline_raw_kernel (further down, 16
-// token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
+// Batched sparse FC on the matrix cores in ONE launch (gfx950 MFMA) with lists in LDS: what the row-step kernel
+// (scap_gemm_rows.hip) does not take -- centred inputs over more column tiles than compute units, int8 layers of 3 tokens or of more
+// than 2^27 weights, int8 blocks of 3-4 tokens -- and calls of 2-4 tokens that name this kernel.  Two kernels: gemm_inline_kernel
+// (below) keeps per-token value lists in LDS (four token slots; 16 over int8 layers of an odd input length); gemm_inline_raw_kernel
+// (further down, 16 token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
 //
 // Workgroup (K split, column tile of 16 lanes x 16 bytes) centres, thresholds and compacts its Kc input
 // channels of every token into LDS exactly as the one-token kernel does (SCAP Alg. 3 steps 1-2; per-token

@@ -136,7 +136,8 @@ int launch_pack_gate_up(const void* gate, const void* up, int64_t rows, int64_t 
                         hipStream_t stream);
 
 // Batched tokens over bf16 or int8 weights on the matrix cores: possible from kMfmaMinTokens tokens on (the
-// workspace then carries the union lists of the two-launch form), chosen by default from kMfmaAutoTokens
+// workspace then carries the union lists of the two-launch form), chosen by default -- beside launch_gemv's rule for 3-4 tokens whose
+// centred input is the operand itself -- from kMfmaAutoTokens
 // (bf16) / kMfmaAutoTokensI8 (int8) tokens on, where launch_gemv's rules for 2-4 tokens have not chosen a kernel before.
 // From 5 tokens on the vector kernel takes two launches' worth of FMAs (vector / matrix cores at 50 %, us: bf16 14336 x
 // 4096, 5 tokens 44.3 / 28.0, 4096 x 14336, 8 tokens 46.3 / 29.2; fp16 4096 x 11008, 5 tokens 34.5 / 22.3); at 4 tokens
