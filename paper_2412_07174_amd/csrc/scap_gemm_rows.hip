@@ -178,6 +178,53 @@ __device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint3
     }
 }
 
+// Hand-over of a plain call: a wavefront finishes the two tokens whose sums it has emitted by itself -- stores
+// acknowledged, one ticket per (tile, wavefront), 128 bytes apart, the last arrival adds the S partial sums in split order -- so that
+// no wavefront waits for another behind the reduction and the last arrivals of a tile's tokens may be different workgroups
+// (finish_tile: one ticket per workgroup, two barriers).  own, own_union: counts that the first wavefront, whose threads have stored its
+// split's, adds up too.  us per call, there / here: 1024 x 4096 bf16, 4
+// tokens, 6.7 / 5.9, 2048 x 2048 fp16, 5 tokens, 6.9 / 6.1, 4096 x 4096 bf16, 8 tokens, 10.8 / 10.0, 14336 x 4096 int8, 12 tokens, 15.2 / 14.8.
+template <int WDT, int TILE>
+__device__ __forceinline__ void finish_slices(const GemvArgs& a, __amdgpu_buffer_rsrc_t pbuf, int tile, const ColConst& mine, uint32_t own,
+                                              bool own_union) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = uniform(tid >> 6);
+    const int b = tid >> 5, g = tid & 31;  // as reduce_waves_and_emit deals them out
+    static_assert(TILE == 128, "32 groups of 4 columns, 16 tokens, 512 threads");
+    if (2 * w >= a.B) return;  // wave-uniform: no token of this wavefront exists
+    wait_memory_ops();         // my coherent stores have been acknowledged
+    int32_t* ticket = a.counters + tile * kCounterStride + 32 * w;
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (uniform(old) != a.S - 1) return;
+    const uint32_t at = (uint32_t)(((b * a.S * a.T + tile) * TILE + 4 * g) * 4), stride = (uint32_t)a.T * TILE * 4u;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int sp0 = 0; sp0 < a.S; sp0 += 8) {  // 8 loads in flight; slots past the last split ask behind the buffer and get zeros
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = load_coherent16(pbuf, sp0 + j < a.S && b < a.B ? at + (uint32_t)(sp0 + j) * stride : kNoRow);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            s.x += v[j].x;
+            s.y += v[j].y;
+            s.z += v[j].z;
+            s.w += v[j].w;
+        }
+    }
+    if (b < a.B) finish_columns<WDT, TILE>(a, tile, b, g, s, nullptr, mine);
+    if (lane == 0) store_dev(ticket, 0);  // ready for the next call
+    if (w == 0 && (own != 0 || own_union)) {
+        for (int l = 0; l <= a.B; ++l) {
+            const bool is_union = l == a.B;
+            if (is_union ? !own_union : !((own >> l) & 1u)) continue;
+            int run = 0;
+            for (int sp = lane; sp < a.Sl; sp += kWave) run += load_dev(&a.seg_cnt[l * a.Sl + sp]);
+            run = wave_sum(run);
+            if (lane == 0) *(is_union ? a.union_nnz_out : a.nnz_out + l) = run;
+        }
+    }
+}
+
 // workgroups of a launch that a compute unit holds at once (registers)
 constexpr int rows_resident(int wdt, int src, bool ragged) {
     return wdt == kI8Half || (src == kRowsCodes && !ragged && wdt != kI8) ? 2 : 1;
@@ -346,7 +393,25 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
     const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
     reduce_waves_and_emit<WDT, WAVES, FUSE, WHOLE, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
-    finish_tile<WDT, WAVES, TILE, SLOTS, FUSE>(a, pbuf, tile, L, mine);
+    if constexpr (FUSE == kFusePlain && TILE == 128) {
+        const uint32_t own = owned_tokens(a, tile);
+        const bool own_union = tile == 0 && a.union_nnz_out != nullptr, lists = a.idx_out != nullptr;
+        if (a.S > 1) finish_slices<WDT, TILE>(a, pbuf, tile, mine, lists ? 0u : own, !lists && own_union);
+        if ((own == 0 && !own_union) || (a.S > 1 && !lists)) return;
+        // lists: a ticket of their own, taken by the workgroup (the sums above are the same without them)
+        wait_memory_ops();
+        __syncthreads();
+        if (a.S > 1) {
+            int32_t* ticket = a.counters + tile * kCounterStride + 16;
+            if (tid == 0) L.flag[0] = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.S - 1;
+            __syncthreads();
+            if (L.flag[0] == 0) return;
+            if (tid == 0) store_dev(ticket, 0);  // ready for the next call
+        }
+        close_lists<WAVES>(a, L, own, own_union);
+    } else {
+        finish_tile<WDT, WAVES, TILE, SLOTS, FUSE>(a, pbuf, tile, L, mine);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------- launch

@@ -709,6 +709,78 @@ __device__ __forceinline__ void emit_group(const GemvArgs& a, __amdgpu_buffer_rs
         store_coherent16(pbuf, (uint32_t)((((b * a.S + split) * a.T + tile) * TILE + 4 * g) * 4), s);
 }
 
+// Counts and gap-free lists of the tile's tokens, and the size of the union, from what the splits left.  Called by every thread of a
+// workgroup that knows all of it to be there.
+template <int WAVES>
+__device__ __forceinline__ void close_lists(const GemvArgs& a, const Lds& L, uint32_t own, bool own_union) {
+    constexpr int NT = WAVES * kWave;
+    const int tid = threadIdx.x;
+    const int w = uniform(tid >> 6);
+    const int lane = tid & 63;
+    // Counts: one wavefront per list, no barrier between them.  (With one token the union list is the token's list.)
+    {
+        int turn = 0;
+        for (int l = 0; l <= a.B; ++l) {
+            const bool is_union = l == a.B;
+            if (is_union ? !own_union : !((own >> l) & 1u)) continue;
+            if (turn++ % WAVES != w) continue;
+            int run = 0;
+            for (int sp = lane; sp < a.Sl; sp += kWave) run += load_dev(&a.seg_cnt[l * a.Sl + sp]);
+            run = wave_sum(run);
+            if (lane == 0) *(is_union ? a.union_nnz_out : a.nnz_out + l) = run;
+        }
+    }
+    if (a.idx_out == nullptr || a.Sl == 1) return;
+    // Each split left its ascending list in place at idx_out[b*K + segment*Kl ...]; close the gaps.
+    // Every entry moves left or stays, so reading a block of source positions, synchronising, then
+    // writing it, block after block from the left, never overwrites an entry that is still to be read.
+    __syncthreads();
+    int* s_off = L.idx;          // [Sl] exclusive offsets
+    int* s_cnt = L.idx + a.Sl;   // [Sl] counts
+    for (int l = 0; l < a.B; ++l) {
+        if (!((own >> l) & 1u)) continue;
+        __syncthreads();
+        if (w == 0) {
+            int run = 0;
+            for (int s0 = 0; s0 < a.Sl; s0 += kWave) {
+                const int sp = s0 + lane;
+                const int v = sp < a.Sl ? load_dev(&a.seg_cnt[l * a.Sl + sp]) : 0;
+                const int inc = wave_inclusive_scan(v);
+                if (sp < a.Sl) {
+                    s_off[sp] = run + inc - v;
+                    s_cnt[sp] = v;
+                }
+                run += __shfl(inc, kWave - 1, kWave);
+            }
+        }
+        __syncthreads();
+        int32_t* base = a.idx_out + (int64_t)l * a.K;
+        constexpr int PER = 16;
+        for (int c0 = 0; c0 < a.K; c0 += NT * PER) {
+            int vals[PER], dsts[PER];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const int p = c0 + j * NT + tid;
+                dsts[j] = -1;
+                vals[j] = 0;
+                if (p < a.K) {
+                    const int seg = p / a.Kl;
+                    const int r = p - seg * a.Kl;
+                    if (r < s_cnt[seg]) {
+                        vals[j] = load_dev(&base[p]);
+                        dsts[j] = s_off[seg] + r;
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (dsts[j] >= 0) base[dsts[j]] = vals[j];
+            __syncthreads();
+        }
+    }
+}
+
 // Arrival ticket; the last arrival of a tile adds the S partials (fixed association), writes y and clears
 // the counter, and closes the gaps between the per-split index lists of the tile's tokens (owned_tokens; one token:
 // tile 0).
@@ -720,8 +792,6 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, __amdgpu_buffer_r
     constexpr int NT = WAVES * kWave;
     constexpr int GROUPS = TILE / 4;
     const int tid = threadIdx.x;
-    const int w = uniform(tid >> 6);
-    const int lane = tid & 63;
     float* s_red = L.red;
     const uint32_t own = BT > 1 ? owned_tokens(a, tile) : (tile == 0 && a.nnz_out != nullptr ? 1u : 0u);
     const bool own_union = tile == 0 && a.union_nnz_out != nullptr;
@@ -825,68 +895,7 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, __amdgpu_buffer_r
         wait_memory_ops();
         __syncthreads();
     }
-    // Counts: one wavefront per list, no barrier between them.  (With one token the union list is the token's list.)
-    {
-        int turn = 0;
-        for (int l = 0; l <= a.B; ++l) {
-            const bool is_union = l == a.B;
-            if (is_union ? !own_union : !((own >> l) & 1u)) continue;
-            if (turn++ % WAVES != w) continue;
-            int run = 0;
-            for (int sp = lane; sp < a.Sl; sp += kWave) run += load_dev(&a.seg_cnt[l * a.Sl + sp]);
-            run = wave_sum(run);
-            if (lane == 0) *(is_union ? a.union_nnz_out : a.nnz_out + l) = run;
-        }
-    }
-    if (a.idx_out == nullptr || a.Sl == 1) return;
-    // Each split left its ascending list in place at idx_out[b*K + segment*Kl ...]; close the gaps.
-    // Every entry moves left or stays, so reading a block of source positions, synchronising, then
-    // writing it, block after block from the left, never overwrites an entry that is still to be read.
-    __syncthreads();
-    int* s_off = L.idx;          // [Sl] exclusive offsets
-    int* s_cnt = L.idx + a.Sl;   // [Sl] counts
-    for (int l = 0; l < a.B; ++l) {
-        if (!((own >> l) & 1u)) continue;
-        __syncthreads();
-        if (w == 0) {
-            int run = 0;
-            for (int s0 = 0; s0 < a.Sl; s0 += kWave) {
-                const int sp = s0 + lane;
-                const int v = sp < a.Sl ? load_dev(&a.seg_cnt[l * a.Sl + sp]) : 0;
-                const int inc = wave_inclusive_scan(v);
-                if (sp < a.Sl) {
-                    s_off[sp] = run + inc - v;
-                    s_cnt[sp] = v;
-                }
-                run += __shfl(inc, kWave - 1, kWave);
-            }
-        }
-        __syncthreads();
-        int32_t* base = a.idx_out + (int64_t)l * a.K;
-        constexpr int PER = 16;
-        for (int c0 = 0; c0 < a.K; c0 += NT * PER) {
-            int vals[PER], dsts[PER];
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int p = c0 + j * NT + tid;
-                dsts[j] = -1;
-                vals[j] = 0;
-                if (p < a.K) {
-                    const int seg = p / a.Kl;
-                    const int r = p - seg * a.Kl;
-                    if (r < s_cnt[seg]) {
-                        vals[j] = load_dev(&base[p]);
-                        dsts[j] = s_off[seg] + r;
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < PER; ++j)
-                if (dsts[j] >= 0) base[dsts[j]] = vals[j];
-            __syncthreads();
-        }
-    }
+    close_lists<WAVES>(a, L, own, own_union);
 }
 
 // LDS bytes one workgroup needs: header + max(list, reduction buffers, offset tables)
