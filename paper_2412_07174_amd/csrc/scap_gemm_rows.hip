@@ -18,9 +18,9 @@
 // 8 KB of rows (int8: per 4), out of L2.
 //
 // What bounds it: the row stream (6.3 TB/s in 256-byte pieces over a long launch, 7.1 over a short one), then the reduction of eight
-// wavefronts (1 us) and the hand-over (2-3 us).  us per call, staged tile / here: 4096 x 28672 bf16, 16 tokens at 70 %, 47.4 / 39.9;
-// 14336 x 4096 26.2 / 24.7; 4096 x 11008 fp16, 8 tokens at 50 %, 23.5 / 20.0; 14336 x 4096 int8, 12 tokens at 70 %, 19.0 / 16.0;
-// 4096 x 4096 bf16, 8 tokens, 13.1 / 10.2.
+// wavefronts (1 us) and the hand-over (2 us).  us per call, staged tile / here: 4096 x 28672 bf16, 16 tokens at 70 %, 50.6 / 42.8;
+// 14336 x 4096 at 50 % 27.7 / 25.2; 4096 x 11008 fp16, 8 tokens at 50 %, 22.7 / 20.6; 14336 x 4096 int8, 12 tokens at 70 %, 19.0 / 16.0;
+// 4096 x 4096 bf16, 8 tokens at 50 %, 12.5 / 10.5.
 //
 #include <algorithm>
 #include <atomic>
