@@ -33,8 +33,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    constexpr bool WHOLE = false;
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);  // behind both uses of the reduction buffer
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + kTreeFloats;  // behind both uses of the reduction buffer
     const int tid = threadIdx.x;
     const int w = uniform(tid >> 6);
     const int lane = tid & 63;
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave) void gemm_inline_kernel(const 
     // reduction (not at the start: no registers for them while the rows stream)
     const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the list is done with
+    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the list is done with
 
     // ------------------------------------------------------------------ 4. last arrival finishes the tile
     finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
@@ -455,8 +454,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, BT>(reinterpret_cast<char*>(smem_raw), a.Kc);
-    constexpr bool WHOLE = false;
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + kTreeFloats;
     char* xs = reinterpret_cast<char*>(L.idx + a.Kc);  // staged inputs [16][Kc * 2 + pad] in place of the value lists
     const uint32_t xrow = (uint32_t)a.Kc * 2 + kRawPad;
     const int tid = threadIdx.x;
@@ -635,7 +633,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
     // reduction (not at the start: no registers for them while the rows stream)
     const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
     const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the tile is done with
+    reduce_waves_and_emit<WDT, WAVES, FUSE, WDT != kI8>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier: the tile is done with
 
     // ------------------------------------------------------------------ 4. last arrival finishes the tile
     finish_tile<WDT, WAVES, TILE, BT, FUSE>(a, pbuf, tile, L, mine);
@@ -766,7 +764,7 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     const int rc = plan_splits(a, tile_cols, bt, kc, kc_forced, budget, kWave, sc);
     if (rc != SCAP_OK) return rc;
     if (a.Kc > kc_cap) return SCAP_ERR_SHAPE;
-    size_t red = (size_t)tree_floats(false) * 4;
+    size_t red = (size_t)kTreeFloats * 4;
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
     *lds_out = lds_bytes(a.Kc, bt, red);

@@ -31,6 +31,7 @@
 namespace scap {
 
 constexpr int kStepRows = 32;  // rows of one matrix instruction
+constexpr int kWideTokens = 4;  // up to so many tokens the K splits of a plain call meet as 64-bit values (finish_wide)
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
 // Elements of the two halves of a word that the pruner drops become 0; flags: 1 in each half that is kept.
@@ -178,52 +179,155 @@ __device__ __forceinline__ void mfma_rows(f32x4_t* __restrict__ acc, const uint3
     }
 }
 
+// A wavefront's sums of the existing tokens go to its 8 KB of LDS, [16 tokens][32 groups of 4 columns], on top of what it has left there before.
+__device__ __forceinline__ void park_sums(const GemvArgs& a, const f32x4_t (&acc)[8], float* s_red, bool more) {
+    int tid = threadIdx.x;
+    asm("" : "+v"(tid));  // (addresses are made here: kept, they would take registers of the loop)
+    const int kg = (tid >> 4) & 3;
+    f32x4_t* const at = reinterpret_cast<f32x4_t*>(s_red) + (tid >> 6) * (kMfmaTokens * 32) + 4 * kg * 32 + 2 * (tid & 15);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (4 * kg + i < a.B) {
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                f32x4_t t = f32x4_t{acc[4 * v][i], acc[4 * v + 1][i], acc[4 * v + 2][i], acc[4 * v + 3][i]};
+                if (more) t += at[i * 32 + v];
+                at[i * 32 + v] = t;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);  // (a few registers at a time)
+    }
+}
+
+__device__ __forceinline__ float4 narrow(const double (&s)[4]) { return make_float4((float)s[0], (float)s[1], (float)s[2], (float)s[3]); }
+__device__ __forceinline__ void add_to(double (&s)[4], const float4& v) {
+    s[0] += (double)v.x;
+    s[1] += (double)v.y;
+    s[2] += (double)v.z;
+    s[3] += (double)v.w;
+}
+
+// The eight wavefronts' sums of a thread's token and 4 columns, in wavefront order, added in 64 bits and rounded once, to a finished value
+// or a split's sum (up to kWideTokens tokens, plain calls: not even that, finish_wide).  The matrix unit rounds twice a step (a sum of 16 products
+// each); eight additions here and those over the splits, in 32 bits, came on top and took calls of 3-4 tokens to up to twice the error of the
+// vector kernels, whose splits meet in fixed point.  Relative error against 64 bits, those / all in 32 bits / so: 4 tokens, 4096 x 4096 bf16 at 50 %
+// 4.0e-8 / 7.8e-8 / 3.7e-8, 1024 x 4096 fp16 at 90 % 4.4e-8 / 7.1e-8 / 4.3e-8, 14336 x 4096 int8 dense 8.4e-8 / 8.8e-8 / 4.5e-8; 8 tokens, before the
+// row steps / 32 bits / so: 8192 x 16384 fp16 at 50 % 1.25e-7 / 1.59e-7 / 0.94e-7.  Two columns a lane and eight loads in flight, the additions cost
+// nothing that shows (1024 x 4096 bf16, 4 tokens, 5.8 us both ways, 2048 x 2048, 16 tokens, 6.8 / 6.6; four columns a lane 6.3).
+template <int WDT, int FUSE>
+__device__ __forceinline__ void add_waves_and_emit(const GemvArgs& a, __amdgpu_buffer_rsrc_t pbuf, int tile, int split, const float* s_red, float* s_fin) {
+    const int b = threadIdx.x >> 5, g = threadIdx.x & 31;
+    __syncthreads();
+    if (b >= a.B) return;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < kInlineWaves; ++w) add_to(t, reinterpret_cast<const float4*>(s_red)[w * (kMfmaTokens * 32) + threadIdx.x]);
+    emit_group<WDT, kMfmaTile, FUSE>(a, pbuf, tile, split, b, g, narrow(t), s_fin, a.S == 1 ? load_col_const<WDT, kMfmaTile>(a, tile, g) : ColConst{});
+}
+
+// Whether the calling wavefront is the last of the tile's workgroups at its ticket: its own stores are acknowledged first.
+__device__ __forceinline__ bool last_arrival(const GemvArgs& a, int32_t* ticket) {
+    wait_memory_ops();
+    int old = 0;
+    if ((threadIdx.x & 63) == 0) old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return uniform(old) == a.S - 1;
+}
+// ... which makes the ticket ready for the next call, and (the first wavefront, whose threads have stored its split's) adds the counts up.
+__device__ __forceinline__ void after_last(const GemvArgs& a, int32_t* ticket, uint32_t own, bool own_union) {
+    const int lane = threadIdx.x & 63;
+    if (lane == 0) store_dev(ticket, 0);
+    if (uniform(threadIdx.x >> 6) != 0 || (own == 0 && !own_union)) return;
+    for (int l = 0; l <= a.B; ++l) {
+        const bool is_union = l == a.B;
+        if (is_union ? !own_union : !((own >> l) & 1u)) continue;
+        int run = 0;
+        for (int sp = lane; sp < a.Sl; sp += kWave) run += load_dev(&a.seg_cnt[l * a.Sl + sp]);
+        run = wave_sum(run);
+        if (lane == 0) *(is_union ? a.union_nnz_out : a.nnz_out + l) = run;
+    }
+}
+
 // Hand-over of a plain call: a wavefront finishes the two tokens whose sums it has emitted by itself -- stores
 // acknowledged, one ticket per (tile, wavefront), 128 bytes apart, the last arrival adds the S partial sums in split order -- so that
 // no wavefront waits for another behind the reduction and the last arrivals of a tile's tokens may be different workgroups
-// (finish_tile: one ticket per workgroup, two barriers).  own, own_union: counts that the first wavefront, whose threads have stored its
-// split's, adds up too.  us per call, there / here: 1024 x 4096 bf16, 4
+// (finish_tile: one ticket per workgroup, two barriers).  own, own_union: counts that are added up, too.  us per call, there / here: 1024 x 4096 bf16, 4
 // tokens, 6.7 / 5.9, 2048 x 2048 fp16, 5 tokens, 6.9 / 6.1, 4096 x 4096 bf16, 8 tokens, 10.8 / 10.0, 14336 x 4096 int8, 12 tokens, 15.2 / 14.8.
 template <int WDT, int TILE>
 __device__ __forceinline__ void finish_slices(const GemvArgs& a, __amdgpu_buffer_rsrc_t pbuf, int tile, const ColConst& mine, uint32_t own,
                                               bool own_union) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = uniform(tid >> 6);
-    const int b = tid >> 5, g = tid & 31;  // as reduce_waves_and_emit deals them out
+    const int w = uniform(threadIdx.x >> 6);
+    const int b = threadIdx.x >> 5, g = threadIdx.x & 31;  // as add_waves_and_emit deals them out
     static_assert(TILE == 128, "32 groups of 4 columns, 16 tokens, 512 threads");
     if (2 * w >= a.B) return;  // wave-uniform: no token of this wavefront exists
-    wait_memory_ops();         // my coherent stores have been acknowledged
     int32_t* ticket = a.counters + tile * kCounterStride + 32 * w;
-    int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (uniform(old) != a.S - 1) return;
+    if (!last_arrival(a, ticket)) return;
     const uint32_t at = (uint32_t)(((b * a.S * a.T + tile) * TILE + 4 * g) * 4), stride = (uint32_t)a.T * TILE * 4u;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};  // (see add_waves_and_emit)
     for (int sp0 = 0; sp0 < a.S; sp0 += 8) {  // 8 loads in flight; slots past the last split ask behind the buffer and get zeros
         float4 v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = load_coherent16(pbuf, sp0 + j < a.S && b < a.B ? at + (uint32_t)(sp0 + j) * stride : kNoRow);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            s.x += v[j].x;
-            s.y += v[j].y;
-            s.z += v[j].z;
-            s.w += v[j].w;
+        for (int j = 0; j < 8; ++j) add_to(s, v[j]);
+    }
+    if (b < a.B) finish_columns<WDT, TILE>(a, tile, b, g, narrow(s), nullptr, mine);
+    after_last(a, ticket, own, own_union);
+}
+
+// The same for up to kWideTokens tokens, from the wavefronts' sums on: wavefront b takes token b, two columns a lane, and hands them
+// over as 64-bit values, [B][S][T][128] -- the splits' sums then meet without a rounding, as they do in fixed point on the vector kernels
+// that ran these calls (add_waves_and_emit).
+template <int WDT>
+__device__ __forceinline__ void finish_wide(const GemvArgs& a, int tile, int split, const float* s_red, uint32_t own, bool own_union) {
+    const int lane = threadIdx.x & 63, b = uniform(threadIdx.x >> 6);
+    __syncthreads();
+    if (b >= a.B) return;
+    const int col = tile * kMfmaTile + 2 * lane;  // N is a multiple of 8: both columns exist or none
+    float2 bias = make_float2(0.f, 0.f), scale = make_float2(1.f, 1.f);
+    if (col < a.N) {
+        if (a.bias) bias = *reinterpret_cast<const float2*>(a.bias + col);
+        if (is_int8(WDT)) {
+            const uint32_t h = *reinterpret_cast<const uint32_t*>(a.col_scale + col);
+            scale = make_float2(f16_bits_to_f32(h & 0xFFFFu), f16_bits_to_f32(h >> 16));
         }
     }
-    if (b < a.B) finish_columns<WDT, TILE>(a, tile, b, g, s, nullptr, mine);
-    if (lane == 0) store_dev(ticket, 0);  // ready for the next call
-    if (w == 0 && (own != 0 || own_union)) {
-        for (int l = 0; l <= a.B; ++l) {
-            const bool is_union = l == a.B;
-            if (is_union ? !own_union : !((own >> l) & 1u)) continue;
-            int run = 0;
-            for (int sp = lane; sp < a.Sl; sp += kWave) run += load_dev(&a.seg_cnt[l * a.Sl + sp]);
-            run = wave_sum(run);
-            if (lane == 0) *(is_union ? a.union_nnz_out : a.nnz_out + l) = run;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int w = 0; w < kInlineWaves; ++w) {
+        const float2 v = reinterpret_cast<const float2*>(s_red)[(w * kMfmaTokens + b) * (kMfmaTile / 2) + lane];
+        s0 += (double)v.x;
+        s1 += (double)v.y;
+    }
+    if (a.S > 1) {
+        const __amdgpu_buffer_rsrc_t wide = make_raw_buffer(a.partial, (uint32_t)a.B * a.S * a.T * kMfmaTile * 8u);
+        const uint32_t at = (uint32_t)((b * a.S * a.T + tile) * kMfmaTile + 2 * lane) * 8u, stride = (uint32_t)a.T * kMfmaTile * 8u;
+        store_coherent16(wide, at + (uint32_t)split * stride,
+                         make_float4(__int_as_float(__double2loint(s0)), __int_as_float(__double2hiint(s0)), __int_as_float(__double2loint(s1)),
+                                     __int_as_float(__double2hiint(s1))));
+        int32_t* ticket = a.counters + tile * kCounterStride + 32 * b;
+        if (!last_arrival(a, ticket)) return;
+        s0 = s1 = 0.0;
+        for (int sp0 = 0; sp0 < a.S; sp0 += 8) {
+            float4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = load_coherent16(wide, sp0 + j < a.S ? at + (uint32_t)(sp0 + j) * stride : kNoRow);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                s0 += __hiloint2double(__float_as_int(v[j].y), __float_as_int(v[j].x));
+                s1 += __hiloint2double(__float_as_int(v[j].w), __float_as_int(v[j].z));
+            }
         }
+        after_last(a, ticket, own, own_union);
+    }
+    if (col < a.N) {
+        float2 y = make_float2((float)s0, (float)s1);
+        if (is_int8(WDT)) y = make_float2(y.x * scale.x, y.y * scale.y);
+        store_coherent8(make_raw_buffer(a.y, (uint32_t)((size_t)a.B * a.N * 4)), (uint32_t)(((int64_t)b * a.N + col) * 4), make_float2(y.x + bias.x, y.y + bias.y));
     }
 }
+
+// LDS floats of the wavefronts' sums: all eight side by side, or (16-byte int8 lanes) a tree
+constexpr int sum_floats(int wdt) { return wdt == kI8 ? kTreeFloats : kInlineWaves * kMfmaTokens * kMfmaTile; }
 
 // workgroups of a launch that a compute unit holds at once (registers)
 constexpr int rows_resident(int wdt, int src, bool ragged) {
@@ -241,8 +345,12 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
 
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, kMfmaTokens>(reinterpret_cast<char*>(smem_raw), 0);
+    // A wavefront's accumulators are added to its place in LDS every so many steps: a long chain would lose what few-row sums keep (fp16, 8192 x
+    // 16384, 8 tokens at 50 %, one chain of 32 steps 1.59e-7, of 8 1.15e-7, of 4 0.94e-7; int8 products fill fewer bits).  us, without / so:
+    // 14336 x 4096 bf16, 8 tokens, 23.4 / 23.6, 4096 x 11008, 16 tokens, 21.9 / 21.9, 14336 x 4096 int8, 8 tokens, 15.3 / 15.3 (every 4 steps 15.5).
+    constexpr int kChainSteps = WDT == kI8Half ? 8 : 4;
     constexpr bool WHOLE = WDT != kI8;  // (16-byte int8 lanes have 256 columns: the sums meet in halves, through a tree)
-    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + tree_floats(WHOLE);
+    if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + sum_floats(WDT);
     const int tid = threadIdx.x;
     const int w = uniform(tid >> 6);
     const int lane = tid & 63;
@@ -348,8 +456,10 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
             mine = (t | (t >> 15)) & 0xffu;
         }
         const uint32_t any = or_of_sixteen(mine);
-        kept_tok += __popc(mine);
-        kept_any += __popc(any);
+        if constexpr (FUSE == kFusePlain) {
+            kept_tok += __popc(mine);
+            kept_any += __popc(any);
+        }
         x = load_x(ahead);
         const uint32_t drop = ~any;
         const uint32_t base = __umul24((uint32_t)((w + st * WAVES) * kStepRows + 8 * kg), row_bytes) + lane_off;
@@ -357,6 +467,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
         for (int j = 0; j < 8; ++j)
             sg.r[j] = load_row_part<WDT>(wbuf, (base + j * row_bytes) | ((drop << (31 - j)) & kNoRow));
     };
+    bool any_parked = false;
     if (n_steps > 0) {
         // Steps st .. st + DEPTH-1 are in flight or in work, the inputs of the DEPTH after them too (loads come back in order: a
         // test that waited for younger inputs would wait for the rows before them).  One way out of the loop: where it also
@@ -368,13 +479,25 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
 #pragma unroll
         for (int u = 0; u < DEPTH - 1; ++u) issue(u, X[u], u + DEPTH, S[u]);
         int st = 0;
-        for (; st + 2 * DEPTH - 1 <= n_steps; st += DEPTH) {
+        const int last = n_steps - 2 * DEPTH + 1;  // turns begin at steps up to here
+        while (st <= last) {
+            const int stop = WHOLE ? min(st + kChainSteps - 1, last) : last;
+            do {
 #pragma unroll
-            for (int u = 0; u < DEPTH; ++u) {
-                issue(st + u + DEPTH - 1, X[(u + DEPTH - 1) % DEPTH], st + u + 2 * DEPTH - 1, S[(u + DEPTH - 1) % DEPTH]);
-                __builtin_amdgcn_sched_barrier(0);
-                mfma_rows<WDT, HALVES>(acc, S[u].op, S[u].r);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < DEPTH; ++u) {
+                    issue(st + u + DEPTH - 1, X[(u + DEPTH - 1) % DEPTH], st + u + 2 * DEPTH - 1, S[(u + DEPTH - 1) % DEPTH]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_rows<WDT, HALVES>(acc, S[u].op, S[u].r);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                st += DEPTH;
+            } while (st <= stop);
+            if (st > last) break;
+            if constexpr (WHOLE) {
+                park_sums(a, acc, L.red, any_parked);
+                any_parked = true;
+#pragma unroll
+                for (int e = 0; e < ELEMS; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             }
         }
 #pragma unroll
@@ -388,15 +511,19 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
         }
     }
 
-    leave_lists<WAVES, SRC>(a, tile, split, k0, kend, kept_tok, kept_any, L);
-    // constants of the column group this thread finishes if its workgroup is the tile's last arrival
-    const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
-    const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
-    reduce_waves_and_emit<WDT, WAVES, FUSE, WHOLE, WHOLE>(a, pbuf, tile, split, acc, L.red, L.fin);  // starts with a barrier
-    if constexpr (FUSE == kFusePlain && TILE == 128) {
+    if constexpr (WHOLE) park_sums(a, acc, L.red, any_parked);
+    if constexpr (FUSE == kFusePlain) leave_lists<WAVES, SRC>(a, tile, split, k0, kend, kept_tok, kept_any, L);  // (a block asks for none of its input)
+    if constexpr (FUSE == kFusePlain && WHOLE) {
         const uint32_t own = owned_tokens(a, tile);
         const bool own_union = tile == 0 && a.union_nnz_out != nullptr, lists = a.idx_out != nullptr;
-        if (a.S > 1) finish_slices<WDT, TILE>(a, pbuf, tile, mine, lists ? 0u : own, !lists && own_union);
+        if (a.B <= kWideTokens) {
+            finish_wide<WDT>(a, tile, split, L.red, lists ? 0u : own, !lists && own_union);
+        } else {
+            const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
+            const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
+            add_waves_and_emit<WDT, FUSE>(a, pbuf, tile, split, L.red, nullptr);
+            if (a.S > 1) finish_slices<WDT, TILE>(a, pbuf, tile, mine, lists ? 0u : own, !lists && own_union);
+        }
         if ((own == 0 && !own_union) || (a.S > 1 && !lists)) return;
         // lists: a ticket of their own, taken by the workgroup (the sums above are the same without them)
         wait_memory_ops();
@@ -410,6 +537,13 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
         }
         close_lists<WAVES>(a, L, own, own_union);
     } else {
+        // constants of the column group this thread finishes if its workgroup is the tile's last arrival
+        const ColConst mine = load_col_const<WDT, TILE>(a, tile, tid % (TILE / 4));
+        const __amdgpu_buffer_rsrc_t pbuf = partial_buffer<TILE>(a);
+        if constexpr (WHOLE)
+            add_waves_and_emit<WDT, FUSE>(a, pbuf, tile, split, L.red, L.fin);
+        else
+            reduce_waves_and_emit<WDT, WAVES, FUSE>(a, pbuf, tile, split, acc, L.red, L.fin);
         finish_tile<WDT, WAVES, TILE, SLOTS, FUSE>(a, pbuf, tile, L, mine);
     }
 }
@@ -449,7 +583,7 @@ void keep_codes(const GemvArgs& a, uint32_t* lo, uint32_t* len) {
 
 template <int WDT, int FUSE, int SRC, bool RAGGED, int SLOTS = kMfmaTokens>
 static int launch_rows_kernel(const GemvArgs& a, hipStream_t stream) {
-    constexpr size_t lds = kHdrBytes + (size_t)tree_floats(WDT != kI8) * 4 +
+    constexpr size_t lds = kHdrBytes + (size_t)sum_floats(WDT) * 4 +
                            (FUSE == kFuseSwiglu ? (size_t)kMfmaTokens * 16 * Vec<WDT>::kElems * 4 : 0);
     static_assert(lds <= kInlineLdsBudget && 2 * lds <= 160 * 1024, "two workgroups per compute unit");
     if (lds > 64 * 1024) {
@@ -535,6 +669,7 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
     const int64_t row_bytes = (int64_t)a.N * (i8 ? 1 : 2);
     const int64_t kc_max = (((int64_t)1 << 31) / row_bytes - 2 * kWave) / kWave * kWave;
     int64_t s_max = (int64_t)(partial_capacity(a.N) / ((size_t)a.T * tile));
+    if (a.B <= kWideTokens) s_max /= 2;
     if (s_max > kMaxSplits) s_max = kMaxSplits;
     if (kc == 0) {
         const int fixed = i8 ? 384 : 192, split = i8 ? 14 : 7;

@@ -104,9 +104,7 @@ constexpr int kInlineSplitRows = 12;  // rows' time that a K split's hand-over c
 // chunks of 64 channels a wavefront compacts from registers: 5 x 16 or 8 x 4 values per lane
 constexpr int inline_max_chunks(int bt) { return bt == 16 ? 5 : 8; }
 
-// LDS floats of the reduction of the wavefronts' sums (and of the final one).  Kernels that run one workgroup per compute
-// unit anyway take all eight wavefronts' sums at once, 64 KB: two barriers and one turn fewer (reduce_waves_and_emit).
-constexpr int tree_floats(bool whole) { return (whole ? 64 : 32) * 1024 / 4; }
+constexpr int kTreeFloats = 32 * 1024 / 4;  // LDS floats of the reduction of the wavefronts' sums (reduce_waves_and_emit)
 // A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
 // offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
 // were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay
@@ -134,8 +132,7 @@ __device__ __forceinline__ uint4 load_row_part(__amdgpu_buffer_rsrc_t rows, uint
 // (FUSE / s_fin: see finish_columns -- with one split the sums are final and may go to the gating step)
 // ONE_LEVEL (8 wavefronts): the form described inside; otherwise a binary tree over the wavefronts.  The
 // two-launch kernel keeps the tree: the one-level form costs it registers it needs for two workgroups per CU.
-// WHOLE: with 64 KB the one-level form takes all wavefronts at once instead of four and four; the same order of sums.
-template <int WDT, int WAVES, int FUSE = kFusePlain, bool ONE_LEVEL = false, bool WHOLE = false>
+template <int WDT, int WAVES, int FUSE = kFusePlain, bool ONE_LEVEL = false>
 __device__ __forceinline__ void reduce_waves_and_emit(const GemvArgs& a, __amdgpu_buffer_rsrc_t pbuf, int tile, int split,
                                                       f32x4_t* __restrict__ acc, float* s_red, float* s_fin = nullptr) {
     constexpr int ELEMS = Vec<WDT>::kElems;
@@ -154,8 +151,8 @@ __device__ __forceinline__ void reduce_waves_and_emit(const GemvArgs& a, __amdgp
         // KB (write-through stores of half-filled 32-byte sectors cost visibly more).  Four barriers per 8
         // columns instead of seven with a tree plus a hand-over to the storing threads (1.3 -> 0.6 us at 16 tokens).
         constexpr int ITEMS = kMfmaTokens * 32;
-        constexpr int H = WHOLE ? WAVES : WAVES / 2;
-        static_assert(H * ITEMS * 16 <= (WHOLE ? 64 : 32) * 1024 && ITEMS == WAVES * kWave, "reduction buffer, one item per thread");
+        constexpr int H = WAVES / 2;
+        static_assert(H * ITEMS * 16 <= kTreeFloats * 4 && ITEMS == WAVES * kWave, "reduction buffer, one item per thread");
         static_assert(ELEMS % 8 == 0, "accumulators are handed over eight columns at a time");
 #pragma unroll
         for (int c0 = 0; c0 < ELEMS; c0 += 8) {

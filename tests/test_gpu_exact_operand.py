@@ -206,3 +206,49 @@ def test_gated_products_below_the_operand_type():
     for b in range(B):
         assert np.count_nonzero(np.abs(gots[b]["z"]) < 2.0 ** -26) > F // 2
         assert np.array_equal(gots[b]["idx_z"], np.nonzero(gots[b]["z"])[0])
+
+
+def _large_and_small(K, N, dt, large, ones):
+    """A layer whose products are 2^24 in channel `large` and 1 in the channels `ones`, with the exact sum of every column."""
+    a, w = (2.0 ** 18, 64) if dt == I8 else (2.0 ** 12, 2.0 ** 12)
+    xdt = F16 if dt == F16 else BF16
+    W = np.zeros((K, N), dtype=np.float32)
+    x = np.zeros(K, dtype=np.float32)
+    W[large], x[large] = w, a
+    W[ones], x[ones] = 1.0, 1.0
+
+    def bits(v, t):
+        if t == F16:
+            return v.astype(np.float16).view(np.uint16)
+        return (np.ascontiguousarray(v, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    if dt == I8:
+        layer = Layer(W.astype(np.int8), dt, np.full(N, 0x3C00, dtype=np.uint16), B=16)
+    else:
+        layer = Layer(bits(W, dt), dt, B=16)
+    return layer, xdt, bits(x, xdt), 2.0 ** 24 + len(ones)
+
+
+@pytest.mark.parametrize("dt", [BF16, F16, I8])
+@pytest.mark.parametrize("K,N", [(256, 144), (4096, 1024)])
+def test_sums_of_wavefronts_and_splits_meet_without_a_rounding(K, N, dt):
+    """2^24 and ones, each 1 in another wavefront's rows or another K split (steps of 32 rows: wavefront step % 8 of its piece; the
+    first and the last step lie in different splits where there are several).  In 32 bits each 1 would be lost on 2^24 (ties to
+    even); the exact sums are representable."""
+    ones = [32, 64, K - 64, K - 32] if K > 256 else [32, 64, 96, 160]
+    layer, xdt, x, want = _large_and_small(K, N, dt, 0, ones)
+    for B in (3, 4, 5, 16):
+        say(f"large and small K={K} N={N} dt={dt} B={B}")
+        y = gpu_sparse_fc(layer, np.tile(x, (B, 1)), xdt, 0.0, 0.0, None)["y"]
+        assert np.all(y == want), (B, y.min(), y.max(), want)
+
+
+@pytest.mark.parametrize("dt", [BF16, F16])
+def test_long_chains_of_a_wavefront_keep_small_products(dt):
+    """One wavefront's rows alone (nine steps, 256 rows apart, of a piece of 2304): 2^24 in the first, ones in a later run of steps, which an
+    accumulator that held 2^24 would lose."""
+    layer, xdt, x, want = _large_and_small(4096, 144, dt, 0, [256 * st for st in (4, 5, 6, 7)])
+    for B in (5, 16):
+        say(f"long chain dt={dt} B={B}")
+        y = gpu_sparse_fc(layer, np.tile(x, (B, 1)), xdt, 0.0, 0.0, None, cfg=(0, 2304, 0, 16))["y"]
+        assert np.all(y == want), (B, y.min(), y.max(), want)
