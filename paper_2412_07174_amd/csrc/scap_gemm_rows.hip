@@ -641,14 +641,13 @@ static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
 // The cost of a split in rows of one workgroup at the rate of a full chip.  Nothing but the weight buffer's offsets bounds a piece
 // (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
 // take: 46 GB/s x 1000 where a full chip has 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
-// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s).  Hence `part` below; a single round
-// pays a little more, for one workgroup per unit has less in flight where few of the rows are kept (4096 x 11008, 5 tokens at 50 / 90 %, S = 2
-// 19.7 / 14.8, S = 5 19.8 / 12.9).  Prologue, reduction and the launch's ends are worth about 192 rows of
-// 256 bytes, half of that for each further round where two workgroups share a unit, and a split's hand-over 7.  From sweeps of all splits
-// over 20 layers, us at the split chosen / the next best: 4096 x 28672 bf16, 16 tokens, S = 1 39.5 / S = 2 44.7; 4096 x 11008, 8
-// tokens, S = 2 19.8 / S = 5 20.1 / S = 3 24.5; 14336 x 4096 S = 8 24.6 / S = 6 26.5; 2048 x 2048 S = 8 7.1 / S = 16 7.5; 8192 x 28672,
-// 6 tokens, S = 1 77.8 / S = 2 81.8, over int8 weights (whose 128-byte pieces leave one workgroup per unit less in flight: 3 % more)
-// S = 2 46.0 / S = 1 49.1.
+// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s): `part`; alone in its round a unit has less in flight, above all where few rows are kept.  One split
+// reads all columns of the same rows at the same time (a few per cent) and hands nothing over (`hand`, `split`).  `fixed`: prologue, reduction and
+// the launch's ends, a quarter of it for each further round where two workgroups share a unit.  Constants fitted to sweeps of all
+// splits over 43 layers, 4, 5 and 12 tokens at 50 and 90 %: the split chosen is 0.35 % (int8) and 0.65 % (16-bit) above the best one on average,
+// 5 and 7.5 % at most.  us at the split chosen / others, at 50 %: 4096 x 28672 bf16, 12 tokens, S = 1 43.6 / S = 2 48.2; 8192 x 28672 bf16, 12 tokens, 1
+// 84.6 / 2 90.0, int8, 5 tokens, 1 48.8 / 2 51.0; 14336 x 4096 bf16, 12 tokens, 8 25.0 / 7 26.9 / 9 32.3; 4096 x 22016 bf16, 5 tokens, 4 35.0 / 1 36.2 / 2 39.6;
+// 4096 x 11008 int8, 5 tokens, 5 12.8 / 2 14.4 / 3 15.4; 2048 x 20480 int8, 5 tokens, 3 12.6 / 1 14.3; 256 x 8192 bf16, 5 tokens, 1 4.5 / 4 5.0.
 // int8 weights run in 8-byte lanes (128-column tiles; 5-16 tokens at 50-70 %, 16-byte / 8-byte lanes: 14336 x 4096 18.0 / 16.0, 4096 x
 // 28672 27.3 / 25.9, 4096 x 4096 10.7 / 8.1); *wdt becomes kI8Half.  Planes also in 16-byte lanes, where there are more narrow tiles than
 // arrival counters.
@@ -672,18 +671,19 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
     if (a.B <= kWideTokens) s_max /= 2;
     if (s_max > kMaxSplits) s_max = kMaxSplits;
     if (kc == 0) {
-        const int fixed = i8 ? 384 : 192, split = i8 ? 14 : 7;
-        const double again = rows_resident(*wdt, src, src != kRowsPlanes && a.K % 8 != 0) == 2 ? 0.5 : 1.0;
+        const int fixed = i8 ? 500 : 340, split = i8 ? 13 : 10, hand = 110;
+        const double again = rows_resident(*wdt, src, src != kRowsPlanes && a.K % 8 != 0) == 2 ? 0.25 : 1.0;
         double best = 0.0;
         for (int64_t sp = 1; sp <= s_max; ++sp) {
             const int64_t c = (int64_t)align_up((size_t)((a.K + sp - 1) / sp), kWave);
             if (c > kc_max) continue;
             const int64_t s = (a.K + c - 1) / c, n = s * a.T, rounds = (n + 255) / 256;
             auto part = [&](int64_t m) {
-                const double x = (double)m / 256.0, alone = n <= 256 ? 0.12 * x * (1.0 - x) + (i8 ? 0.03 : 0.0) : 0.0;
-                return m == 0 ? 0.0 : std::max(0.55, 0.25 + 0.75 * x + alone);
+                const double x = (double)m / 256.0;
+                return m == 0 ? 0.0 : n <= 256 ? std::max(0.55, 0.36 + 0.64 * x + 0.25 * x * (1.0 - x)) : std::max(0.55, 0.25 + 0.75 * x);
             };
-            const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s);
+            const double rows = (double)c * ((double)(n / 256) + part(n % 256));
+            const double cost = rows * (s == 1 ? 0.96 : 1.0) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s) + (s > 1 ? hand : 0);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 kc = (int)c;
