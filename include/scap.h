@@ -78,7 +78,7 @@ typedef enum {
  * 512-channel list segments by the two-launch form, whose unroll (1, 2, 4; int8: 1, 2) counts 16-row blocks
  * in flight per wavefront).  By default batches of 5 or more tokens run on
  * the matrix cores, and so do 4 tokens (3 up to 2^25 weights) with m = 0 or dense mode and activations of the weights' type (int8: bf16)
- * over at most 32768 columns (int8: and 2^27 weights); of the other calls of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
+ * over at most 32768 columns (K not a multiple of 8: and 5 * 2^23 weights; int8: and 2^26 weights, 2^25 beyond 16384 columns); of the other calls of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
  * 16384 columns, and those over bf16 layers with K >= 2 N (K a multiple of 8) whose input is dense or that have at most 1024
  * columns and K > 512.  Over int8 weights they also run there when rows_per_group is given, which may then be up to 4096 in
  * layers with N > 4 K or a K that is not a multiple of 8. */
@@ -244,12 +244,15 @@ size_t scap_swiglu_workspace_bytes(int64_t K, int64_t F, int64_t N, int64_t B);
  * Alg. 3):   z = scap_fc(x; W_up) * silu(scap_fc(x; W_gate)),   y = scap_fc(z; W_down)
  * in two launches.  The first reads the kept rows of the interleaved gate|up matrix; the workgroup that
  * completes a column tile forms z in fp32 (silu(t) = t / (1 + exp(-t))), subtracts m_z, applies the strict
- * threshold tau_z and leaves the kept channels compacted in the workspace.  The second takes those lists as
- * its input.  z is never rounded to 16 bits.
+ * threshold tau_z and leaves the kept channels in the workspace: as compacted lists of fp32 values, or, from 5 tokens on
+ * and for int8 blocks of 3-4 up to 2^27 gate|up weights, as the two 16-bit halves (value and remainder) that the matrix unit multiplies.
+ * The second takes those as its input.  z is never rounded to 16 bits; in two halves z - m_z keeps 16 bits of its mantissa (fp16
+ * weights: 22), as it does in every product on the matrix cores that is not exact by itself.
  *   W_gu, gu_scale   DEVICE  [K, 2F] from scap_pack_gate_up (and its packed fp16 scales for int8, else NULL).
  *   W_down, down_scale DEVICE [F, N] K-major (scales for int8, else NULL); same dtype wdt as W_gu.
- *   x                DEVICE  [B, K], dtype xdt.   B <= 16 (matrix cores from 5 tokens, int8 from 3, and the first launch of 2-4 with m_x = 0); each token
- *                            has its own masks, a weight row is read when any token keeps its channel
+ *   x                DEVICE  [B, K], dtype xdt.   B <= 16 (matrix cores from 5 tokens, int8 from 3, and, with m_x = 0, activations of the weights'
+ *                            type (int8: bf16) and 2F <= 32768, the first launch of 3-4 tokens -- of 2 in small layers
+ *                            and with a short input where its column tiles fill the chip); each token has its own masks, a weight row is read when any token keeps its channel
  *                            (Appendix C).
  *   m_x, tau_x       constants of the block input;  b_gu_fused  DEVICE fp32 [2F] packed fused bias or NULL
  *                    (scap_fold_bias on W_gu with the packed bias gives it).

@@ -846,17 +846,16 @@ int launch_gemm_inline(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg
     const int wdt_in = wdt;
     int bt = 0;
     size_t lds = 0;
-    // 16 token slots, and the centred input is the operand: a kernel of its own.  (Rows that the caller names have to fit here all
-    // the same.)
+    // 16 token slots: row step by row step where that is the faster kernel.  (Rows that the caller names have to fit here all the same.)
     const int src = exact_operand(a, wdt) ? kRowsCodes : kRowsCentre;
-    const bool exact = a.B > 4 || (slots16 && (wdt != kI8 || ((src == kRowsCodes || a.B == 4) && a.N <= kRowsFewCols && (int64_t)a.K * a.N <= kRowsFewI8Weights)));
-    if (exact && kc == 0) {
+    const bool rows = a.B > 4 ? rows_pay(a, wdt) : slots16 && wdt != kI8;
+    if (rows && kc == 0) {
         const int rc = launch_gemm_rows(a, wdt, src, kFusePlain, 0, stream);
         if (rc != SCAP_ERR_SHAPE) return rc;
     }
     const int rc = plan_inline_lanes(a, &wdt, kc, kc != 0, kFusePlain, &bt, &lds, slots16);
     if (rc != SCAP_OK) return rc;
-    if (exact && kc != 0) {
+    if (rows && kc != 0) {
         const int rc2 = launch_gemm_rows(a_in, wdt_in, src, kFusePlain, kc, stream);
         if (rc2 != SCAP_ERR_SHAPE) return rc2;
     }
@@ -888,8 +887,7 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     size_t lds_up = 0, lds_dn = 0;
     int wup = wdt, wdn = wdt;
     const bool exact = exact_operand(up, wdt);
-    if (up.B > 4 || (exact && up.N <= kRowsFewCols && (int64_t)up.K * up.N <= kRowsFewI8Weights && gemm_rows_plans(up, wdt, kRowsCodes) &&
-                     gemm_rows_plans(dn, wdt, kRowsPlanes))) {
+    if (up.B > 4 || ((int64_t)up.K * up.N <= ((int64_t)1 << 27) && rows_pay_gating(up, wdt) && gemm_rows_plans(dn, wdt, kRowsPlanes))) {
         // 16 token slots: the gated product travels as planes of operand halves, and the down launch takes them row step by row step
         const int src = exact ? kRowsCodes : kRowsCentre;
         const bool codes = gemm_rows_plans(up, wdt, src);

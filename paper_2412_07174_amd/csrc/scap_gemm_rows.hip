@@ -31,6 +31,7 @@
 namespace scap {
 
 constexpr int kStepRows = 32;  // rows of one matrix instruction
+constexpr int kRowsFewCols = 32768;  // 2-4 tokens: most columns that run here
 constexpr int kWideTokens = 4;  // up to so many tokens the K splits of a plain call meet as 64-bit values (finish_wide)
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
@@ -552,6 +553,48 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
 bool exact_operand(const GemvArgs& a, int wdt) {
     if (a.xdt != (wdt == kF16 ? kF16 : kBF16)) return false;
     return a.mode == kModeDense || (a.mode == kModeSparse && a.m == 0.f);
+}
+
+// A row that no token keeps costs its issue slot here, and over int8 weights its widening, where the list kernels never meet it: what the row steps
+// gain at 50-70 % in a large layer turns over where few rows are kept.  The lines lie where calls up to 90 % are at most 3 % slower than on those
+// kernels (the worst that are left: 8192 x 16384 int8, 8 tokens, 6 %, odd lengths over int8 weights, 5-8 tokens, 5-7 %); at 95 % many are, by up to 20 %.
+// us there / here at 50, 90 and 95 % (inputs behind a norm):
+// 4 tokens: 4096 x 4096 bf16 14.0 / 9.5, 10.5 / 6.5, 10.5 / 6.4; 4096 x 28672 43.3 / 39.3, 22.9 / 23.4, 18.4 / 19.8; 4096 x 16384 int8 21.6 / 15.4, 13.7 / 12.6,
+// 12.4 / 12.1; 1024 x 20480 int8 10.9 / 8.5, 8.3 / 7.2, 7.9 / 7.1.  Beyond: 8192 x 16384 int8 30.5 / 26.7, 17.1 / 20.9, 14.6 / 19.9; 4096 x 20480 int8 23.0 / 20.2,
+// 13.8 / 15.0, 12.2 / 14.4; odd lengths (70 and 90 %) 4097 x 8192 bf16 16.3 / 13.1, 12.3 / 11.2, beyond 4097 x 11008 18.8 / 17.5, 13.6 / 15.4.
+// 3 tokens, whose lists are shorter, from 2^25 weights on: 2048 x 16384 int8 12.5 / 9.6, 9.5 / 8.6, 8.7 / 8.4, beyond 8192 x 16384 29.4 / 24.7, 15.9 / 20.1, 14.0 / 19.5.
+// 5-6 tokens over int8 weights: 8192 x 8192 20.2 / 16.5, 13.0 / 13.0, 11.1 / 12.4; 4096 x 11008 (70 and 90 %) 14.3 / 12.4, 11.1 / 11.2.  Beyond: 8192 x 16384 31.2 / 27.3, 18.2 / 20.9,
+// 15.0 / 20.0; 2048 x 28672 17.0 / 14.0, 10.7 / 11.4, 8.7 / 10.9; odd (70 and 90 %) 8193 x 8192 19.7 / 15.1, 16.2 / 14.6, 4097 x 12288 15.8 / 14.2, 12.9 / 13.5, beyond 16383 x 8192 30.1 / 28.5, 22.4 / 25.6; centred 4096 x 11008 16.0 / 13.4, 11.4 / 12.2, 10.2 / 12.0,
+// 1024 x 28672 (50 and 90 %) 11.0 / 9.2, 7.3 / 8.2, odd 11185 x 1472 11.3 / 11.2, 9.5 / 10.1, 8.9 / 10.0.  From 7 tokens on the union is larger (8 tokens, 4096 x 22016 at 90 %
+// 19.0 / 19.0, 8192 x 16384 20.5 / 21.8, 12 tokens 23.5 / 22.5) but for wide layers of odd length with centred inputs (12 tokens, 572 x 22016 8.1 / 8.6).
+bool rows_pay(const GemvArgs& a, int wdt) {
+    constexpr int64_t k32M = (int64_t)1 << 25;
+    const int64_t weights = (int64_t)a.K * a.N;
+    const bool exact = exact_operand(a, wdt), odd = a.K % 8 != 0, wide = a.N > 16384;
+    if (a.B <= 4) {
+        if (!exact || a.B < 3 || a.N > kRowsFewCols) return false;
+        if (a.B == 3) return weights <= k32M;
+        if (odd) return 4 * weights <= 5 * k32M;
+        return wdt != kI8 || weights <= (wide ? k32M : 2 * k32M);
+    }
+    if (wdt != kI8) return true;
+    if (odd) return exact ? a.B > 6 || 2 * weights <= 5 * k32M : a.B > 6 && !wide;
+    return a.B > 6 || weights * (exact ? 1 : 2) <= (wide ? k32M : 2 * k32M);
+}
+
+// The gate|up launch of a block with centred inputs of the operand's type.  us per block, two- to four-slot or general kernels / here: 4 tokens 1408 -> 6656
+// fp16 26.9 / 22.5, 4224 -> 14400 bf16 79.4 / 68.8, 4096 -> 11008 59.7 / 56.4 (90 and 95 % 44.7 / 42.6, 40.9 / 42.4); 3 tokens 3328 -> 2368 23.9 / 19.6, 5504 -> 12192 76.3 / 69.9
+// (51.3 / 51.1, 46.0 / 48.0).  Not beyond one round of tiles (2280 -> 19032, 4 tokens, 59.6 / 62.0; 3840 -> 22864, 3 tokens at 94 %, 48.7 / 55.6).
+// Two tokens: small layers (2176 -> 4880 bf16 21.8 / 21.1, 3264 -> 4448 24.7 / 22.4, at 90 % 19.5 / 19.5), and short inputs where the tiles alone fill the chip,
+// no split and nothing handed over: 50 / 70 / 90 %, 1024 -> 14336 bf16 25.1 / 21.7, -, 19.7 / 18.4, 2048 -> 14336 34.0 / 31.4, -, 24.8 / 24.8, 1024 -> 8448 20.8 / 18.0, 19.3 / 17.0, 17.7 / 16.6, int8
+// 18.1 / 16.3, 17.6 / 16.3, 16.4 / 15.8, 1280 -> 14336 int8 21.2 / 19.4, 20.2 / 18.7, 18.5 / 18.1.  Beyond: 2560 -> 14992 bf16 42.7 / 40.2, 36.0 / 34.2, 28.7 / 30.5, 1792 -> 8992 25.2 /
+// 24.3, 22.9 / 21.9, 19.5 / 21.1, 4096 -> 14336 55.2 / 52.8, -, 36.8 / 40.1; int8 1536 -> 14336 21.8 / 19.8, 20.8 / 20.1, 18.1 / 18.8, 4096 -> 14336 (40, 70, 90 %) 36.6 / 35.3, 30.9 / 33.7, 25.1 / 30.5.
+bool rows_pay_gating(const GemvArgs& a, int wdt) {
+    int splits = 0;
+    if (!exact_operand(a, wdt) || a.N > kRowsFewCols || !gemm_rows_plans(a, wdt, kRowsCodes, &splits)) return false;
+    if (a.B > 2) return true;
+    if (wdt == kI8) return splits == 1 && a.K <= 1280;
+    return (int64_t)a.K * a.N <= ((int64_t)1 << 25) || (splits == 1 && a.K <= (a.N >= 24576 ? 2304 : 1024));
 }
 
 // The interval of magnitude codes that the pruner keeps: [lo, lo + len) of the 16-bit patterns without their sign.

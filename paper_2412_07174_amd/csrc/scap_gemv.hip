@@ -112,14 +112,9 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
         return rc == SCAP_ERR_SHAPE ? SCAP_ERR_CONFIG : rc;
     }
     if (lanes == 1) return launch_gemm_mfma(a, wdt, cfg, stream);
-    // 3-4 tokens whose centred input is the matrix operand itself: row step by row step on the matrix cores (products exact, sums in
-    // fp32, as on the vector kernels).  us, four- / three-slot kernel here / rows: 4 tokens 4096 x 4096 bf16 at 50 / 95 % 14.2 / 10.3 and
-    // 10.3 / 7.2, 8192 x 28672 88 / 79 and 34.7 / 35.1, 4096 x 11008 21.9 / 20.2 and 11.8 / 12.6, 14336 x 4096 int8 20.6 / 15.5 and 12.3 / 11.7; 3 tokens
-    // 4096 x 4096 bf16 12.1 / 10.1 and 8.6 / 7.0, 6144 x 3072 int8 11.1 / 9.3 and 8.0 / 8.0.  Larger layers of 3 tokens only gain where
-    // little is pruned (4096 x 11008 bf16 at 50 / 90 % 20.0 / 19.3 and 11.6 / 13.8, int8 15.1 / 13.3 and 10.6 / 12.3), nor do 2 tokens gain
-    // everywhere (1830 x 25104 at 90 % 9.4 / 12.5), nor very large int8 layers (7744 x 32560, 4 tokens, 63.9 / 69.0).
-    if ((a.B == 4 || (a.B == 3 && (int64_t)a.K * a.N <= ((int64_t)1 << 25))) && lanes == 0 && a.mode != kModeFold && exact_operand(a, wdt) &&
-        a.N <= kRowsFewCols && (wdt != kI8 || (int64_t)a.K * a.N <= kRowsFewI8Weights) &&
+    // 3-4 tokens whose centred input is the matrix operand itself: row step by row step on the matrix cores (products exact, the sums of
+    // wavefronts and splits in 64 bits)
+    if (a.B <= 4 && lanes == 0 && a.mode != kModeFold && rows_pay(a, wdt) &&
         !(cfg && (cfg->flags || cfg->waves_per_group || cfg->rows_per_group || cfg->unroll))) {
         const int rc = launch_gemm_rows(a, wdt, kRowsCodes, kFusePlain, 0, stream);
         if (rc != SCAP_ERR_SHAPE) return rc;

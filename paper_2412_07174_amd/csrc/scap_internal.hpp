@@ -157,9 +157,10 @@ int launch_gemm_inline(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, h
 constexpr int kRowsCodes = 0;   // x: 16-bit inputs
 constexpr int kRowsPlanes = 1;  // x, zl_lo: heads and tails
 constexpr int kRowsCentre = 2;  // x: 16-bit inputs of any type, centred in fp32 and split
-constexpr int64_t kRowsFewI8Weights = (int64_t)1 << 27;  // 2-4 tokens: largest int8 layer, and most columns, that run so
-constexpr int kRowsFewCols = 32768;
 bool exact_operand(const GemvArgs& a, int wdt);
+// Whether a plain call of three or more tokens, or the gate|up launch of a block of 2-4, is the faster one on that kernel.
+bool rows_pay(const GemvArgs& a, int wdt);
+bool rows_pay_gating(const GemvArgs& a, int wdt);
 bool gemm_rows_plans(const GemvArgs& a, int wdt, int src, int* splits = nullptr);
 int launch_gemm_rows(const GemvArgs& a, int wdt, int src, int fuse, int kc, hipStream_t stream);
 // The fused block's two launches on the same kernel (bf16 / int8, up to 16 tokens).

@@ -33,16 +33,8 @@ static int launch_block(GemvArgs up, GemvArgs dn, int wdt, int flags, hipStream_
     const GemvArgs up_in = up, dn_in = dn;
     const bool two = (BT == 2 || BT == 4) && up.B >= 2 && !(flags & SCAP_CFG_GENERAL_KERNEL);
     // Inputs that are the matrix operand themselves: the gate|up launch row step by row step on the matrix cores, which leaves the same
-    // lists; products exact, sums in fp32 as here.  us per block, before / so: 4 tokens 1408 -> 6656 fp16 26.9 / 22.5, 4224 -> 14400 bf16
-    // 79.4 / 68.8, 4096 -> 11008 57.9 / 55.5; 3 tokens 3328 -> 2368 23.9 / 19.6, 5504 -> 12192 73.0 / 66.8.  Not beyond one round of tiles
-    // (2280 -> 19032, 4 tokens, 59.6 / 62.0; 3840 -> 22864, 3 tokens at 94 %, 48.7 / 55.6).  Two tokens: small layers (2176 -> 4880 21.8 /
-    // 21.1, 3176 -> 4416 25.1 / 22.4, but 5856 -> 10048 at 93 % 36.7 / 40.7, 4096 -> 6392 34.4 / 35.8), and where the tiles alone fill the
-    // chip, no split and nothing handed over (1664 -> 15104 29.6 / 25.2); over int8 weights, whose two-token kernel is faster, only
-    // there (4096 -> 14336 35.7 / 34.0, 1792 -> 14336 21.4 / 21.4, with two splits 3840 -> 7272 26.5 / 29.1).
-    int splits = 0;
-    const bool rows = two && !(flags & SCAP_CFG_PARK_SLICES) && exact_operand(up_in, wdt) && up_in.N <= kRowsFewCols &&
-                      gemm_rows_plans(up_in, wdt, kRowsCodes, &splits) &&
-                      (up_in.B > 2 || splits == 1 || (wdt != kI8 && (int64_t)up_in.K * up_in.N <= ((int64_t)1 << 25)));
+    // lists (products exact; K splits in fp32, as on the general kernel)
+    const bool rows = two && !(flags & SCAP_CFG_PARK_SLICES) && rows_pay_gating(up_in, wdt);
     if (two && !rows) {
         const int rc = launch_swiglu_block2_pair(up_in, dn_in, wdt, flags, stream);
         if (rc != kG1NotApplicable) return rc;
