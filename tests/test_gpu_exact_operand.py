@@ -47,6 +47,22 @@ def sums_within_fp32(got, layer, D, bias, what):
     assert np.all(off <= bound), f"{what}: {np.max(off / bound)} times the bound"
 
 
+def counts_alone(layer, X, xdt, m, tau, bias, got):
+    """The counts without the lists -- each alone, both, together with y -- against those of the call with lists (checked against the
+    oracle), on tickets of their own; y is the same to the bit whichever outputs are asked for."""
+    B = X.shape[0]
+    for nnz, union in ((True, True), (True, False), (False, True)):
+        y = torch.full((B, layer.N), float("nan"), dtype=torch.float32, device="cuda")
+        n = torch.full((B,), -7, dtype=torch.int32, device="cuda") if nnz else None
+        u = torch.full((1,), -7, dtype=torch.int32, device="cuda") if union else None
+        scap.sparse_fc(layer.W, to_dev(X, xdt), m, tau, f32_dev(bias), col_scale=layer.scale, y=y, nnz_out=n, union_nnz_out=u, workspace=layer.ws)
+        torch.cuda.synchronize()
+        what = f"counts alone K={layer.K} N={layer.N} B={B} tau={tau} nnz={nnz} union={union}"
+        assert not nnz or np.array_equal(n.cpu().numpy(), got["nnz"]), what
+        assert not union or int(u.item()) == got["union_nnz"], what
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), got["y"].view(np.uint32)), what
+
+
 SHAPES = [
     # K, N: one row, less than a step, around one step, around eight steps, odd lengths, ragged tiles, several splits
     (1, 16), (8, 16), (31, 144), (32, 128), (33, 272), (255, 128), (256, 1040), (264, 2048), (777, 144), (1000, 4112), (4097, 528),
@@ -71,6 +87,7 @@ def test_exact_operand_shapes(K, N, dt):
         scap.sparse_fc(layer.W, to_dev(X[:B], xdt), 0.0, tau, f32_dev(bias), col_scale=layer.scale, y=plain, workspace=layer.ws)
         torch.cuda.synchronize()
         assert np.array_equal(plain.cpu().numpy().view(np.uint32), got["y"].view(np.uint32)), "y depends on the outputs requested"
+        counts_alone(layer, X[:B], xdt, 0.0, tau, bias, got)
         # the general vector kernel: the same channels
         if K >= 64:
             other = gpu_sparse_fc(layer, X[:B], xdt, 0.0, tau, bias, cfg=(0, 0, 0, 64))
@@ -101,6 +118,7 @@ def test_centred_operand_shapes(K, N, dt, xdt):
         exact = D @ wide(layer) + bias[None, :]
         bound = ((np.count_nonzero(D, axis=1)[:, None] + 4) * 2.0 ** -24 + half) * (np.abs(D) @ W) + 2.0 ** -22 * np.abs(exact) + 1e-6
         assert np.all(np.abs(got["y"] - exact) <= bound), (K, N, B, m, tau)
+        counts_alone(layer, X[:B], xdt, m, tau, bias, got)
     y = scap.dense_fc(layer.W, to_dev(X[:7], xdt), f32_dev(bias), col_scale=layer.scale, workspace=layer.ws)
     torch.cuda.synchronize()
     exact = Xf[:7].astype(np.float64) @ wide(layer) + bias[None, :]
@@ -165,6 +183,7 @@ def test_exact_operand_few_tokens(K, N, dt):
     for B, tau in ((3, 0.4), (4, 0.4), (4, 0.0)):
         say(f"exact operand, few tokens K={K} N={N} dt={dt} B={B} tau={tau}")
         got, _ = check_against_oracle(layer, X[:B], xdt, 0.0, tau, None, what=f"K={K} N={N} B={B} tau={tau}")
+        counts_alone(layer, X[:B], xdt, 0.0, tau, None, got)
         sums_within_fp32(got["y"], layer, np.where(np.abs(Xf[:B]) > np.float32(tau), Xf[:B], 0.0), None, f"K={K} N={N} B={B} tau={tau}")
 
 
@@ -180,7 +199,7 @@ def test_subnormal_inputs_keep_their_products():
 
 
 @pytest.mark.parametrize("dt", [BF16, F16, I8])
-@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (264, 520, 144, 2), (1001, 1032, 272, 3), (2048, 4104, 512, 4), (8, 16384, 144, 2), (8, 16392, 144, 4), (2048, 8200, 144, 2), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
+@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (264, 520, 144, 2), (1001, 1032, 272, 2), (1001, 14336, 144, 2), (1001, 1032, 272, 3), (2048, 4104, 512, 4), (8, 16384, 144, 2), (8, 16392, 144, 4), (2048, 8200, 144, 2), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
 def test_exact_operand_blocks(K, F, N, B, dt):
     """The block's gate|up launch on this kernel (centred inputs) against the oracle, token by token."""
     from test_gpu_swiglu import Block
@@ -192,7 +211,13 @@ def test_exact_operand_blocks(K, F, N, B, dt):
     for tau_x, tau_z in ((0.0, 0.0), (0.5, float(np.median(zs))), (1.1, float(np.quantile(zs, 0.9))), (0.5, 1e9)):
         say(f"exact operand block K={K} F={F} N={N} B={B} dt={dt} tau_x={tau_x} tau_z={tau_z:.4g}")
         blk.check_batch(X, xdt, 0.0, tau_x, None, None, 0.0, tau_z, None, f"exact operand block {K} {F} {N} {B}")
-        blk.check_batch(X, xdt, 0.05, tau_x, None, None, 0.001, tau_z, None, f"centred operand block {K} {F} {N} {B}")
+        gots = blk.check_batch(X, xdt, 0.05, tau_x, None, None, 0.001, tau_z, None, f"centred operand block {K} {F} {N} {B}")
+        nnz = torch.full((B,), -7, dtype=torch.int32, device="cuda")  # the counts without the lists
+        y = scap.swiglu_block(blk.W_gu, blk.W_down, to_dev(X, xdt), 0.05, tau_x, None, 0.001, tau_z, None, gu_scale=blk.gu_scale,
+                              down_scale=blk.down_scale, nnz_z_out=nnz, workspace=blk.ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(nnz.cpu().numpy(), [g["idx_z"].size for g in gots])
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), np.stack([g["y"] for g in gots]).view(np.uint32))
 
 
 def test_gated_products_below_the_operand_type():
@@ -252,3 +277,29 @@ def test_long_chains_of_a_wavefront_keep_small_products(dt):
         say(f"long chain dt={dt} B={B}")
         y = gpu_sparse_fc(layer, np.tile(x, (B, 1)), xdt, 0.0, 0.0, None, cfg=(0, 2304, 0, 16))["y"]
         assert np.all(y == want), (B, y.min(), y.max(), want)
+
+
+@pytest.mark.parametrize("B", [5, 16])
+def test_blocks_of_more_columns_than_narrow_tiles(B):
+    """int8 down launch in 16-byte lanes (256-column tiles, the sums through a tree): more than 1024 tiles of 128 columns."""
+    from test_gpu_swiglu import Block
+    K, F, N = 64, 72, 131104
+    blk = Block(K, F, N, I8, seed=9990, std=0.05, B=B)
+    X = wl.laplace(B, K, 9991, BF16, loc=0.0, scale=0.8)
+    for m in (0.0, 0.05):
+        say(f"int8 block of many columns B={B} m={m}")
+        blk.check_batch(X, BF16, m, 0.4, None, None, 0.0, 0.01, None, f"many columns B={B} m={m}")
+
+
+@pytest.mark.parametrize("m", [0.0, 0.1])
+def test_longest_inputs(m):
+    """2^20 channels, and a block whose gate|up launch has more of them than LDS-sized pieces could cover: a piece may be as long as the layer."""
+    from test_gpu_swiglu import Block
+    layer = layer_of(1 << 20, 16, F16, 9960)
+    X = wl.laplace(5, 1 << 20, 9961, F16, loc=m, scale=0.6)
+    say(f"longest input m={m}")
+    check_against_oracle(layer, X, F16, m, 1.2, None, what=f"2^20 channels m={m}")
+    blk = Block(700008, 8, 16, BF16, seed=9962, std=0.002, B=6)
+    X = wl.laplace(6, 700008, 9963, BF16, loc=m, scale=0.6)
+    say(f"long block m={m}")
+    blk.check_batch(X, BF16, m, 1.2, None, None, 0.0, 0.05, None, f"long block m={m}")

@@ -543,7 +543,7 @@ STAGED = [
 
 @pytest.mark.parametrize("K,N,B,wdt,xdt", STAGED)
 def test_staged_tile_kernel_shapes(K, N, B, wdt, xdt):
-    """More than 4 tokens with K a multiple of 8 run on the kernel that stages the raw input tile: shortest inputs,
+    """More than 4 tokens with K a multiple of 8 (up to 256 column tiles: row step by row step): shortest inputs,
     one chunk and many, ragged last split, both activation types with both weight types, centring on and off, from
     everything kept to almost nothing kept; and the dense call on the same kernel."""
     if wdt == I8:
@@ -564,11 +564,17 @@ def test_staged_tile_kernel_shapes(K, N, B, wdt, xdt):
 
 @pytest.mark.parametrize("wdt", [BF16, F16])
 def test_staged_tile_kernel_lists_a_superset_of_the_union(wdt):
-    """A wavefront whose first 64-channel chunk is kept entirely lists its other chunks without testing them.
+    """A wavefront of the staged tile whose first 64-channel chunk is kept entirely lists its other chunks without testing them.
     Here every fourth chunk holds large values and the three after it values that every token drops, with 1792
     channels per workgroup (4 chunks per wavefront): the lists are four times the union, and y, the per-token
-    lists and the size of the union (column tile 0 counts it exactly when it is asked for) must not change."""
-    K, N, B = 7168, 392, 16
+    lists and the size of the union (column tile 0 counts it exactly when it is asked for) must not change.  With few
+    columns and m = 0 such calls run row step by row step; beyond 32768 columns with m != 0 on the staged tile."""
+    for K, N, m in ((7168, 392, 0.0), (3584, 32784, 2.0 ** -7)):
+        _lists_a_superset(wdt, K, N, m)
+
+
+def _lists_a_superset(wdt, K, N, m):
+    B = 16
     W = wl.weights(K, N, 541, wdt)
     layer = Layer(W, wdt, B=16)
     rng = np.random.default_rng(542)
@@ -583,11 +589,11 @@ def test_staged_tile_kernel_lists_a_superset_of_the_union(wdt):
     bias = rng.standard_normal(N).astype(np.float32)
     for cfg in ((0, 1792, 0, 16), None):
         say(f"superset lists wdt={wdt} cfg={cfg}")
-        got, want = check_against_oracle(layer, X, wdt, 0.0, 0.5, bias, cfg=cfg, what=f"superset cfg={cfg}")
+        got, want = check_against_oracle(layer, X, wdt, m, 0.5, bias, cfg=cfg, what=f"superset K={K} cfg={cfg}")
         assert want["union_nnz"] == (K // 256) * 64 - 1 + 1
         # the rows that are read, and so the order of every sum, must not depend on which outputs were asked for
         plain = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
-        scap.sparse_fc(layer.W, to_dev(X, wdt), 0.0, 0.5, f32_dev(bias), y=plain, workspace=layer.ws, cfg=cfg)
+        scap.sparse_fc(layer.W, to_dev(X, wdt), m, 0.5, f32_dev(bias), y=plain, workspace=layer.ws, cfg=cfg)
         torch.cuda.synchronize()
         assert np.array_equal(plain.cpu().numpy().view(np.uint32), got["y"].view(np.uint32)), "y depends on the outputs requested"
 

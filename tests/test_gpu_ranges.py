@@ -269,7 +269,8 @@ def test_calibration_of_small_and_awkward_samples(dt):
                 assert np.array_equal(np.float32(got), np.float32(want), equal_nan=True), (v[:5], est, s, got, want)
 
 
-# the staged-tile kernel as it is planned: workgroups of up to 512 channels and longer ones, narrow layers
+# centred batches as they are planned (row steps up to 256 column tiles, int8 layers of odd length with 5-6 tokens on the staged tile):
+# workgroups of up to 512 channels and longer ones, narrow layers
 @pytest.mark.parametrize("wdt", [BF16, F16, I8])
 @pytest.mark.parametrize("K,N", [(64, 128), (512, 512), (4096, 1024), (4104, 1040), (8192, 2048), (5000, 8208)])
 def test_staged_tile_short_and_long_workgroups(K, N, wdt):
@@ -281,9 +282,8 @@ def test_staged_tile_short_and_long_workgroups(K, N, wdt):
             check_against_oracle(layer, X, xdt, 0.1, tau, None, what=f"K={K} N={N} wdt={wdt} B={B} tau={tau}")
 
 
-# each form of its prologue (1, 2, 4 or 5 chunks of 64 channels per wavefront) at the longest and shortest workgroup that
-# takes it, the last workgroup cut inside a chunk; 130 column tiles make more than 256 workgroups, i.e. the 16-deep matrix
-# instruction over 16-bit weights, few tiles the 32-deep one and its larger reduction
+# pieces that the caller names, the last one cut inside a step; 130 column tiles make more than 256 workgroups.  (Row steps; the pieces are
+# those of the staged tile's prologues, which test_staged_tile_of_many_columns reaches)
 @pytest.mark.parametrize("wdt,N", [(BF16, 144), (F16, 144), (I8, 272), (BF16, 130 * 128)])
 @pytest.mark.parametrize("rows,K", [(2368, 2408), (2368, 4720), (2112, 2120), (2048, 4088), (1088, 2160), (1024, 1032), (576, 1144), (512, 1016)])
 def test_staged_tile_prologues(rows, K, wdt, N):
@@ -295,7 +295,7 @@ def test_staged_tile_prologues(rows, K, wdt, N):
             check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
 
 
-# the same over input lengths that are not a multiple of 8 (the staged tile in 8-byte lanes for int8 weights), more than
+# the same over input lengths that are not a multiple of 8 (int8 weights and 5 tokens: the staged tile in 8-byte lanes), more than
 # 256 workgroups among them
 @pytest.mark.parametrize("wdt,N", [(BF16, 144), (F16, 144), (I8, 144), (I8, 130 * 128)])
 @pytest.mark.parametrize("rows,K", [(2368, 2403), (2112, 2113), (1088, 2157), (1024, 1031), (576, 1141), (512, 1017), (64, 7)])
@@ -308,8 +308,8 @@ def test_staged_tile_prologues_of_odd_lengths(rows, K, wdt, N):
             check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
 
 
-# int8 layers around the choice between 16- and 8-byte lanes: both plans cost the same at 28672 columns (16-byte lanes), a
-# tile less or more and 8-byte lanes are cheaper; 3-4 tokens take the same kernel
+# int8 layers around the choice between 16- and 8-byte lanes of the staged tile: both plans cost the same at 28672 columns (16-byte lanes), a
+# tile less or more and 8-byte lanes are cheaper (3-5 tokens; 16 tokens: row steps)
 @pytest.mark.parametrize("K,N", [(1048, 28672), (2056, 28672), (1048, 24576), (2040, 28416), (1023, 28672), (2049, 20496)])
 def test_int8_batches_of_both_lane_widths(K, N):
     layer, xdt = _layer(K, N, I8, 1210 + K)
@@ -319,7 +319,7 @@ def test_int8_batches_of_both_lane_widths(K, N):
         check_against_oracle(layer, X, xdt, 0.1, 0.8, None, what=f"K={K} N={N} B={B}")
 
 
-# ... and of the block's launch that reads lists: 16-byte lanes for the longer of the two
+# blocks with centred inputs over int8 weights (both launches row step by row step) around the sizes where a launch's tiles fill the chip
 @pytest.mark.parametrize("K,F,N", [(64, 6144, 8192), (64, 2048, 8208), (136, 4104, 1040)])
 def test_int8_blocks_of_both_lane_widths(K, F, N):
     blk = Block(K, F, N, I8, 1310 + K, B=16)
@@ -506,3 +506,37 @@ def test_splits_that_start_their_lists_in_turn(K, N, dt):
         for tau in (0.0, 0.6, 2.6, 1e9):
             print(f"splits in turn K={K} N={N} B={B} tau={tau}", flush=True)
             check_against_oracle(layer, X[:B], xdt, 0.1, tau, None, what=f"K={K} N={N} B={B} tau={tau}")
+
+
+# the staged tile where centred batches still run on it: more column tiles than compute units.  Each form of its prologue (1, 2, 4 or 5 chunks
+# of 64 channels per wavefront, pieces on either side of 1536 rows among those of 4) at the shortest and longest piece, even and odd lengths;
+# int8 weights in either lane width
+@pytest.mark.parametrize("wdt,N", [(BF16, 32784), (F16, 32784), (I8, 32784)])
+@pytest.mark.parametrize("rows,K", [(512, 520), (576, 584), (1088, 1096), (1600, 1608), (2112, 2120), (512, 517), (576, 583), (1088, 1091), (64, 7)])
+def test_staged_tile_of_many_columns(rows, K, wdt, N):
+    layer, xdt = _layer(K, N, wdt, 2200 + K)
+    for B in (5, 16):
+        X = wl.laplace(B, K, 2201 + K, xdt, loc=0.1, scale=0.5)
+        for cfg in ((0, rows, 0, 16), None) if B == 5 else ((0, rows, 0, 16),):
+            print(f"many columns rows={rows} K={K} N={N} wdt={wdt} B={B} cfg={cfg}", flush=True)
+            check_against_oracle(layer, X, xdt, 0.1, 1.1, None, cfg=cfg, what=f"{rows} {K} {N} {wdt} {B} {cfg}")
+
+
+# ... and the gate|up launch of blocks there, whose last arrivals leave planes of operand halves.  511 tiles of 128 columns take two rounds, so pieces are
+# as long as the input: 16-bit weights in every chunk form, even and odd lengths; int8 in 16-byte lanes; then int8 in 8-byte lanes (three rounds of two
+# pieces; odd lengths), with the last 256-column tile half past F, and odd lengths on the 16-slot value lists (16 tokens)
+@pytest.mark.parametrize("dt,K,F", [(dt, K, 32704) for K in (264, 1000, 1088, 1600, 2120, 267, 583, 1101) for dt in (BF16, F16)] +
+                                   [(I8, K, 32704) for K in (264, 504, 1000, 1600, 2120, 267, 1601)] +
+                                   [(I8, 264, 16456), (I8, 2000, 24576), (I8, 3000, 24576), (I8, 1040, 22088), (I8, 1041, 22088), (I8, 1601, 22088)])
+def test_centred_blocks_of_many_columns(dt, K, F):
+    N, xdt = 144, F16 if dt == F16 else BF16
+    blk = Block(K, F, N, dt, 2300 + K, std=0.03, B=16)
+    X = wl.laplace(16, K, 2301 + K, xdt, loc=0.1, scale=0.5)
+    zc = oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[0], 0.1, 0.5, 0.0, 0.0, dt, xdt, gate_scale=blk.sg, up_scale=blk.su, down_scale=blk.sd, nthreads=8)["z"]
+    tau_z = float(np.median(np.abs(zc)))
+    for B in (5, 16):
+        print(f"centred block of many columns {K}->{F} dt={dt} B={B}", flush=True)
+        gots = blk.run_batch(X[:B], xdt, 0.1, 0.5, None, None, 0.0, tau_z, None)
+        for b in sorted({0, B // 2, B - 1}):
+            want = oracle.swiglu_block(blk.Wg, blk.Wu, blk.Wd, X[b], 0.1, 0.5, 0.0, tau_z, dt, xdt, gate_scale=blk.sg, up_scale=blk.su, down_scale=blk.sd, nthreads=8)
+            blk.compare(gots[b], want, 0.0, tau_z, f"centred block of many columns {K} {F} dt={dt} B={B} token {b}", matrix_cores=True)

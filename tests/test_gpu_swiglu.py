@@ -430,9 +430,9 @@ def test_ffn_block_full_size_batched(dt, B):
         assert abs(gots[b]["idx_z"].size / F - 0.4) < 0.06
 
 
-# bf16 batches whose gate|up launch runs two workgroups per compute unit, in pieces of more than 1024 rows: up to 512 workgroups
-# in pieces on either side of 1536 rows, and more of them
-@pytest.mark.parametrize("K,F", [(1088, 16448), (1600, 16448), (1600, 32832)])
+# bf16 batches whose gate|up launch runs two workgroups per compute unit, in several pieces and, with up to 512 tiles, in one of more
+# than 1024 rows, on either side of 1536
+@pytest.mark.parametrize("K,F", [(1088, 16448), (1600, 16448), (1600, 32832), (1088, 32704), (1600, 32704)])
 def test_blocks_of_long_pieces_and_many_workgroups(K, F):
     N = 64
     blk = Block(K, F, N, BF16, seed=3200 + K, std=0.03, B=5)

@@ -64,6 +64,12 @@ def test_staged_tile_leaves_room_for_two_workgroups(kernels):
         assert r["vgpr_count"] <= 128, (name, r)
 
 
+def test_row_steps_leave_room_for_two_workgroups_where_the_plan_counts_on_it(kernels):
+    """Inputs that are the operand, whole octets, 16-bit weights; all forms of 8-byte int8 lanes."""
+    for name, r in _of(kernels, r"scap::gemm_rows_kernel<([01], [01], 0, false|3, [01], \d, (true|false)), \d+>").items():
+        assert r["vgpr_count"] <= 128, (name, r)
+
+
 def test_batch_kernels_keep_everything_in_registers(kernels):
-    for name, r in _of(kernels, r"scap::gemm_inline(_raw)?_kernel<.*>").items():
+    for name, r in _of(kernels, r"scap::gemm_(inline|inline_raw|rows)_kernel<.*>").items():
         assert r["private_segment_fixed_size"] == 0 and r["vgpr_spill_count"] == 0, (name, r)
