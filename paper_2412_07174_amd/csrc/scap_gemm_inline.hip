@@ -445,7 +445,7 @@ __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile
 }
 
 // ALONE: one workgroup per compute unit (int8 weights in 16-byte lanes, 194 registers); the others leave room for two.
-template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC, bool LONG>
+template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC>
 __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inline_raw_kernel(const GemvArgs a) {
     constexpr int WAVES = kInlineWaves;
     constexpr int BT = kMfmaTokens;
@@ -477,19 +477,8 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
     const int cg = lane & 15;  // column group (B/C index n); also the token whose values this lane supplies (A index m)
     const int kg = lane >> 4;  // row group: list rows 4*kg .. 4*kg+3 of a block
     const int col0 = tile * TILE + cg * ELEMS;
-    // Two forms of the row loads.  LONG -- fp16 weights and the gate|up launch of a bf16 block, pieces of 1537-2048 rows, all workgroups on the chip at once (up to two
-    // per compute unit) -- keeps plain loads of row 0 for the slots past the list's end and the channels of two blocks ahead in
-    // registers: 4096 x 28672, 16 tokens, takes 49.9 us instead of 51.1, 8192 x 16384 56.0 instead of 56.5, 14336 x 8192 48.4 instead
-    // of 49.0 (over bf16 weights they take the same, but the gating launch, whose epilogue leaves the compiler less room, gains:
-    // block 4096 -> 14336 -> 1024, 16 tokens, 64.9 instead of 65.8, 4096 -> 11008 55.6 / 55.8; 8192 -> 28672, three rounds of
-    // workgroups, 197 against 190 without).  With shorter pieces it is the slower form (11584 x 7040 38.2 against 37.0, 4096
-    // x 22016 47.4 against 40.1), over odd input lengths (14337 x 4096, 10 tokens, 34.6 against 31.1), and in launches of more
-    // workgroups or of one per unit (12280 x 15296 83.3 against 73.2, 30424 x 4672 77.6 against 61.0; bf16 69.2 and 60.8, 16384 x 28672
-    // 185 and 161).
-    static_assert(!LONG || (!ALONE && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu)) && MAXC == 4 && !RAGGED), "what launch_inline_raw chooses it for");
-    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : (LONG ? 0u : kNoRow);
+    const uint32_t lane_off = (col0 < a.N) ? (uint32_t)col0 * Vec<WDT>::kBytes : kNoRow;
     const uint32_t row_bytes = (uint32_t)a.N * Vec<WDT>::kBytes;
-    const char* wbase = reinterpret_cast<const char*>(a.W);
     const __amdgpu_buffer_rsrc_t wbuf = weight_rows(a, k0, row_bytes);
     const bool tok_ok = cg < a.B;  // token slots past B carry zeros
     const char* xs_tok = xs + (size_t)min(cg, a.B - 1) * xrow;
@@ -540,13 +529,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool ok = j < en.left;
-            if constexpr (LONG) {
-                const uint32_t row = ok ? (uint32_t)rj[j] : 0u;
-                const uint4 v = load_weights16(wbase + (uint64_t)row * row_bytes + lane_off);
-                st.r[j] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-            } else {
-                st.r[j] = load_row_part<WDT>(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
-            }
+            st.r[j] = load_row_part<WDT>(wbuf, ok ? __umul24((uint32_t)(rj[j] - k0), row_bytes) + lane_off : kNoRow);
             const float dv = act_code_to_f32(en.code[j], bf16_sel) - m_eff;  // one fp32 subtraction
             const bool keep = ok & tok_ok & (dense | (fabsf(dv) > a.tau));    // strict; NaN is pruned
             dm[j] = keep ? dv : 0.f;
@@ -558,30 +541,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
         split_operand<WDT>(st.d, a_hi, a_lo);
         mfma_block<WDT>(acc, a_hi, a_lo, st.r);
     };
-    if constexpr (LONG) {
-        Rows R;
-        Entries E0, E1;
-        Stage A, Bs;
-        rows_of(w, R);
-        codes_of(R, E0);
-        rows_of(w + WAVES, R);
-        codes_of(R, E1);
-        rows_of(w + 2 * WAVES, R);
-        issue(E0, A);
-        for (int blk = w; blk < n_blocks;) {
-            codes_of(R, E0);
-            rows_of(blk + 3 * WAVES, R);
-            issue(E1, Bs);
-            compute(A);
-            blk += WAVES;
-            if (blk >= n_blocks) break;
-            codes_of(R, E1);
-            rows_of(blk + 3 * WAVES, R);
-            issue(E0, A);
-            compute(Bs);
-            blk += WAVES;
-        }
-    } else if (w < n_blocks) {
+    if (w < n_blocks) {
         Rows R;
         Entries E;
         Stage A, Bs;
@@ -660,7 +620,7 @@ static int launch_inline(const GemvArgs& a, size_t lds, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
 
-template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC, bool LONG = false>
+template <int WDT, int FUSE, bool ALONE, bool RAGGED, int MAXC>
 static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t stream) {
     if (lds > kInlineLdsBudget) return SCAP_ERR_SHAPE;
     if (lds > 64 * 1024) {
@@ -669,13 +629,13 @@ static int launch_inline_raw_chunks(const GemvArgs& a, size_t lds, hipStream_t s
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SCAP_ERR_HIP;
         if (!asked[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC, LONG>),
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kInlineLdsBudget) != hipSuccess)
                 return SCAP_ERR_HIP;
             asked[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC, LONG>), dim3((unsigned)(a.S * a.T)),
+    hipLaunchKernelGGL((gemm_inline_raw_kernel<WDT, FUSE, ALONE, RAGGED, MAXC>), dim3((unsigned)(a.S * a.T)),
                        dim3(kInlineWaves * kWave), lds, stream, a);
     return hipGetLastError() == hipSuccess ? SCAP_OK : SCAP_ERR_HIP;
 }
@@ -685,22 +645,16 @@ static int launch_inline_raw(const GemvArgs& a, size_t lds, hipStream_t stream) 
     if (a.Kc <= 1 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 1>(a, lds, stream);
     if (a.Kc <= 2 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 2>(a, lds, stream);
     if constexpr (!RAGGED || is_int8(WDT)) {
-        if (a.Kc <= 4 * kInlineWaves * kWave) {
-            if constexpr (!RAGGED && !ALONE && (WDT == kF16 || (WDT == kBF16 && FUSE == kFuseSwiglu))) {
-                if (a.Kc > 3 * kInlineWaves * kWave && (long)a.S * a.T <= 512) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 4, true>(a, lds, stream);
-            }
-            return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 4>(a, lds, stream);
-        }
+        if (a.Kc <= 4 * kInlineWaves * kWave) return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, 4>(a, lds, stream);
     }
     // (the gating launch over narrow int8 tiles: pieces of at most four chunks, plan_inline)
-    if constexpr (WDT == kI8Half && FUSE == kFuseSwiglu && !RAGGED)
+    if constexpr (WDT == kI8Half && FUSE == kFuseSwiglu)
         return SCAP_ERR_SHAPE;
     else
         return launch_inline_raw_chunks<WDT, FUSE, ALONE, RAGGED, kRawChunks>(a, lds, stream);
 }
 
-// 16 token slots: the staged-tile kernel, or the value-list kernel where the inputs are the gated product's lists;
-// 4 slots: the value-list kernel (not fp16 weights: 2-4 tokens stay on the vector kernels).
+// 16 token slots: the staged-tile kernel; 4 slots: the value-list kernel (not fp16 weights: 2-4 tokens stay on the vector kernels).
 // An input length that is not a multiple of 8: the staged-tile kernel too (5461 x 2744 bf16, 8 tokens 19.7 -> 17.7 us
 // per call, block 4095 -> 6144 -> 4096 56.0 -> 51.9), but not with int8 weights in 16-byte lanes, where a wavefront has
 // only two chunks to test and the value lists stay 3 % faster (5461 x 2752, 16 tokens 23.3 against 24.0).
@@ -708,24 +662,20 @@ __host__ constexpr bool staged_tile(int wdt, int K) { return wdt != kI8 || K % 8
 
 template <int WDT, int FUSE>
 static int launch_inline_wdt(const GemvArgs& a, int bt, size_t lds, hipStream_t stream) {
-    if (bt == kMfmaTokens) {
-        if constexpr (FUSE == kFuseList) {
-            return SCAP_ERR_CONFIG;  // (16 slots: planes instead of lists, scap_gemm_rows.hip)
-        } else {
+    if constexpr (FUSE != kFuseList) {  // (lists of a gated product have four slots: batches leave planes, scap_gemm_rows.hip)
+        if (bt == kMfmaTokens) {
             if constexpr (WDT == kI8) {
                 if (!staged_tile(WDT, a.K)) return launch_inline<WDT, kMfmaTokens, FUSE>(a, lds, stream);
-            } else if constexpr (WDT == kI8Half) {
-                if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
             } else {
                 if (a.K % 8 != 0) return launch_inline_raw<WDT, FUSE, false, true>(a, lds, stream);
             }
             return launch_inline_raw<WDT, FUSE, WDT == kI8, false>(a, lds, stream);
         }
     }
-    if constexpr (WDT == kF16 || WDT == kI8Half)
-        return SCAP_ERR_CONFIG;
-    else
+    if constexpr (WDT == kI8 || (WDT == kBF16 && FUSE == kFusePlain))  // (16-bit blocks of 2-4 tokens: scap_swiglu.hip)
         return launch_inline<WDT, 4, FUSE>(a, lds, stream);
+    else
+        return SCAP_ERR_CONFIG;
 }
 
 template <int FUSE>
@@ -747,14 +697,10 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     if (wdt == kF16 && bt != kMfmaTokens) return SCAP_ERR_CONFIG;  // fp16: the 16-slot kernels only
     const int tile_cols = wdt == kI8 ? 2 * kMfmaTile : kMfmaTile;
     size_t budget = kInlineLdsBudget;
-    int kc_cap = kMaxSplits * kWave * 1024;  // no cap
-    if (fuse == kFuseList) {
-        kc_cap = 64 * kWave;  // gather_lists: at most 64 segments of 64 channels per workgroup
-    } else {
-        kc_cap = kInlineWaves * kWave * inline_max_chunks(bt);
-        // (a fifth chunk there takes the gating form past its scalar registers)
-        if (wdt == kI8Half && fuse == kFuseSwiglu && bt == kMfmaTokens) kc_cap = kInlineWaves * kWave * 4;
-    }
+    int kc_cap = kInlineWaves * kWave * inline_max_chunks(bt);
+    if (fuse == kFuseList) kc_cap = 64 * kWave;  // gather_lists: at most 64 segments of 64 channels per workgroup
+    // (a fifth chunk there takes the gating form past its scalar registers)
+    if (wdt == kI8Half && fuse == kFuseSwiglu) kc_cap = kInlineWaves * kWave * 4;
     const size_t by_cap = kHdrBytes + (size_t)kc_cap * 4 * (1 + bt);
     if (by_cap < budget) budget = by_cap;
     // 16 slots: a split's partial sums cost the tile's last arrival as much time as kInlineSplitRows rows (sweeps of kc; 4096 x 1024,
@@ -768,7 +714,7 @@ static int plan_inline(GemvArgs& a, int wdt, int kc, bool kc_forced, int fuse, i
     if (fuse == kFuseSwiglu) red += (size_t)bt * tile_cols * 4;
     *bt_out = bt;
     *lds_out = lds_bytes(a.Kc, bt, red);
-    if (bt == kMfmaTokens && fuse != kFuseList && staged_tile(wdt, a.K)) {  // staged-tile form: the inputs as they are in place of the value lists
+    if (bt == kMfmaTokens && staged_tile(wdt, a.K)) {  // staged-tile form: the inputs as they are in place of the value lists
         const size_t body = (size_t)a.Kc * 4 + raw_tile_bytes(a.Kc);
         *lds_out = kHdrBytes + (body > red ? body : red);
     }
@@ -801,8 +747,6 @@ static bool narrow_tiles_fit(const GemvArgs& narrow, const GemvArgs& wide) {
 // tokens, wide / narrow, us: 1024 x 4096 12.0 / 8.5, 4096 x 4096 14.0 / 10.9, 14336 x 4096 21.5 / 19.6, 4096 x 24576 35.3 /
 // 30.3, 16384 x 16384 69.7 / 66.4), where narrow tiles fit; where the two cost the same (4096 x 28672) so do the launches.  At
 // 97-99 % of the cost few tokens gain less than many: 8192 x 16384, 5 tokens, 32.3 / 33.5, 16 tokens 36.3 / 35.9.
-// The launch that reads lists gains less from the narrow tiles (block 2048 -> 8192 -> 2048, 16 tokens,
-// 34.1 / 28.9, 4096 -> 8192 -> 4096 40.5 / 39.3, but 4096 -> 11008 -> 4096 48.9 / 49.4 and 8192 -> 16384 -> 8192 99.5 / 109.7).
 // An input length that is not a multiple of 8: the staged tile exists for narrow tiles only.  It beats the value lists up to 2^26
 // weights (16 tokens, lists / tile: 513 x 1024 17.0 / 8.8, 5461 x 2752 23.3 / 12.5, 14337 x 4096 27.3 / 24.2; not with four times the
 // workgroups: 1023 x 48016, 12 tokens, 25.1 / 26.4); beyond, with up to 8 tokens, where rows start on a cache line or the pieces are
@@ -817,15 +761,14 @@ static int plan_inline_lanes(GemvArgs& a, int* wdt, int kc, bool kc_forced, int 
     int bt = 0;
     size_t lds = 0;
     if (plan_inline(h, kI8Half, kc, kc_forced, fuse, &bt, &lds, slots16) != SCAP_OK) return rc;
-    if (fuse != kFuseList && in.K % 8 != 0) {
+    if (in.K % 8 != 0) {
         const int64_t n = (int64_t)h.S * h.T, w = (int64_t)a.S * a.T;
         const bool little = (int64_t)in.K * in.N <= ((int64_t)1 << 26) && (n < 4 * w || h.Kc < 512);
         const bool few = in.N % kMfmaTile == 0 || h.Kc <= 640 || (h.Kc <= 1536 && n <= 2 * w);
         // (3-4 tokens: against the 4-slot lists, which launch_gemm_inline takes where this stays wide)
         if (!(in.B <= 4 ? little && narrow_tiles_fit(h, a) : little || (in.B <= 8 && few))) return rc;
-    } else {
-        const int percent = fuse == kFuseList ? 77 : 99;
-        if (inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * percent || !narrow_tiles_fit(h, a)) return rc;
+    } else if (inline_cost(h, kMfmaTile) * 100 >= inline_cost(a, 2 * kMfmaTile) * 99 || !narrow_tiles_fit(h, a)) {
+        return rc;
     }
     a = h;
     *lds_out = lds;
@@ -885,7 +828,7 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     GemvArgs up = up_in, dn = dn_in;
     int bt_up = 0, bt_dn = 0;
     size_t lds_up = 0, lds_dn = 0;
-    int wup = wdt, wdn = wdt;
+    int wup = wdt;
     const bool exact = exact_operand(up, wdt);
     if (up.B > 4 || ((int64_t)up.K * up.N <= ((int64_t)1 << 27) && rows_pay_gating(up, wdt) && gemm_rows_plans(dn, wdt, kRowsPlanes))) {
         // 16 token slots: the gated product travels as planes of operand halves, and the down launch takes them row step by row step
@@ -905,19 +848,20 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
         if (rc != SCAP_OK) return rc;
         return launch_gemm_rows(dn, wdt, kRowsPlanes, kFusePlain, 0, stream);
     }
-    int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
+    // 4 token slots: lists of values
+    int rc = plan_inline(up, wdt, 0, false, kFuseSwiglu, &bt_up, &lds_up);
     if (rc != SCAP_OK) return rc;
     up.Kl = up.Kc;
     up.Sl = up.S;
-    rc = plan_inline_lanes(dn, &wdn, 0, false, kFuseList, &bt_dn, &lds_dn);
+    rc = plan_inline(dn, wdt, 0, false, kFuseList, &bt_dn, &lds_dn);
     if (rc != SCAP_OK) return rc;
     dn.Kl = kWave;
     dn.Sl = (dn.K + kWave - 1) / kWave;
     const size_t tables = kHdrBytes + (size_t)dn.Sl * 4;  // offsets of every segment (a tile's last arrival, for its tokens' lists)
     if (lds_dn < tables) lds_dn = tables;
-    rc = launch_inline_any<kFuseSwiglu>(up, wup, bt_up, lds_up, stream);
+    rc = launch_inline_any<kFuseSwiglu>(up, wdt, bt_up, lds_up, stream);
     if (rc != SCAP_OK) return rc;
-    return launch_inline_any<kFuseList>(dn, wdn, bt_dn, lds_dn, stream);
+    return launch_inline_any<kFuseList>(dn, wdt, bt_dn, lds_dn, stream);
 }
 
 }  // namespace scap

@@ -656,7 +656,10 @@ template <int FUSE, int SLOTS = kMfmaTokens>
 static int launch_codes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
     if (wdt == kBF16) return launch_codes<kBF16, FUSE, SLOTS>(a, stream);
     if (wdt == kF16) return launch_codes<kF16, FUSE, SLOTS>(a, stream);
-    return wdt == kI8Half ? launch_codes<kI8Half, FUSE, SLOTS>(a, stream) : SCAP_ERR_CONFIG;
+    if constexpr (SLOTS != 4) {  // (int8 blocks of 3-4 tokens leave planes)
+        if (wdt == kI8Half) return launch_codes<kI8Half, FUSE, SLOTS>(a, stream);
+    }
+    return SCAP_ERR_CONFIG;
 }
 
 template <int WDT, int FUSE>
