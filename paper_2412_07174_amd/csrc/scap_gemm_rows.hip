@@ -686,14 +686,15 @@ static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
 //
 // The cost of a split in rows of one workgroup at the rate of a full chip.  Nothing but the weight buffer's offsets bounds a piece
 // (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
-// take: 46 GB/s x 1000 where a full chip has 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
-// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s): `part`; alone in its round a unit has less in flight, above all where few rows are kept.  One split
-// reads all columns of the same rows at the same time (a few per cent) and hands nothing over (`hand`, `split`).  `fixed`: prologue, reduction and
-// the launch's ends, a quarter of it for each further round where two workgroups share a unit.  Constants fitted to sweeps of all
+// take: 46 GB/s where its share of a full chip's stream is 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
+// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s): `part`; alone in its round a unit has less in flight, above all where few rows are kept.  One split whose
+// tiles all run at once reads all columns of the same rows at the same time (a few per cent), and one split hands nothing over (`hand`, `split`).  `fixed`:
+// prologue, reduction and the launch's ends, a quarter of it for each further round where two workgroups share a unit.  Constants fitted to sweeps of all
 // splits over 43 layers, 4, 5 and 12 tokens at 50 and 90 %: the split chosen is 0.35 % (int8) and 0.65 % (16-bit) above the best one on average,
 // 5 and 7.5 % at most.  us at the split chosen / others, at 50 %: 4096 x 28672 bf16, 12 tokens, S = 1 43.6 / S = 2 48.2; 8192 x 28672 bf16, 12 tokens, 1
 // 84.6 / 2 90.0, int8, 5 tokens, 1 48.8 / 2 51.0; 14336 x 4096 bf16, 12 tokens, 8 25.0 / 7 26.9 / 9 32.3; 4096 x 22016 bf16, 5 tokens, 4 35.0 / 1 36.2 / 2 39.6;
-// 4096 x 11008 int8, 5 tokens, 5 12.8 / 2 14.4 / 3 15.4; 2048 x 20480 int8, 5 tokens, 3 12.6 / 1 14.3; 256 x 8192 bf16, 5 tokens, 1 4.5 / 4 5.0.
+// 4096 x 11008 int8, 5 tokens, 5 12.8 / 2 14.4 / 3 15.4; 2048 x 20480 int8, 5 tokens, 3 12.6 / 1 14.3; 256 x 8192 bf16, 5 tokens, 1 4.5 / 4 5.0; beyond 256
+// tiles 4096 x 49152 int8, 5 tokens, 2 42.0 / 1 46.9, 2048 x 45056 bf16 2 35.0 / 1 37.7, 4096 x 65536 bf16 1 83.8 / 2 85.4.
 // int8 weights run in 8-byte lanes (128-column tiles; 5-16 tokens at 50-70 %, 16-byte / 8-byte lanes: 14336 x 4096 18.0 / 16.0, 4096 x
 // 28672 27.3 / 25.9, 4096 x 4096 10.7 / 8.1); *wdt becomes kI8Half.  Planes also in 16-byte lanes, where there are more narrow tiles than
 // arrival counters.
@@ -729,7 +730,7 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
                 return m == 0 ? 0.0 : n <= 256 ? std::max(0.55, 0.36 + 0.64 * x + 0.25 * x * (1.0 - x)) : std::max(0.55, 0.25 + 0.75 * x);
             };
             const double rows = (double)c * ((double)(n / 256) + part(n % 256));
-            const double cost = rows * (s == 1 ? 0.96 : 1.0) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s) + (s > 1 ? hand : 0);
+            const double cost = rows * (s == 1 && n <= 256 ? 0.96 : 1.0) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s) + (s > 1 ? hand : 0);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 kc = (int)c;
