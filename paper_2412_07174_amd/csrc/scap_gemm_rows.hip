@@ -556,30 +556,31 @@ bool exact_operand(const GemvArgs& a, int wdt) {
 }
 
 // A row that no token keeps costs its issue slot here, and over int8 weights its widening, where the list kernels never meet it: what the row steps
-// gain at 50-70 % in a large layer turns over where few rows are kept.  The lines lie where calls up to 90 % are at most 3 % slower than on those
-// kernels (the worst that are left: 8192 x 16384 int8, 8 tokens, 6 %, odd lengths over int8 weights, 5-8 tokens, 5-7 %); at 95 % many are, by up to 20 %.
-// us there / here at 50, 90 and 95 % (inputs behind a norm):
-// 4 tokens: 4096 x 4096 bf16 14.0 / 9.5, 10.5 / 6.5, 10.5 / 6.4; 4096 x 28672 43.3 / 39.3, 22.9 / 23.4, 18.4 / 19.8; 4096 x 16384 int8 21.6 / 15.4, 13.7 / 12.6,
-// 12.4 / 12.1; 1024 x 20480 int8 10.9 / 8.5, 8.3 / 7.2, 7.9 / 7.1.  Beyond: 8192 x 16384 int8 30.5 / 26.7, 17.1 / 20.9, 14.6 / 19.9; 4096 x 20480 int8 23.0 / 20.2,
-// 13.8 / 15.0, 12.2 / 14.4; odd lengths (70 and 90 %) 4097 x 8192 bf16 16.3 / 13.1, 12.3 / 11.2, beyond 4097 x 11008 18.8 / 17.5, 13.6 / 15.4.
-// 3 tokens, whose lists are shorter, from 2^25 weights on: 2048 x 16384 int8 12.5 / 9.6, 9.5 / 8.6, 8.7 / 8.4, beyond 8192 x 16384 29.4 / 24.7, 15.9 / 20.1, 14.0 / 19.5.
-// 5-6 tokens over int8 weights: 8192 x 8192 20.2 / 16.5, 13.0 / 13.0, 11.1 / 12.4; 4096 x 11008 (70 and 90 %) 14.3 / 12.4, 11.1 / 11.2.  Beyond: 8192 x 16384 31.2 / 27.3, 18.2 / 20.9,
-// 15.0 / 20.0; 2048 x 28672 17.0 / 14.0, 10.7 / 11.4, 8.7 / 10.9; odd (70 and 90 %) 8193 x 8192 19.7 / 15.1, 16.2 / 14.6, 4097 x 12288 15.8 / 14.2, 12.9 / 13.5, beyond 16383 x 8192 30.1 / 28.5, 22.4 / 25.6; centred 4096 x 11008 16.0 / 13.4, 11.4 / 12.2, 10.2 / 12.0,
-// 1024 x 28672 (50 and 90 %) 11.0 / 9.2, 7.3 / 8.2, odd 11185 x 1472 11.3 / 11.2, 9.5 / 10.1, 8.9 / 10.0.  From 7 tokens on the union is larger (8 tokens, 4096 x 22016 at 90 %
-// 19.0 / 19.0, 8192 x 16384 20.5 / 21.8, 12 tokens 23.5 / 22.5) but for wide layers of odd length with centred inputs (12 tokens, 572 x 22016 8.1 / 8.6).
+// gain at 50-70 % in a large layer turns over where few rows are kept, and the host does not know how many that will be.  From sweeps of 52 layers at 50,
+// 70 and 90 % on either kernel: a kind of call runs here up to the size where its loss at 90 % outweighs the gain at 50-70 %, about 10 % against 10 %.
+// us there / here at 50 and 90 %, inside / beyond the line (odd: an input length that is not a multiple of 8):
+// 3 tokens, whose lists are shorter, 2^25 weights: bf16 4096 x 4096 11.8 / 8.8, 9.1 / 6.4; beyond 8192 x 8192 24.7 / 23.1, 13.2 / 14.1, int8 4096 x 14336 17.1 / 14.8, 10.7 / 12.1.
+// 4 tokens, 16-bit weights: 8192 x 16384 47.4 / 44.0, 24.1 / 24.5; odd 9001 x 9600 35.5 / 29.7, 19.9 / 20.7; beyond 16383 x 8192 48.0 / 46.5, 24.8 / 27.1.
+// 4 tokens, int8: 5120 x 13824 20.5 / 16.6, 14.4 / 14.0, wide 4096 x 28672 28.7 / 25.0, 17.6 / 18.9, odd 6001 x 11008 24.4 / 19.4, 15.9 / 17.0; beyond 12288 x 8192
+// 24.5 / 21.4, 14.5 / 16.8, odd 9001 x 9600 24.6 / 22.6, 16.6 / 19.8.
+// 5-6 tokens, int8 (5 here): 16384 x 4096 19.8 / 16.7, 12.9 / 13.0, wide 8192 x 28672 54.5 / 48.2, 33.6 / 35.2, odd 4095 x 28672 32.0 / 27.4, 21.8 / 23.8; beyond 8192 x 16384 31.1 /
+// 27.3, 17.9 / 20.9, odd 8191 x 16384 34.1 / 29.0, 21.4 / 24.9.  Centred: 5120 x 13824 21.7 / 17.9, 15.7 / 16.1, wide 2048 x 20480 15.4 / 13.2, 10.8 / 11.4, odd 8193 x 8192
+// 22.7 / 18.2, 16.5 / 16.6; beyond 6144 x 14336 25.1 / 22.3, 15.7 / 19.2, wide 4096 x 28672 29.3 / 27.4, 19.2 / 22.6, odd 9001 x 9600 26.4 / 23.9, 18.5 / 23.1.
+// The worst that are left at 90 %: 10-17 % (wide layers whose tiles fill 160 of 256 units in one split, 3001 x 20480 int8, 5 tokens centred 14.2 / 16.4; 7-8 tokens, 8192 x 16384
+// int8 20.5 / 23.1 against 32.7 / 29.0 at 50 %); at 95 % more.  From 12 tokens on the union is large enough everywhere (8192 x 16384, 12 tokens, 23.2 / 23.1).
 bool rows_pay(const GemvArgs& a, int wdt) {
-    constexpr int64_t k32M = (int64_t)1 << 25;
     const int64_t weights = (int64_t)a.K * a.N;
+    const auto up_to = [&](int n) { return weights <= (int64_t)n << 23; };
     const bool exact = exact_operand(a, wdt), odd = a.K % 8 != 0, wide = a.N > 16384;
     if (a.B <= 4) {
         if (!exact || a.B < 3 || a.N > kRowsFewCols) return false;
-        if (a.B == 3) return weights <= k32M;
-        if (odd) return 4 * weights <= 5 * k32M;
-        return wdt != kI8 || weights <= (wide ? k32M : 2 * k32M);
+        if (a.B == 3) return up_to(4);
+        if (wdt != kI8) return !odd || up_to(14);
+        return up_to(odd ? 9 : wide ? 16 : 10);
     }
-    if (wdt != kI8) return true;
-    if (odd) return exact ? a.B > 6 || 2 * weights <= 5 * k32M : a.B > 6 && !wide;
-    return a.B > 6 || weights * (exact ? 1 : 2) <= (wide ? k32M : 2 * k32M);
+    if (wdt != kI8 || a.B > 6) return true;
+    if (odd) return up_to(exact ? 14 : 10);
+    return wide ? exact || up_to(5) : up_to(10);
 }
 
 // The gate|up launch of a block with centred inputs of the operand's type.  us per block, two- to four-slot or general kernels / here: 4 tokens 1408 -> 6656

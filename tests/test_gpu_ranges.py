@@ -269,8 +269,7 @@ def test_calibration_of_small_and_awkward_samples(dt):
                 assert np.array_equal(np.float32(got), np.float32(want), equal_nan=True), (v[:5], est, s, got, want)
 
 
-# centred batches as they are planned (row steps up to 256 column tiles, int8 layers of odd length with 5-6 tokens on the staged tile):
-# workgroups of up to 512 channels and longer ones, narrow layers
+# centred batches as they are planned (row steps up to 256 column tiles): workgroups of up to 512 channels and longer ones, narrow layers
 @pytest.mark.parametrize("wdt", [BF16, F16, I8])
 @pytest.mark.parametrize("K,N", [(64, 128), (512, 512), (4096, 1024), (4104, 1040), (8192, 2048), (5000, 8208)])
 def test_staged_tile_short_and_long_workgroups(K, N, wdt):
@@ -295,8 +294,7 @@ def test_staged_tile_prologues(rows, K, wdt, N):
             check_against_oracle(layer, X, xdt, 0.1, tau, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N} {wdt} {B} {tau}")
 
 
-# the same over input lengths that are not a multiple of 8 (int8 weights and 5 tokens: the staged tile in 8-byte lanes), more than
-# 256 workgroups among them
+# the same over input lengths that are not a multiple of 8, more than 256 workgroups among them
 @pytest.mark.parametrize("wdt,N", [(BF16, 144), (F16, 144), (I8, 144), (I8, 130 * 128)])
 @pytest.mark.parametrize("rows,K", [(2368, 2403), (2112, 2113), (1088, 2157), (1024, 1031), (576, 1141), (512, 1017), (64, 7)])
 def test_staged_tile_prologues_of_odd_lengths(rows, K, wdt, N):
@@ -309,7 +307,7 @@ def test_staged_tile_prologues_of_odd_lengths(rows, K, wdt, N):
 
 
 # int8 layers around the choice between 16- and 8-byte lanes of the staged tile: both plans cost the same at 28672 columns (16-byte lanes), a
-# tile less or more and 8-byte lanes are cheaper (3-5 tokens; 16 tokens: row steps)
+# tile less or more and 8-byte lanes are cheaper (3-4 tokens, and 5 over the larger layers of even length; else row steps)
 @pytest.mark.parametrize("K,N", [(1048, 28672), (2056, 28672), (1048, 24576), (2040, 28416), (1023, 28672), (2049, 20496)])
 def test_int8_batches_of_both_lane_widths(K, N):
     layer, xdt = _layer(K, N, I8, 1210 + K)
@@ -484,8 +482,7 @@ def test_three_tokens_over_pieces_past_the_kernels_limit():
         check_against_oracle(layer, X[:B], xdt, 0.1, 0.9, None, what=f"K={K} N={N} B={B}")
 
 
-# 16-bit batches in pieces of more than 1024 rows and more than 256 workgroups: up to 512 of them in pieces on either side of 1536
-# rows, more of them, pieces of more than 2048
+# 16-bit batches in pieces of more than 1024 rows and more than 256 workgroups: up to 512 of them, more of them, pieces of more than 2048
 @pytest.mark.parametrize("wdt", [BF16, F16])
 @pytest.mark.parametrize("K,N,rows", [(2048, 33000, 2048), (1600, 33000, 1600), (1536, 33000, 1536), (4096, 33000, 2048), (2368, 33000, 2368)])
 def test_batches_of_long_pieces_and_many_workgroups(K, N, rows, wdt):
@@ -520,6 +517,15 @@ def test_staged_tile_of_many_columns(rows, K, wdt, N):
         for cfg in ((0, rows, 0, 16), None) if B == 5 else ((0, rows, 0, 16),):
             print(f"many columns rows={rows} K={K} N={N} wdt={wdt} B={B} cfg={cfg}", flush=True)
             check_against_oracle(layer, X, xdt, 0.1, 1.1, None, cfg=cfg, what=f"{rows} {K} {N} {wdt} {B} {cfg}")
+
+
+# ... int8 weights in 8-byte lanes, odd length, pieces of more than four chunks: rows that start on a cache line, 5-8 tokens
+def test_staged_tile_of_odd_lengths_in_long_pieces():
+    rows, K, N = 2112, 2117, 32896
+    layer, xdt = _layer(K, N, I8, 2250)
+    X = wl.laplace(5, K, 2251, xdt, loc=0.1, scale=0.5)
+    print(f"odd length in long pieces rows={rows} K={K} N={N}", flush=True)
+    check_against_oracle(layer, X, xdt, 0.1, 1.1, None, cfg=(0, rows, 0, 16), what=f"{rows} {K} {N}")
 
 
 # ... and the gate|up launch of blocks there, whose last arrivals leave planes of operand halves.  511 tiles of 128 columns take two rounds, so pieces are
