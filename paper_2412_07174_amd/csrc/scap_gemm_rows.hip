@@ -587,15 +587,16 @@ bool rows_pay(const GemvArgs& a, int wdt) {
 // fp16 26.9 / 22.5, 4224 -> 14400 bf16 79.4 / 68.8, 4096 -> 11008 59.7 / 56.4 (90 and 95 % 44.7 / 42.6, 40.9 / 42.4); 3 tokens 3328 -> 2368 23.9 / 19.6, 5504 -> 12192 76.3 / 69.9
 // (51.3 / 51.1, 46.0 / 48.0).  Not beyond one round of tiles (2280 -> 19032, 4 tokens, 59.6 / 62.0; 3840 -> 22864, 3 tokens at 94 %, 48.7 / 55.6).
 // Two tokens: small layers (2176 -> 4880 bf16 21.8 / 21.1, 3264 -> 4448 24.7 / 22.4, at 90 % 19.5 / 19.5), and short inputs where the tiles alone fill the chip,
-// no split and nothing handed over: 50 / 70 / 90 %, 1024 -> 14336 bf16 25.1 / 21.7, -, 19.7 / 18.4, 2048 -> 14336 34.0 / 31.4, -, 24.8 / 24.8, 1024 -> 8448 20.8 / 18.0, 19.3 / 17.0, 17.7 / 16.6, int8
-// 18.1 / 16.3, 17.6 / 16.3, 16.4 / 15.8, 1280 -> 14336 int8 21.2 / 19.4, 20.2 / 18.7, 18.5 / 18.1.  Beyond: 2560 -> 14992 bf16 42.7 / 40.2, 36.0 / 34.2, 28.7 / 30.5, 1792 -> 8992 25.2 /
-// 24.3, 22.9 / 21.9, 19.5 / 21.1, 4096 -> 14336 55.2 / 52.8, -, 36.8 / 40.1; int8 1536 -> 14336 21.8 / 19.8, 20.8 / 20.1, 18.1 / 18.8, 4096 -> 14336 (40, 70, 90 %) 36.6 / 35.3, 30.9 / 33.7, 25.1 / 30.5.
+// no split and nothing handed over, up to the length where the loss at 90 % outweighs the gain at 40-50 % (as in rows_pay). At 40, 70 and 90 %: bf16 1024 -> 14336 24.6 / 21.3,
+// 21.4 / 18.6, 18.9 / 17.2, 2048 -> 11008 28.6 / 26.5, 24.2 / 21.7, 20.0 / 20.0, 4096 -> 14336 47.1 / 45.8, 36.1 / 34.6, 26.2 / 28.8, beyond 6144 -> 14336 62.4 / 61.1, 45.3 / 43.5, 29.9 / 35.5; int8
+// 1024 -> 8448 18.2 / 16.2, 17.2 / 15.8, 16.1 / 15.6, 2048 -> 14336 23.6 / 22.0, 20.7 / 20.6, 18.2 / 19.6, beyond 3072 -> 14336 29.1 / 27.2, 23.8 / 25.7, 19.9 / 23.6, 4096 -> 14336 33.1 / 31.9,
+// 26.4 / 28.9, 21.4 / 26.8.
 bool rows_pay_gating(const GemvArgs& a, int wdt) {
     int splits = 0;
     if (!exact_operand(a, wdt) || a.N > kRowsFewCols || !gemm_rows_plans(a, wdt, kRowsCodes, &splits)) return false;
     if (a.B > 2) return true;
-    if (wdt == kI8) return splits == 1 && a.K <= 1280;
-    return (int64_t)a.K * a.N <= ((int64_t)1 << 25) || (splits == 1 && a.K <= (a.N >= 24576 ? 2304 : 1024));
+    if (wdt == kI8) return splits == 1 && a.K <= 2048;
+    return (int64_t)a.K * a.N <= ((int64_t)1 << 25) || (splits == 1 && a.K <= 4096);
 }
 
 // The interval of magnitude codes that the pruner keeps: [lo, lo + len) of the 16-bit patterns without their sign.
