@@ -1,8 +1,8 @@
 // Batched sparse FC on the matrix cores in ONE launch (gfx950 MFMA) with lists in LDS: what the row-step kernel
-// (scap_gemm_rows.hip) does not take -- centred inputs over more column tiles than compute units, int8 layers of 3 tokens or of more
-// than 2^27 weights, int8 blocks of 3-4 tokens -- and calls of 2-4 tokens that name this kernel.  Two kernels: gemm_inline_kernel
-// (below) keeps per-token value lists in LDS (four token slots; 16 over int8 layers of an odd input length); gemm_inline_raw_kernel
-// (further down, 16 token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
+// (scap_gemm_rows.hip) does not take -- centred inputs over more column tiles than compute units; over int8 weights 3-4 tokens that rows_pay
+// refuses, large layers of 5-6 tokens, blocks of 3-4 tokens that rows_pay_gating refuses -- and calls of 2-4 tokens that name this kernel.
+// Two kernels: gemm_inline_kernel (below) keeps per-token value lists in LDS (four token slots; 16 over int8 layers of an odd input length);
+// gemm_inline_raw_kernel (further down, 16 token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
 //
 // Workgroup (K split, column tile of 16 lanes x 16 bytes) centres, thresholds and compacts its Kc input
 // channels of every token into LDS exactly as the one-token kernel does (SCAP Alg. 3 steps 1-2; per-token
@@ -204,7 +204,7 @@ __device__ __forceinline__ float word_half_to_f32(uint32_t wd, int half) {
 // read back from the staged tile with one channel per lane.  Returns the list length; ends with a barrier.
 // RAGGED (16-bit weights, int8 in 8-byte lanes): K is not a multiple of 8 -- token rows start at any 2-byte boundary and the last octet is cut.  A template
 // argument: the tests for it cost a kernel that does not need them 1 us (14336 x 4096 int8, 12 tokens: 23.3 -> 24.2 us).
-// It exists with the 16-deep matrix instruction, and not for 16-byte int8 lanes.
+// It does not exist for 16-byte int8 lanes.
 template <int WAVES, int MAXC, bool SUPERSET, bool RAGGED>
 __device__ __forceinline__ int stage_inputs_and_list(const GemvArgs& a, int tile, int split, const Lds& L, char* xs,
                                                      uint32_t xrow) {
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(kInlineWaves* kWave, ALONE ? 2 : 4) void gemm_inlin
     // clamped position and no weights (zeros).  The loop runs as long as there is a next block to fetch and the last one
     // is multiplied behind it (TAIL): a stage of loads past the end, even of lanes that fetch nothing, costs a wavefront
     // as much time in the load pipe as a stage of rows (removing the one stage that the loop issued in vain: 1024 x 4096
-    // bf16, 16 tokens, 9.7 -> 9.1 us, 4096 x 4096 13.8 -> 13.1; a second one added 1.2 us).  In the 16-deep form over 16-bit
+    // bf16, 16 tokens, 9.7 -> 9.1 us, 4096 x 4096 13.8 -> 13.1; a second one added 1.2 us).  Over 16-bit
     // weights the copy of the stage behind the loop does not fit the 128 registers of two workgroups per unit.
     constexpr bool TAIL = is_int8(WDT);
     struct Rows {

@@ -1,27 +1,28 @@
-// Batched sparse FC on the matrix cores where the centred input IS the 16-bit input: m = 0 (inputs that are already
-// centred: everything behind a norm, a GLU block's inputs) or dense mode, activations of the operand's own type (bf16
-// over bf16 and int8 weights, fp16 over fp16 weights).  Then x - m needs no second half, and the pruner can decide on
-// the 16-bit codes:
-//
-//   |x| > tau  <=>  (code & 0x7fff) > code(tau), and no NaN  <=>  (code & 0x7fff) - lo < len  as unsigned 16-bit numbers
-//
-// with code(tau) the largest 16-bit value that is not above tau (exact: a value above tau is above code(tau), too): two
-// elements a lane and instruction.
-//
-// No list and no staging: a wavefront takes steps of 32 rows.  Lane l loads 8 consecutive inputs of token l % 16 (16 bytes; the
-// operand layout of the 32-deep matrix instruction), prunes them in registers -- that is the operand --, ORs the tokens' keep bits
-// over its row of 16 lanes, and asks for its part of the 8 rows; a row that no token keeps is asked for at an offset behind
-// the buffer and costs an issue slot, no memory traffic.  Nothing is exchanged between wavefronts before the sums are added, so the
-// first weight rows are asked for one memory latency after the kernel starts, and a piece may be as long as the layer.
-// The staged-tile kernel (scap_gemm_inline.hip: m != 0) tests and lists a piece before its first row: 3.6 us of 18.7 on 14336 x 4096
+// Batched sparse FC on the matrix cores, row step by row step: most calls of 5-16 tokens and many of 3-4 (rows_pay), both launches of a
+// batch's block and the gate|up launch of many blocks of 2-4 tokens.  No list and no staging: a wavefront takes steps of 32 rows.  Lane l takes
+// 8 consecutive inputs of token l % 16 (16 bytes; the operand layout of the 32-deep matrix instruction), prunes them in registers -- that
+// is the operand --, ORs the tokens' keep bits over its row of 16 lanes, and asks for its part of the 8 rows; a row that no token keeps is
+// asked for at an offset behind the buffer and costs an issue slot, no memory traffic.  Nothing is exchanged between wavefronts before the
+// sums are added, so the first weight rows are asked for one memory latency after the kernel starts, and a piece may be as long as the layer.
+// The staged-tile kernel (scap_gemm_inline.hip) tests and lists a piece before its first row: 3.6 us of 18.7 on 14336 x 4096
 // int8, 12 tokens, 4.3-6.7 of 46 on 4096 x 28672 bf16, 16 tokens, and its pieces have to fit LDS.  Here inputs are 1 KB more per
 // 8 KB of rows (int8: per 4), out of L2.
 //
-// What bounds it: the row stream (6.3 TB/s in 256-byte pieces over a long launch, 7.1 over a short one), then the reduction of eight
-// wavefronts (1 us) and the hand-over (2 us).  us per call, staged tile / here: 4096 x 28672 bf16, 16 tokens at 70 %, 50.6 / 42.8;
-// 14336 x 4096 at 50 % 27.7 / 25.2; 4096 x 11008 fp16, 8 tokens at 50 %, 22.7 / 20.6; 14336 x 4096 int8, 12 tokens at 70 %, 19.0 / 16.0;
-// 4096 x 4096 bf16, 8 tokens at 50 %, 12.5 / 10.5.
+// Where the operand comes from (SRC):
+// kRowsCodes -- the centred input IS the 16-bit input: m = 0 (inputs that are already centred: everything behind a norm, a GLU block's inputs)
+// or dense mode, activations of the operand's own type (bf16 over bf16 and int8 weights, fp16 over fp16 weights).  Then x - m needs no second half,
+// and the pruner decides on the 16-bit codes, two elements a lane and instruction:
 //
+//   |x| > tau  <=>  (code & 0x7fff) > code(tau), and no NaN  <=>  (code & 0x7fff) - lo < len  as unsigned 16-bit numbers
+//
+// with code(tau) the largest 16-bit value that is not above tau (exact: a value above tau is above code(tau), too).
+// kRowsPlanes -- the gated product of a block as the gate|up launch leaves it: planes of operand heads and tails, a pruned channel 0 in both.
+// kRowsCentre -- any m and activation type: centred and tested in fp32, split into head and tail in registers.
+//
+// What bounds it: the row stream (6.3 TB/s in 256-byte pieces over a long launch, 7.1 over a short one), then the reduction of eight
+// wavefronts (1 us) and the hand-over (2 us).  us per call, staged tile (3-4 tokens: four-slot kernel) / here: 4096 x 28672 bf16, 16 tokens at 70 %,
+// 48.5 / 40.2, centred 51.0 / 44.5; 14336 x 4096, 16 tokens at 50 %, 27.3 / 24.9; 4096 x 11008 fp16, 8 tokens at 50 %, 22.4 / 20.1; 14336 x 4096 int8,
+// 12 tokens at 70 %, 18.3 / 14.6; 4096 x 4096 bf16, 8 tokens at 50 %, 12.3 / 10.1, 4 tokens 13.9 / 9.6.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -710,9 +711,11 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
             tile = 2 * kMfmaTile;
     }
     a.T = (a.N + tile - 1) / tile;
-    // Centred inputs: one workgroup per compute unit (173-220 registers), so layers of more tiles than units stay on the staged-tile
-    // kernel, which runs two (us, there / here: 1024 x 36000 bf16, 6 tokens at 90 %, 17.4 / 20.6, 4096 x 40000, 8 tokens, 66.1 /
-    // 69.7, int8 50.1 / 55.9, 2047 x 40000 int8 33.8 / 38.7, but 4096 x 57344 bf16 91.7 / 84.9).
+    // Centred inputs of layers of more tiles than compute units stay on the staged-tile kernel.  Over 16-bit weights (144-157 registers, one
+    // workgroup per unit) neither is the faster one throughout (us at 50 and 90 %, there / here: 4096 x 40000 bf16, 5 tokens, 61.9 / 61.4, 34.7 / 37.1, 2047 x
+    // 40000 37.2 / 38.4, 25.9 / 29.4, 1024 x 65536 26.5 / 25.1, 14.3 / 15.8, but 4096 x 57344 87.2 / 81.9, 48.6 / 43.5, 512 x 40000 16.0 / 12.4, 12.8 / 9.0).  Over
+    // int8 weights (110-125 registers, two per unit) the limit is the same one and not the best: 8 tokens 4096 x 40000 48.2 / 47.6, 35.8 / 34.9, 1024 x 36000
+    // 20.3 / 17.8, 16.8 / 14.0, 1024 x 65536 18.0 / 16.1, 13.7 / 13.9.
     if (a.T > (src == kRowsCentre ? 256 : kMaxTiles)) return SCAP_ERR_SHAPE;
     const int64_t row_bytes = (int64_t)a.N * (i8 ? 1 : 2);
     const int64_t kc_max = (((int64_t)1 << 31) / row_bytes - 2 * kWave) / kWave * kWave;

@@ -148,7 +148,8 @@ int launch_gemv(const GemvArgs& a_in, int wdt, const scap_launch_cfg* cfg, hipSt
         const int rc = launch_gemv1b(a, wdt, cfg ? cfg->flags : 0, stream);
         if (rc != kG1NotApplicable) return rc;
     }
-    // 3-4 tokens in the 16-slot staged-tile kernel: faster than the 4-slot lists for int8 weights (3 tokens at 50 %, lists /
+    // 3-4 tokens in the 16-slot staged-tile kernel (over bf16 weights launch_gemm_inline takes the row steps, here and above; the figures are
+    // the staged tile's): faster than the 4-slot lists for int8 weights (3 tokens at 50 %, lists /
     // here, us: 512 x 24576 13.4 / 7.2, 1024 x 28672 15.9 / 10.3, 4096 x 24576 34.2 / 25.8, 4096 x 28672 29.2 / 27.5; in layers
     // wider than 4 K and over odd lengths launch_gemm_inline still takes the lists where they are the better plan), and than the
     // vector kernel for a long input into a narrow bf16 layer (14336 x 4096, 4 tokens:

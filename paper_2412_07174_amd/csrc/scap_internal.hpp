@@ -151,10 +151,10 @@ int launch_gemm_mfma(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hip
 // The same in one launch: each workgroup compacts its own inputs into LDS (up to 160 KB on gfx950).
 // SCAP_ERR_SHAPE when the input is too long to split into LDS-sized pieces.
 int launch_gemm_inline(const GemvArgs& a, int wdt, const scap_launch_cfg* cfg, hipStream_t stream, bool slots16 = false);
-// The same without lists or staged inputs, 16 token slots (scap_gemm_rows.hip): where the centred input is the 16-bit operand itself
-// (m = 0 or dense mode, activations of the operand's type: exact_operand), and where the inputs are planes of operand halves (the
-// gated product).  kc: rows per workgroup, or 0.  SCAP_ERR_SHAPE where it cannot split the layer.
-constexpr int kRowsCodes = 0;   // x: 16-bit inputs
+// The same without lists or staged inputs, 16 token slots (scap_gemm_rows.hip).  src says what the inputs are; exact_operand: the centred input is
+// the 16-bit operand itself (m = 0 or dense mode, activations of the operand's type).  kc: rows per workgroup, or 0.  SCAP_ERR_SHAPE where it cannot
+// split the layer (kRowsCentre: where it has more column tiles than there are compute units).
+constexpr int kRowsCodes = 0;   // x: 16-bit inputs that are the operand
 constexpr int kRowsPlanes = 1;  // x, zl_lo: heads and tails
 constexpr int kRowsCentre = 2;  // x: 16-bit inputs of any type, centred in fp32 and split
 bool exact_operand(const GemvArgs& a, int wdt);
@@ -163,7 +163,8 @@ bool rows_pay(const GemvArgs& a, int wdt);
 bool rows_pay_gating(const GemvArgs& a, int wdt);
 bool gemm_rows_plans(const GemvArgs& a, int wdt, int src, int* splits = nullptr);
 int launch_gemm_rows(const GemvArgs& a, int wdt, int src, int fuse, int kc, hipStream_t stream);
-// The fused block's two launches on the same kernel (bf16 / int8, up to 16 tokens).
+// The fused block's two launches on the matrix cores: row steps (more than 4 tokens, int8 from 3 where rows_pay_gating; a gate|up launch that
+// they cannot split on the staged tile), else the value lists of 4 token slots.
 int launch_swiglu_block_inline(const GemvArgs& up, const GemvArgs& down, int wdt, hipStream_t stream);
 
 // Fill `n` int32 words with zero using a kernel (safe to record into a HIP graph).

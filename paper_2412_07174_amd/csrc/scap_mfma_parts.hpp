@@ -1,11 +1,9 @@
 // Pieces shared by the kernels that run the gathered product on the matrix cores (gfx950 MFMA):
 //
 //     Y[16 tokens, 16 columns] += D[16 tokens, 16 rows] * W[16 rows, 16 columns]     v_mfma_f32_16x16x16_bf16
-//     Y[16 tokens, 16 columns] += D[16 tokens, 32 rows] * W[32 rows, 16 columns]     v_mfma_f32_16x16x32_bf16
 //
-// (the second, gfx950's own shape, in the staged-tile kernel: mfma_block32 below -- same lane layout with 8
-// instead of 4 k-slots per lane, A[m = l%16][k = 8*(l/16) + j], B[k = 8*(l/16) + j][n = l%16], j = 0..7, fed from
-// two 16-row blocks of the list at a time; half the matrix instructions for the same rows)
+// (gfx950's own 32-deep shape, v_mfma_f32_16x16x32_bf16, in the row-step kernel: mfma_rows in scap_gemm_rows.hip -- same lane layout with 8
+// instead of 4 k-slots per lane, A[m = l%16][k = 8*(l/16) + j], B[k = 8*(l/16) + j][n = l%16], j = 0..7)
 //
 // Operand layout without any transposition.  For this instruction lane l holds
 //     A[m = l%16][k = 4*(l/16) + j],   B[k = 4*(l/16) + j][n = l%16],   C[m = 4*(l/16) + i][n = l%16],  i,j = 0..3.
@@ -107,7 +105,8 @@ constexpr int kTreeFloats = 32 * 1024 / 4;  // LDS floats of the reduction of th
 // A workgroup's rows of W as a buffer: a lane whose list slot does not exist, or whose columns lie past N, asks for an
 // offset behind its end; the hardware returns zeros for it and fetches nothing.  (Before, such lanes read row 0 and
 // were zeroed by selects: every wavefront of the launch asked for the same few cache lines at its end.)  Offsets stay
-// below kNoRow: at most 4096 rows of 1024 tiles x 256 bytes.
+// below kNoRow: a list kernel's piece has at most 4096 rows, of at most 1024 tiles x 256 bytes; a row-step piece may be as long as the layer, but
+// plan_rows keeps Kc (a multiple of the step) times the row's bytes below 2^31.
 constexpr uint32_t kNoRow = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const GemvArgs& a, int k0, uint32_t row_bytes) {
     return make_raw_buffer(const_cast<char*>(reinterpret_cast<const char*>(a.W)) + (uint64_t)k0 * row_bytes,

@@ -1,6 +1,7 @@
 // Fused SwiGLU feed-forward block (SCAP Appendix B, Alg. 2, each scap_fc in the centred form of Alg. 3), gfx950.
 //
-// Two launches of the column-gathered GEMV body:
+// Two launches of the column-gathered GEMV body (here; one token: scap_gemv1.hpp, batches: scap_gemm_rows.hip and scap_gemm_inline.hip, which take the
+// same two steps):
 //   1. gate|up: the weights of the gate and up projections are interleaved in groups of 4 columns, so that
 //      the workgroup that finishes a column tile holds matching gate and up pre-activations.  It forms
 //      z = silu(gate) * up, applies the next layer's centring and threshold, and writes the kept channels of
@@ -98,8 +99,8 @@ static int launch_block_wdt(const GemvArgs& up, const GemvArgs& down, int flags,
 // two-token block on the general kernels
 int launch_swiglu_block(const GemvArgs& up, const GemvArgs& down, int wdt, hipStream_t stream, int flags1) {
     // Matrix cores: more than 4 tokens, and int8 from 3 tokens on, where the vector kernel is bound by its
-    // per-element converts.  Their lists use 4 or 16 token slots, like the vector kernel's for
-    // 3-4 tokens, so the choice only has to be the same for both launches.
+    // per-element converts.  Between the launches the gated product is planes of operand halves, or lists of 4 token
+    // slots; launch_swiglu_block_inline chooses for both launches.
     if (up.B == 1 && !(flags1 & SCAP_CFG_GENERAL_KERNEL)) {  // the one-token kernel with the gating epilogue / the list prologue
         const int rc = launch_swiglu_block1(up, down, wdt, flags1 & (SCAP_CFG_PARTIAL_SUMS | SCAP_CFG_PARK_SLICES),
                                             flags1 & SCAP_CFG_PARTIAL_SUMS, stream);
