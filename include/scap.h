@@ -246,7 +246,7 @@ size_t scap_swiglu_workspace_bytes(int64_t K, int64_t F, int64_t N, int64_t B);
  * in two launches.  The first reads the kept rows of the interleaved gate|up matrix; the workgroup that
  * completes a column tile forms z in fp32 (silu(t) = t / (1 + exp(-t))), subtracts m_z, applies the strict
  * threshold tau_z and leaves the kept channels in the workspace: as compacted lists of fp32 values, or, from 5 tokens on
- * and for int8 blocks of 3-4 up to 2^27 gate|up weights, as the two 16-bit halves (value and remainder) that the matrix unit multiplies.
+ * and for int8 blocks of 3-4 with m_x = 0 and bf16 activations (up to 32768 gate|up columns and 2^27 gate|up weights), as the two 16-bit halves (value and remainder) that the matrix unit multiplies.
  * The second takes those as its input.  z is never rounded to 16 bits; in two halves z - m_z keeps 16 bits of its mantissa (fp16
  * weights: 22), as it does in every product on the matrix cores that is not exact by itself.
  *   W_gu, gu_scale   DEVICE  [K, 2F] from scap_pack_gate_up (and its packed fp16 scales for int8, else NULL).

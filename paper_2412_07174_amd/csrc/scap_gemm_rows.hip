@@ -348,8 +348,9 @@ __global__ __launch_bounds__(kInlineWaves* kWave, 2 * rows_resident(WDT, SRC, RA
     extern __shared__ uint4 smem_raw[];
     Lds L = carve_lds<WAVES, kMfmaTokens>(reinterpret_cast<char*>(smem_raw), 0);
     // A wavefront's accumulators are added to its place in LDS every so many steps: a long chain would lose what few-row sums keep (fp16, 8192 x
-    // 16384, 8 tokens at 50 %, one chain of 32 steps 1.59e-7, of 8 1.15e-7, of 4 0.94e-7; int8 products fill fewer bits).  us, without / so:
-    // 14336 x 4096 bf16, 8 tokens, 23.4 / 23.6, 4096 x 11008, 16 tokens, 21.9 / 21.9, 14336 x 4096 int8, 8 tokens, 15.3 / 15.3 (every 4 steps 15.5).
+    // 16384, 8 tokens at 50 %, one chain of 32 steps 1.59e-7, of 8 1.15e-7, of 4 0.94e-7; over 63 layers at 0, 50 and 90 % no error above that before the row
+    // steps but one, by 3 %, with 8 steps over 16-bit weights eight, by up to 9 %; int8 products fill fewer bits).  us, without / so: 14336 x 4096 bf16, 8 tokens,
+    // 23.4 / 23.6, 4096 x 11008, 16 tokens, 21.9 / 21.9, blocks 4096 -> 14336, 16 tokens, 64.7 / 65.3, 14336 x 4096 int8, 8 tokens, 15.3 / 15.3 (every 4 steps 15.5).
     constexpr int kChainSteps = WDT == kI8Half ? 8 : 4;
     constexpr bool WHOLE = WDT != kI8;  // (16-byte int8 lanes have 256 columns: the sums meet in halves, through a tree)
     if constexpr (FUSE == kFuseSwiglu) L.fin = L.red + sum_floats(WDT);

@@ -92,7 +92,7 @@ struct GemvArgs {
     int32_t* zl_cnt;  // [1 + BT][ceil(F/64)] entries per segment: union first, then per token; [ceil(F/32)]: the three
                       // counts in the low bytes of one word, union lowest
     int F;            // channels of the gated product (half the columns of the gate|up launch)
-    // Batches of 5 and more (gate_to_planes): zl_d is the plane of operand heads, [BT][F rounded up to 64] 16-bit values, this
+    // Batches of 5 and more, int8 blocks of 3-4 on the row steps (gate_to_planes): zl_d is the plane of operand heads, [BT][F rounded up to 64] 16-bit values, this
     // the plane of tails.
     uint16_t* zl_lo;
     // kernel over row steps (scap_gemm_rows.hip): the magnitude codes [keep_lo, keep_lo + keep_len) are kept; elements between the
