@@ -830,17 +830,17 @@ int launch_swiglu_block_inline(const GemvArgs& up_in, const GemvArgs& dn_in, int
     size_t lds_up = 0, lds_dn = 0;
     int wup = wdt;
     const bool exact = exact_operand(up, wdt);
-    if (up.B > 4 || ((int64_t)up.K * up.N <= ((int64_t)1 << 27) && rows_pay_gating(up, wdt) && gemm_rows_plans(dn, wdt, kRowsPlanes))) {
+    if (up.B > 4 || ((int64_t)up.K * up.N <= ((int64_t)1 << 27) && rows_pay_gating(up, wdt) && gemm_rows_plans(dn, wdt, kRowsPlanes, kFusePlain))) {
         // 16 token slots: the gated product travels as planes of operand halves, and the down launch takes them row step by row step
         const int src = exact ? kRowsCodes : kRowsCentre;
-        const bool codes = gemm_rows_plans(up, wdt, src);
+        const bool codes = gemm_rows_plans(up, wdt, src, kFuseSwiglu);
         if (!codes) {
             const int rc = plan_inline_lanes(up, &wup, 0, false, kFuseSwiglu, &bt_up, &lds_up);
             if (rc != SCAP_OK) return rc;
             up.Kl = up.Kc;
             up.Sl = up.S;
         }
-        if (!gemm_rows_plans(dn, wdt, kRowsPlanes)) return SCAP_ERR_SHAPE;
+        if (!gemm_rows_plans(dn, wdt, kRowsPlanes, kFusePlain)) return SCAP_ERR_SHAPE;
         up.zl_lo = dn.zl_lo = reinterpret_cast<uint16_t*>(up.zl_d) + (size_t)block_token_slots(up.B) * plane_pitch(up.F);
         dn.seg_cnt = up.seg_cnt;
         const int rc = codes ? launch_gemm_rows(up, wdt, src, kFuseSwiglu, 0, stream)

@@ -588,17 +588,18 @@ bool rows_pay(const GemvArgs& a, int wdt) {
 // The gate|up launch of a block with centred inputs of the operand's type.  us per block, two- to four-slot or general kernels / here: 4 tokens 1408 -> 6656
 // fp16 26.9 / 22.5, 4224 -> 14400 bf16 79.4 / 68.8, 4096 -> 11008 59.7 / 56.4 (90 and 95 % 44.7 / 42.6, 40.9 / 42.4); 3 tokens 3328 -> 2368 23.9 / 19.6, 5504 -> 12192 76.3 / 69.9
 // (51.3 / 51.1, 46.0 / 48.0).  Not beyond one round of tiles (2280 -> 19032, 4 tokens, 59.6 / 62.0; 3840 -> 22864, 3 tokens at 94 %, 48.7 / 55.6).
-// Two tokens: small layers (2176 -> 4880 bf16 21.8 / 21.1, 3264 -> 4448 24.7 / 22.4, at 90 % 19.5 / 19.5), and short inputs where the tiles alone fill the chip,
-// no split and nothing handed over, up to the length where the loss at 90 % outweighs the gain at 40-50 % (as in rows_pay). At 40, 70 and 90 %: bf16 1024 -> 14336 24.6 / 21.3,
-// 21.4 / 18.6, 18.9 / 17.2, 2048 -> 11008 28.6 / 26.5, 24.2 / 21.7, 20.0 / 20.0, 4096 -> 14336 47.1 / 45.8, 36.1 / 34.6, 26.2 / 28.8, beyond 6144 -> 14336 62.4 / 61.1, 45.3 / 43.5, 29.9 / 35.5; int8
-// 1024 -> 8448 18.2 / 16.2, 17.2 / 15.8, 16.1 / 15.6, 2048 -> 14336 23.6 / 22.0, 20.7 / 20.6, 18.2 / 19.6, beyond 3072 -> 14336 29.1 / 27.2, 23.8 / 25.7, 19.9 / 23.6, 4096 -> 14336 33.1 / 31.9,
-// 26.4 / 28.9, 21.4 / 26.8.
+// Two tokens: small layers (2176 -> 4880 bf16 21.8 / 21.1, 3264 -> 4448 24.7 / 22.4, at 90 % 19.5 / 19.5), and short inputs into many columns, whose tiles
+// fill the chip in one split, nothing handed over, while the gains at 40, 70 and 90 % add up or nearly (as in rows_pay).  At 40, 70 and 90 %, to 512 outputs (tiles: gate|up
+// columns / 128): bf16 1024 channels, 224 tiles 21.9 / 18.2, 18.4 / 15.4, 15.6 / 14.4; 2048, 132 tiles 23.0 / 22.4, 19.7 / 18.3, 16.4 / 17.2, 224 tiles 29.3 / 27.8, 24.0 / 21.3, 18.8 / 19.2; 3072, 200 tiles
+// 35.2 / 33.3, 27.2 / 25.7, 19.8 / 22.1; beyond 3072, 172 tiles 32.6 / 31.5, 25.9 / 25.5, 19.8 / 21.7, 4096, 224 tiles 44.8 / 43.8, 33.0 / 31.5, 22.4 / 26.8; int8 256 channels, 104 tiles 14.1 / 11.2, 13.8 /
+// 10.9, 13.2 / 10.6; 1024, 104 tiles 16.2 / 14.4, 15.1 / 14.1, 14.2 / 13.8; 1536, 132 tiles 17.4 / 16.1, 16.5 / 16.0, 14.8 / 15.5; 2048, 224 tiles 21.5 / 20.0, 18.9 / 18.8, 16.5 / 18.2; beyond 2048, 150 tiles 19.7 /
+// 18.6, 17.7 / 18.0, 15.5 / 17.4; whole blocks 3072 -> 14336 29.1 / 27.2, 23.8 / 25.7, 19.9 / 23.6, 4096 -> 14336 33.1 / 31.9, 26.4 / 28.9, 21.4 / 26.8.
 bool rows_pay_gating(const GemvArgs& a, int wdt) {
     int splits = 0;
-    if (!exact_operand(a, wdt) || a.N > kRowsFewCols || !gemm_rows_plans(a, wdt, kRowsCodes, &splits)) return false;
+    if (!exact_operand(a, wdt) || a.N > kRowsFewCols || !gemm_rows_plans(a, wdt, kRowsCodes, kFuseSwiglu, &splits)) return false;
     if (a.B > 2) return true;
-    if (wdt == kI8) return splits == 1 && a.K <= 2048;
-    return (int64_t)a.K * a.N <= ((int64_t)1 << 25) || (splits == 1 && a.K <= 4096);
+    if (wdt == kI8) return splits == 1 && a.K <= 2048 && a.N >= (int64_t)10 * a.K;
+    return (int64_t)a.K * a.N <= ((int64_t)1 << 25) || (splits == 1 && a.N >= (int64_t)8 * a.K);
 }
 
 // The interval of magnitude codes that the pruner keeps: [lo, lo + len) of the 16-bit patterns without their sign.
@@ -691,18 +692,20 @@ static int launch_planes_any(const GemvArgs& a, int wdt, hipStream_t stream) {
 // The cost of a split in rows of one workgroup at the rate of a full chip.  Nothing but the weight buffer's offsets bounds a piece
 // (no inputs in LDS), and a launch of fewer workgroups than compute units is not slower for it until a unit asks for more than it can
 // take: 46 GB/s where its share of a full chip's stream is 25 (a sweep that reads 256-byte pieces with 32 / 64 / 128 / 192 / 224 / 256 workgroups:
-// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s): `part`; alone in its round a unit has less in flight, above all where few rows are kept.  One split whose
-// tiles all run at once reads all columns of the same rows at the same time (a few per cent), and one split hands nothing over (`hand`, `split`).  `fixed`:
-// prologue, reduction and the launch's ends, a quarter of it for each further round where two workgroups share a unit.  Constants fitted to sweeps of all
-// splits over 43 layers, 4, 5 and 12 tokens at 50 and 90 %: the split chosen is 0.35 % (int8) and 0.65 % (16-bit) above the best one on average,
-// 5 and 7.5 % at most.  us at the split chosen / others, at 50 %: 4096 x 28672 bf16, 12 tokens, S = 1 43.6 / S = 2 48.2; 8192 x 28672 bf16, 12 tokens, 1
-// 84.6 / 2 90.0, int8, 5 tokens, 1 48.8 / 2 51.0; 14336 x 4096 bf16, 12 tokens, 8 25.0 / 7 26.9 / 9 32.3; 4096 x 22016 bf16, 5 tokens, 4 35.0 / 1 36.2 / 2 39.6;
+// 1.5 / 2.8 / 5.1 / 6.0 / 6.3 / 6.1 TB/s): `part`, in a further round with less to win, since units that run two workgroups set its end.  One split hands
+// nothing over (`hand`, `split`); a gating launch's hand-over is the dearer one: one ticket a workgroup, and the last arrival fetches all tokens' sums before
+// it gates them.  `round`: a workgroup's prologue and reduction in each further round, less where two share a unit.  One set of constants, fitted to 2200
+// sweeps of the splits over 196 layers, even and odd lengths, codes, centred inputs, planes and gating launches, both weight types, 4-13 tokens at 50-90 %.  The split
+// chosen is above the best one by, on average, 16-bit / int8: plain codes 0.7 / 0.5 %, gating 0.4 / 0.3 %, centred 0.6 / 0.6 %, odd lengths 0.5 / 1.0 %, planes 0.5 / 0.2 %; the worst are
+// 10-14 %, at 90 % (7168 x 6656 bf16, 5 tokens, 4 splits 13.8 / 9 12.3).  us at the split chosen / others, at 50 %: 4096 x 28672 bf16, 12 tokens, S = 1 43.6 / S = 2 48.2; 8192 x 28672 bf16,
+// 12 tokens, 1 84.6 / 2 90.0, int8, 5 tokens, 1 48.8 / 2 51.0; 7808 x 13184 bf16, 12 tokens at 70 %, 2 32.5 / 4 37.2, as gate|up launch of a block 2 40.9 / 4 44.1, int8, 5 tokens, 2 29.6 / 4
+// 30.7; 14336 x 4096 bf16, 12 tokens, 8 25.0 / 7 26.9 / 9 32.3; 4096 x 22016 bf16, 5 tokens, 4 35.0 / 1 36.2 / 2 39.6;
 // 4096 x 11008 int8, 5 tokens, 5 12.8 / 2 14.4 / 3 15.4; 2048 x 20480 int8, 5 tokens, 3 12.6 / 1 14.3; 256 x 8192 bf16, 5 tokens, 1 4.5 / 4 5.0; beyond 256
 // tiles 4096 x 49152 int8, 5 tokens, 2 42.0 / 1 46.9, 2048 x 45056 bf16 2 35.0 / 1 37.7, 4096 x 65536 bf16 1 83.8 / 2 85.4.
 // int8 weights run in 8-byte lanes (128-column tiles; 5-16 tokens at 50-70 %, 16-byte / 8-byte lanes: 14336 x 4096 18.0 / 16.0, 4096 x
 // 28672 27.3 / 25.9, 4096 x 4096 10.7 / 8.1); *wdt becomes kI8Half.  Planes also in 16-byte lanes, where there are more narrow tiles than
 // arrival counters.
-static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
+static int plan_rows(GemvArgs& a, int* wdt, int src, int fuse, int kc) {
     const bool i8 = *wdt == kI8;
     int tile = kMfmaTile;
     if (i8) {
@@ -724,19 +727,18 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
     if (a.B <= kWideTokens) s_max /= 2;
     if (s_max > kMaxSplits) s_max = kMaxSplits;
     if (kc == 0) {
-        const int fixed = i8 ? 500 : 340, split = i8 ? 13 : 10, hand = 110;
-        const double again = rows_resident(*wdt, src, src != kRowsPlanes && a.K % 8 != 0) == 2 ? 0.25 : 1.0;
+        const int split = 12, hand = fuse == kFuseSwiglu ? 280 : 130;
+        const int round = rows_resident(*wdt, src, src != kRowsPlanes && a.K % 8 != 0) == 2 ? 125 : 300;
         double best = 0.0;
         for (int64_t sp = 1; sp <= s_max; ++sp) {
             const int64_t c = (int64_t)align_up((size_t)((a.K + sp - 1) / sp), kWave);
             if (c > kc_max) continue;
-            const int64_t s = (a.K + c - 1) / c, n = s * a.T, rounds = (n + 255) / 256;
+            const int64_t s = (a.K + c - 1) / c, n = s * a.T;
             auto part = [&](int64_t m) {
                 const double x = (double)m / 256.0;
-                return m == 0 ? 0.0 : n <= 256 ? std::max(0.55, 0.36 + 0.64 * x + 0.25 * x * (1.0 - x)) : std::max(0.55, 0.25 + 0.75 * x);
+                return m == 0 ? 0.0 : std::max(0.55, n <= 256 ? 0.45 + 0.55 * x + 0.1 * x * (1.0 - x) : 0.4 + 0.6 * x);
             };
-            const double rows = (double)c * ((double)(n / 256) + part(n % 256));
-            const double cost = rows * (s == 1 && n <= 256 ? 0.96 : 1.0) + fixed + fixed * again * (double)(rounds - 1) + (double)(split * s) + (s > 1 ? hand : 0);
+            const double cost = (double)c * ((double)(n / 256) + part(n % 256)) + (double)(round * ((n + 255) / 256 - 1) + split * s) + (s > 1 ? hand : 0);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 kc = (int)c;
@@ -754,9 +756,9 @@ static int plan_rows(GemvArgs& a, int* wdt, int src, int kc) {
     return SCAP_OK;
 }
 
-bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src, int* splits) {
+bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src, int fuse, int* splits) {
     GemvArgs a = a_in;
-    if (plan_rows(a, &wdt, src, 0) != SCAP_OK) return false;
+    if (plan_rows(a, &wdt, src, fuse, 0) != SCAP_OK) return false;
     if (splits) *splits = a.S;
     return true;
 }
@@ -764,7 +766,7 @@ bool gemm_rows_plans(const GemvArgs& a_in, int wdt, int src, int* splits) {
 int launch_gemm_rows(const GemvArgs& a_in, int wdt, int src, int fuse, int kc, hipStream_t stream) {
     GemvArgs a = a_in;
     if (a.B < 1 || a.B > kMfmaTokens || (src == kRowsCodes && !exact_operand(a, wdt))) return SCAP_ERR_CONFIG;
-    const int rc = plan_rows(a, &wdt, src, kc);
+    const int rc = plan_rows(a, &wdt, src, fuse, kc);
     if (rc != SCAP_OK) return rc;
     if (src == kRowsPlanes) {
         a.mode = kModeSparse;  // (the planes hold what is kept)

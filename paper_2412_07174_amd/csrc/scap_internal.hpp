@@ -161,7 +161,7 @@ bool exact_operand(const GemvArgs& a, int wdt);
 // Whether a plain call of three or more tokens, or the gate|up launch of a block of 2-4, is the faster one on that kernel.
 bool rows_pay(const GemvArgs& a, int wdt);
 bool rows_pay_gating(const GemvArgs& a, int wdt);
-bool gemm_rows_plans(const GemvArgs& a, int wdt, int src, int* splits = nullptr);
+bool gemm_rows_plans(const GemvArgs& a, int wdt, int src, int fuse, int* splits = nullptr);
 int launch_gemm_rows(const GemvArgs& a, int wdt, int src, int fuse, int kc, hipStream_t stream);
 // The fused block's two launches on the matrix cores: row steps (more than 4 tokens, int8 from 3 where rows_pay_gating; a gate|up launch that
 // they cannot split on the staged tile), else the value lists of 4 token slots.
