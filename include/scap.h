@@ -78,7 +78,7 @@ typedef enum {
  * 512-channel list segments by the two-launch form, whose unroll (1, 2, 4; int8: 1, 2) counts 16-row blocks
  * in flight per wavefront).  By default batches of 5 or more tokens run on
  * the matrix cores, and so do 4 tokens (3 up to 2^25 weights) with m = 0 or dense mode and activations of the weights' type (int8: bf16)
- * over at most 32768 columns (K not a multiple of 8: and 7 * 2^24 weights; int8: and 5 * 2^24 weights, 2^27 beyond 16384 columns, K not a
+ * over at most 32768 columns (K not a multiple of 8: and 7 * 2^24 weights; int8: and 7 * 2^25 weights, K not a
  * multiple of 8 9 * 2^23); of the other calls of 3-4 tokens those over int8 layers of more than 4096 columns and 2^26 weights or of more than
  * 16384 columns, and those over bf16 layers with K >= 2 N (K a multiple of 8) whose input is dense or that have at most 1024
  * columns and K > 512.  Over int8 weights they also run there when rows_per_group is given, which may then be up to 4096 in

@@ -1,6 +1,6 @@
 // Batched sparse FC on the matrix cores in ONE launch (gfx950 MFMA) with lists in LDS: what the row-step kernel
 // (scap_gemm_rows.hip) does not take -- centred inputs over more column tiles than compute units; over int8 weights 3-4 tokens that rows_pay
-// refuses, large layers of 5-6 tokens, blocks of 3-4 tokens that rows_pay_gating refuses -- and calls of 2-4 tokens that name this kernel.
+// refuses, 5-6 tokens over large layers of an odd input length, blocks of 3-4 tokens that rows_pay_gating refuses -- and calls of 2-4 tokens that name this kernel.
 // Two kernels: gemm_inline_kernel (below) keeps per-token value lists in LDS (four token slots; 16 over int8 layers of an odd input length);
 // gemm_inline_raw_kernel (further down, 16 token slots) stages the raw input tile instead and forms the centred values when the MFMA operand is assembled.
 //

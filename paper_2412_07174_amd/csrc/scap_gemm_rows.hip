@@ -558,31 +558,29 @@ bool exact_operand(const GemvArgs& a, int wdt) {
 }
 
 // A row that no token keeps costs its issue slot here, and over int8 weights its widening, where the list kernels never meet it: what the row steps
-// gain at 50-70 % in a large layer turns over where few rows are kept, and the host does not know how many that will be.  From sweeps of 52 layers at 50,
-// 70 and 90 % on either kernel: a kind of call runs here up to the size where its loss at 90 % outweighs the gain at 50-70 %, about 10 % against 10 %.
-// us there / here at 50 and 90 %, inside / beyond the line (odd: an input length that is not a multiple of 8):
-// 3 tokens, whose lists are shorter, 2^25 weights: bf16 4096 x 4096 11.8 / 8.8, 9.1 / 6.4; beyond 8192 x 8192 24.7 / 23.1, 13.2 / 14.1, int8 4096 x 14336 17.1 / 14.8, 10.7 / 12.1.
-// 4 tokens, 16-bit weights: 8192 x 16384 47.4 / 44.0, 24.1 / 24.5; odd 9001 x 9600 35.5 / 29.7, 19.9 / 20.7; beyond 16383 x 8192 48.0 / 46.5, 24.8 / 27.1.
-// 4 tokens, int8: 5120 x 13824 20.5 / 16.6, 14.4 / 14.0, wide 4096 x 28672 28.7 / 25.0, 17.6 / 18.9, odd 6001 x 11008 24.4 / 19.4, 15.9 / 17.0; beyond 12288 x 8192
-// 24.5 / 21.4, 14.5 / 16.8, odd 9001 x 9600 24.6 / 22.6, 16.6 / 19.8.
-// 5-6 tokens, int8 (5 here): 16384 x 4096 19.8 / 16.7, 12.9 / 13.0, wide 8192 x 28672 54.5 / 48.2, 33.6 / 35.2, odd 4095 x 28672 32.0 / 27.4, 21.8 / 23.8; beyond 8192 x 16384 31.1 /
-// 27.3, 17.9 / 20.9, odd 8191 x 16384 34.1 / 29.0, 21.4 / 24.9.  Centred: 5120 x 13824 21.7 / 17.9, 15.7 / 16.1, wide 2048 x 20480 15.4 / 13.2, 10.8 / 11.4, odd 8193 x 8192
-// 22.7 / 18.2, 16.5 / 16.6; beyond 6144 x 14336 25.1 / 22.3, 15.7 / 19.2, wide 4096 x 28672 29.3 / 27.4, 19.2 / 22.6, odd 9001 x 9600 26.4 / 23.9, 18.5 / 23.1.
-// The worst that are left at 90 %: 10-17 % (wide layers whose tiles fill 160 of 256 units in one split, 3001 x 20480 int8, 5 tokens centred 14.2 / 16.4; 7-8 tokens, 8192 x 16384
-// int8 20.5 / 23.1 against 32.7 / 29.0 at 50 %); at 95 % more.  From 12 tokens on the union is large enough everywhere (8192 x 16384, 12 tokens, 23.2 / 23.1).
+// gain at 50-70 % in a large layer turns over where few rows are kept, and the host does not know how many that will be.  From sweeps of 230 layers at 50,
+// 70 and 90 % on either kernel: a kind of call runs here where its gains at the three add up.  us there / here at 50, 70 and 90 %, inside / beyond the line (odd: an input length that is
+// not a multiple of 8):
+// 3 tokens, whose lists are shorter, 2^25 weights (50 and 90 %): bf16 4096 x 4096 11.8 / 8.8, 9.1 / 6.4; beyond 8192 x 8192 24.7 / 23.1, 13.2 / 14.1.
+// 4 tokens, 16-bit weights (50 and 90 %): 8192 x 16384 47.4 / 44.0, 24.1 / 24.5; odd 9001 x 9600 35.5 / 29.7, 19.9 / 20.7; beyond 16383 x 8192 48.0 / 46.5, 24.8 / 27.1.
+// 4 tokens, int8: 5120 x 13824 21.5 / 17.5, 19.1 / 17.2, 15.0 / 14.4; 8192 x 14336 30.2 / 26.5, 25.2 / 24.3, 17.1 / 20.2; 28672 x 8192 50.0 / 43.7, 41.7 / 37.6, 28.7 / 32.3; wide 8192 x 26752 48.1 / 41.6, 41.2 /
+// 40.6, 29.1 / 33.5; beyond 16384 x 20480 66.6 / 64.5, 56.1 / 53.1, 36.3 / 43.1; odd 16385 x 4608 23.1 / 19.4, 20.6 / 19.4, 16.5 / 16.6; beyond 8193 x 10112 23.9 / 22.5, 21.2 / 22.2, 16.5 / 19.2.
+// 5-6 tokens, int8 (5 here): 8192 x 14336 31.1 / 27.3, 26.8 / 24.6, 18.4 / 20.6; 16384 x 12416 48.2 / 37.9, 40.9 / 35.2, 30.5 / 30.2; 16384 x 28672 94.4 / 89.3, 79.6 / 74.0, 51.2 / 57.4; odd 13889 x
+// 12032 41.8 / 35.9, 37.0 / 34.8, 28.2 / 30.2; centred 5376 x 16384 26.2 / 20.9, 22.8 / 19.6, 16.2 / 17.6, 16384 x 7424 31.1 / 27.1, 28.1 / 26.7, 20.4 / 24.6, 4096 x 28672 30.1 / 27.9, 27.5 / 25.4, 19.9 / 22.6;
+// centred and odd (50 and 90 %) 8193 x 8192 22.7 / 18.2, 16.5 / 16.6; beyond 9001 x 9600 26.4 / 23.9, 18.5 / 23.1.
+// What that leaves at 90 %: up to 17 % more (16384 x 7424 centred, 8192 x 14336 int8, 4 tokens); at 95 % more.  From 12 tokens on the union is large enough everywhere
+// (8192 x 16384, 12 tokens, 23.2 / 23.1).
 bool rows_pay(const GemvArgs& a, int wdt) {
     const int64_t weights = (int64_t)a.K * a.N;
     const auto up_to = [&](int n) { return weights <= (int64_t)n << 23; };
-    const bool exact = exact_operand(a, wdt), odd = a.K % 8 != 0, wide = a.N > 16384;
+    const bool exact = exact_operand(a, wdt), odd = a.K % 8 != 0;
     if (a.B <= 4) {
         if (!exact || a.B < 3 || a.N > kRowsFewCols) return false;
         if (a.B == 3) return up_to(4);
         if (wdt != kI8) return !odd || up_to(14);
-        return up_to(odd ? 9 : wide ? 16 : 10);
+        return up_to(odd ? 9 : 28);
     }
-    if (wdt != kI8 || a.B > 6) return true;
-    if (odd) return up_to(exact ? 14 : 10);
-    return wide ? exact || up_to(5) : up_to(10);
+    return wdt != kI8 || a.B > 6 || !odd || exact || up_to(10);
 }
 
 // The gate|up launch of a block with centred inputs of the operand's type.  us per block, two- to four-slot or general kernels / here: 4 tokens 1408 -> 6656

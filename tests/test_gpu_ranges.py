@@ -307,7 +307,7 @@ def test_staged_tile_prologues_of_odd_lengths(rows, K, wdt, N):
 
 
 # int8 layers around the choice between 16- and 8-byte lanes of the staged tile: both plans cost the same at 28672 columns (16-byte lanes), a
-# tile less or more and 8-byte lanes are cheaper (3-4 tokens, and 5 over the larger layers of even length; else row steps)
+# tile less or more and 8-byte lanes are cheaper (3-4 tokens; 5 and more run row by row)
 @pytest.mark.parametrize("K,N", [(1048, 28672), (2056, 28672), (1048, 24576), (2040, 28416), (1023, 28672), (2049, 20496)])
 def test_int8_batches_of_both_lane_widths(K, N):
     layer, xdt = _layer(K, N, I8, 1210 + K)
