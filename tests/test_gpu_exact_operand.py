@@ -199,7 +199,7 @@ def test_subnormal_inputs_keep_their_products():
 
 
 @pytest.mark.parametrize("dt", [BF16, F16, I8])
-@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (264, 520, 144, 2), (1001, 1032, 272, 2), (1001, 14336, 144, 2), (1001, 1032, 272, 3), (2048, 4104, 512, 4), (8, 16384, 144, 2), (8, 16392, 144, 4), (2048, 8200, 144, 2), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
+@pytest.mark.parametrize("K,F,N,B", [(264, 520, 144, 5), (264, 520, 144, 2), (1001, 1032, 272, 2), (1001, 14336, 144, 2), (1001, 1032, 272, 3), (2048, 4104, 512, 4), (8, 16384, 144, 2), (8, 16392, 144, 4), (2048, 8200, 144, 2), (2056, 8200, 144, 2), (1032, 6656, 144, 2), (1001, 1032, 272, 9), (2048, 4104, 512, 16), (33, 8, 16, 8)])
 def test_exact_operand_blocks(K, F, N, B, dt):
     """The block's gate|up launch on this kernel (centred inputs) against the oracle, token by token."""
     from test_gpu_swiglu import Block
